@@ -823,214 +823,6 @@ void cnn_fused_kernel(CnnArgs a, Forward f) {
   if (tid < kMaxK && sh.ticks[tid] && a.count_ticks) atomicAdd(&a.st->r_ticks[tid], sh.ticks[tid]);
 }
 
-// ---------------------------------------------------------------- FP64 tier
-// The frame normalised in fp64 exactly as defined, the canonical (unfolded) fp32 weights
-// widened to fp64, fp64 accumulation.  The first esc_cap escalated entries of each predicate are
-// evaluated layer-parallel across the whole GPU: layer 1 with one thread per output activation,
-// layers 2 and 3 with one wave per output activation whose lanes split the (tap, channel) sum
-// (weights laid out [co][3][3][ci] so the lanes read consecutive weights and activations) and
-// reduce it with cross-lane adds; any entries beyond that run one per workgroup.
-__device__ inline double frame_norm64(const FrameSrc& fr, uint32_t idx, int y, int x, int c) {
-  const int64_t o = (int64_t)idx * fr.elems + ((int64_t)y * fr.hw + x) * 3 + c;
-  double v;
-  if (fr.dtype == HYDRO_DTYPE_BF16) v = (double)(float)static_cast<const __bf16*>(fr.base)[o];
-  else v = (double)static_cast<const uint8_t*>(fr.base)[o] / 255.0;
-  return (v - 0.5) * 4.0;
-}
-
-__device__ inline int mult_dev(int variant) { return variant == CNN_W1 ? 1 : variant == CNN_W2 ? 2 : 4; }
-
-// Activation (after ReLU) of output (p, o) of `layer` for one entry.  `in` is the previous layer's
-// output ([H][H][Cin] fp64) for layers 1 and 2.
-__device__ inline double conv64_at(const CnnArgs& a, int slot, int layer, uint32_t idx, const double* in, int p, int o) {
-  const int m = mult_dev(a.variant[slot]);
-  const int cin = layer == 0 ? 3 : layer == 1 ? 16 * m : 32 * m;
-  const int hin = layer == 0 ? H0 : layer == 1 ? H1 : H2;
-  const int hout = hin / 2;
-  const int i = p / hout, j = p % hout;
-  const float* W = a.wt_canon[slot][layer];
-  double s = (double)a.b_canon[slot][layer][o];
-  for (int u = 0; u < 3; ++u) {
-    const int y = 2 * i + u - 1;
-    if (y < 0 || y >= hin) continue;
-    for (int v = 0; v < 3; ++v) {
-      const int x = 2 * j + v - 1;
-      if (x < 0 || x >= hin) continue;
-      const float* w = W + ((o * 3 + u) * 3 + v) * cin;
-      if (layer == 0) {
-        for (int c = 0; c < 3; ++c) s = fma((double)w[c], frame_norm64(a.fr, idx, y, x, c), s);
-      } else {
-        const double* xin = in + (y * hin + x) * cin;
-        for (int c = 0; c < cin; ++c) s = fma((double)w[c], xin[c], s);
-      }
-    }
-  }
-  return s > 0.0 ? s : 0.0;
-}
-
-__device__ inline int64_t act_off(int layer, int m) {
-  // per entry: [layer-1 output | layer-2 output]; layer 3 reuses the layer-1 region
-  return layer == 1 ? (int64_t)H1 * H1 * 16 * m : 0;
-}
-
-__device__ inline void f64_decode(const CnnArgs& a, int layer, int64_t gi, const int* ne, const int64_t* outs,
-                                  int& slot, int& e, int& p, int& o) {
-  slot = 0;
-  int64_t rem = gi;
-  for (int i = 0; i < a.n_preds; ++i) {
-    const int64_t c = ne[i] * outs[i];
-    if (rem < c) { slot = i; break; }
-    rem -= c;
-  }
-  e = (int)(rem / outs[slot]);
-  const int oi = (int)(rem % outs[slot]);
-  const int m = mult_dev(a.variant[slot]);
-  const int cout = layer == 0 ? 16 * m : layer == 1 ? 32 * m : 64 * m;
-  p = oi / cout;
-  o = oi % cout;
-}
-
-__global__ __launch_bounds__(256) void cnn_f64_layer_kernel(CnnArgs a, int layer) {
-  int64_t total = 0;
-  int64_t outs[kMaxK];
-  int ne[kMaxK];
-  for (int i = 0; i < a.n_preds; ++i) {
-    const int m = mult_dev(a.variant[i]);
-    const int hout = layer == 0 ? H1 : layer == 1 ? H2 : H3;
-    const int cout = layer == 0 ? 16 * m : layer == 1 ? 32 * m : 64 * m;
-    ne[i] = min(a.q.counts[a.pred[i]], a.esc_cap);
-    outs[i] = (int64_t)hout * hout * cout;
-    total += ne[i] * outs[i];
-  }
-  if (layer == 0) {
-    // layer 1 (27 products per output): one thread per output
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; gi < total; gi += stride) {
-      int slot, e, p, o;
-      f64_decode(a, 0, gi, ne, outs, slot, e, p, o);
-      const int m = mult_dev(a.variant[slot]);
-      const uint32_t idx = entry_idx(a.q.entries[(int64_t)a.pred[slot] * a.q.cap + e]);
-      double* act = a.esc_act[slot] + (int64_t)e * a.esc_stride;
-      act[p * 16 * m + o] = conv64_at(a, slot, 0, idx, nullptr, p, o);
-    }
-    return;
-  }
-  // layers 2 and 3: one wave per output, lanes over (tap, input channel)
-  const int lane = threadIdx.x & 63;
-  const int64_t nwaves = (int64_t)gridDim.x * 4;
-  for (int64_t gi = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); gi < total; gi += nwaves) {
-    int slot, e, p, o;
-    f64_decode(a, layer, gi, ne, outs, slot, e, p, o);
-    const int m = mult_dev(a.variant[slot]);
-    const int cin = layer == 1 ? 16 * m : 32 * m;
-    const int cout = layer == 1 ? 32 * m : 64 * m;
-    const int hin = layer == 1 ? H1 : H2, hout = hin / 2;
-    const int i = p / hout, j = p % hout;
-    double* act = a.esc_act[slot] + (int64_t)e * a.esc_stride;
-    const double* in = layer == 1 ? act + act_off(0, m) : act + act_off(1, m);
-    const float* W = a.wt_canon[slot][layer] + (int64_t)o * 9 * cin;
-    double s = 0.0;
-    for (int kk = lane; kk < 9 * cin; kk += 64) {
-      const int t = kk / cin, c = kk % cin;
-      const int y = 2 * i + t / 3 - 1, x = 2 * j + t % 3 - 1;
-      if (y >= 0 && x >= 0 && y < hin && x < hin) s = fma((double)W[kk], in[(y * hin + x) * cin + c], s);
-    }
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) {
-      s += (double)a.b_canon[slot][layer][o];
-      double* out = layer == 1 ? act + act_off(1, m) : act;   // layers 1 and 3 share a region
-      out[p * cout + o] = s > 0.0 ? s : 0.0;
-    }
-  }
-}
-
-// Pool, FC, margin and decision: one wave per escalated entry.
-__device__ inline void cnn_head64(const CnnArgs& a, const Forward& f, int slot, uint32_t e, const double* act3,
-                                  bool active) {
-  const int lane = threadIdx.x & 63;
-  const int m = mult_dev(a.variant[slot]);
-  const int C3 = 64 * m;
-  double zp[kClasses];
-#pragma unroll
-  for (int c = 0; c < kClasses; ++c) zp[c] = 0.0;
-  if (active) {
-    const float* fw = a.fc_w[slot];
-    for (int ch = lane; ch < C3; ch += 64) {
-      double sum = 0.0;
-      for (int p = 0; p < H3 * H3; ++p) sum += act3[p * C3 + ch];
-      const double gch = sum / 64.0;
-#pragma unroll
-      for (int c = 0; c < kClasses; ++c) zp[c] = fma(gch, (double)fw[ch * kClasses + c], zp[c]);
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < kClasses; ++c)
-    for (int o = 32; o >= 1; o >>= 1) zp[c] += __shfl_xor(zp[c], o);
-  const int k = a.pred[slot];
-  const uint32_t idx = entry_idx(e);
-  bool lead = active && lane == 0;
-  bool pass = false;
-  if (lead) {
-    double z[kClasses];
-    for (int c = 0; c < kClasses; ++c) z[c] = (double)a.fc_b[slot][c] + zp[c];
-    if (f.logits != nullptr)
-      for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)idx * kClasses + c] = z[c];
-    pass = class_margin(z, a.class_mask[slot]) > (double)theta_of(f, k, idx);
-  }
-  if (f.logits == nullptr) forward_decision(f, k, e, lead, false, pass);
-}
-
-__global__ __launch_bounds__(256) void cnn_f64_head_kernel(CnnArgs a, Forward f) {
-  int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) total += min(a.q.counts[a.pred[i]], a.esc_cap);
-  const int wave = threadIdx.x >> 6;
-  const int nw = gridDim.x * 4;
-  for (int base = blockIdx.x * 4; base < total; base += nw) {
-    const int t = base + wave;
-    const bool active = t < total;
-    int slot = 0, off = t;
-    for (int i = 0; i < a.n_preds; ++i) {
-      const int c = min(a.q.counts[a.pred[i]], a.esc_cap);
-      if (off < c) { slot = i; break; }
-      off -= c;
-    }
-    if (!active) { slot = 0; off = 0; }
-    const uint32_t e = active ? a.q.entries[(int64_t)a.pred[slot] * a.q.cap + off] : 0u;
-    const double* act3 = a.esc_act[slot] + (int64_t)off * a.esc_stride;
-    cnn_head64(a, f, slot, e, act3, active);
-  }
-}
-
-// Entries beyond esc_cap: one workgroup per entry, per-block scratch.
-__global__ __launch_bounds__(256) void cnn_f64_rest_kernel(CnnArgs a, Forward f) {
-  const int tid = threadIdx.x;
-  double* A = a.scratch64 + (int64_t)blockIdx.x * a.scratch64_per_block;
-  double* B = A + a.scratch64_per_block / 2;
-  int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) total += max(0, a.q.counts[a.pred[i]] - a.esc_cap);
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    int slot = 0, off = t;
-    for (int i = 0; i < a.n_preds; ++i) {
-      const int c = max(0, a.q.counts[a.pred[i]] - a.esc_cap);
-      if (off < c) { slot = i; break; }
-      off -= c;
-    }
-    off += a.esc_cap;
-    const int k = a.pred[slot];
-    const uint32_t e = a.q.entries[(int64_t)k * a.q.cap + off];
-    const uint32_t idx = entry_idx(e);
-    const int m = mult_dev(a.variant[slot]);
-    for (int q = tid; q < H1 * H1 * 16 * m; q += 256) A[q] = conv64_at(a, slot, 0, idx, nullptr, q / (16 * m), q % (16 * m));
-    __syncthreads();
-    for (int q = tid; q < H2 * H2 * 32 * m; q += 256) B[q] = conv64_at(a, slot, 1, idx, A, q / (32 * m), q % (32 * m));
-    __syncthreads();
-    for (int q = tid; q < H3 * H3 * 64 * m; q += 256) A[q] = conv64_at(a, slot, 2, idx, B, q / (64 * m), q % (64 * m));
-    __syncthreads();
-    if (tid < 64) cnn_head64(a, f, slot, e, A, true);
-    __syncthreads();
-  }
-}
-
 // ---------------------------------------------------------------- host helpers
 int cnn_variant_of(int in_hw, int n_layers, const int* widths) {
   if (in_hw != 64 || n_layers != 3) return CNN_NONE;
@@ -1098,10 +890,21 @@ void cnn_pack_layer(int variant, int layer, int prec, const float* w_canon, floa
 void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s) {
   if (a.n_preds == 0) return;
   if (tier == TIER_F64) {
-    for (int layer = 0; layer < 3; ++layer)
-      hipLaunchKernelGGL(cnn_f64_layer_kernel, dim3(grid * 4), dim3(256), 0, s, a, layer);
-    hipLaunchKernelGGL(cnn_f64_head_kernel, dim3(grid), dim3(256), 0, s, a, f);
-    hipLaunchKernelGGL(cnn_f64_rest_kernel, dim3(a.rest_grid), dim3(256), 0, s, a, f);
+    F64Args b{};
+    b.n_preds = a.n_preds;
+    for (int i = 0; i < a.n_preds; ++i) {
+      const int m = mult_of(a.variant[i]);
+      b.pred[i] = a.pred[i]; b.class_mask[i] = a.class_mask[i]; b.n_layers[i] = 3; b.in_hw[i] = H0;
+      for (int l = 0; l < 3; ++l) {
+        b.widths[i][l] = (16 << l) * m;
+        b.wt[i][l] = a.wt_canon[i][l]; b.bias[i][l] = a.b_canon[i][l];
+      }
+      b.fc_w[i] = a.fc_w[i]; b.fc_b[i] = a.fc_b[i]; b.esc_act[i] = a.esc_act[i];
+    }
+    b.esc_stride = a.esc_stride; b.esc_off = a.esc_off; b.esc_cap = a.esc_cap;
+    b.scratch = a.scratch64; b.per_block = a.scratch64_per_block; b.scratch_off = a.scratch64_per_block / 2;
+    b.rest_grid = a.rest_grid; b.q = a.q; b.fr = a.fr;
+    launch_f64_cnn(b, f, grid, s);
     return;
   }
   // FP32: one persistent launch over every queue of the pass.  BF16: one launch per width class
@@ -1122,7 +925,7 @@ void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hip
       b.pred[j] = a.pred[i]; b.variant[j] = a.variant[i]; b.class_mask[j] = a.class_mask[i];
       for (int l = 0; l < 3; ++l) {
         b.w_bf[j][l] = a.w_bf[i][l]; b.w_s3[j][l] = a.w_s3[i][l]; b.bias[j][l] = a.bias[i][l];
-        b.w_canon[j][l] = a.w_canon[i][l]; b.b_canon[j][l] = a.b_canon[i][l]; b.wt_canon[j][l] = a.wt_canon[i][l];
+        b.b_canon[j][l] = a.b_canon[i][l]; b.wt_canon[j][l] = a.wt_canon[i][l];
       }
       b.fc_w[j] = a.fc_w[i]; b.fc_b[j] = a.fc_b[i]; b.esc_act[j] = a.esc_act[i];
     }

@@ -5,64 +5,101 @@
 // 5.3: in queue order (each workgroup takes every gridDim-th tuple), or largest estimated work
 // first (the crop's area, the paper's input-size heuristic) from a shared counter, so that no
 // workgroup is left with a long tail of large crops.
+//
+// The convolutions run on FP64 matrix instructions (conv64.h).  65,536 crops of 64x64 frames, sides
+// log-uniform 2..64, 16-32-64 CNN, largest first: 2.64 ms of kernel time (36 GFLOP; about twice that
+// with the last tile of each layer filled up, most crops being smaller than a tile in layers 2 and
+// 3), against 12.9 ms with one output per thread.  Query 13.85 -> 3.09 ms.
+#include "conv64.h"
 #include "engine.h"
 
 namespace hydro {
 
 constexpr int kCropThreads = 256;
+constexpr int kOrderThreads = 1024;
 constexpr int kCropBuckets = 256;
+// Activations of a crop that fit this many doubles (both ping-pong buffers: crops up to about 26 x 26
+// with the 16-32-64 widths, four in five of a log-uniform side distribution) stay in LDS; 32 KB
+// each leaves room for four workgroups per CU.
+constexpr int kCropLds = 4096;
 
 // One workgroup per crop predicate slot: queue positions in decreasing order of crop area
-// (bucketed: area * 255 / frame area), and the work counter of the following launch reset.
-__global__ __launch_bounds__(kCropThreads) void k_crop_order(CropArgs a) {
+// (bucketed: area * 255 / frame area), and the work counter of the following launch reset.  Bound
+// by the latency of its gathers (entry, then crop): 16 waves and unrolled loops keep them in flight.
+__global__ __launch_bounds__(kOrderThreads) void k_crop_order(CropArgs a) {
   __shared__ int hist[kCropBuckets];
   const int slot = blockIdx.x;
   const int k = a.pred[slot];
   const int c = a.q.counts[k];
-  const int64_t full = (int64_t)a.fh * a.fw;
-  for (int b = threadIdx.x; b < kCropBuckets; b += kCropThreads) hist[b] = 0;
+  const int full = a.fh * a.fw;
+  const uint32_t* ent = a.q.entries + (int64_t)k * a.q.cap;
+  const int2* crops = reinterpret_cast<const int2*>(a.crops);
+  if (threadIdx.x < kCropBuckets) hist[threadIdx.x] = 0;
   if (slot == 0 && threadIdx.x == 0) *a.next = 0;
   __syncthreads();
   auto bucket = [&](int i) {
-    const uint32_t idx = entry_idx(a.q.entries[(int64_t)k * a.q.cap + i]);
-    const int64_t area = (int64_t)a.crops[idx * 4 + 2] * a.crops[idx * 4 + 3];
-    return (kCropBuckets - 1) - (int)(area * (kCropBuckets - 1) / full);   // larger area, smaller bucket
+    const int2 hw = crops[(int64_t)entry_idx(ent[i]) * 2 + 1];
+    return (kCropBuckets - 1) - (int)((int64_t)hw.x * hw.y * (kCropBuckets - 1) / full);   // larger area, smaller bucket
   };
-  for (int i = threadIdx.x; i < c; i += kCropThreads) atomicAdd(&hist[bucket(i)], 1);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < c; i += kOrderThreads) atomicAdd(&hist[bucket(i)], 1);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int b = 0; b < kCropBuckets; ++b) {
-      const int n = hist[b];
-      hist[b] = run;
-      run += n;
+  if (threadIdx.x < kWave) {            // exclusive scan of the 256 counts, four per lane
+    const int lane = threadIdx.x;
+    int v[4], sum = 0;
+    for (int u = 0; u < 4; ++u) {
+      v[u] = sum;
+      sum += hist[4 * lane + u];
     }
+    int inc = sum;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int up = __shfl_up(inc, o);
+      if (lane >= o) inc += up;
+    }
+    for (int u = 0; u < 4; ++u) hist[4 * lane + u] = inc - sum + v[u];
   }
   __syncthreads();
   uint32_t* ord = a.order + (int64_t)slot * a.q.cap;
-  for (int i = threadIdx.x; i < c; i += kCropThreads) ord[atomicAdd(&hist[bucket(i)], 1)] = (uint32_t)i;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < c; i += kOrderThreads) ord[atomicAdd(&hist[bucket(i)], 1)] = (uint32_t)i;
 }
 
-// Normalised input value of the crop at (y, x) (zero padding outside the crop).
-__device__ inline double crop_in(const CropArgs& a, uint32_t idx, int y0, int x0, int h, int w, int y, int x, int ch) {
-  if (y < 0 || x < 0 || y >= h || x >= w) return 0.0;
-  const int64_t o = (int64_t)idx * a.fr.elems + ((int64_t)(y0 + y) * a.fw + (x0 + x)) * 3 + ch;
-  double v;
-  if (a.fr.dtype == HYDRO_DTYPE_BF16) v = (double)(float)static_cast<const __bf16*>(a.fr.base)[o];
-  else if (a.fr.dtype == HYDRO_DTYPE_U8) v = (double)static_cast<const uint8_t*>(a.fr.base)[o] / 255.0;
-  else v = (double)static_cast<const float*>(a.fr.base)[o];
-  return (v - 0.5) * 4.0;
+// All layers of one crop; the activations ping-pong between buf and buf + off.  Returns the last
+// layer's output.
+__device__ inline const double* crop_layers(const CropArgs& a, int slot, const Image64& im, int h, int w, double* buf,
+                                            int64_t off, int wave) {
+  Conv64 L;
+  L.cin = 3;
+  L.hin = h;
+  L.win = w;
+  const int nl = a.n_layers[slot];
+  for (int l = 0; l < nl; ++l) {
+    L.w = a.wt[slot][l];
+    L.bias = a.bias[slot][l];
+    L.cout = crop_pad(a.widths[slot][l]);
+    L.ho = (L.hin + 1) / 2;
+    L.wo = (L.win + 1) / 2;
+    double* out = buf + ((l & 1) ? off : 0);
+    if (l == 0) conv64_wg<true>(L, im, nullptr, out, wave, kCropThreads / 64);
+    else conv64_wg<false>(L, im, buf + ((l & 1) ? 0 : off), out, wave, kCropThreads / 64);
+    __syncthreads();
+    L.hin = L.ho;
+    L.win = L.wo;
+    L.cin = L.cout;
+  }
+  return buf + (((nl - 1) & 1) ? off : 0);
 }
 
-__global__ __launch_bounds__(kCropThreads) void k_crop_cnn(CropArgs a, Forward f) {
-  __shared__ double g_s[256];
-  __shared__ double z_s[kClasses];
+// Four workgroups per CU: 122 VGPRs; left to itself the compiler takes 132, which lets in three
+// (query 3.47 against 3.09 ms).
+__global__ __launch_bounds__(kCropThreads, 4) void k_crop_cnn(CropArgs a, Forward f) {
+  __shared__ __attribute__((aligned(32))) double act_s[kCropLds];
+  __shared__ double part[kCropThreads], g_s[256], z_s[kClasses];
   __shared__ int item_s;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, wave = tid >> 6;
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i) total += a.q.counts[a.pred[i]];
-  double* buf0 = a.scratch + (int64_t)blockIdx.x * 2 * a.act_doubles;
-  double* buf1 = buf0 + a.act_doubles;
+  double* buf = a.scratch + (int64_t)blockIdx.x * 2 * a.act_doubles;
   for (int t0 = blockIdx.x;; t0 += gridDim.x) {
     // the next work item: the queue's t0-th (queue order) or the counter's (largest first)
     if (a.balance) {
@@ -70,7 +107,6 @@ __global__ __launch_bounds__(kCropThreads) void k_crop_cnn(CropArgs a, Forward f
       __syncthreads();
     }
     const int t = a.balance ? item_s : t0;
-    if (a.balance) __syncthreads();          // everyone has read item_s before it changes
     if (t >= total) break;
     int slot = 0, off = t;
     for (int i = 0; i < a.n_preds; ++i) {
@@ -83,64 +119,38 @@ __global__ __launch_bounds__(kCropThreads) void k_crop_cnn(CropArgs a, Forward f
     const uint32_t e = a.q.entries[(int64_t)k * a.q.cap + pos];
     const uint32_t idx = entry_idx(e);
     const unsigned long long c0 = wall_clock64();
-    const int y0 = a.crops[idx * 4], x0 = a.crops[idx * 4 + 1];
-    int hin = a.crops[idx * 4 + 2], win = a.crops[idx * 4 + 3], cin = 3;
-    double* in = nullptr;
-    double* out = buf0;
+    const int4 box = reinterpret_cast<const int4*>(a.crops)[idx];     // y0, x0, h, w
+    const Image64 im = image64(a.fr, idx, a.fw, box.x, box.y);
+    // doubles that the even and the odd layers' outputs take
+    int need0 = 0, need1 = 0, hl = box.z, wl = box.w;
     for (int l = 0; l < a.n_layers[slot]; ++l) {
-      const int ho = (hin + 1) / 2, wo = (win + 1) / 2, co = a.widths[slot][l];
-      const float* W = a.wt[slot][l];
-      const float* B = a.bias[slot][l];
-      for (int o = tid; o < ho * wo * co; o += kCropThreads) {
-        const int oc = o % co, p = o / co, i = p / wo, j = p % wo;
-        double s = 0.0;
-        for (int u = 0; u < 3; ++u)
-          for (int v = 0; v < 3; ++v) {
-            const int y = 2 * i + u - 1, x = 2 * j + v - 1;
-            if (y < 0 || x < 0 || y >= hin || x >= win) continue;
-            const float* wr = W + (int64_t)(u * 3 + v) * cin * co + oc;
-            for (int ch = 0; ch < cin; ++ch) {
-              const double xv = l == 0 ? crop_in(a, idx, y0, x0, hin, win, y, x, ch)
-                                       : in[((int64_t)y * win + x) * cin + ch];
-              s = fma((double)wr[(int64_t)ch * co], xv, s);
-            }
-          }
-        s += (double)B[oc];
-        out[o] = s > 0.0 ? s : 0.0;
-      }
-      __syncthreads();
-      in = out;
-      out = out == buf0 ? buf1 : buf0;
-      hin = ho;
-      win = wo;
-      cin = co;
+      hl = (hl + 1) / 2;
+      wl = (wl + 1) / 2;
+      const int n = hl * wl * crop_pad(a.widths[slot][l]);
+      if (l & 1) need1 = max(need1, n);
+      else need0 = max(need0, n);
     }
-    // mean over the final positions, FC, margin, decision
-    for (int ch = tid; ch < cin; ch += kCropThreads) {
-      double s = 0.0;
-      for (int p = 0; p < hin * win; ++p) s += in[(int64_t)p * cin + ch];
-      g_s[ch] = s / (double)(hin * win);
+    const int C = a.widths[slot][a.n_layers[slot] - 1];
+    if (need0 + need1 <= kCropLds) {
+      const double* act = crop_layers(a, slot, im, box.z, box.w, act_s, need0, wave);
+      head64_wg<kCropThreads>(act, hl * wl, C, crop_pad(C), a.fc_w[slot], a.fc_b[slot], part, g_s, z_s);
+    } else {
+      const double* act = crop_layers(a, slot, im, box.z, box.w, buf, a.act_doubles, wave);
+      head64_wg<kCropThreads>(act, hl * wl, C, crop_pad(C), a.fc_w[slot], a.fc_b[slot], part, g_s, z_s);
     }
-    __syncthreads();
-    if (tid < kClasses) {
-      double z = (double)a.fc_b[slot][tid];
-      for (int ch = 0; ch < cin; ++ch) z = fma(g_s[ch], (double)a.fc_w[slot][ch * kClasses + tid], z);
-      z_s[tid] = z;
-    }
-    __syncthreads();
     if (tid < kWave) {
       const double d = class_margin(z_s, a.class_mask[slot]);
       const bool pass = d > (double)theta_of(f, k, idx);
       forward_decision(f, k, e, tid == 0, false, pass);
       if (tid == 0 && f.count_eval) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - c0));
     }
-    __syncthreads();          // g_s, z_s and the buffers are reused by the next item
+    __syncthreads();          // item_s, z_s and the buffers are reused by the next item
   }
 }
 
 void launch_crop_pass(const CropArgs& a, const Forward& f, int grid, hipStream_t s) {
   if (a.n_preds == 0) return;
-  if (a.balance) hipLaunchKernelGGL(k_crop_order, dim3(a.n_preds), dim3(kCropThreads), 0, s, a);
+  if (a.balance) hipLaunchKernelGGL(k_crop_order, dim3(a.n_preds), dim3(kOrderThreads), 0, s, a);
   hipLaunchKernelGGL(k_crop_cnn, dim3(grid), dim3(kCropThreads), 0, s, a, f);
 }
 

@@ -55,12 +55,12 @@ struct CnnArgs {
   const float* bias[kMaxK][3];      // fp32, layer 1 folded
   const float* fc_w[kMaxK];         // [c_last][10]
   const float* fc_b[kMaxK];
-  const float* w_canon[kMaxK][3];   // [co][ci][3][3]
   const float* b_canon[kMaxK][3];
   float pad_raw;                    // raw frame value that normalises to 0
   const float* wt_canon[kMaxK][3];  // FP64 tier: canonical weights as [co][3][3][ci]
   double* esc_act[kMaxK];           // FP64 tier: per-entry activations (esc_cap entries per slot)
-  int64_t esc_stride;               // doubles per entry
+  int64_t esc_stride;               // doubles per entry: outputs of layers 1 and 3, then layer 2's
+  int64_t esc_off;                  // ... which starts here
   int esc_cap;                      // entries handled layer-parallel; the rest run one per block
   double* scratch64;                // FP64 tier fallback: per-block activation scratch
   int64_t scratch64_per_block;      // doubles
@@ -125,7 +125,9 @@ struct CropArgs {
   uint32_t class_mask[kMaxK];
   int n_layers[kMaxK];
   int widths[kMaxK][HYDRO_MAX_LAYERS];
-  const float* wt[kMaxK][HYDRO_MAX_LAYERS];   // [3][3][ci][co] (output channels last), fp32
+  // fp32 weights [co][3][3][ci] and biases, channel counts padded (crop_pad) with zeros: a padded
+  // channel's activation is zero and its weights are, so the sums are the layer's own
+  const float* wt[kMaxK][HYDRO_MAX_LAYERS];
   const float* bias[kMaxK][HYDRO_MAX_LAYERS];
   const float* fc_w[kMaxK];                    // [c_last][10]
   const float* fc_b[kMaxK];
@@ -140,6 +142,30 @@ struct CropArgs {
   uint32_t* order;             // balance: queue positions by decreasing area, [kMaxK][cap]
   int* next;                   // balance: the launch's work counter (set to 0 by the order kernel)
 };
+// FP64 tier of a pass's CNN predicates (f64.hip).
+struct F64Args {
+  int n_preds;
+  int pred[kMaxK];
+  uint32_t class_mask[kMaxK];
+  int n_layers[kMaxK];
+  int in_hw[kMaxK];
+  int widths[kMaxK][HYDRO_MAX_LAYERS];            // multiples of 16
+  const float* wt[kMaxK][HYDRO_MAX_LAYERS];       // [co][3][3][ci]
+  const float* bias[kMaxK][HYDRO_MAX_LAYERS];
+  const float* fc_w[kMaxK];
+  const float* fc_b[kMaxK];
+  double* esc_act[kMaxK];      // [esc_cap] entries of esc_stride doubles; the even layers' outputs at
+  int64_t esc_stride, esc_off; // 0, the odd ones' at esc_off
+  int esc_cap;
+  double* scratch;             // entries beyond esc_cap: per block, the same at 0 and scratch_off
+  int64_t per_block, scratch_off;
+  int rest_grid;               // blocks with scratch
+  Queues q;
+  FrameSrc fr;
+};
+void launch_f64_cnn(const F64Args& a, const Forward& f, int grid, hipStream_t s);
+
+__host__ __device__ inline int crop_pad(int c) { return (c + 15) & ~15; }   // channels of an MFMA tile
 void launch_crop_pass(const CropArgs& a, const Forward& f, int grid, hipStream_t s);
 
 // Arithmetic tiers of the dedicated 4-layer CNN kernels.

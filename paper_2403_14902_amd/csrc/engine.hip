@@ -965,16 +965,18 @@ static int pack_models(hydro_session* s) {
       for (int l = 0; l < m.n_layers; ++l) {
         const int co = m.widths[l];
         cr.widths[i][l] = co;
-        // [tap][ci][co]: the lanes of a wave, which hold consecutive output channels, read
-        // consecutive weights
-        std::vector<float> wt(hm.cw[l].size());
-        for (int o = 0; o < co; ++o)
+        // [co][tap][ci], channel counts padded to whole MFMA tiles
+        const int cop = crop_pad(co), cip = l == 0 ? 3 : crop_pad(cin);
+        std::vector<float> wt((size_t)cop * 9 * cip, 0.f), bias(cop, 0.f);
+        for (int o = 0; o < co; ++o) {
+          bias[o] = hm.cb[l][o];
           for (int c = 0; c < cin; ++c)
-            for (int t = 0; t < 9; ++t) wt[((size_t)t * cin + c) * co + o] = hm.cw[l][((size_t)o * cin + c) * 9 + t];
+            for (int t = 0; t < 9; ++t) wt[((size_t)o * 9 + t) * cip + c] = hm.cw[l][((size_t)o * cin + c) * 9 + t];
+        }
         float* dp;
         if ((rc = upload(s, wt.data(), wt.size(), &dp))) return rc;
         cr.wt[i][l] = dp;
-        if ((rc = upload(s, hm.cb[l].data(), hm.cb[l].size(), &dp))) return rc;
+        if ((rc = upload(s, bias.data(), bias.size(), &dp))) return rc;
         cr.bias[i][l] = dp;
         cin = co;
       }
@@ -1175,10 +1177,8 @@ static int pack_models(hydro_session* s) {
         }
         if ((rc = upload(s, bias.data(), bias.size(), &dp))) return rc;
         ca.bias[i][l] = dp;
-        if ((rc = upload(s, hm.cw[l].data(), hm.cw[l].size(), &dp))) return rc;
-        ca.w_canon[i][l] = dp;
         {
-          // [co][3][3][ci]: the FP64 tier's lanes walk the input channels of one tap
+          // [co][3][3][ci]: the FP64 tier's lanes read consecutive input channels of one tap
           std::vector<float> wt(hm.cw[l].size());
           for (int o = 0; o < co; ++o)
             for (int c = 0; c < cin; ++c)
@@ -1260,6 +1260,7 @@ static int pack_models(hydro_session* s) {
     for (int i = 0; i < ca.n_preds; ++i) {
       const int m = ca.variant[i] == CNN_W1 ? 1 : ca.variant[i] == CNN_W2 ? 2 : 4;
       ca.esc_stride = std::max<int64_t>(ca.esc_stride, (int64_t)32 * 32 * 16 * m + 16 * 16 * 32 * m);
+      ca.esc_off = std::max<int64_t>(ca.esc_off, (int64_t)32 * 32 * 16 * m);
     }
     ca.esc_cap = esc_cap;
     for (int i = 0; i < ca.n_preds; ++i)
@@ -1499,22 +1500,31 @@ static int session_create(const hydro_model* models, int32_t k, const hydro_poli
   s->out_cap = cap;
   if (!s->crop_preds.empty()) {
     // activations of the largest crop (the whole frame), two buffers per workgroup
-    int64_t act = 0;
+    // (act_raw, w_pad: before and by channel padding, for the allocation-free array's limit)
+    int64_t act = 0, act_raw = 0, w_pad = 0;
     for (int k : s->crop_preds) {
       const hydro_model& m = s->models[k].m;
-      int h = frame_h, w = frame_w;
+      int h = frame_h, w = frame_w, cin = 3;
       for (int l = 0; l < m.n_layers; ++l) {
         h = (h + 1) / 2;
         w = (w + 1) / 2;
-        act = std::max<int64_t>(act, (int64_t)h * w * m.widths[l]);
+        const int co = m.widths[l], cip = l == 0 ? 3 : crop_pad(cin);
+        act = std::max<int64_t>(act, (int64_t)h * w * crop_pad(co));
+        act_raw = std::max<int64_t>(act_raw, (int64_t)h * w * co);
+        w_pad += (int64_t)crop_pad(co) * (9 * cip + 1) - (int64_t)co * (9 * cin + 1);
+        cin = co;
       }
     }
-    // four workgroups per CU (a quarter of what the kernel's registers allow): more hides the
-    // latency of the serial FP64 chains when a round holds many crops, fewer shortens the tail
-    // of the largest crop, which alone bounds a round that holds few
+    // four workgroups per CU, as many as the LDS of k_crop_cnn lets in
     s->crop_grid = s->n_cu * 4;
+    const int64_t act_pad = (act + 31) / 32 * 32;
+    if (s->arena) {
+      // padded channels take no more of the array than the unpadded ones would: fewer workgroups
+      const int64_t budget = (int64_t)s->n_cu * 4 * 2 * ((act_raw + 31) / 32 * 32) * 8 - w_pad * 4 - 8192;
+      s->crop_grid = (int)std::max<int64_t>(1, std::min<int64_t>(s->crop_grid, budget / (2 * act_pad * 8)));
+    }
     CropArgs& ca = s->crop;
-    ca.act_doubles = (act + 31) / 32 * 32;
+    ca.act_doubles = act_pad;
     ca.fh = frame_h;
     ca.fw = frame_w;
     ca.balance = s->pol.balance;
@@ -1717,7 +1727,7 @@ static void enqueue_tier(hydro_session* s, int tier, const FrameSrc& fr, const F
         b.pred[0] = a.pred[i]; b.variant[0] = a.variant[i]; b.class_mask[0] = a.class_mask[i];
         for (int l = 0; l < 3; ++l) {
           b.w_bf[0][l] = a.w_bf[i][l]; b.w_s3[0][l] = a.w_s3[i][l]; b.bias[0][l] = a.bias[i][l];
-          b.w_canon[0][l] = a.w_canon[i][l]; b.b_canon[0][l] = a.b_canon[i][l];
+          b.b_canon[0][l] = a.b_canon[i][l];
         }
         b.fc_w[0] = a.fc_w[i]; b.fc_b[0] = a.fc_b[i];
         b.esc_act[0] = a.esc_act[i];

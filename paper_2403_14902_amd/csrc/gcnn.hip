@@ -8,7 +8,7 @@
 // per-tier scratch (bf16 or fp32, NHWC per frame).  Layer 1 reads the raw frame (bf16 or uint8,
 // exact in bf16) with the normalisation folded into its weights and border taps set to the raw
 // value that normalises to zero.  A head launch pools, applies FC and decides.  The FP64 tier
-// evaluates the same layers with one wave per output activation.
+// is in f64.hip.
 #include "engine.h"
 
 namespace hydro {
@@ -489,179 +489,6 @@ __global__ __launch_bounds__(256) void gcnn_head_kernel(GcnnArgs a, Forward f) {
   }
 }
 
-// ---------------------------------------------------------------- FP64 tier
-__device__ inline double g_frame64(const FrameSrc& fr, uint32_t idx, int hw, int y, int x, int c) {
-  const int64_t o = (int64_t)idx * fr.elems + ((int64_t)y * hw + x) * 3 + c;
-  double v;
-  if (fr.dtype == HYDRO_DTYPE_BF16) v = (double)(float)static_cast<const __bf16*>(fr.base)[o];
-  else v = (double)static_cast<const uint8_t*>(fr.base)[o] / 255.0;
-  return (v - 0.5) * 4.0;
-}
-
-// One wave per output activation of every escalated frame (up to esc_cap per predicate).
-__global__ __launch_bounds__(256) void gconv64_layer_kernel(GcnnArgs a, int layer) {
-  int64_t total = 0;
-  int64_t outs[kMaxK];
-  int ne[kMaxK];
-  for (int i = 0; i < a.n_preds; ++i) {
-    ne[i] = layer < a.n_layers[i] ? min(a.q.counts[a.pred[i]], a.esc_cap) : 0;
-    const int hout = a.in_hw[i] >> (layer + 1);
-    outs[i] = layer < a.n_layers[i] ? (int64_t)hout * hout * a.widths[i][layer] : 0;
-    total += ne[i] * outs[i];
-  }
-  const int lane = threadIdx.x & 63;
-  for (int64_t gi = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); gi < total; gi += (int64_t)gridDim.x * 4) {
-    int slot = 0;
-    int64_t rem = gi;
-    for (int i = 0; i < a.n_preds; ++i) {
-      const int64_t c = ne[i] * outs[i];
-      if (rem < c) { slot = i; break; }
-      rem -= c;
-    }
-    const int e = (int)(rem / outs[slot]);
-    const int oi_all = (int)(rem % outs[slot]);
-    const int cout = a.widths[slot][layer];
-    const int cin = layer == 0 ? 3 : a.widths[slot][layer - 1];
-    const int hin = a.in_hw[slot] >> layer, hout = hin >> 1;
-    const int p = oi_all / cout, o = oi_all % cout, i = p / hout, j = p % hout;
-    const uint32_t idx = entry_idx(a.q.entries[(int64_t)a.pred[slot] * a.q.cap + e]);
-    double* act = a.esc_act[slot] + (int64_t)e * a.esc_stride;
-    const double* in = layer == 0 ? nullptr : act + ((layer - 1) & 1) * a.esc_half;
-    const float* W = a.wt_canon[slot][layer] + (int64_t)o * 9 * cin;   // [co][3][3][ci]
-    double s = 0.0;
-    for (int kk = lane; kk < 9 * cin; kk += 64) {
-      const int t = kk / cin, c = kk % cin;
-      const int y = 2 * i + t / 3 - 1, x = 2 * j + t % 3 - 1;
-      if (y < 0 || x < 0 || y >= hin || x >= hin) continue;
-      const double xv = layer == 0 ? g_frame64(a.fr, idx, hin, y, x, c) : in[((int64_t)y * hin + x) * cin + c];
-      s = fma((double)W[kk], xv, s);
-    }
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) {
-      s += (double)a.b_canon[slot][layer][o];
-      act[(layer & 1) * a.esc_half + (int64_t)p * cout + o] = s > 0.0 ? s : 0.0;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void gcnn64_head_kernel(GcnnArgs a, Forward f) {
-  int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) total += min(a.q.counts[a.pred[i]], a.esc_cap);
-  const int lane = threadIdx.x & 63;
-  for (int base = blockIdx.x * 4; base < total; base += gridDim.x * 4) {
-    const int t = base + (threadIdx.x >> 6);
-    const bool active = t < total;
-    int slot = 0, off = t;
-    for (int i = 0; i < a.n_preds; ++i) {
-      const int c = min(a.q.counts[a.pred[i]], a.esc_cap);
-      if (off < c) { slot = i; break; }
-      off -= c;
-    }
-    if (!active) { slot = 0; off = 0; }
-    const int k = a.pred[slot];
-    const uint32_t e = active ? a.q.entries[(int64_t)k * a.q.cap + off] : 0u;
-    const int L = a.n_layers[slot];
-    const int hl = a.in_hw[slot] >> L, P = hl * hl;
-    const int cl = a.widths[slot][L - 1];
-    double zp[kClasses];
-#pragma unroll
-    for (int c = 0; c < kClasses; ++c) zp[c] = 0.0;
-    if (active) {
-      const double* act = a.esc_act[slot] + (int64_t)off * a.esc_stride + ((L - 1) & 1) * a.esc_half;
-      const float* fw = a.fc_w[slot];
-      for (int ch = lane; ch < cl; ch += 64) {
-        double s = 0.0;
-        for (int p = 0; p < P; ++p) s += act[(int64_t)p * cl + ch];
-        const double gch = s / (double)P;
-#pragma unroll
-        for (int c = 0; c < kClasses; ++c) zp[c] = fma(gch, (double)fw[ch * kClasses + c], zp[c]);
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < kClasses; ++c)
-      for (int o = 32; o >= 1; o >>= 1) zp[c] += __shfl_xor(zp[c], o);
-    bool pass = false;
-    const bool lead = active && lane == 0;
-    if (lead) {
-      double z[kClasses];
-      for (int c = 0; c < kClasses; ++c) z[c] = zp[c] + (double)a.fc_b[slot][c];
-      const uint32_t idx = entry_idx(e);
-      if (f.logits != nullptr)
-        for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)idx * kClasses + c] = z[c];
-      pass = class_margin(z, a.class_mask[slot]) > (double)theta_of(f, k, idx);
-    }
-    if (f.logits == nullptr) forward_decision(f, k, e, lead, false, pass);
-  }
-}
-
-// Escalated entries beyond esc_cap: one workgroup per entry, per-block scratch.
-__global__ __launch_bounds__(256) void gcnn64_rest_kernel(GcnnArgs a, Forward f, double* scratch, int64_t per_block) {
-  const int tid = threadIdx.x;
-  double* buf[2] = {scratch + (int64_t)blockIdx.x * per_block, scratch + (int64_t)blockIdx.x * per_block + per_block / 2};
-  int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) total += max(0, a.q.counts[a.pred[i]] - a.esc_cap);
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    int slot = 0, off = t;
-    for (int i = 0; i < a.n_preds; ++i) {
-      const int c = max(0, a.q.counts[a.pred[i]] - a.esc_cap);
-      if (off < c) { slot = i; break; }
-      off -= c;
-    }
-    off += a.esc_cap;
-    const int k = a.pred[slot];
-    const uint32_t e = a.q.entries[(int64_t)k * a.q.cap + off];
-    const uint32_t idx = entry_idx(e);
-    const int L = a.n_layers[slot];
-    for (int layer = 0; layer < L; ++layer) {
-      const int cout = a.widths[slot][layer];
-      const int cin = layer == 0 ? 3 : a.widths[slot][layer - 1];
-      const int hin = a.in_hw[slot] >> layer, hout = hin >> 1;
-      const double* in = buf[(layer + 1) & 1];
-      double* out = buf[layer & 1];
-      for (int q = tid; q < hout * hout * cout; q += 256) {
-        const int p = q / cout, o = q % cout, i = p / hout, j = p % hout;
-        const float* W = a.wt_canon[slot][layer] + (int64_t)o * 9 * cin;
-        double s = (double)a.b_canon[slot][layer][o];
-        for (int t9 = 0; t9 < 9; ++t9) {
-          const int y = 2 * i + t9 / 3 - 1, x = 2 * j + t9 % 3 - 1;
-          if (y < 0 || x < 0 || y >= hin || x >= hin) continue;
-          for (int c = 0; c < cin; ++c) {
-            const double xv = layer == 0 ? g_frame64(a.fr, idx, hin, y, x, c) : in[((int64_t)y * hin + x) * cin + c];
-            s = fma((double)W[t9 * cin + c], xv, s);
-          }
-        }
-        out[q] = s > 0.0 ? s : 0.0;
-      }
-      __syncthreads();
-    }
-    if (tid < 64) {
-      const int lane = tid;
-      const int hl = a.in_hw[slot] >> L, P = hl * hl, cl = a.widths[slot][L - 1];
-      const double* act = buf[(L - 1) & 1];
-      double zp[kClasses];
-      for (int c = 0; c < kClasses; ++c) zp[c] = 0.0;
-      for (int ch = lane; ch < cl; ch += 64) {
-        double s = 0.0;
-        for (int p = 0; p < P; ++p) s += act[(int64_t)p * cl + ch];
-        const double gch = s / (double)P;
-        for (int c = 0; c < kClasses; ++c) zp[c] = fma(gch, (double)a.fc_w[slot][ch * kClasses + c], zp[c]);
-      }
-      for (int c = 0; c < kClasses; ++c)
-        for (int o = 32; o >= 1; o >>= 1) zp[c] += __shfl_xor(zp[c], o);
-      bool pass = false;
-      if (lane == 0) {
-        double z[kClasses];
-        for (int c = 0; c < kClasses; ++c) z[c] = zp[c] + (double)a.fc_b[slot][c];
-        if (f.logits != nullptr)
-          for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)idx * kClasses + c] = z[c];
-        pass = class_margin(z, a.class_mask[slot]) > (double)theta_of(f, k, idx);
-      }
-      if (f.logits == nullptr) forward_decision(f, k, e, lane == 0, false, pass);
-    }
-    __syncthreads();
-  }
-}
-
 void launch_gcnn_layerwise(const GcnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s);
 
 // ---------------------------------------------------------------- host side
@@ -740,9 +567,20 @@ void launch_gcnn_layerwise(const GcnnArgs& a, const Forward& f, int tier, int gr
   int maxl = 0;
   for (int i = 0; i < a.n_preds; ++i) maxl = a.n_layers[i] > maxl ? a.n_layers[i] : maxl;
   if (tier == TIER_F64) {
-    for (int l = 0; l < maxl; ++l) hipLaunchKernelGGL(gconv64_layer_kernel, dim3(grid * 8), dim3(256), 0, s, a, l);
-    hipLaunchKernelGGL(gcnn64_head_kernel, dim3(grid), dim3(256), 0, s, a, f);
-    hipLaunchKernelGGL(gcnn64_rest_kernel, dim3(a.rest_grid), dim3(256), 0, s, a, f, a.rest_scratch, a.rest_per_block);
+    F64Args b{};
+    b.n_preds = a.n_preds;
+    for (int i = 0; i < a.n_preds; ++i) {
+      b.pred[i] = a.pred[i]; b.class_mask[i] = a.class_mask[i]; b.n_layers[i] = a.n_layers[i]; b.in_hw[i] = a.in_hw[i];
+      for (int l = 0; l < a.n_layers[i]; ++l) {
+        b.widths[i][l] = a.widths[i][l];
+        b.wt[i][l] = a.wt_canon[i][l]; b.bias[i][l] = a.b_canon[i][l];
+      }
+      b.fc_w[i] = a.fc_w[i]; b.fc_b[i] = a.fc_b[i]; b.esc_act[i] = a.esc_act[i];
+    }
+    b.esc_stride = a.esc_stride; b.esc_off = a.esc_half; b.esc_cap = a.esc_cap;
+    b.scratch = a.rest_scratch; b.per_block = a.rest_per_block; b.scratch_off = a.rest_per_block / 2;
+    b.rest_grid = a.rest_grid; b.q = a.q; b.fr = a.fr;
+    launch_f64_cnn(b, f, grid, s);
     return;
   }
   const bool bf = a.prec == HYDRO_PREC_BF16 && tier == TIER_FIRST;
