@@ -31,11 +31,12 @@ struct MlpArgs {
   int64_t part_cap;
   double* esc_h[kMaxK];             // FP64 tier: partial hidden sums [chunk][esc_cap][hidden]
   int esc_cap;
-  float* splitk_ws;                 // split-K partial sums, split_slots tiles of 128 x 128
-  int* split_cnt;                   // per base tile: parts finished (zero between launches)
-  int split_below;                  // launches with fewer (rows x hidden) tiles than this split K
-  int split_target;                 // ... into about this many tiles
+  float* splitk_ws;                 // raw sums of split tiles' parts: split_slots tiles of 128 x 128
   int split_slots;
+  int split_below;                  // >= 0: only launches of fewer tiles split K (-1: no such limit)
+  int n_cu;
+  int bm, bn, bk;                   // the GEMM launch's tile (rows, hidden units) and k-block
+  int units;                        // ... and workgroups resident at once
   Queues q;
   FrameSrc fr;
   DevState* st;
@@ -198,7 +199,7 @@ void gcnn_pack_layer(int layer, int cin, int cout, int prec, const float* w, flo
 constexpr int MLP_TILE_CONFIGS = 4;
 int mlp_f64_chunks(int d_in);    // input chunks of the FP64 MLP hidden pass
 void launch_mlp_pass(const MlpArgs& a, const Forward& f, int tier, int grid, hipStream_t s);
-void launch_mlp_gemm(const MlpArgs& b, int cfg, bool bf, int grid, hipStream_t s);
+void launch_mlp_gemm(MlpArgs& b, int cfg, bool bf, hipStream_t s);
 int mlp_tile_bn(int cfg);
 // Copy every per-predicate field of slot i of src into slot j of dst.
 void mlp_copy_slot(MlpArgs& dst, int j, const MlpArgs& src, int i);

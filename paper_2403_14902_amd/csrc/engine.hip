@@ -1047,14 +1047,10 @@ static int pack_models(hydro_session* s) {
         // split-K workspace shared by the MLP predicates: 1024 tiles of 128 x 128 fp32 (64 MB;
         // 8 MB in allocation-free sessions, which split fewer tiles)
         ma.split_slots = s->arena ? 128 : 1024;
-        // HYDRO_SPLITK_BELOW overrides the tile count under which a launch splits K
+        // HYDRO_SPLITK_BELOW: only launches of fewer tiles split K (tests; 0: none does)
         const char* sb = getenv("HYDRO_SPLITK_BELOW");
-        ma.split_below = (sb && *sb) ? atoi(sb) : s->n_cu / 2;
-        ma.split_target = 2 * s->n_cu;
+        ma.split_below = (sb && *sb) ? std::max(0, atoi(sb)) : -1;
         if ((rc = sess_alloc(s, (void**)&ma.splitk_ws, (size_t)ma.split_slots * 128 * 128 * sizeof(float)))) return rc;
-        if ((rc = sess_alloc(s, (void**)&ma.split_cnt, (size_t)ma.split_slots * sizeof(int)))) return rc;
-        HIP_TRY(hipMemsetAsync(ma.split_cnt, 0, (size_t)ma.split_slots * sizeof(int), s->stream));
-        HIP_TRY(hipStreamSynchronize(s->stream));
       }
       {
         // HYDRO_MLP_TILE forces one tile configuration (tests exercise each)
@@ -1199,6 +1195,7 @@ static int pack_models(hydro_session* s) {
     }
   }
   ma.esc_cap = esc_cap;
+  ma.n_cu = s->n_cu;
   if (s->gcnn.n_preds > 0) {
     GcnnArgs& ga = s->gcnn;
     ga.pad_raw = pad_raw;
@@ -1840,9 +1837,13 @@ static int autotune_mlp(hydro_session* s) {
       float best_ms = 1e30f;
       for (int cfg = 0; cfg < MLP_TILE_CONFIGS; ++cfg) {
         const bool bf = s->pol.precision == HYDRO_PREC_BF16;
-        launch_mlp_gemm(b, cfg, bf, s->n_cu * 4, st);
+        MlpArgs c = b;
+        launch_mlp_gemm(c, cfg, bf, st);
         HIP_TRY(hipEventRecord(e0, st));
-        for (int rep = 0; rep < 3; ++rep) launch_mlp_gemm(b, cfg, bf, s->n_cu * 4, st);
+        for (int rep = 0; rep < 3; ++rep) {
+          c = b;
+          launch_mlp_gemm(c, cfg, bf, st);
+        }
         HIP_TRY(hipEventRecord(e1, st));
         HIP_TRY(hipEventSynchronize(e1));
         float ms = 0;

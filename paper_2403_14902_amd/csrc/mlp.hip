@@ -35,20 +35,132 @@ __device__ inline void load_frame_run(const FrameSrc& fr, uint32_t idx, int64_t 
   for (int j = 0; j < N; ++j) out[j] = static_cast<T>((float)buf[j]);
 }
 
-// Split-K: when a launch has fewer (rows x hidden) tiles than split_below (small queues, e.g.
-// the re-score bands), every tile's K range is divided into S parts computed by different
-// workgroups, S ~ split_target / tiles.  Each part stores its raw sums in the workspace and
-// counts itself in the tile's counter; the part that arrives last adds the S sums in split order
-// (deterministic whichever part is last), resets the counter and runs the usual epilogue.  S is
-// a pure function of the queue counts.
-constexpr int SPLIT_MAX = 8;
-__device__ inline int mlp_splits(int base_total, int nk_min, const MlpArgs& a) {
-  if (a.splitk_ws == nullptr || base_total <= 0 || base_total >= a.split_below) return 1;
-  int sp = (a.split_target + base_total - 1) / base_total;
-  sp = min(sp, SPLIT_MAX);
-  sp = min(sp, a.split_slots / base_total);
-  sp = min(sp, nk_min / 4);
-  return max(sp, 1);
+// How a GEMM launch is cut into work units.  Its (rows x hidden) tiles fill the GPU's resident
+// workgroups (MlpArgs::units of them) a whole number of times; the tiles that are left over, or
+// all of them in a short launch (a re-score band, a late round), are split along K into S parts
+// each, so that they fill the GPU once more.  A whole tile ends in partial logits; a part stores its
+// raw sums in the workspace, and the head kernel, which runs next on the stream, adds a tile's parts
+// in order (so the result does not depend on which part finished first, and no part waits for or
+// signals another).  S is a power of two and a function of the queue counts alone.
+// Against splitting only launches of less than half a CU's tile each, by parts that counted
+// themselves and left the sum to the last one to arrive (a device-scope fence per part): the FP32
+// band of a 3,072-input query 84 + 7 (head) -> 28 + 18 us a round; the six-MLP query (131,072 x 12,288
+// bf16) 9.7 -> 6.5 ms together with the XCD order below.
+constexpr int SPLIT_MAX = 16;
+constexpr int SPLIT_MIN_K = 4;       // k-blocks per part, at least
+struct MlpPlan { int full, rest, S, units; };
+__device__ inline MlpPlan mlp_plan(const MlpArgs& a) {
+  int tiles = 0, nk = 1 << 30;
+  for (int i = 0; i < a.n_preds; ++i) {
+    tiles += ((a.q.counts[a.pred[i]] + a.bm - 1) / a.bm) * (a.hidden[i] / a.bn);
+    nk = min(nk, a.d_in[i] / a.bk);
+  }
+  MlpPlan p{tiles, 0, 1, tiles};
+  const bool may = a.split_below < 0 || tiles < a.split_below;
+  const int full = tiles / a.units * a.units, rest = tiles - full;
+  if (may && a.splitk_ws != nullptr && rest > 0) {
+    const int most = min(min(a.units / rest, SPLIT_MAX), min(a.split_slots / rest, nk / SPLIT_MIN_K));
+    int S = 1;
+    while (2 * S <= most) S *= 2;
+    if (S > 1) p = MlpPlan{full, rest, S, full + rest * S};
+  }
+  return p;
+}
+
+// Work unit u: its tile, K range and workspace tile (ws < 0: a whole tile).  Consecutive workgroups
+// go to the eight XCDs in turn, each with an L2 of its own; units are dealt so that every XCD gets
+// consecutive tiles, whose hidden-unit tiles (the fastest index) read the same frame rows: each
+// row then comes from HBM once, not once per XCD (8,192 x 12,288 bf16 rows x 2,048 units: 1,105 TFLOP/s;
+// tiles dealt in turn averaged 494 over the six-MLP query's launches, now 780 with its short ones).
+struct MlpUnit { int slot, mt, nt, kb0, kb1, ws; };
+__device__ inline MlpUnit mlp_unit(const MlpArgs& a, const MlpPlan& p, int u) {
+  const int base = u < p.full ? u / a.units * a.units : p.full;
+  const int n = min(a.units, (u < p.full ? p.full : p.units) - base), v = u - base;
+  const int x = v & 7, each = n >> 3, more = n & 7;
+  const int w = base + x * each + min(x, more) + (v >> 3);
+  int t = w, part = 0;
+  MlpUnit m;
+  m.ws = -1;
+  if (w >= p.full && p.S > 1) {
+    t = p.full + (w - p.full) % p.rest;
+    part = (w - p.full) / p.rest;
+    m.ws = (t - p.full) * p.S + part;
+  }
+  m.slot = m.mt = m.nt = 0;
+  for (int i = 0; i < a.n_preds; ++i) {
+    const int n_nt = a.hidden[i] / a.bn;
+    const int tiles = ((a.q.counts[a.pred[i]] + a.bm - 1) / a.bm) * n_nt;
+    if (t < tiles) {
+      m.slot = i;
+      m.mt = t / n_nt;
+      m.nt = t % n_nt;
+      break;
+    }
+    t -= tiles;
+  }
+  const int nk = a.d_in[m.slot] / a.bk;
+  m.kb0 = m.ws < 0 ? 0 : (int)((int64_t)nk * part / p.S);
+  m.kb1 = m.ws < 0 ? nk : (int)((int64_t)nk * (part + 1) / p.S);
+  return m;
+}
+
+// End of a unit for one wave, which holds rows row0 + 16 i + 4 g + r and hidden units col0 + 16 j + l16
+// of the tile in acc[i][j][r].  A part: raw sums to the workspace, [column][row], four consecutive rows
+// per store.  A whole tile: H = ReLU(acc + b1'), partial logits over the wave's hidden units, lane
+// l16 storing class l16 of each row.
+template <int BM, int BN, int MT, int NT>
+__device__ inline void mlp_finish(const MlpArgs& a, const MlpUnit& m, floatx4 (&acc)[MT][NT], int row0, int col0) {
+  const int lane = lane_id(), g = lane >> 4, l16 = lane & 15;
+  if (m.ws >= 0) {
+    float* wt = a.splitk_ws + (int64_t)m.ws * (BM * BN);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        *reinterpret_cast<float4*>(&wt[(col0 + j * 16 + l16) * BM + row0 + i * 16 + 4 * g]) =
+            make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+    return;
+  }
+  const float* b1 = a.b1_fold[m.slot];
+  const float* w2 = a.w2[m.slot];
+  const int cnt = a.q.counts[a.pred[m.slot]];
+  const int c0 = m.nt * BN + col0 + l16;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const float bb = b1[c0 + j * 16];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = fmaxf(acc[i][j][r] + bb, 0.f);
+  }
+  float zv[MT][4];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) zv[i][r] = 0.f;
+  for (int c = 0; c < kClasses; ++c) {
+    float w2v[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) w2v[j] = w2[(c0 + j * 16) * kClasses + c];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) s += acc[i][j][r] * w2v[j];
+        s = row_sum16(s);
+        zv[i][r] = l16 == c ? s : zv[i][r];
+      }
+  }
+  float* part = a.partial[m.slot] + (int64_t)((m.nt * BN + col0) / (16 * NT)) * a.part_cap * kClasses;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int rr = m.mt * BM + row0 + i * 16 + 4 * g + r;
+      if (l16 < kClasses && rr < cnt) part[(int64_t)rr * kClasses + l16] = zv[i][r];
+    }
 }
 
 // Tile shapes (rows of queued tuples x hidden units) an autotuner may pick per predicate.
@@ -63,40 +175,16 @@ __global__ __launch_bounds__(256) void mlp_gemm_kernel(MlpArgs a) {
   constexpr int FM = WM / 16, FN = WN / 16;       // MFMA tiles per wave
   __shared__ __attribute__((aligned(16))) T As[2][BM * LD];
   __shared__ __attribute__((aligned(16))) T Bs[2][BN * LD];
-  __shared__ int s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int ar = tid / TPA, ak = (tid % TPA) * PA;   // this thread's frame row in the tile, k offset
   const int br = tid / TPB, bk = (tid % TPB) * PB;   // this thread's weight row in the tile, k offset
 
-  int base_total = 0, nk_min = 1 << 30;
-  for (int i = 0; i < a.n_preds; ++i) {
-    const int cnt = a.q.counts[a.pred[i]];
-    base_total += ((cnt + BM - 1) / BM) * (a.hidden[i] / BN);
-    nk_min = min(nk_min, a.d_in[i] / BK);
-  }
-  const int S = mlp_splits(base_total, nk_min, a);
-  const int total = base_total * S;
-
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    const int tb = t / S, sp = t % S;
-    int slot = 0, mt = 0, nt = 0;
-    {
-      int acc0 = 0;
-      for (int i = 0; i < a.n_preds; ++i) {
-        const int cnt = a.q.counts[a.pred[i]];
-        const int n_nt = a.hidden[i] / BN;
-        const int tiles = ((cnt + BM - 1) / BM) * n_nt;
-        if (tb < acc0 + tiles) {
-          slot = i;
-          mt = (tb - acc0) / n_nt;
-          nt = (tb - acc0) % n_nt;
-          break;
-        }
-        acc0 += tiles;
-      }
-    }
+  const MlpPlan plan = mlp_plan(a);
+  for (int u = blockIdx.x; u < plan.units; u += gridDim.x) {
+    const MlpUnit m = mlp_unit(a, plan, u);
+    const int slot = m.slot, mt = m.mt, nt = m.nt;
     const int k = a.pred[slot];
     const int cnt = a.q.counts[k];
     const int D = a.d_in[slot];
@@ -165,8 +253,7 @@ __global__ __launch_bounds__(256) void mlp_gemm_kernel(MlpArgs a) {
       }
     };
 
-    const int nk_all = D / BK;
-    const int kt0 = (int)((int64_t)nk_all * sp / S), nk = (int)((int64_t)nk_all * (sp + 1) / S);
+    const int kt0 = m.kb0, nk = m.kb1;
 #pragma unroll
     for (int u = 0; u < NS - 1; ++u)
       if (kt0 + u < nk) gload(kt0 + u, u);
@@ -190,133 +277,130 @@ __global__ __launch_bounds__(256) void mlp_gemm_kernel(MlpArgs a) {
       }
     }
 
-    if (S > 1) {
-      // raw sums of this K range: ws[tb][sp][column in tile][row in tile], each lane's four
-      // consecutive rows in one 16-byte store
-      float* wt = a.splitk_ws + (int64_t)tb * S * (BM * BN);
-      auto at = [&](int q, int i, int j) -> float4* {
-        return reinterpret_cast<float4*>(
-            &wt[(int64_t)q * (BM * BN) + (wn * WN + j * 16 + (lane & 15)) * BM + wm * WM + i * 16 + 4 * (lane >> 4)]);
-      };
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) *at(sp, i, j) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-      __threadfence();
-      __syncthreads();
-      if (tid == 0) s_last = atomicAdd(&a.split_cnt[tb], 1) == S - 1;
-      __syncthreads();
-      if (!s_last) {
-        if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
-        continue;
-      }
-      __threadfence();
-      if (tid == 0) a.split_cnt[tb] = 0;      // ready for the next launch
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          floatx4 sum = (floatx4){0.f, 0.f, 0.f, 0.f};
-          for (int q = 0; q < S; ++q) {
-            float4 v;
-            if (q == sp) v = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-            else v = *at(q, i, j);
-            sum[0] += v.x; sum[1] += v.y; sum[2] += v.z; sum[3] += v.w;
-          }
-          acc[i][j] = sum;
-        }
-    }
-    // epilogue: H = ReLU(acc + b1'), partial logits over this wave's WN hidden columns
-    const float* b1 = a.b1_fold[slot];
-    const float* w2 = a.w2[slot];
-    const int col0 = nt * BN + wn * WN + (lane & 15);
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const float bb = b1[col0 + j * 16];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] = fmaxf(acc[i][j][r] + bb, 0.f);
-    }
-    float* part = a.partial[slot] + ((int64_t)(nt * 2 + wn) * a.part_cap) * kClasses;
-    for (int c = 0; c < kClasses; ++c) {
-      float w2v[FN];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) w2v[j] = w2[(col0 + j * 16) * kClasses + c];
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float s = 0.f;
-#pragma unroll
-          for (int j = 0; j < FN; ++j) s += acc[i][j][r] * w2v[j];
-          s = row_sum16(s);
-          const int rr = mt * BM + wm * WM + i * 16 + 4 * (lane >> 4) + r;
-          if ((lane & 15) == 0 && rr < cnt) part[(int64_t)rr * kClasses + c] = s;
-        }
-    }
+    mlp_finish<BM, BN, FM, FN>(a, m, acc, wm * WM, wn * WN);
     __syncthreads();
     if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
   }
 }
 
-// Head: z = b2 + sum of partial logits; margin; decision / deferral; forwarding.
+// GEMM2 of one row's hidden units c = cg, cg + ng, ... of a split tile.  Every part of a column, and
+// four columns at a time, are requested before the first is used: the parts come from other
+// XCDs' writes, past the L2, and their latency is all that this costs.
+template <int S>
+__device__ inline void mlp_split_cols(const float* wt, int64_t tsz, int bm, int bn, int cg, int ng, const float* b1,
+                                      const float* w2, float (&z)[kClasses]) {
+  constexpr int CU = S >= 16 ? 2 : 4;
+  for (int c0 = cg; c0 < bn; c0 += CU * ng) {        // bn is a multiple of CU * ng
+    float v[CU][S];
+#pragma unroll
+    for (int u = 0; u < CU; ++u)
+#pragma unroll
+      for (int p = 0; p < S; ++p) v[u][p] = wt[(int64_t)p * tsz + (int64_t)(c0 + u * ng) * bm];
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int c = c0 + u * ng;
+      float h = 0.f;
+#pragma unroll
+      for (int p = 0; p < S; ++p) h += v[u][p];
+      h = fmaxf(h + b1[c], 0.f);
+      const float2* w = reinterpret_cast<const float2*>(w2 + (int64_t)c * kClasses);
+#pragma unroll
+      for (int cc = 0; cc < kClasses / 2; ++cc) {
+        const float2 x = w[cc];
+        z[2 * cc] = fmaf(h, x.x, z[2 * cc]);
+        z[2 * cc + 1] = fmaf(h, x.y, z[2 * cc + 1]);
+      }
+    }
+  }
+}
+
+// Head: z = b2 + the partial logits of the whole tiles + GEMM2 of the split ones (their parts added in
+// order, then bias and ReLU); margin; decision / deferral; forwarding.  One workgroup per RG rows of
+// one predicate: 64, or 16 when those would leave CUs idle (a re-score band), since a split tile's
+// parts are most of what it reads.  Thread (row, group): the groups share a row's hidden units.
 __global__ __launch_bounds__(256) void mlp_head_kernel(MlpArgs a, Forward f) {
+  __shared__ float zs[256 * kClasses];
+  const int tid = threadIdx.x;
+  const MlpPlan plan = mlp_plan(a);
+  int groups64 = 0;
+  for (int i = 0; i < a.n_preds; ++i) groups64 += (a.q.counts[a.pred[i]] + 63) / 64;
+  const int RG = groups64 < a.n_cu ? 16 : 64, ng = 256 / RG;
+  const int row = tid & (RG - 1), cg = tid / RG;
   int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) total += a.q.counts[a.pred[i]];
-  const int stride = gridDim.x * blockDim.x;
-  for (int base = blockIdx.x * blockDim.x; base < total; base += stride) {
-    int g = base + threadIdx.x;
-    bool active = g < total;
-    // find predicate slot (uniform work per lane; K <= 8)
-    int slot = 0, off = g;
+  for (int i = 0; i < a.n_preds; ++i) total += (a.q.counts[a.pred[i]] + RG - 1) / RG;
+  for (int t = blockIdx.x; t < total; t += gridDim.x) {
+    int slot = 0, off = t, tile0 = 0;         // tile0: the slot's first tile in the launch's order
     for (int i = 0; i < a.n_preds; ++i) {
-      int c = a.q.counts[a.pred[i]];
-      if (off < c || i == a.n_preds - 1) { slot = i; break; }
+      const int cnt = a.q.counts[a.pred[i]], c = (cnt + RG - 1) / RG;
+      slot = i;
+      if (off < c) break;
       off -= c;
+      tile0 += ((cnt + a.bm - 1) / a.bm) * (a.hidden[i] / a.bn);
     }
-    int k = a.pred[slot];
-    uint32_t e = 0;
-    bool pass = false, defer = false;
-    if (active) {
-      e = a.q.entries[(int64_t)k * a.q.cap + off];
-      float z[kClasses];
-      const float* b2 = a.b2[slot];
+    const int k = a.pred[slot], cnt = a.q.counts[k];
+    const int rr = off * RG + row, rc = min(rr, cnt - 1);
+    const int n_nt = a.hidden[slot] / a.bn, mt = off * RG / a.bm;
+    const int first = tile0 + mt * n_nt;      // this row group's tiles: first .. first + n_nt - 1
+    float z[kClasses];
 #pragma unroll
-      for (int c = 0; c < kClasses; ++c) z[c] = b2[c];
-      const int parts = a.hidden[slot] / a.part_w[slot];
-      const float* part = a.partial[slot];
-      for (int p = 0; p < parts; ++p) {
-        const float* pp = part + ((int64_t)p * a.part_cap + off) * kClasses;
+    for (int c = 0; c < kClasses; ++c) z[c] = 0.f;
+    const int whole = plan.S > 1 ? max(0, min(n_nt, plan.full - first)) : n_nt;
+    const int ppt = a.bn / a.part_w[slot];    // partial-logit parts per tile
+    for (int p = cg; p < whole * ppt; p += ng) {
+      const float2* pp = reinterpret_cast<const float2*>(a.partial[slot] + ((int64_t)p * a.part_cap + rc) * kClasses);
 #pragma unroll
-        for (int c = 0; c < kClasses; ++c) z[c] += pp[c];
+      for (int c = 0; c < kClasses / 2; ++c) {
+        const float2 v = pp[c];
+        z[2 * c] += v.x;
+        z[2 * c + 1] += v.y;
       }
-      if (f.logits != nullptr) {
-        for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)entry_idx(e) * kClasses + c] = (double)z[c];
-        continue;
+    }
+    const float* b1 = a.b1_fold[slot];
+    const float* w2 = a.w2[slot];
+    const int64_t tsz = (int64_t)a.bm * a.bn;
+    for (int nt = whole; nt < n_nt; ++nt) {
+      const float* wt = a.splitk_ws + (int64_t)(first + nt - plan.full) * plan.S * tsz + (rc - mt * a.bm);
+      const float *tb1 = b1 + nt * a.bn, *tw2 = w2 + (int64_t)nt * a.bn * kClasses;
+      if (plan.S == 2) mlp_split_cols<2>(wt, tsz, a.bm, a.bn, cg, ng, tb1, tw2, z);
+      else if (plan.S == 4) mlp_split_cols<4>(wt, tsz, a.bm, a.bn, cg, ng, tb1, tw2, z);
+      else if (plan.S == 8) mlp_split_cols<8>(wt, tsz, a.bm, a.bn, cg, ng, tb1, tw2, z);
+      else mlp_split_cols<16>(wt, tsz, a.bm, a.bn, cg, ng, tb1, tw2, z);
+    }
+#pragma unroll
+    for (int c = 0; c < kClasses; ++c) zs[c * 256 + tid] = z[c];
+    __syncthreads();
+    if (tid < kWave) {
+      const bool active = tid < RG && rr < cnt;
+      const uint32_t e = active ? a.q.entries[(int64_t)k * a.q.cap + rr] : 0u;
+      bool pass = false, defer = false;
+      if (active) {
+        const float* b2 = a.b2[slot];
+#pragma unroll
+        for (int c = 0; c < kClasses; ++c) {
+          float s = b2[c];
+          for (int g = 0; g < ng; ++g) s += zs[c * 256 + g * RG + row];
+          z[c] = s;
+        }
+        if (f.logits != nullptr) {
+          for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)entry_idx(e) * kClasses + c] = (double)z[c];
+        } else {
+          const float d = class_margin(z, a.class_mask[slot]), th = theta_of(f, k, entry_idx(e));
+          defer = f.defer.entries != nullptr && fabsf(d - th) < f.tau[k];
+          pass = d > th;
+        }
       }
-      float d = class_margin(z, a.class_mask[slot]);
-      float th = theta_of(f, k, entry_idx(e));
-      float gap = d - th;
-      defer = f.defer.entries != nullptr && fabsf(gap) < f.tau[k];
-      pass = d > th;
+      if (f.logits == nullptr) forward_decision(f, k, e, active, defer, pass);
     }
-    if (f.logits != nullptr) continue;
-    // all lanes of every wave reach this point; k differs per lane only at predicate seams,
-    // so forward per distinct k present in the wave
-    for (int i = 0; i < a.n_preds; ++i) {
-      int kk = a.pred[i];
-      if (__ballot(active && k == kk) == 0) continue;
-      forward_decision(f, kk, e, active && k == kk, defer, pass);
-    }
+    __syncthreads();           // zs is reused by the next group
   }
 }
 
 // FP64 tier: frames normalised in fp64 exactly as defined; canonical fp32 weights widened to
 // fp64.  The first esc_cap escalated entries of each predicate are evaluated across many
 // workgroups: work item = (predicate, group of 8 entries, 256 hidden units, 256-long chunk of
-// the input) -> partial hidden sums; a head (one wave per entry) adds the chunks, applies
-// ReLU, GEMM2, the margin and the decision.  Entries beyond esc_cap run one group per block.
+// the input) -> partial hidden sums; a second launch adds the chunks (one workgroup per entry:
+// with one wave, H / 64 x D / 256 dependent loads took up to 0.3 ms of a round), applies ReLU, GEMM2,
+// the margin and the decision.  Entries beyond esc_cap run there, one group per block.
 constexpr int F64_B = 8;
 constexpr int F64_DCH = 256;
 int mlp_f64_chunks(int d_in) { return (d_in + F64_DCH - 1) / F64_DCH; }
@@ -391,69 +475,62 @@ __global__ __launch_bounds__(256) void mlp_f64_hidden_kernel(MlpArgs a) {
   }
 }
 
-__device__ inline void mlp_head64(const MlpArgs& a, const Forward& f, int slot, uint32_t e, int ei, bool active) {
-  const int lane = threadIdx.x & 63;
-  const int k = a.pred[slot];
-  const int D = a.d_in[slot], H = a.hidden[slot];
-  const int nch = (D + F64_DCH - 1) / F64_DCH;
-  double zp[kClasses];
-#pragma unroll
-  for (int c = 0; c < kClasses; ++c) zp[c] = 0.0;
-  if (active) {
-    const float* b1 = a.b1_canon[slot];
-    const float* w2 = a.w2[slot];
-    for (int j = lane; j < H; j += 64) {
-      double h = (double)b1[j];
-      for (int c = 0; c < nch; ++c) h += a.esc_h[slot][((int64_t)c * a.esc_cap + ei) * H + j];
-      h = h > 0.0 ? h : 0.0;
-#pragma unroll
-      for (int c = 0; c < kClasses; ++c) zp[c] = fma(h, (double)w2[j * kClasses + c], zp[c]);
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < kClasses; ++c)
-    for (int o = 32; o >= 1; o >>= 1) zp[c] += __shfl_xor(zp[c], o);
-  const uint32_t idx = entry_idx(e);
-  const bool lead = active && lane == 0;
-  bool pass = false;
-  if (lead) {
-    double z[kClasses];
-    for (int c = 0; c < kClasses; ++c) z[c] = (double)a.b2[slot][c] + zp[c];
-    if (f.logits != nullptr)
-      for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)idx * kClasses + c] = z[c];
-    pass = class_margin(z, a.class_mask[slot]) > (double)theta_of(f, k, idx);
-  }
-  if (f.logits == nullptr) forward_decision(f, k, e, lead, false, pass);
-}
+// Decisions of the layer-parallel entries; entries beyond esc_cap: groups of 4 per block, the whole
+// input and hidden width in one block.
+constexpr int R64_B = 4;
+constexpr int R64_DCH = 256;
 
-__global__ __launch_bounds__(256) void mlp_f64_head_kernel(MlpArgs a, Forward f) {
-  int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) total += min(a.q.counts[a.pred[i]], a.esc_cap);
-  const int wave = threadIdx.x >> 6;
-  for (int base = blockIdx.x * 4; base < total; base += gridDim.x * 4) {
-    const int t = base + wave;
-    const bool active = t < total;
+__global__ __launch_bounds__(256) void mlp_f64_entry_kernel(MlpArgs a, Forward f) {
+  __shared__ double xs[R64_B][R64_DCH];
+  __shared__ double zred[4][R64_B][kClasses];
+  __shared__ uint32_t ents[R64_B];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the layer-parallel entries: their hidden units' chunk sums added, ReLU, GEMM2, decision
+  int heads = 0;
+  for (int i = 0; i < a.n_preds; ++i) heads += min(a.q.counts[a.pred[i]], a.esc_cap);
+  for (int t = blockIdx.x; t < heads; t += gridDim.x) {
     int slot = 0, off = t;
     for (int i = 0; i < a.n_preds; ++i) {
       const int c = min(a.q.counts[a.pred[i]], a.esc_cap);
       if (off < c) { slot = i; break; }
       off -= c;
     }
-    if (!active) { slot = 0; off = 0; }
-    const uint32_t e = active ? a.q.entries[(int64_t)a.pred[slot] * a.q.cap + off] : 0u;
-    mlp_head64(a, f, slot, e, off, active);
+    const int k = a.pred[slot], D = a.d_in[slot], H = a.hidden[slot];
+    const int nch = (D + F64_DCH - 1) / F64_DCH;
+    double zp[kClasses];
+#pragma unroll
+    for (int c = 0; c < kClasses; ++c) zp[c] = 0.0;
+    for (int j = tid; j < H; j += 256) {
+      double h = (double)a.b1_canon[slot][j];
+      const double* hp = a.esc_h[slot] + (int64_t)off * H + j;
+#pragma unroll 16
+      for (int c = 0; c < nch; ++c) h += hp[(int64_t)c * a.esc_cap * H];
+      h = h > 0.0 ? h : 0.0;
+#pragma unroll
+      for (int c = 0; c < kClasses; ++c) zp[c] = fma(h, (double)a.w2[slot][j * kClasses + c], zp[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < kClasses; ++c) {
+      for (int o = 32; o >= 1; o >>= 1) zp[c] += __shfl_xor(zp[c], o);
+      if (lane == 0) zred[wave][0][c] = zp[c];
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const uint32_t e = a.q.entries[(int64_t)k * a.q.cap + off];
+      const uint32_t idx = entry_idx(e);
+      bool pass = false;
+      if (lane == 0) {
+        double z[kClasses];
+        for (int c = 0; c < kClasses; ++c)
+          z[c] = (double)a.b2[slot][c] + ((zred[0][0][c] + zred[1][0][c]) + (zred[2][0][c] + zred[3][0][c]));
+        if (f.logits != nullptr)
+          for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)idx * kClasses + c] = z[c];
+        pass = class_margin(z, a.class_mask[slot]) > (double)theta_of(f, k, idx);
+      }
+      if (f.logits == nullptr) forward_decision(f, k, e, lane == 0, false, pass);
+    }
+    __syncthreads();
   }
-}
-
-// Entries beyond esc_cap: groups of 4 per block, the whole input and hidden width in one block.
-constexpr int R64_B = 4;
-constexpr int R64_DCH = 256;
-
-__global__ __launch_bounds__(256) void mlp_f64_rest_kernel(MlpArgs a, Forward f) {
-  __shared__ double xs[R64_B][R64_DCH];
-  __shared__ double zred[4][R64_B][kClasses];
-  __shared__ uint32_t ents[R64_B];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i) total += (max(0, a.q.counts[a.pred[i]] - a.esc_cap) + R64_B - 1) / R64_B;
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
@@ -554,8 +631,7 @@ int mlp_tile_bn(int cfg) { return cfg == 0 || cfg == 1 ? 128 : 64; }
 // tile, eight waves of 64 x 64.  Each k-block (64 elements: 128 bytes of every frame row and
 // weight row) is copied global -> LDS with global_load_lds_dwordx4 into a three-stage ring, one
 // barrier per k-block; the 16-byte chunks of row r sit at slot chunk ^ (r mod 8), so the MFMA
-// operand reads of 16 rows spread over the banks.  Split-K and the epilogue as in
-// mlp_gemm_kernel (workspace tiles of 256 x 128: the launch passes half the 128 x 128 slots).
+// operand reads of 16 rows spread over the banks.
 constexpr int MD_BM = 256, MD_BN = 128, MD_NS = 3;
 __global__ __launch_bounds__(512) void mlp_gemm_dma_kernel(MlpArgs a) {
   constexpr int UPR = 8, ROWB = 128, BKE = 64;             // 16-byte units per row, bytes, elements
@@ -565,40 +641,16 @@ __global__ __launch_bounds__(512) void mlp_gemm_dma_kernel(MlpArgs a) {
   constexpr int WM = 64, WN = 64, MT = WM / 16, NT = WN / 16;
   static_assert(UNITS % 512 == 0 && (MD_BM * UPR) % 512 == 0, "stage rows fill the waves' loads");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[MD_NS * STAGE];
-  __shared__ int s_last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
   const int wm = wave & 3, wn = wave >> 2;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
   const int u_slot = lane % UPR;
 
-  int base_total = 0, nk_min = 1 << 30;
-  for (int i = 0; i < a.n_preds; ++i) {
-    const int cnt = a.q.counts[a.pred[i]];
-    base_total += ((cnt + MD_BM - 1) / MD_BM) * (a.hidden[i] / MD_BN);
-    nk_min = min(nk_min, a.d_in[i] / BKE);
-  }
-  const int S = mlp_splits(base_total, nk_min, a);
-  const int total = base_total * S;
-
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    const int tb = t / S, sp = t % S;
-    int slot = 0, mt = 0, nt = 0;
-    {
-      int acc0 = 0;
-      for (int i = 0; i < a.n_preds; ++i) {
-        const int cnt = a.q.counts[a.pred[i]];
-        const int n_nt = a.hidden[i] / MD_BN;
-        const int tiles = ((cnt + MD_BM - 1) / MD_BM) * n_nt;
-        if (tb < acc0 + tiles) {
-          slot = i;
-          mt = (tb - acc0) / n_nt;
-          nt = (tb - acc0) % n_nt;
-          break;
-        }
-        acc0 += tiles;
-      }
-    }
+  const MlpPlan plan = mlp_plan(a);
+  for (int u = blockIdx.x; u < plan.units; u += gridDim.x) {
+    const MlpUnit m = mlp_unit(a, plan, u);
+    const int slot = m.slot, mt = m.mt, nt = m.nt;
     const int k = a.pred[slot];
     const int cnt = a.q.counts[k];
     const int D = a.d_in[slot];
@@ -657,8 +709,7 @@ __global__ __launch_bounds__(512) void mlp_gemm_dma_kernel(MlpArgs a) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.a[i], fr.b[j], acc[i][j], 0, 0, 0);
     };
 
-    const int nk_all = D / BKE;
-    const int kt0 = (int)((int64_t)nk_all * sp / S), kt1 = (int)((int64_t)nk_all * (sp + 1) / S);
+    const int kt0 = m.kb0, kt1 = m.kb1;
     const int nkb = kt1 - kt0;
     // Ring of MD_NS k-blocks (k-block kb in buffer kb % MD_NS).  Fragments are read one MFMA step
     // ahead, and the barrier that publishes k-block kb + 1 and frees buffer kb sits between a
@@ -687,70 +738,7 @@ __global__ __launch_bounds__(512) void mlp_gemm_dma_kernel(MlpArgs a) {
       mma(F1);
     }
 
-    if (S > 1) {
-      // raw sums of this K range: ws[tb][sp][column in tile][row in tile]
-      float* wt = a.splitk_ws + (int64_t)tb * S * (MD_BM * MD_BN);
-      auto at = [&](int q, int i, int j) -> float4* {
-        return reinterpret_cast<float4*>(
-            &wt[(int64_t)q * (MD_BM * MD_BN) + (wn * WN + j * 16 + l16) * MD_BM + wm * WM + i * 16 + 4 * g]);
-      };
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) *at(sp, i, j) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-      __threadfence();
-      __syncthreads();
-      if (tid == 0) s_last = atomicAdd(&a.split_cnt[tb], 1) == S - 1;
-      __syncthreads();
-      if (!s_last) {
-        if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
-        continue;
-      }
-      __threadfence();
-      if (tid == 0) a.split_cnt[tb] = 0;      // ready for the next launch
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          floatx4 sum = (floatx4){0.f, 0.f, 0.f, 0.f};
-          for (int q = 0; q < S; ++q) {
-            float4 v;
-            if (q == sp) v = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-            else v = *at(q, i, j);
-            sum[0] += v.x; sum[1] += v.y; sum[2] += v.z; sum[3] += v.w;
-          }
-          acc[i][j] = sum;
-        }
-    }
-    // epilogue: H = ReLU(acc + b1'), partial logits over this wave's 64 hidden columns
-    const float* b1 = a.b1_fold[slot];
-    const float* w2 = a.w2[slot];
-    const int col0 = nt * MD_BN + wn * WN + l16;
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const float bb = b1[col0 + j * 16];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] = fmaxf(acc[i][j][r] + bb, 0.f);
-    }
-    float* part = a.partial[slot] + ((int64_t)(nt * 2 + wn) * a.part_cap) * kClasses;
-    for (int c = 0; c < kClasses; ++c) {
-      float w2v[NT];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) w2v[j] = w2[(col0 + j * 16) * kClasses + c];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float sacc = 0.f;
-#pragma unroll
-          for (int j = 0; j < NT; ++j) sacc += acc[i][j][r] * w2v[j];
-          sacc = row_sum16(sacc);
-          const int rr = mt * MD_BM + wm * WM + i * 16 + 4 * g + r;
-          if (l16 == 0 && rr < cnt) part[(int64_t)rr * kClasses + c] = sacc;
-        }
-    }
+    mlp_finish<MD_BM, MD_BN, MT, NT>(a, m, acc, wm * WM, wn * WN);
     __syncthreads();
     if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
   }
@@ -772,40 +760,16 @@ __global__ __launch_bounds__(256) void mlp_gemm_s3_kernel(MlpArgs a) {
   constexpr int WM = 64, WN = 64, MT = WM / 16, NT = WN / 16;
   static_assert(UNITS % 256 == 0 && (M3_BM * UPR) % 256 == 0, "stage rows fill the waves' loads");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[M3_NS * STAGE];
-  __shared__ int s_last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
   const int wm = wave >> 1, wn = wave & 1;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
   const int u_slot = lane % UPR;
 
-  int base_total = 0, nk_min = 1 << 30;
-  for (int i = 0; i < a.n_preds; ++i) {
-    const int cnt = a.q.counts[a.pred[i]];
-    base_total += ((cnt + M3_BM - 1) / M3_BM) * (a.hidden[i] / M3_BN);
-    nk_min = min(nk_min, a.d_in[i] / BKE);
-  }
-  const int S = mlp_splits(base_total, nk_min, a);
-  const int total = base_total * S;
-
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    const int tb = t / S, sp = t % S;
-    int slot = 0, mt = 0, nt = 0;
-    {
-      int acc0 = 0;
-      for (int i = 0; i < a.n_preds; ++i) {
-        const int cnt = a.q.counts[a.pred[i]];
-        const int n_nt = a.hidden[i] / M3_BN;
-        const int tiles = ((cnt + M3_BM - 1) / M3_BM) * n_nt;
-        if (tb < acc0 + tiles) {
-          slot = i;
-          mt = (tb - acc0) / n_nt;
-          nt = (tb - acc0) % n_nt;
-          break;
-        }
-        acc0 += tiles;
-      }
-    }
+  const MlpPlan plan = mlp_plan(a);
+  for (int u = blockIdx.x; u < plan.units; u += gridDim.x) {
+    const MlpUnit m = mlp_unit(a, plan, u);
+    const int slot = m.slot, mt = m.mt, nt = m.nt;
     const int k = a.pred[slot];
     const int cnt = a.q.counts[k];
     const int D = a.d_in[slot], H = a.hidden[slot];
@@ -868,8 +832,7 @@ __global__ __launch_bounds__(256) void mlp_gemm_s3_kernel(MlpArgs a) {
       }
     };
 
-    const int nk_all = D / BKE;
-    const int kt0 = (int)((int64_t)nk_all * sp / S), kt1 = (int)((int64_t)nk_all * (sp + 1) / S);
+    const int kt0 = m.kb0, kt1 = m.kb1;
     const int nkb = kt1 - kt0;
     // two stages: block kb + 1 is copied while block kb is read; the barrier at the top of each
     // iteration also retires every wave's reads of the buffer the next copy overwrites
@@ -882,104 +845,51 @@ __global__ __launch_bounds__(256) void mlp_gemm_s3_kernel(MlpArgs a) {
       compute(kb & 1);
     }
 
-    if (S > 1) {
-      float* wt = a.splitk_ws + (int64_t)tb * S * (M3_BM * M3_BN);
-      auto at = [&](int q, int i, int j) -> float4* {
-        return reinterpret_cast<float4*>(
-            &wt[(int64_t)q * (M3_BM * M3_BN) + (wn * WN + j * 16 + l16) * M3_BM + wm * WM + i * 16 + 4 * g]);
-      };
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) *at(sp, i, j) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-      __threadfence();
-      __syncthreads();
-      if (tid == 0) s_last = atomicAdd(&a.split_cnt[tb], 1) == S - 1;
-      __syncthreads();
-      if (!s_last) {
-        if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
-        continue;
-      }
-      __threadfence();
-      if (tid == 0) a.split_cnt[tb] = 0;
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          floatx4 sum = (floatx4){0.f, 0.f, 0.f, 0.f};
-          for (int q = 0; q < S; ++q) {
-            float4 v;
-            if (q == sp) v = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-            else v = *at(q, i, j);
-            sum[0] += v.x; sum[1] += v.y; sum[2] += v.z; sum[3] += v.w;
-          }
-          acc[i][j] = sum;
-        }
-    }
-    const float* b1 = a.b1_fold[slot];
-    const float* w2 = a.w2[slot];
-    const int col0 = nt * M3_BN + wn * WN + l16;
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const float bb = b1[col0 + j * 16];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] = fmaxf(acc[i][j][r] + bb, 0.f);
-    }
-    float* part = a.partial[slot] + ((int64_t)(nt * 2 + wn) * a.part_cap) * kClasses;
-    for (int c = 0; c < kClasses; ++c) {
-      float w2v[NT];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) w2v[j] = w2[(col0 + j * 16) * kClasses + c];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float sacc = 0.f;
-#pragma unroll
-          for (int j = 0; j < NT; ++j) sacc += acc[i][j][r] * w2v[j];
-          sacc = row_sum16(sacc);
-          const int rr = mt * M3_BM + wm * WM + i * 16 + 4 * g + r;
-          if (l16 == 0 && rr < cnt) part[(int64_t)rr * kClasses + c] = sacc;
-        }
-    }
+    mlp_finish<M3_BM, M3_BN, MT, NT>(a, m, acc, wm * WM, wn * WN);
     __syncthreads();
     if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
   }
 }
 
 template <typename T, int BM, int BN>
-static void launch_gemm_t(const MlpArgs& b, int grid, hipStream_t s) {
+static void launch_gemm_t(MlpArgs& b, hipStream_t s) {
+  b.bm = BM;
+  b.bn = BN;
+  b.bk = MlpTile<T>::BK;
+  b.units = 2 * b.n_cu;          // workgroups that the kernel's registers let in: two or three per CU
+  const dim3 grid(b.units * 4);
   if (b.fr.dtype == HYDRO_DTYPE_BF16)
-    hipLaunchKernelGGL((mlp_gemm_kernel<T, __bf16, BM, BN>), dim3(grid), dim3(256), 0, s, b);
+    hipLaunchKernelGGL((mlp_gemm_kernel<T, __bf16, BM, BN>), grid, dim3(256), 0, s, b);
   else if (b.fr.dtype == HYDRO_DTYPE_U8)
-    hipLaunchKernelGGL((mlp_gemm_kernel<T, uint8_t, BM, BN>), dim3(grid), dim3(256), 0, s, b);
+    hipLaunchKernelGGL((mlp_gemm_kernel<T, uint8_t, BM, BN>), grid, dim3(256), 0, s, b);
   else
-    hipLaunchKernelGGL((mlp_gemm_kernel<T, float, BM, BN>), dim3(grid), dim3(256), 0, s, b);
+    hipLaunchKernelGGL((mlp_gemm_kernel<T, float, BM, BN>), grid, dim3(256), 0, s, b);
 }
 
-void launch_mlp_gemm(const MlpArgs& b, int cfg, bool bf, int grid, hipStream_t s) {
+// Picks and launches the GEMM; the tile shape it used is left in b for the head.
+void launch_mlp_gemm(MlpArgs& b, int cfg, bool bf, hipStream_t s) {
   bool dma = bf && b.fr.dtype == HYDRO_DTYPE_BF16 && (cfg == 0 || cfg == 1);
   for (int i = 0; i < b.n_preds && dma; ++i) dma = b.d_in[i] % 64 == 0 && b.hidden[i] % MD_BN == 0;
   bool s3 = !bf && b.fr.dtype == HYDRO_DTYPE_BF16 && (cfg == 0 || cfg == 1);
   for (int i = 0; i < b.n_preds && s3; ++i) s3 = b.w1_s3[i] != nullptr;
-  if (s3) {
-    hipLaunchKernelGGL(mlp_gemm_s3_kernel, dim3(grid), dim3(256), 0, s, b);
-  } else if (dma) {
-    MlpArgs c = b;
-    c.split_slots = b.split_slots / 2;     // workspace tiles of 256 x 128
-    hipLaunchKernelGGL(mlp_gemm_dma_kernel, dim3(grid), dim3(512), 0, s, c);
+  if (s3 || dma) {
+    b.bm = s3 ? M3_BM : MD_BM;
+    b.bn = s3 ? M3_BN : MD_BN;
+    b.bk = 64;
+    b.units = b.n_cu;            // the ring takes a CU's LDS
+    b.split_slots = (int)((int64_t)b.split_slots * 128 * 128 / (b.bm * b.bn));
+    if (s3) hipLaunchKernelGGL(mlp_gemm_s3_kernel, dim3(b.units * 4), dim3(256), 0, s, b);
+    else hipLaunchKernelGGL(mlp_gemm_dma_kernel, dim3(b.units * 4), dim3(512), 0, s, b);
   } else if (bf) {
-    if (cfg == 0) launch_gemm_t<__bf16, 128, 128>(b, grid, s);
-    else if (cfg == 1) launch_gemm_t<__bf16, 64, 128>(b, grid, s);
-    else if (cfg == 2) launch_gemm_t<__bf16, 128, 64>(b, grid, s);
-    else launch_gemm_t<__bf16, 64, 64>(b, grid, s);
+    if (cfg == 0) launch_gemm_t<__bf16, 128, 128>(b, s);
+    else if (cfg == 1) launch_gemm_t<__bf16, 64, 128>(b, s);
+    else if (cfg == 2) launch_gemm_t<__bf16, 128, 64>(b, s);
+    else launch_gemm_t<__bf16, 64, 64>(b, s);
   } else {
-    if (cfg == 0) launch_gemm_t<float, 128, 128>(b, grid, s);
-    else if (cfg == 1) launch_gemm_t<float, 64, 128>(b, grid, s);
-    else if (cfg == 2) launch_gemm_t<float, 128, 64>(b, grid, s);
-    else launch_gemm_t<float, 64, 64>(b, grid, s);
+    if (cfg == 0) launch_gemm_t<float, 128, 128>(b, s);
+    else if (cfg == 1) launch_gemm_t<float, 64, 128>(b, s);
+    else if (cfg == 2) launch_gemm_t<float, 128, 64>(b, s);
+    else launch_gemm_t<float, 64, 64>(b, s);
   }
 }
 
@@ -1006,11 +916,10 @@ void launch_mlp_pass(const MlpArgs& a, const Forward& f, int tier, int grid, hip
   if (a.n_preds == 0) return;
   if (tier == TIER_F64) {
     hipLaunchKernelGGL(mlp_f64_hidden_kernel, dim3(grid * 2), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(mlp_f64_head_kernel, dim3(grid), dim3(256), 0, s, a, f);
-    hipLaunchKernelGGL(mlp_f64_rest_kernel, dim3(grid), dim3(256), 0, s, a, f);
+    hipLaunchKernelGGL(mlp_f64_entry_kernel, dim3(grid), dim3(256), 0, s, a, f);
     return;
   }
-  // one GEMM launch per tile shape present among the predicates
+  // one GEMM and head launch per tile shape present among the predicates
   const bool bf = a.prec == HYDRO_PREC_BF16 && tier == TIER_FIRST;
   for (int cfg = 0; cfg < MLP_TILE_CONFIGS; ++cfg) {
     MlpArgs b = a;
@@ -1020,9 +929,9 @@ void launch_mlp_pass(const MlpArgs& a, const Forward& f, int tier, int grid, hip
       mlp_copy_slot(b, b.n_preds++, a, i);
     }
     if (b.n_preds == 0) continue;
-    launch_mlp_gemm(b, cfg, bf, grid, s);
+    launch_mlp_gemm(b, cfg, bf, s);
+    hipLaunchKernelGGL(mlp_head_kernel, dim3(grid), dim3(256), 0, s, b, f);
   }
-  hipLaunchKernelGGL(mlp_head_kernel, dim3(grid), dim3(256), 0, s, a, f);
 }
 
 }  // namespace hydro

@@ -76,3 +76,31 @@ def test_mlp6_ungrouped_matches(c3):
     # edge), so the escalations agree to a few tuples, and stay a small fraction
     assert all(abs(a[1] - b[1]) <= 3 for a, b in zip(out[0], out[1]))
     assert sum(e for _, e in out[0]) <= 0.01 * sum(v for v, _ in out[0])
+
+
+@pytest.mark.parametrize("n", [1, 17, 256, 257, 2048 + 1, 9000])
+@pytest.mark.parametrize("tier", [0, 1])
+def test_mlp_whole_and_split_tiles(n, tier):
+    """Queues whose tiles all split along K (few rows), fill the GPU exactly or leave a split rest
+    behind whole tiles, rows that do not fill a tile: logits against FP64 numpy.  Rounding errors are
+    independent: a bf16 weight's has a standard deviation below 2^-9 of it, each of 768 fp32 sums
+    one below 2^-24 of a partial sum (within four standard deviations of the products' sum);
+    eight of the logit's standard deviation bound every row (a lost or doubled part is about 1)."""
+    d_in, hidden = 768, 2048
+    rng = np.random.default_rng(n)
+    frames = hs.f64_to_bf16_bits(rng.random((n, 16, 16, 3)))
+    w = hs.make_model(hs.ModelDesc(arch="mlp", seed=910, d_in=d_in, hidden=hidden))
+    s = hydro.Session([hydro.ModelSpec.from_weights(w, 0b0000011111)], hydro.make_policy("score", precision="bf16"), 16, n)
+    z = s.logits(0, tier, torch.from_numpy(frames).cuda(), "bf16")
+    s.close()
+    x = (ho.frames_to_f64(frames, "bf16").reshape(n, -1) - 0.5) * 4.0
+    t = {k: v.astype(np.float64) for k, v in w.tensors.items()}
+    pre = x @ t["W1"] + t["b1"]
+    z64 = np.maximum(pre, 0.0) @ t["W2"] + t["b2"]
+    # the folded form multiplies the raw frame (at most 1) by 4 W1
+    size = 4.0 * np.sqrt((t["W1"] ** 2).sum(axis=0))
+    sigma = size * 2.0**-9 if tier == 0 else 4.0 * size * np.sqrt(d_in) * 2.0**-24
+    bound = 8.0 * np.sqrt((sigma**2) @ (t["W2"] ** 2))
+    err = np.abs(z - z64).max(axis=0)
+    log(f"[gpu] mlp {n} rows tier {tier}: max |z - z64| {err.max():.3e}, bound {bound.min():.3e}")
+    assert np.all(err <= bound)
