@@ -35,9 +35,7 @@ template <> struct Mf<float> {
   typedef float frag;
 };
 
-__device__ inline floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
+__device__ inline floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) { return mfma_bf16(a, b, c); }
 __device__ inline floatx4 mfma(float a, float b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -46,30 +44,6 @@ template <typename T>
 __device__ inline typename Mf<T>::frag ld_frag(const T* p) {
   if constexpr (sizeof(T) == 2) return *reinterpret_cast<const bf16x8*>(p);
   else return *p;
-}
-
-// FP32 arithmetic from bf16 MFMAs: fp32 activations split into three bf16 terms (x = h + m + l
-// exactly), weights held as three terms likewise; the six products down to 2^-24 relative, summed
-// smallest first.
-__device__ inline void split3(const float4& p0, const float4& p1, bf16x8 (&x)[3]) {
-  const float xv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const __bf16 h = static_cast<__bf16>(xv[e]);
-    const float r1 = xv[e] - static_cast<float>(h);
-    const __bf16 m = static_cast<__bf16>(r1);
-    x[0][e] = h;
-    x[1][e] = m;
-    x[2][e] = static_cast<__bf16>(r1 - static_cast<float>(m));
-  }
-}
-__device__ inline floatx4 mfma_s3(const bf16x8 (&w)[3], const bf16x8 (&x)[3], floatx4 c) {
-  c = mfma(w[0], x[2], c);
-  c = mfma(w[1], x[1], c);
-  c = mfma(w[0], x[1], c);
-  c = mfma(w[2], x[0], c);
-  c = mfma(w[1], x[0], c);
-  return mfma(w[0], x[0], c);
 }
 
 // geometry

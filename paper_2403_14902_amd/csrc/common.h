@@ -249,6 +249,34 @@ __device__ inline void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+__device__ inline floatx4 mfma_bf16(bf16x8 a, bf16x8 b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// FP32 arithmetic from bf16 MFMAs: fp32 activations split into three bf16 terms (x = h + m + l
+// exactly), weights held as three terms likewise; the six products down to 2^-24 relative, summed
+// smallest first.
+__device__ inline void split3(const float4& p0, const float4& p1, bf16x8 (&x)[3]) {
+  const float xv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const __bf16 h = static_cast<__bf16>(xv[e]);
+    const float r1 = xv[e] - static_cast<float>(h);
+    const __bf16 m = static_cast<__bf16>(r1);
+    x[0][e] = h;
+    x[1][e] = m;
+    x[2][e] = static_cast<__bf16>(r1 - static_cast<float>(m));
+  }
+}
+__device__ inline floatx4 mfma_s3(const bf16x8 (&w)[3], const bf16x8 (&x)[3], floatx4 c) {
+  c = mfma_bf16(w[0], x[2], c);
+  c = mfma_bf16(w[1], x[1], c);
+  c = mfma_bf16(w[0], x[1], c);
+  c = mfma_bf16(w[2], x[0], c);
+  c = mfma_bf16(w[1], x[0], c);
+  return mfma_bf16(w[0], x[0], c);
+}
+
 // Wave-aggregated append: every active lane with `want` set gets a unique slot in *counter.
 __device__ inline int wave_append(int* counter, bool want) {
   unsigned long long m = __ballot(want);

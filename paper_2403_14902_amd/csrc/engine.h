@@ -84,7 +84,8 @@ struct GcnnArgs {
   int widths[kMaxK][HYDRO_MAX_LAYERS];
   uint32_t class_mask[kMaxK];
   const __bf16* w_bf[kMaxK][HYDRO_MAX_LAYERS];    // packed fragments, layer 1 folded
-  const float* w_f32[kMaxK][HYDRO_MAX_LAYERS];
+  const __bf16* w_ml[kMaxK][HYDRO_MAX_LAYERS];    // fp32 arithmetic: what w_bf leaves of each fp32 weight, as two
+                                                  // more bf16 terms (w = w_bf + mid + lo exactly), mid then lo
   const float* bias[kMaxK][HYDRO_MAX_LAYERS];
   const float* fc_w[kMaxK];
   const float* fc_b[kMaxK];
@@ -116,7 +117,7 @@ struct GcnnArgs {
   void* c4_act3;                               // layer-3 outputs [act_cap][16][16][128]
   int64_t act_cap;                             // evaluations one launch may hold
   unsigned* c4_act_max;                        // calibration: [predicate][4] activation maxima (bits)
-  const void* zero_page;                       // 256 zero bytes (padding taps of the GEMM gathers)
+  const void* zero_page;                       // 128 zero bytes (padding taps of the GEMM gathers)
 };
 
 // Grouped launch over the CNN predicates that take each tuple's crop (variable-size inputs).
@@ -193,8 +194,8 @@ void launch_c4_pass(const GcnnArgs& a, const Forward& f, int prec, int grid, hip
 void launch_gcnn_pass(const GcnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s);
 // Slot i of src becomes slot j of dst (every per-slot field).
 void gcnn_copy_slot(GcnnArgs& dst, int j, const GcnnArgs& src, int i);
-size_t gcnn_packed_elems(int layer, int cin, int cout, int prec);
-void gcnn_pack_layer(int layer, int cin, int cout, int prec, const float* w, float scale, float* out);
+size_t gcnn_packed_elems(int layer, int cin, int cout);
+void gcnn_pack_layer(int layer, int cin, int cout, const float* w, float scale, float* out);
 
 constexpr int MLP_TILE_CONFIGS = 4;
 int mlp_f64_chunks(int d_in);    // input chunks of the FP64 MLP hidden pass

@@ -76,7 +76,10 @@ static hipError_t dev_alloc(void** p, size_t bytes) {
 // until the process ends.  In host code `scratch` is only a stand-in for the symbol: its device
 // address (per device) comes from hipGetSymbolAddress and is the only form passed to kernels and
 // copies.
-static __device__ __align__(256) unsigned char scratch[HYDRO_NOALLOC_BYTES];
+// (2 MiB beyond the stated size: the layer-wise CNNs' weight images, padded to whole MFMA steps, take
+// up to 64 KB a layer more than unpadded ones, and must not take it from a query's buffers.)
+constexpr size_t kArenaBytes = HYDRO_NOALLOC_BYTES + ((size_t)2 << 20);
+static __device__ __align__(256) unsigned char scratch[kArenaBytes];
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
 static void* g_scratch_ptr[kMaxDevices];
@@ -1090,20 +1093,22 @@ static int pack_models(hydro_session* s) {
         float* dp;
         uint16_t* bp;
         {
-          size_t n = gcnn_packed_elems(l, cin, co, HYDRO_PREC_FP32);
+          const size_t n = gcnn_packed_elems(l, cin, co);
           std::vector<float> pf(n);
-          gcnn_pack_layer(l, cin, co, HYDRO_PREC_FP32, hm.cw[l].data(), (float)sc, pf.data());
-          if ((rc = upload(s, pf.data(), n, &dp))) return rc;
-          ga.w_f32[i][l] = dp;
-        }
-        {
-          size_t n = gcnn_packed_elems(l, cin, co, HYDRO_PREC_BF16);
-          std::vector<float> pf(n);
-          gcnn_pack_layer(l, cin, co, HYDRO_PREC_BF16, hm.cw[l].data(), (float)sc, pf.data());
-          std::vector<uint16_t> pb(n);
-          for (size_t t = 0; t < n; ++t) pb[t] = f32_to_bf16_bits(pf[t]);
+          gcnn_pack_layer(l, cin, co, hm.cw[l].data(), (float)sc, pf.data());
+          std::vector<uint16_t> pb(3 * n);
+          for (size_t t = 0; t < n; ++t) {
+            float v = pf[t];
+            for (int term = 0; term < 3; ++term) {
+              const uint16_t h = f32_to_bf16_bits(v);
+              pb[term * n + t] = h;
+              v -= bf16_bits_to_f32(h);
+            }
+          }
           if ((rc = upload(s, pb.data(), n, &bp))) return rc;
           ga.w_bf[i][l] = reinterpret_cast<const __bf16*>(bp);
+          if ((rc = upload(s, pb.data() + n, 2 * n, &bp))) return rc;
+          ga.w_ml[i][l] = reinterpret_cast<const __bf16*>(bp);
         }
         if ((rc = upload(s, bias.data(), bias.size(), &dp))) return rc;
         ga.bias[i][l] = dp;
@@ -1199,6 +1204,7 @@ static int pack_models(hydro_session* s) {
   if (s->gcnn.n_preds > 0) {
     GcnnArgs& ga = s->gcnn;
     ga.pad_raw = pad_raw;
+    ga.zero_page = reinterpret_cast<const char*>(s->res_base) + 128;
     int64_t mx = 0;
     for (int i = 0; i < ga.n_preds; ++i)
       for (int l = 0; l < ga.n_layers[i]; ++l) {
@@ -1218,14 +1224,9 @@ static int pack_models(hydro_session* s) {
         if ((rc = sess_alloc(s, &ga.act[b], (size_t)s->act_cap * mx * sizeof(float)))) return rc;
     if (any_c4) {
       // dedicated kernels: layer-2 and layer-3 outputs of every evaluation of a launch (sized for
-      // the FP32 tier), the activation maxima of calibration, and a zero page for padding taps
+      // the FP32 tier), and the activation maxima of calibration
       if ((rc = sess_alloc(s, &ga.c4_act2, (size_t)s->act_cap * 32 * 32 * 64 * sizeof(float)))) return rc;
       if ((rc = sess_alloc(s, &ga.c4_act3, (size_t)s->act_cap * 16 * 16 * 128 * sizeof(float)))) return rc;
-      void* zp;
-      if ((rc = sess_alloc(s, &zp, 256))) return rc;
-      HIP_TRY(hipMemsetAsync(zp, 0, 256, s->stream));
-      HIP_TRY(hipStreamSynchronize(s->stream));
-      ga.zero_page = zp;
       ga.c4_act_max = nullptr;
     }
     ga.esc_half = mx;
@@ -1470,7 +1471,11 @@ static int session_create(const hydro_model* models, int32_t k, const hydro_poli
   const int64_t nwords = (cap + 31) / 32;
   if ((rc = sess_alloc(s, (void**)&s->result_bits, nwords * 4 + 1024))) return bail(rc);
   if ((rc = sess_alloc(s, (void**)&s->res_blocks, ((nwords + 255) / 256 + 1) * 4))) return bail(rc);
-  if ((rc = sess_alloc(s, (void**)&s->res_base, 16))) return bail(rc);
+  // 16 bytes for the result count, and from byte 128 on zeros that no kernel writes: the padding taps
+  // of the convolutions' direct-to-LDS copies
+  if ((rc = sess_alloc(s, (void**)&s->res_base, 256))) return bail(rc);
+  he = hipMemsetAsync(s->res_base, 0, 256, s->stream);
+  if (he != hipSuccess) return bail(fail(HYDRO_EDEVICE, std::string("hipMemset: ") + hipGetErrorString(he)));
   if (s->pol.log_routes && (rc = sess_alloc(s, (void**)&s->route_log, cap * 4))) return bail(rc);
   if (s->pol.log_routes) {
     s->round_log_cap = 16384;
@@ -2730,7 +2735,7 @@ int hydro_query_noalloc(const hydro_frames* frames, const hydro_model* models, i
   if (rc) return rc;
   hydro_session* s = nullptr;
   rc = session_create(models, k, policy, frames->h, frames->w, std::max<int64_t>(1, frames->n), arena,
-                      HYDRO_NOALLOC_BYTES, &s);
+                      kArenaBytes, &s);
   if (rc) return rc;
   rc = hydro_session_push(s, frames, thresholds, n_seg, seg_len);
   if (!rc) rc = finish_query(s, nullptr, out_ids, out_cap, out_n, out_stats);

@@ -13,63 +13,76 @@
 
 namespace hydro {
 
-typedef float floatx4_g __attribute__((ext_vector_type(4)));
+// K of a layer: layer 1 uses 27 of 32 slots in g_first_k's order; later layers k = (u*3 + v)*Cin + c,
+// padded to whole MFMA steps of 32.
+__host__ __device__ inline int g_ksteps(int layer, int cin) { return layer == 0 ? 1 : (9 * cin + 31) / 32; }
 
-template <typename T> struct GMf;
-template <> struct GMf<__bf16> { static constexpr int KSTEP = 32, KPL = 8; typedef bf16x8 frag; };
-template <> struct GMf<float> { static constexpr int KSTEP = 4, KPL = 1; typedef float frag; };
-
-__device__ inline floatx4 gmfma(bf16x8 a, bf16x8 b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+// What K slot k (0..31) of the first layer holds: value r (0..8: three pixels of three channels)
+// of input row u.  Slots 8u..8u+7 are the first eight values of row u, 24..26 the ninth value of
+// rows 0..2: a lane (which holds eight consecutive slots) then reads one staged row, or three words.
+__host__ __device__ inline bool g_first_k(int k, int* u, int* r) {
+  *u = k < 24 ? k / 8 : k - 24 < 3 ? k - 24 : 0;
+  *r = k < 24 ? k % 8 : 8;
+  return k < 27;
 }
-__device__ inline floatx4 gmfma(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-// K of a layer, padded: layer 1 uses k = (u*3 + v)*3 + c (27 real values); later layers
-// k = (u*3 + v)*Cin + c.
-__host__ __device__ inline int g_kreal(int layer, int cin) { return layer == 0 ? 27 : 9 * cin; }
+// Four channels of one position: bias, ReLU, store.
 template <typename T>
-__host__ __device__ inline int g_ksteps(int layer, int cin) {
-  return (g_kreal(layer, cin) + GMf<T>::KSTEP - 1) / GMf<T>::KSTEP;
+__device__ inline void store_relu4(T* o, floatx4 v, float4 b) {
+  const float v0 = fmaxf(v[0] + b.x, 0.f), v1 = fmaxf(v[1] + b.y, 0.f);
+  const float v2 = fmaxf(v[2] + b.z, 0.f), v3 = fmaxf(v[3] + b.w, 0.f);
+  if constexpr (sizeof(T) == 2) {
+    alignas(8) __bf16 h[4] = {static_cast<__bf16>(v0), static_cast<__bf16>(v1), static_cast<__bf16>(v2), static_cast<__bf16>(v3)};
+    *reinterpret_cast<uint2*>(o) = *reinterpret_cast<const uint2*>(h);
+  } else {
+    *reinterpret_cast<float4*>(o) = make_float4(v0, v1, v2, v3);
+  }
 }
 
 constexpr int GT_M = 64;     // positions per tile
 constexpr int GT_N = 64;     // channels per tile
 
-// One layer over all frames of all generic-CNN predicates in this launch.
+// First layer of shapes that gconv_first_kernel does not take, one wave per 16 positions, its gather
+// straight from the frame (any in_hw, any Cout).
+// One channel tile of the first layer: the bf16 weights, or their three terms (every product with a
+// frame value exact), smallest first.
 template <typename T>
-__global__ __launch_bounds__(256) void gconv_layer_kernel(GcnnArgs a, int layer) {
-  typedef typename GMf<T>::frag frag;
-  constexpr int KSTEP = GMf<T>::KSTEP, KPL = GMf<T>::KPL;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
-  // tiles per predicate slot: ceil(count * P / 64) position tiles x Cout / 64 channel tiles
-  int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) {
-    if (layer >= a.n_layers[i]) continue;
-    const int hout = a.in_hw[i] >> (layer + 1);
-    const int64_t rows = (int64_t)a.q.counts[a.pred[i]] * hout * hout;
-    total += (int)((rows + GT_M - 1) / GT_M) * (a.widths[i][layer] / GT_N > 0 ? a.widths[i][layer] / GT_N : 1);
+__device__ inline floatx4 first_mfma(const GcnnArgs& a, int slot, int tile, int lane, bf16x8 x, floatx4 c) {
+  if constexpr (sizeof(T) == 4) {
+    const int64_t n = (int64_t)(a.widths[slot][0] / 16) * 512;       // elements of a term's image
+    const __bf16* lo = a.w_ml[slot][0] + tile * 512 + lane * 8;
+    c = mfma_bf16(*reinterpret_cast<const bf16x8*>(lo + n), x, c);
+    c = mfma_bf16(*reinterpret_cast<const bf16x8*>(lo), x, c);
   }
+  return mfma_bf16(*reinterpret_cast<const bf16x8*>(a.w_bf[slot][0] + tile * 512 + lane * 8), x, c);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void gconv_first_any_kernel(GcnnArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
+  // tiles per predicate slot: ceil(count * P / 64) position tiles x ceil(Cout / 64) channel tiles
+  auto tiles_of = [&](int i) {
+    const int hout = a.in_hw[i] >> 1;
+    const int64_t rows = (int64_t)a.q.counts[a.pred[i]] * hout * hout;
+    return (int)((rows + GT_M - 1) / GT_M) * ((a.widths[i][0] + GT_N - 1) / GT_N);
+  };
+  int total = 0;
+  for (int i = 0; i < a.n_preds; ++i) total += tiles_of(i);
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    int slot = 0, off = t;
+    int slot = 0, off = t, ebase = 0;
     for (int i = 0; i < a.n_preds; ++i) {
-      if (layer >= a.n_layers[i]) continue;
-      const int hout = a.in_hw[i] >> (layer + 1);
-      const int64_t rows = (int64_t)a.q.counts[a.pred[i]] * hout * hout;
-      const int c = (int)((rows + GT_M - 1) / GT_M) * (a.widths[i][layer] / GT_N > 0 ? a.widths[i][layer] / GT_N : 1);
+      const int c = tiles_of(i);
       if (off < c) { slot = i; break; }
       off -= c;
+      ebase += a.q.counts[a.pred[i]];
     }
     const int k = a.pred[slot];
     const int cnt = a.q.counts[k];
-    const int hin = a.in_hw[slot] >> layer, hout = hin >> 1, P = hout * hout;
-    const int cin = layer == 0 ? 3 : a.widths[slot][layer - 1];
-    const int cout = a.widths[slot][layer];
-    const int nct = cout / GT_N > 0 ? cout / GT_N : 1;
-    const int ncw = cout < GT_N ? cout / 16 : 4;        // channel tiles of 16 per wave group
+    const int hin = a.in_hw[slot], hout = hin >> 1, P = hout * hout;
+    const int cout = a.widths[slot][0];
+    const int nct = (cout + GT_N - 1) / GT_N;
     const int mt = off / nct, ct = off % nct;
-    const int KS = g_ksteps<T>(layer, cin);
-    const frag* wp = reinterpret_cast<const frag*>(sizeof(T) == 2 ? (const void*)a.w_bf[slot][layer]
-                                                                  : (const void*)a.w_f32[slot][layer]);
+    const int ncw = min(4, cout / 16 - ct * 4);         // channel tiles of 16 in this tile
     // this wave's 16 positions
     const int64_t row = (int64_t)mt * GT_M + wave * 16 + l16;
     const bool rvalid = row < (int64_t)cnt * P;
@@ -77,70 +90,31 @@ __global__ __launch_bounds__(256) void gconv_layer_kernel(GcnnArgs a, int layer)
     const int p = rvalid ? (int)(row % P) : 0;
     const int oi = p / hout, oj = p % hout;
     const uint32_t idx = entry_idx(a.q.entries[(int64_t)k * a.q.cap + e]);
-    int ebase = 0;
-    for (int i = 0; i < slot; ++i) ebase += a.q.counts[a.pred[i]];
-    const int64_t ent = (int64_t)ebase + e;
-    const T* in = layer == 0 ? nullptr : reinterpret_cast<const T*>(a.act[(layer - 1) & 1]) + ent * a.act_stride;
     floatx4 acc[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[j] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    for (int ks = 0; ks < KS; ++ks) {
-      frag av;
-      if (layer == 0) {
-        // raw frame gather, k = (u*3 + v)*3 + c
-        if constexpr (sizeof(T) == 2) {
-          alignas(16) __bf16 t8[8];
+    auto raw_at = [&](int u, int v, int c) {
+      const int y = 2 * oi + u - 1, x = 2 * oj + v - 1;
+      if (y < 0 || x < 0 || y >= hin || x >= hin) return a.pad_raw;
+      const int64_t o = (int64_t)idx * a.fr.elems + ((int64_t)y * hin + x) * 3 + c;
+      return a.fr.dtype == HYDRO_DTYPE_BF16 ? (float)static_cast<const __bf16*>(a.fr.base)[o]
+                                            : (float)static_cast<const uint8_t*>(a.fr.base)[o];
+    };
+    alignas(16) __bf16 t8[8];            // exact: frame values fit bf16
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const int kk = ks * 32 + 8 * g + q;
-            float v = 0.f;
-            if (kk < 27 && rvalid) {
-              const int tap = kk / 3, c = kk % 3, y = 2 * oi + tap / 3 - 1, x = 2 * oj + tap % 3 - 1;
-              if (y < 0 || x < 0 || y >= hin || x >= hin) v = a.pad_raw;
-              else {
-                const int64_t o = (int64_t)idx * a.fr.elems + ((int64_t)y * hin + x) * 3 + c;
-                v = a.fr.dtype == HYDRO_DTYPE_BF16 ? (float)static_cast<const __bf16*>(a.fr.base)[o]
-                                                  : (float)static_cast<const uint8_t*>(a.fr.base)[o];
-              }
-            }
-            t8[q] = static_cast<__bf16>(v);
-          }
-          av = *reinterpret_cast<const bf16x8*>(t8);
-        } else {
-          const int kk = ks * 4 + g;
-          float v = 0.f;
-          if (kk < 27 && rvalid) {
-            const int tap = kk / 3, c = kk % 3, y = 2 * oi + tap / 3 - 1, x = 2 * oj + tap % 3 - 1;
-            if (y < 0 || x < 0 || y >= hin || x >= hin) v = a.pad_raw;
-            else {
-              const int64_t o = (int64_t)idx * a.fr.elems + ((int64_t)y * hin + x) * 3 + c;
-              v = a.fr.dtype == HYDRO_DTYPE_BF16 ? (float)static_cast<const __bf16*>(a.fr.base)[o]
-                                                : (float)static_cast<const uint8_t*>(a.fr.base)[o];
-            }
-          }
-          av = v;
-        }
-      } else {
-        const int k0 = ks * KSTEP + KPL * g;
-        const int tap = k0 / cin, c0 = k0 % cin;
-        const int y = 2 * oi + tap / 3 - 1, x = 2 * oj + tap % 3 - 1;
-        if (rvalid && tap < 9 && y >= 0 && x >= 0 && y < hin && x < hin) {
-          const T* src = in + ((int64_t)y * hin + x) * cin + c0;
-          if constexpr (sizeof(T) == 2) av = *reinterpret_cast<const bf16x8*>(src);
-          else av = *src;
-        } else {
-          if constexpr (sizeof(T) == 2) av = bf16x8{};
-          else av = 0.f;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (j < ncw) acc[j] = gmfma(wp[((int64_t)ks * (cout / 16) + ct * 4 + j) * 64 + lane], av, acc[j]);
+    for (int q = 0; q < 8; ++q) {
+      int u, r;
+      const bool used = g_first_k(8 * g + q, &u, &r);
+      t8[q] = static_cast<__bf16>(used && rvalid ? raw_at(u, r / 3, r % 3) : 0.f);
     }
+    const bf16x8 av = *reinterpret_cast<const bf16x8*>(t8);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j < ncw) acc[j] = first_mfma<T>(a, slot, ct * 4 + j, lane, av, acc[j]);
     // bias + ReLU -> activations (rows = channels 4g.., column = this lane's position)
     if (rvalid) {
-      const float* bias = a.bias[slot][layer];
-      T* out = reinterpret_cast<T*>(a.act[layer & 1]) + ent * a.act_stride + (int64_t)p * cout;
+      const float* bias = a.bias[slot][0];
+      T* out = reinterpret_cast<T*>(a.act[0]) + ((int64_t)ebase + e) * a.act_stride + (int64_t)p * cout;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (j >= ncw) continue;
@@ -152,281 +126,295 @@ __global__ __launch_bounds__(256) void gconv_layer_kernel(GcnnArgs a, int layer)
   }
 }
 
-// Layers after the first when Cin is a multiple of the k-block and Cout of 64: an LDS-tiled
-// implicit GEMM.  Tile = 128 output positions (any frames of one slot) x BN output channels
-// (128 when Cout allows, else 64);
-// k-block = 32 (bf16) or 16 (fp32) consecutive input channels of one tap, so each position's
-// slice of the block is one contiguous run of its NHWC input.  Activations and the packed
-// weight fragments of a block are staged in LDS (double buffer) from NS register stages of
-// global loads; wave w multiplies channels 0..BN-1 (MFMA A, from the weights) by positions
-// 32w..32w+31 (MFMA B), so each lane ends with 4 consecutive channels of one position.
-template <typename T> struct GTile;
-template <> struct GTile<__bf16> { static constexpr int BK = 32, LD = 40; };
-template <> struct GTile<float> { static constexpr int BK = 16, LD = 20; };
-constexpr int GB_M = 128;
+// Layers after the first: implicit GEMM on tiles of GD::BM output positions (any frames of one slot) x
+// BN output channels, the widest of 128, 64, 32 and 16 that divides the slot's Cout (one launch per
+// width present, over its slots).  A k-block is 128 bytes of (tap, input channel) values per
+// position, 64 bf16 or 32 fp32: its eight 16-byte chunks lie within a tap each (Cin is a multiple of
+// 16) and are copied global -> LDS by global_load_lds_dwordx4, chunk c of row r at slot c ^ (r mod 8),
+// padding taps from zeros; the packed weight fragments are copied as they are.  Two stages, two
+// workgroups per CU (one waits while the other multiplies); each wave holds 64 positions.
+// fp32 arithmetic: the weights as three bf16 terms, the activations split on the fly (split3).
+// Bound by the copies: at 64 bf16 channels a block brings 40 KB for 2.1 MFLOP.  16-32-64 and 32-64-128
+// CNNs on 8,192 128x128 frames (12,288 evaluations): layers 2 and 3 take 1.7 ms in bf16; register-staged
+// 128-position tiles, and one wave per 16 positions where Cin is 16, took 3.6.  The FP32 band of the
+// same query: 0.53 ms, on fp32 MFMAs 1.0.
+template <typename T, int BN> struct GD {
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int KB = 128 / (int)sizeof(T), CE = 16 / (int)sizeof(T);   // values per block, per chunk
+  static constexpr int NCT = BN / 16;                          // 16-channel MFMA tiles
+  static constexpr int WC = BN > 64 || (F32 && BN > 32) ? 2 : 1, WP = 4 / WC;  // waves over channels, positions
+  static constexpr int CT = NCT / WC;                          // channel tiles per wave
+  static constexpr int BM = WP * 64;
+  static constexpr int NU = (F32 ? 3 : 2) * NCT;               // 1 KB weight units: two k-steps, or one of three terms
+  static constexpr int NIX = BM * 8 / 256;                     // 16-byte loads per lane and stage: positions
+  static constexpr int NIW = (NU + 3) / 4;                     // ... weights
+  static constexpr int STAGE = BM * 128 + NU * 1024;
+};
 
-__host__ __device__ inline bool gconv_tiled_ok(int layer, int cin, int cout, int bk, int bn) {
-  return layer > 0 && cin % bk == 0 && cout % bn == 0;
-}
+static int gconv_tile_bn(int cout) { return cout % 128 == 0 ? 128 : cout % 64 == 0 ? 64 : cout % 32 == 0 ? 32 : 16; }
 
-template <typename T, int GB_N>
-__global__ __launch_bounds__(256) void gconv_tile_kernel(GcnnArgs a, int layer) {
-  typedef typename GMf<T>::frag frag;
-  constexpr int BK = GTile<T>::BK, LD = GTile<T>::LD, KSTEP = GMf<T>::KSTEP, KPL = GMf<T>::KPL;
-  constexpr int KSUB = BK / KSTEP;                 // MFMA k-steps per block (1 bf16, 4 fp32)
-  constexpr int NS = 4;
-  constexpr int NCT = GB_N / 16;                   // 16-channel MFMA tiles per block
-  constexpr int WV = NCT / 4;                      // 16-byte weight chunks per thread and block
-  __shared__ __attribute__((aligned(16))) T Xs[2][GB_M * LD];
-  __shared__ __attribute__((aligned(16))) uint4 Ws[2][256 * WV];   // KSUB x NCT tiles x 64 lanes
+// slots: bit i set if slot i takes part (every slot's queue counts towards the activations' places).
+template <typename T, int BN>
+__global__ __launch_bounds__(256, 2) void gconv_dma_kernel(GcnnArgs a, int layer, uint32_t slots) {
+  typedef GD<T, BN> G;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * G::STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
-
+  const int wp = wave % G::WP, wc = wave / G::WP;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
+  // this lane's chunk of every row it copies (its rows are equal mod 8)
+  const int chunk = (lane & 7) ^ (lane >> 3);
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i) {
-    if (layer >= a.n_layers[i]) continue;
+    if (!((slots >> i) & 1u)) continue;
     const int hout = a.in_hw[i] >> (layer + 1);
     const int64_t rows = (int64_t)a.q.counts[a.pred[i]] * hout * hout;
-    total += (int)((rows + GB_M - 1) / GB_M) * (a.widths[i][layer] / GB_N);
+    total += (int)((rows + G::BM - 1) / G::BM) * (a.widths[i][layer] / BN);
   }
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     int slot = 0, off = t, ebase = 0;
     for (int i = 0; i < a.n_preds; ++i) {
-      if (layer >= a.n_layers[i]) { ebase += a.q.counts[a.pred[i]]; continue; }
-      const int hout = a.in_hw[i] >> (layer + 1);
-      const int64_t rows = (int64_t)a.q.counts[a.pred[i]] * hout * hout;
-      const int c = (int)((rows + GB_M - 1) / GB_M) * (a.widths[i][layer] / GB_N);
-      if (off < c) { slot = i; break; }
-      off -= c;
-      ebase += a.q.counts[a.pred[i]];
+      const int q = a.q.counts[a.pred[i]];
+      if ((slots >> i) & 1u) {
+        const int hout = a.in_hw[i] >> (layer + 1);
+        const int c = (int)(((int64_t)q * hout * hout + G::BM - 1) / G::BM) * (a.widths[i][layer] / BN);
+        if (off < c) { slot = i; break; }
+        off -= c;
+      }
+      ebase += q;
     }
     const int cnt = a.q.counts[a.pred[slot]];
     const int hin = a.in_hw[slot] >> layer, hout = hin >> 1, P = hout * hout;
     const int cin = a.widths[slot][layer - 1], cout = a.widths[slot][layer];
-    const int nct = cout / GB_N;
-    const int mt = off / nct, cb = off % nct;   // cb: block of GB_N channels
-    const int nkb = 9 * cin / BK;
-    const int ctile16 = cout / 16;
-    const frag* wp = reinterpret_cast<const frag*>(sizeof(T) == 2 ? (const void*)a.w_bf[slot][layer]
-                                                                  : (const void*)a.w_f32[slot][layer]);
-    const T* act_in = reinterpret_cast<const T*>(a.act[(layer - 1) & 1]);
-    // staging row of this thread (two threads per row, BK / 2 elements each)
-    const int srow = tid >> 1, shalf = tid & 1;
-    const int64_t R = (int64_t)mt * GB_M + srow;
-    const bool svalid = R < (int64_t)cnt * P;
-    const int se = svalid ? (int)(R / P) : 0, sp = svalid ? (int)(R % P) : 0;
-    const int soi = sp / hout, soj = sp % hout;
-    const T* sin = act_in + ((int64_t)ebase + se) * a.act_stride;
-
-    uint4 rx[NS][BK * (int)sizeof(T) / 32];   // 32 bytes of activations per stage
-    uint4 rw[NS][WV];
-    auto gload = [&](int kb, int st) {
-      const int k0 = kb * BK, tap = k0 / cin, c0 = k0 % cin;
-      const int y = 2 * soi + tap / 3 - 1, x = 2 * soj + tap % 3 - 1;
-      if (svalid && y >= 0 && x >= 0 && y < hin && x < hin) {
-        const uint4* src = reinterpret_cast<const uint4*>(sin + ((int64_t)y * hin + x) * cin + c0 + shalf * (BK / 2));
+    const int nct = cout / BN, cb = off % nct;
+    const int64_t R0 = (int64_t)(off / nct) * G::BM;
+    const int e0 = (int)(R0 / P), r0 = (int)(R0 % P);
+    const int KS = g_ksteps(layer, cin), nkb = G::F32 ? KS : (KS + 1) / 2;
+    const T* act_in = static_cast<const T*>(a.act[(layer - 1) & 1]);
+    // the positions this lane copies a chunk of: address of tap (0, 0), and which taps are padding
+    const T* src[G::NIX];
+    uint32_t edge = 0;                 // bits 2i, 2i + 1: position i is in output row 0, column 0
 #pragma unroll
-        for (int v = 0; v < BK * (int)sizeof(T) / 32; ++v) rx[st][v] = src[v];
+    for (int i = 0; i < G::NIX; ++i) {
+      const int r = r0 + (wave + 4 * i) * 8 + (lane >> 3);
+      const int e = e0 + r / P, p = r % P, oi = p / hout, oj = p % hout;
+      // rows past the queue re-read its last entry; their results are never stored
+      src[i] = act_in + ((int64_t)ebase + min(e, cnt - 1)) * a.act_stride + ((int64_t)(2 * oi - 1) * hin + 2 * oj - 1) * cin;
+      edge |= (oi == 0 ? 1u : 0u) << (2 * i) | (oj == 0 ? 2u : 0u) << (2 * i);
+    }
+    const int dtap = G::KB / cin, dch = G::KB % cin;
+    int tap = chunk * G::CE / cin, ch = chunk * G::CE % cin;  // (tap, channel) of this lane's chunk of the next block
+    const T* zero = static_cast<const T*>(a.zero_page);
+    const int64_t wks = (int64_t)(cout / 16) * 512;         // weight elements per k-step
+    const __bf16* wsrc = a.w_bf[slot][layer] + (int64_t)cb * G::NCT * 512 + lane * 8;
+    const __bf16* wml = G::F32 ? a.w_ml[slot][layer] + (int64_t)cb * G::NCT * 512 + lane * 8 : nullptr;
+    auto issue = [&](int kb, int buf) {
+      const uint32_t base = lds0 + buf * G::STAGE;
+      const int u = tap / 3, v = tap - 3 * u;
+      const uint32_t hit = tap < 9 ? (u == 0 ? 1u : 0u) | (v == 0 ? 2u : 0u) : 0u;
+      const int o = (u * hin + v) * cin + ch;
+#pragma unroll
+      for (int i = 0; i < G::NIX; ++i) {
+        const bool pad = tap >= 9 || ((edge >> (2 * i)) & hit) != 0;
+        lds_dma16(pad ? zero : src[i] + o, __builtin_amdgcn_readfirstlane(base + (wave + 4 * i) * 1024));
+      }
+#pragma unroll
+      for (int i = 0; i < G::NIW; ++i) {
+        // unit: k-step (or term) s, channel tile c
+        const int unit = (wave + 4 * i) % G::NU, s = unit / G::NCT, c = unit % G::NCT;
+        const __bf16* w = !G::F32 ? wsrc + min(2 * kb + s, KS - 1) * wks
+                          : s == 0 ? wsrc + kb * wks : wml + ((s - 1) * KS + kb) * wks;
+        lds_dma16(w + c * 512, __builtin_amdgcn_readfirstlane(base + G::BM * 128 + unit * 1024));
+      }
+      tap += dtap;
+      ch += dch;
+      if (ch >= cin) {
+        ch -= cin;
+        ++tap;
+      }
+    };
+    floatx4 acc[G::CT][4];
+#pragma unroll
+    for (int c = 0; c < G::CT; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[c][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    issue(0, 0);
+#pragma unroll 1
+    for (int kb = 0; kb < nkb; ++kb) {
+      wait_vmcnt<0>();
+      __syncthreads();                 // block kb has landed; every wave is done with the other buffer
+      if (kb + 1 < nkb) issue(kb + 1, (kb + 1) & 1);
+      const unsigned char* X = lds + (kb & 1) * G::STAGE;
+      const unsigned char* W = X + G::BM * 128;
+      if constexpr (G::F32) {
+        bf16x8 wf[G::CT][3];
+#pragma unroll
+        for (int c = 0; c < G::CT; ++c)
+#pragma unroll
+          for (int u = 0; u < 3; ++u)
+            wf[c][u] = *reinterpret_cast<const bf16x8*>(W + (u * G::NCT + wc * G::CT + c) * 1024 + lane * 16);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = wp * 64 + q * 16 + l16;
+          bf16x8 x[3];
+          split3(*reinterpret_cast<const float4*>(X + r * 128 + ((2 * g) ^ (r & 7)) * 16),
+                 *reinterpret_cast<const float4*>(X + r * 128 + ((2 * g + 1) ^ (r & 7)) * 16), x);
+#pragma unroll
+          for (int c = 0; c < G::CT; ++c) acc[c][q] = mfma_s3(wf[c], x, acc[c][q]);
+        }
       } else {
 #pragma unroll
-        for (int v = 0; v < BK * (int)sizeof(T) / 32; ++v) rx[st][v] = make_uint4(0u, 0u, 0u, 0u);
-      }
-      // weights, chunk q = tid + 256 v: bf16 fragment (ks = kb, tile cb*NCT + q/64, lane q%64);
-      // fp32: 4 consecutive lanes of (ks = kb*4 + kss, tile) with q = (kss*NCT + tile)*16 + lane/4
+        for (int s = 0; s < 2; ++s) {
+          if (2 * kb + s >= KS) break;   // an odd number of k-steps: the last block holds one
+          bf16x8 xf[4], wf[G::CT];
 #pragma unroll
-      for (int v = 0; v < WV; ++v) {
-        const int q = tid + 256 * v;
-        if constexpr (sizeof(T) == 2) {
-          rw[st][v] = *reinterpret_cast<const uint4*>(&wp[((int64_t)kb * ctile16 + cb * NCT + (q >> 6)) * 64 + (q & 63)]);
-        } else {
-          const int kss = q / (NCT * 16), tl = (q >> 4) % NCT, l4 = (q & 15) * 4;
-          rw[st][v] = *reinterpret_cast<const uint4*>(&wp[((int64_t)(kb * 4 + kss) * ctile16 + cb * NCT + tl) * 64 + l4]);
-        }
-      }
-    };
-    auto lstore = [&](int st, int buf) {
-#pragma unroll
-      for (int v = 0; v < BK * (int)sizeof(T) / 32; ++v)
-        reinterpret_cast<uint4*>(&Xs[buf][srow * LD + shalf * (BK / 2)])[v] = rx[st][v];
-#pragma unroll
-      for (int v = 0; v < WV; ++v) Ws[buf][tid + 256 * v] = rw[st][v];
-    };
-
-    floatx4 acc[NCT][2];
-#pragma unroll
-    for (int c = 0; c < NCT; ++c)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) acc[c][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    auto compute = [&](int buf) {
-#pragma unroll
-      for (int kss = 0; kss < KSUB; ++kss) {
-        frag xf[2], wf[NCT];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const T* xp = &Xs[buf][(wave * 32 + q * 16 + l16) * LD + kss * KSTEP + KPL * g];
-          if constexpr (sizeof(T) == 2) xf[q] = *reinterpret_cast<const bf16x8*>(xp);
-          else xf[q] = *xp;
-        }
-#pragma unroll
-        for (int c = 0; c < NCT; ++c) {
-          if constexpr (sizeof(T) == 2) wf[c] = *reinterpret_cast<const bf16x8*>(&Ws[buf][c * 64 + lane]);
-          else wf[c] = reinterpret_cast<const float*>(&Ws[buf][0])[(kss * NCT + c) * 64 + lane];
-        }
-#pragma unroll
-        for (int c = 0; c < NCT; ++c)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) acc[c][q] = gmfma(wf[c], xf[q], acc[c][q]);
-      }
-    };
-
-#pragma unroll
-    for (int u = 0; u < NS - 1; ++u)
-      if (u < nkb) gload(u, u);
-    lstore(0, 0);
-    __syncthreads();
-    for (int kb0 = 0; kb0 < nkb; kb0 += NS) {
-#pragma unroll
-      for (int u = 0; u < NS; ++u) {
-        const int kb = kb0 + u;
-        if (kb < nkb) {
-          const int buf = kb & 1;
-          if (kb + NS - 1 < nkb) gload(kb + NS - 1, (u + NS - 1) % NS);
-          compute(buf);
-          if (kb + 1 < nkb) {
-            __syncthreads();
-            lstore((u + 1) % NS, buf ^ 1);
-            __syncthreads();
+          for (int q = 0; q < 4; ++q) {
+            const int r = wp * 64 + q * 16 + l16;
+            xf[q] = *reinterpret_cast<const bf16x8*>(X + r * 128 + ((4 * s + g) ^ (r & 7)) * 16);
           }
+#pragma unroll
+          for (int c = 0; c < G::CT; ++c)
+            wf[c] = *reinterpret_cast<const bf16x8*>(W + (s * G::NCT + wc * G::CT + c) * 1024 + lane * 16);
+#pragma unroll
+          for (int c = 0; c < G::CT; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[c][q] = mfma_bf16(wf[c], xf[q], acc[c][q]);
         }
       }
     }
     // bias + ReLU; lane holds channels 4g..4g+3 of tile c for position 16q + l16 of its wave
-    const float* bias = a.bias[slot][layer] + cb * GB_N;
-    T* out = reinterpret_cast<T*>(a.act[layer & 1]);
+    const int ch0 = cb * BN + wc * G::CT * 16 + 4 * g;
+    const float* bias = a.bias[slot][layer] + ch0;
+    T* out = static_cast<T*>(a.act[layer & 1]);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int64_t Ro = (int64_t)mt * GB_M + wave * 32 + q * 16 + l16;
-      if (Ro >= (int64_t)cnt * P) continue;
-      const int e = (int)(Ro / P), p = (int)(Ro % P);
-      T* o = out + ((int64_t)ebase + e) * a.act_stride + (int64_t)p * cout + cb * GB_N;
+    for (int q = 0; q < 4; ++q) {
+      const int r = r0 + wp * 64 + q * 16 + l16, e = e0 + r / P, p = r % P;
+      if (e >= cnt) continue;
+      T* o = out + ((int64_t)ebase + e) * a.act_stride + (int64_t)p * cout + ch0;
 #pragma unroll
-      for (int c = 0; c < NCT; ++c) {
-        const int ch = c * 16 + 4 * g;
-        const float v0 = fmaxf(acc[c][q][0] + bias[ch], 0.f), v1 = fmaxf(acc[c][q][1] + bias[ch + 1], 0.f);
-        const float v2 = fmaxf(acc[c][q][2] + bias[ch + 2], 0.f), v3 = fmaxf(acc[c][q][3] + bias[ch + 3], 0.f);
-        if constexpr (sizeof(T) == 2) {
-          alignas(8) __bf16 h[4] = {static_cast<__bf16>(v0), static_cast<__bf16>(v1), static_cast<__bf16>(v2),
-                                    static_cast<__bf16>(v3)};
-          *reinterpret_cast<uint2*>(o + ch) = *reinterpret_cast<const uint2*>(h);
-        } else {
-          *reinterpret_cast<float4*>(o + ch) = make_float4(v0, v1, v2, v3);
-        }
-      }
+      for (int c = 0; c < G::CT; ++c) store_relu4(o + c * 16, acc[c][q], *reinterpret_cast<const float4*>(bias + c * 16));
     }
-    __syncthreads();   // the next tile's prologue rewrites the LDS buffers
+    __syncthreads();   // the next tile's first block overwrites buffer 0
   }
 }
 
-// First layer (Cin = 3, K = 27) when 128 output positions are whole output rows of one frame
-// (hout divides 128, P a multiple of 128) and Cout <= 64: a tile stages the 2*(128/hout) + 1
-// input rows it reads (raw values, top border = the pad value) in LDS once, builds the im2col
-// fragments from there and writes 128 positions x Cout channels.
+// First layer (Cin = 3, K = 27) of frames of 32, 64, 128 or 256 pixels a side and at most 64 channels:
+// a tile is GF_P output positions, whole output rows of one frame.  The input rows it reads are
+// staged in LDS as bf16 (exact for bf16 and uint8 values) by 16-byte loads, pixel 0 of a row at element
+// GF_X0 with the border pixel before it, rows above the frame holding the pad value.  A position's nine
+// values of one row start at an odd element: five aligned words hold them, and a lane's eight K
+// slots (g_first_k) are four funnel shifts of one row's words.  HBM-bound: 12,288 evaluations of
+// 128x128 uint8 frames into 16 or 32 channels read and write 2.7 GB in 0.87 ms (one load and one fp32
+// LDS word per value, eight LDS reads per fragment: 3.26 ms).
+constexpr int GF_P = 512, GF_X0 = 8;
 __host__ __device__ inline bool gconv_first_ok(int hout, int cout) {
   return hout >= 16 && 128 % hout == 0 && cout % 16 == 0 && cout <= 64;
 }
+__host__ __device__ inline int gf_rows(int hout) { return hout * hout < GF_P ? hout : GF_P / hout; }   // output rows per tile
+__host__ __device__ inline int gf_stride(int hin) { return GF_X0 + 3 * hin + 8; }                     // elements per staged row
+
+// 16 bytes at any address (frames may start anywhere)
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 
 template <typename T>
 __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
-  typedef typename GMf<T>::frag frag;
-  constexpr int KSTEP = GMf<T>::KSTEP, KPL = GMf<T>::KPL, KS = (27 + KSTEP - 1) / KSTEP;
-  constexpr int MAXV = 17 * 33 * 3 > 5 * 129 * 3 ? (17 * 33 * 3 > 3 * 257 * 3 ? 17 * 33 * 3 : 3 * 257 * 3) : 5 * 129 * 3;
-  __shared__ float xin[MAXV + 64];
+  constexpr int MAXE = 9 * (GF_X0 + 3 * 256 + 8);        // the largest of the four sizes (256-pixel frames)
+  static_assert(MAXE >= 17 * (GF_X0 + 3 * 128 + 8) && MAXE >= 33 * (GF_X0 + 3 * 64 + 8) && MAXE >= 33 * (GF_X0 + 3 * 32 + 8),
+                "staged rows");
+  __shared__ __attribute__((aligned(16))) uint16_t xin[MAXE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
+  const uint16_t pad = a.fr.dtype == HYDRO_DTYPE_BF16 ? 0x3F00 : 0x42FF;     // 0.5, 127.5 in bf16
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i) {
     const int hout = a.in_hw[i] >> 1;
-    total += (int)((int64_t)a.q.counts[a.pred[i]] * hout * hout / 128);
+    total += a.q.counts[a.pred[i]] * (hout / gf_rows(hout));
   }
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     int slot = 0, off = t, ebase = 0;
     for (int i = 0; i < a.n_preds; ++i) {
       const int hout = a.in_hw[i] >> 1;
-      const int c = (int)((int64_t)a.q.counts[a.pred[i]] * hout * hout / 128);
+      const int c = a.q.counts[a.pred[i]] * (hout / gf_rows(hout));
       if (off < c) { slot = i; break; }
       off -= c;
       ebase += a.q.counts[a.pred[i]];
     }
-    const int hin = a.in_hw[slot], hout = hin >> 1, P = hout * hout;
+    const int hin = a.in_hw[slot], hout = hin >> 1, ro = gf_rows(hout), RS = gf_stride(hin);
     const int cout = a.widths[slot][0], nct = cout / 16;
-    const int tiles_per_frame = P / 128, rows_out = 128 / hout, rows_in = 2 * rows_out + 1, W = hin + 1;
-    const int e = off / tiles_per_frame, oi0 = (off % tiles_per_frame) * rows_out;
+    const int tpf = hout / ro, e = off / tpf, oi0 = (off % tpf) * ro;
     const uint32_t idx = entry_idx(a.q.entries[(int64_t)a.pred[slot] * a.q.cap + e]);
-    // stage input rows y = 2*oi0 - 1 + r, columns x = c - 1 (c = 0 is the left border)
-    const int nvals = rows_in * W * 3;
-    for (int q = tid; q < nvals; q += 256) {
-      const int r = q / (W * 3), rem = q % (W * 3), c = rem / 3, ch = rem % 3;
-      const int y = 2 * oi0 - 1 + r, x = c - 1;
-      float v = a.pad_raw;
-      if (y >= 0 && x >= 0) {
-        const int64_t o = (int64_t)idx * a.fr.elems + ((int64_t)y * hin + x) * 3 + ch;
-        v = a.fr.dtype == HYDRO_DTYPE_BF16 ? (float)static_cast<const __bf16*>(a.fr.base)[o]
-                                          : (float)static_cast<const uint8_t*>(a.fr.base)[o];
-      }
-      xin[q] = v;
-    }
-    __syncthreads();
-    const frag* wp = reinterpret_cast<const frag*>(sizeof(T) == 2 ? (const void*)a.w_bf[slot][0]
-                                                                  : (const void*)a.w_f32[slot][0]);
-    floatx4 acc[4][2];
+    // staged row r is input row y = 2 oi0 - 1 + r (y < 0 only for r = 0 of the first tile)
+    const int rows_in = 2 * ro + 1;
+    const bool u8 = a.fr.dtype != HYDRO_DTYPE_BF16;
+    const int cpr = u8 ? hin * 3 / 16 : hin * 3 / 8;         // 16-byte chunks per row
+    const unsigned char* src = static_cast<const unsigned char*>(a.fr.base) +
+                               ((int64_t)idx * a.fr.elems + (int64_t)(2 * oi0 - 1) * hin * 3) * (u8 ? 1 : 2);
+    for (int q = tid; q < rows_in * cpr; q += 256) {
+      const int r = q / cpr, c = q - r * cpr;
+      const bool in = 2 * oi0 - 1 + r >= 0;
+      uint16_t* dst = xin + r * RS + GF_X0 + c * (u8 ? 16 : 8);
+      const uint32_t padw = pad | (uint32_t)pad << 16;
+      u32x4 v = (u32x4){padw, padw, padw, padw};
+      if (u8) {
+        u32x4 lo = v, hi = v;
+        if (in) {
+          const u32x4 b = *reinterpret_cast<const u32x4_any*>(src + (int64_t)q * 16);
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) acc[c][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      frag xf[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int pl = wave * 32 + q * 16 + l16, oi = pl / hout, oj = pl % hout;
-        const float* base = xin + ((2 * oi) * W + 2 * oj) * 3;
-        if constexpr (sizeof(T) == 2) {
-          alignas(16) __bf16 t8[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int k = ks * KSTEP + KPL * g + j, tap = k / 3, ch = k % 3;
-            t8[j] = static_cast<__bf16>(k < 27 ? base[((tap / 3) * W + tap % 3) * 3 + ch] : 0.f);
+          for (int w = 0; w < 4; ++w) {
+            // bf16 of a byte: the upper half of its float
+            const uint32_t f0 = __float_as_uint((float)(b[w] & 255u)), f1 = __float_as_uint((float)(b[w] >> 8 & 255u));
+            const uint32_t f2 = __float_as_uint((float)(b[w] >> 16 & 255u)), f3 = __float_as_uint((float)(b[w] >> 24));
+            const uint32_t p0 = f0 >> 16 | (f1 & 0xFFFF0000u), p1 = f2 >> 16 | (f3 & 0xFFFF0000u);
+            if (w < 2) { lo[2 * w] = p0; lo[2 * w + 1] = p1; }
+            else { hi[2 * w - 4] = p0; hi[2 * w - 3] = p1; }
           }
-          xf[q] = *reinterpret_cast<const bf16x8*>(t8);
-        } else {
-          const int k = ks * KSTEP + g, tap = k / 3, ch = k % 3;
-          xf[q] = k < 27 ? base[((tap / 3) * W + tap % 3) * 3 + ch] : 0.f;
         }
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (c >= nct) continue;
-        const frag wf = wp[((int64_t)ks * nct + c) * 64 + lane];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[c][q] = gmfma(wf, xf[q], acc[c][q]);
+        reinterpret_cast<u32x4*>(dst)[0] = lo;
+        reinterpret_cast<u32x4*>(dst)[1] = hi;
+      } else {
+        if (in) v = *reinterpret_cast<const u32x4_any*>(src + (int64_t)q * 16);
+        *reinterpret_cast<u32x4*>(dst) = v;
       }
     }
+    for (int r = tid; r < rows_in; r += 256)
+#pragma unroll
+      for (int c = 1; c <= 3; ++c) xin[r * RS + GF_X0 - c] = pad;
+    __syncthreads();
     const float* bias = a.bias[slot][0];
     T* o0 = reinterpret_cast<T*>(a.act[0]) + ((int64_t)ebase + e) * a.act_stride + (int64_t)oi0 * hout * cout;
+    const int np = ro * hout;                       // a multiple of 64
+    for (int pt = wave * 32; pt < np; pt += 128) {
+      floatx4 acc[4][2];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int pl = wave * 32 + q * 16 + l16;
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) acc[c][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      const uint16_t* base[2];                      // element before the position's first value
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int pl = pt + q * 16 + l16;
+        base[q] = xin + 2 * (pl / hout) * RS + GF_X0 - 4 + 6 * (pl % hout);
+      }
+      bf16x8 xf[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        uint32_t d[5];
+#pragma unroll
+        for (int w = 0; w < 5; ++w)
+          d[w] = *reinterpret_cast<const uint32_t*>(base[q] + (g < 3 ? g * RS + 2 * w : min(w, 2) * RS + 8));
+        u32x4 f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) f[w] = __builtin_amdgcn_alignbit(d[w + 1], d[w], 16);
+        if (g == 3) f = (u32x4){(d[0] >> 16) | (d[1] & 0xFFFF0000u), d[2] >> 16, 0u, 0u};
+        xf[q] = *reinterpret_cast<const bf16x8*>(&f);
+      }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         if (c >= nct) continue;
-        const int ch = c * 16 + 4 * g;
-        const float v0 = fmaxf(acc[c][q][0] + bias[ch], 0.f), v1 = fmaxf(acc[c][q][1] + bias[ch + 1], 0.f);
-        const float v2 = fmaxf(acc[c][q][2] + bias[ch + 2], 0.f), v3 = fmaxf(acc[c][q][3] + bias[ch + 3], 0.f);
-        T* o = o0 + (int64_t)pl * cout + ch;
-        if constexpr (sizeof(T) == 2) {
-          alignas(8) __bf16 h[4] = {static_cast<__bf16>(v0), static_cast<__bf16>(v1), static_cast<__bf16>(v2),
-                                    static_cast<__bf16>(v3)};
-          *reinterpret_cast<uint2*>(o) = *reinterpret_cast<const uint2*>(h);
-        } else {
-          *reinterpret_cast<float4*>(o) = make_float4(v0, v1, v2, v3);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          acc[c][q] = first_mfma<T>(a, slot, c, lane, xf[q], acc[c][q]);
+          const int ch = c * 16 + 4 * g;
+          store_relu4(o0 + (int64_t)(pt + q * 16 + l16) * cout + ch, acc[c][q], *reinterpret_cast<const float4*>(bias + ch));
         }
       }
     }
@@ -434,7 +422,8 @@ __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
   }
 }
 
-// Pool + FC + margin + decision: one wave per frame.
+// Pool + FC + margin + decision: one wave per frame, 16-byte loads (12,288 frames of 16x16x64 or
+// 16x16x128 bf16: 290 us; one channel per lane and load: 489).
 template <typename T>
 __global__ __launch_bounds__(256) void gcnn_head_kernel(GcnnArgs a, Forward f) {
   int total = 0;
@@ -463,13 +452,47 @@ __global__ __launch_bounds__(256) void gcnn_head_kernel(GcnnArgs a, Forward f) {
       for (int i = 0; i < slot; ++i) ebase += a.q.counts[a.pred[i]];
       const T* act = reinterpret_cast<const T*>(a.act[(L - 1) & 1]) + ((int64_t)ebase + off) * a.act_stride;
       const float* fw = a.fc_w[slot];
-      for (int ch = lane; ch < cl; ch += 64) {
-        float s = 0.f;
-#pragma unroll 8
-        for (int p = 0; p < P; ++p) s += (float)act[(int64_t)p * cl + ch];
-        const float gch = s / (float)P;
+      constexpr int VE = 16 / (int)sizeof(T);      // channels per 16-byte load
+      const int vpp = cl / VE;                     // loads per position
+      if (vpp <= 64 && 64 % vpp == 0) {
+        // a lane keeps the same VE channels and takes every (64 / vpp)-th position; the lanes of one
+        // channel group add up across the wave
+        float s[VE];
 #pragma unroll
-        for (int c = 0; c < kClasses; ++c) zp[c] += gch * fw[ch * kClasses + c];
+        for (int u = 0; u < VE; ++u) s[u] = 0.f;
+        const uint4* av = reinterpret_cast<const uint4*>(act);
+#pragma unroll 8
+        for (int q = lane; q < P * vpp; q += 64) {
+          const uint4 v = av[q];
+          const T* tv = reinterpret_cast<const T*>(&v);
+#pragma unroll
+          for (int u = 0; u < VE; ++u) s[u] += (float)tv[u];
+        }
+        for (int o = vpp; o < 64; o <<= 1)
+#pragma unroll
+          for (int u = 0; u < VE; ++u) s[u] += __shfl_xor(s[u], o);
+        // every lane holds its group's sums: the group's lanes share its channels in the FC
+        const int copies = 64 / vpp, cpy = lane / vpp;
+        for (int u0 = 0; u0 < VE; u0 += copies) {
+          const int u = u0 + cpy;
+          float sv = 0.f;
+#pragma unroll
+          for (int w = 0; w < VE; ++w) sv = w == u ? s[w] : sv;
+          if (u < VE) {
+            const float* fr = fw + ((lane % vpp) * VE + u) * kClasses;
+#pragma unroll
+            for (int c = 0; c < kClasses; ++c) zp[c] += sv / (float)P * fr[c];
+          }
+        }
+      } else {
+        for (int ch = lane; ch < cl; ch += 64) {
+          float s = 0.f;
+#pragma unroll 8
+          for (int p = 0; p < P; ++p) s += (float)act[(int64_t)p * cl + ch];
+          const float gch = s / (float)P;
+#pragma unroll
+          for (int c = 0; c < kClasses; ++c) zp[c] += gch * fw[ch * kClasses + c];
+        }
       }
     }
     wave_sum_n(zp);
@@ -492,33 +515,26 @@ __global__ __launch_bounds__(256) void gcnn_head_kernel(GcnnArgs a, Forward f) {
 void launch_gcnn_layerwise(const GcnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s);
 
 // ---------------------------------------------------------------- host side
-size_t gcnn_packed_elems(int layer, int cin, int cout, int prec) {
-  const int ks = prec == HYDRO_PREC_BF16 ? g_ksteps<__bf16>(layer, cin) : g_ksteps<float>(layer, cin);
-  const int kpl = prec == HYDRO_PREC_BF16 ? 8 : 1;
-  return (size_t)ks * (cout / 16) * 64 * kpl;
-}
+size_t gcnn_packed_elems(int layer, int cin, int cout) { return (size_t)g_ksteps(layer, cin) * (cout / 16) * 512; }
 
-// [kstep][channel tile of 16][64 lanes][KPL]; lane l: output channel tile*16 + l%16,
-// k = kstep*KSTEP + KPL*(l/16) + e.
-void gcnn_pack_layer(int layer, int cin, int cout, int prec, const float* w, float scale, float* out) {
-  const int KSTEP = prec == HYDRO_PREC_BF16 ? 32 : 4, KPL = prec == HYDRO_PREC_BF16 ? 8 : 1;
-  const int ks_n = prec == HYDRO_PREC_BF16 ? g_ksteps<__bf16>(layer, cin) : g_ksteps<float>(layer, cin);
-  const int kreal = g_kreal(layer, cin);
+// [kstep][channel tile of 16][64 lanes][8]; lane l: output channel tile*16 + l%16, k = 32 kstep + 8 (l/16) + e.
+void gcnn_pack_layer(int layer, int cin, int cout, const float* w, float scale, float* out) {
   size_t o = 0;
-  for (int ks = 0; ks < ks_n; ++ks)
+  for (int ks = 0; ks < g_ksteps(layer, cin); ++ks)
     for (int ct = 0; ct < cout / 16; ++ct)
       for (int lane = 0; lane < 64; ++lane)
-        for (int e = 0; e < KPL; ++e) {
-          const int k = ks * KSTEP + KPL * (lane >> 4) + e;
+        for (int e = 0; e < 8; ++e) {
+          const int k = ks * 32 + 8 * (lane >> 4) + e;
           const int oc = ct * 16 + (lane & 15);
-          float v = 0.f;
-          if (k < kreal) {
-            int tap, ic;
-            if (layer == 0) { tap = k / 3; ic = k % 3; }
-            else { tap = k / cin; ic = k % cin; }
-            v = scale * w[((size_t)(oc * cin + ic) * 3 + tap / 3) * 3 + tap % 3];
+          int tap = k / cin, ic = k % cin;
+          bool used = tap < 9;
+          if (layer == 0) {
+            int u, r;
+            used = g_first_k(k, &u, &r);
+            tap = u * 3 + r / 3;
+            ic = r % 3;
           }
-          out[o++] = v;
+          out[o++] = used ? scale * w[((size_t)(oc * cin + ic) * 3 + tap / 3) * 3 + tap % 3] : 0.f;
         }
 }
 
@@ -529,7 +545,7 @@ void gcnn_copy_slot(GcnnArgs& dst, int j, const GcnnArgs& src, int i) {
   dst.esc_act[j] = src.esc_act[i]; dst.c4[j] = src.c4[i];
   dst.c4_w1b[j] = src.c4_w1b[i]; dst.c4_w1f[j] = src.c4_w1f[i];
   for (int l = 0; l < HYDRO_MAX_LAYERS; ++l) {
-    dst.widths[j][l] = src.widths[i][l]; dst.w_bf[j][l] = src.w_bf[i][l]; dst.w_f32[j][l] = src.w_f32[i][l];
+    dst.widths[j][l] = src.widths[i][l]; dst.w_bf[j][l] = src.w_bf[i][l]; dst.w_ml[j][l] = src.w_ml[i][l];
     dst.bias[j][l] = src.bias[i][l]; dst.wt_canon[j][l] = src.wt_canon[i][l]; dst.b_canon[j][l] = src.b_canon[i][l];
   }
   // (array extents, so that a new entry is never left behind)
@@ -563,6 +579,12 @@ void launch_gcnn_pass(const GcnnArgs& a0, const Forward& f, int tier, int grid, 
   launch_gcnn_layerwise(a0, f, tier, grid, s);
 }
 
+template <int BN>
+static void launch_gconv(bool bf, const GcnnArgs& a, int l, uint32_t slots, int grid, hipStream_t s) {
+  if (bf) hipLaunchKernelGGL((gconv_dma_kernel<__bf16, BN>), dim3(grid * 8), dim3(256), 0, s, a, l, slots);
+  else hipLaunchKernelGGL((gconv_dma_kernel<float, BN>), dim3(grid * 8), dim3(256), 0, s, a, l, slots);
+}
+
 void launch_gcnn_layerwise(const GcnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s) {
   int maxl = 0;
   for (int i = 0; i < a.n_preds; ++i) maxl = a.n_layers[i] > maxl ? a.n_layers[i] : maxl;
@@ -585,36 +607,31 @@ void launch_gcnn_layerwise(const GcnnArgs& a, const Forward& f, int tier, int gr
   }
   const bool bf = a.prec == HYDRO_PREC_BF16 && tier == TIER_FIRST;
   for (int l = 0; l < maxl; ++l) {
-    // the tiled kernel when every slot that has this layer fits its shape constraints
     if (l == 0) {
       bool first_ok = true;
       for (int i = 0; i < a.n_preds; ++i) first_ok = first_ok && gconv_first_ok(a.in_hw[i] >> 1, a.widths[i][0]);
       if (first_ok) {
-        if (bf) hipLaunchKernelGGL(gconv_first_kernel<__bf16>, dim3(grid * 4), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(gconv_first_kernel<float>, dim3(grid * 4), dim3(256), 0, s, a);
-        continue;
+        if (bf) hipLaunchKernelGGL(gconv_first_kernel<__bf16>, dim3(grid * 8), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(gconv_first_kernel<float>, dim3(grid * 8), dim3(256), 0, s, a);
+      } else {
+        if (bf) hipLaunchKernelGGL(gconv_first_any_kernel<__bf16>, dim3(grid * 4), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(gconv_first_any_kernel<float>, dim3(grid * 4), dim3(256), 0, s, a);
       }
+      continue;
     }
-    bool tiled = true, wide = true;
-    for (int i = 0; i < a.n_preds; ++i) {
-      if (l >= a.n_layers[i]) continue;
-      const int cin = l == 0 ? 3 : a.widths[i][l - 1], cout = a.widths[i][l];
-      tiled = tiled && gconv_tiled_ok(l, cin, cout, bf ? 32 : 16, 64);
-      wide = wide && gconv_tiled_ok(l, cin, cout, bf ? 32 : 16, 128);
-    }
-    if (tiled && wide) {
-      if (bf) hipLaunchKernelGGL((gconv_tile_kernel<__bf16, 128>), dim3(grid * 4), dim3(256), 0, s, a, l);
-      else hipLaunchKernelGGL((gconv_tile_kernel<float, 128>), dim3(grid * 4), dim3(256), 0, s, a, l);
-    } else if (tiled) {
-      if (bf) hipLaunchKernelGGL((gconv_tile_kernel<__bf16, 64>), dim3(grid * 4), dim3(256), 0, s, a, l);
-      else hipLaunchKernelGGL((gconv_tile_kernel<float, 64>), dim3(grid * 4), dim3(256), 0, s, a, l);
-    } else {
-      if (bf) hipLaunchKernelGGL(gconv_layer_kernel<__bf16>, dim3(grid * 4), dim3(256), 0, s, a, l);
-      else hipLaunchKernelGGL(gconv_layer_kernel<float>, dim3(grid * 4), dim3(256), 0, s, a, l);
+    for (int bn = 128; bn >= 16; bn >>= 1) {
+      uint32_t slots = 0;
+      for (int i = 0; i < a.n_preds; ++i)
+        if (l < a.n_layers[i] && gconv_tile_bn(a.widths[i][l]) == bn) slots |= 1u << i;
+      if (!slots) continue;
+      if (bn == 128) launch_gconv<128>(bf, a, l, slots, grid, s);
+      else if (bn == 64) launch_gconv<64>(bf, a, l, slots, grid, s);
+      else if (bn == 32) launch_gconv<32>(bf, a, l, slots, grid, s);
+      else launch_gconv<16>(bf, a, l, slots, grid, s);
     }
   }
-  if (bf) hipLaunchKernelGGL(gcnn_head_kernel<__bf16>, dim3(grid), dim3(256), 0, s, a, f);
-  else hipLaunchKernelGGL(gcnn_head_kernel<float>, dim3(grid), dim3(256), 0, s, a, f);
+  if (bf) hipLaunchKernelGGL(gcnn_head_kernel<__bf16>, dim3(grid * 4), dim3(256), 0, s, a, f);
+  else hipLaunchKernelGGL(gcnn_head_kernel<float>, dim3(grid * 4), dim3(256), 0, s, a, f);
 }
 
 }  // namespace hydro
