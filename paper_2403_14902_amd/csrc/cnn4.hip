@@ -181,8 +181,17 @@ void c4_front_kernel(GcnnArgs a) {
       }                                                                                            \
     }                                                                                              \
   } while (0)
-  bool pf_valid = false;      // pf holds the first band of frame pf_idx
+  bool pf_valid = false;      // pf holds band pf_band of frame pf_idx
   uint32_t pf_idx = 0;
+  int pf_band = 0;
+  // Few frames (a re-score band, a small query): a frame's bands are shared among up to eight
+  // workgroups, as many as leave every workgroup one item at most.  A segment that does not start at
+  // band 0 first runs layer 1 alone of the band before it (its last row is the one above the
+  // segment).  One frame in FP32: 90 -> 22 us.
+  int segs = 1;
+  while (segs < F_NB && total * segs * 2 <= (int)gridDim.x) segs *= 2;
+  const int seg_nb = F_NB / segs;
+  total *= segs;
 
   // per-slot state (reloaded when the slot changes)
   int cur = -1;
@@ -192,7 +201,8 @@ void c4_front_kernel(GcnnArgs a) {
   float inv_s1 = 1.f, inv_s2 = 1.f;
 
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    int slot = 0, off = t, ebase = 0;
+    int slot = 0, off = t / segs, ebase = 0;
+    const int b0 = (t % segs) * seg_nb, bs = max(b0 - 1, 0);     // first band, first band run
     for (int i = 0; i < a.n_preds; ++i) {
       const int c = a.c4[i] ? a.q.counts[a.pred[i]] : 0;
       if (off < c) { slot = i; break; }
@@ -246,10 +256,12 @@ void c4_front_kernel(GcnnArgs a) {
     // the work item after this one (its first band is prefetched during this frame's last band)
     const unsigned char* next_frame = nullptr;
     uint32_t nidx = 0;
+    int nbs = 0;
     {
       const int t2 = t + gridDim.x;
       if (t2 < total) {
-        int off2 = t2, eb2 = 0, s2 = -1;
+        int off2 = t2 / segs, eb2 = 0, s2 = -1;
+        nbs = max((t2 % segs) * seg_nb - 1, 0);
         for (int i = 0; i < a.n_preds; ++i) {
           const int c = a.c4[i] ? a.q.counts[a.pred[i]] : 0;
           if (off2 < c) { s2 = i; break; }
@@ -262,22 +274,24 @@ void c4_front_kernel(GcnnArgs a) {
         }
       }
     }
-    if (!(pf_valid && pf_idx == idx)) C4_FISSUE(frame, 0);
-    C4_FCOMMIT(0);
+    if (!(pf_valid && pf_idx == idx && pf_band == bs)) C4_FISSUE(frame, bs);
+    C4_FCOMMIT(bs);
     pf_valid = false;
     T* out2 = reinterpret_cast<T*>(a.c4_act2) + ent * (32 * 32 * 64);
     unsigned* amax1 = a.c4_act_max ? a.c4_act_max + k * 4 + 0 : nullptr;
     unsigned* amax2 = a.c4_act_max ? a.c4_act_max + k * 4 + 1 : nullptr;
 
-    for (int b = 0; b < F_NB; ++b) {
+    const int be = b0 + seg_nb;
+    for (int b = bs; b < be; ++b) {
       {
         // next band of this frame, or the first band of the next work item (this frame again when
         // there is none: a load whose data is not used); in flight over this band's layers 1 and 2
-        const unsigned char* src = b + 1 < F_NB ? frame : next_frame != nullptr ? next_frame : frame;
-        C4_FISSUE(src, b + 1 < F_NB ? b + 1 : 0);
-        if (b + 1 == F_NB && next_frame != nullptr) {
+        const unsigned char* src = b + 1 < be ? frame : next_frame != nullptr ? next_frame : frame;
+        C4_FISSUE(src, b + 1 < be ? b + 1 : nbs);
+        if (b + 1 == be && next_frame != nullptr) {
           pf_valid = true;
           pf_idx = nidx;
+          pf_band = nbs;
         }
       }
       // the ring slot of layer-1 row -1 is zero for the first band
@@ -339,6 +353,7 @@ void c4_front_kernel(GcnnArgs a) {
         if constexpr (P == C4_F32) c4_track_max(amax1, m);
       }
       __syncthreads();
+      if (b >= b0) {             // (the band before a segment: layer 1 only)
 
       // ---- layer 2: output row 4b + w, columns 0..31 (two position tiles).  The FP8 and FP32
       // tiers split the k-steps over two accumulation chains (the BF16 tier has no registers
@@ -501,8 +516,9 @@ void c4_front_kernel(GcnnArgs a) {
           dst[off / 16] = *reinterpret_cast<const u32x4*>(tw + (off / RB) * F_TPITCH<P> + off % RB);
         }
       }
+      }
       __syncthreads();   // the next band restages the frame rows and overwrites ring rows
-      if (b + 1 < F_NB) C4_FCOMMIT(b + 1);
+      if (b + 1 < be) C4_FCOMMIT(b + 1);
     }
     if (tid == 0) ticks_s[k] += wall_clock64() - t0;
   }
@@ -689,6 +705,233 @@ __device__ inline void c4_gemm_epilogue(const GcnnArgs& a, const Forward& f, con
   }
 }
 
+// Layers 3 and 4 of a launch that holds few frames (a re-score band, a late round, a small query),
+// where the tiles above leave most CUs idle and one tile's time is the launch's: tiles of 64
+// positions x 128 channels (layer 3 four per frame, layer 4 two), eight waves of 16 positions x 64
+// channels, in a ring of four or five stages.  The products and the order in which they are added
+// are the large tiles', and so is the pooling's and the head's, so a frame's logits do not depend on
+// which tiles it took.  Layer 4: the two workgroups of a frame leave its pooled channels in the
+// (now free) layer-2 activations with device-scope exchanges, each complete before its workgroup
+// counts itself, and the second to arrive finishes the frame.
+// A re-score band of some 20 frames through layers 3 + 4 in FP32: 50 + 86 -> 18 + 36 us.  A launch takes
+// these tiles while its items fill the GPU at most C4_FEW times (layer 3 up to 128 frames, layer 4
+// up to 256); beyond, the large tiles, which read each weight once per two or four frames, are ahead.
+constexpr int C4_FEW = 2;
+template <int P, int LAYER>
+__device__ inline bool c4_is_few(const GcnnArgs& a) {
+  typedef GemmShape<P, LAYER> S;
+  int frames = 0;
+  for (int i = 0; i < a.n_preds; ++i) frames += a.c4[i] ? a.q.counts[a.pred[i]] : 0;
+  return (int64_t)frames * (S::HOUT * S::HOUT / 64) * (S::COUT / 128) <= (int64_t)C4_FEW * gridDim.x;
+}
+
+template <int P, int LAYER, bool X3, int LDS_BYTES>
+__device__ inline void c4_few(const GcnnArgs& a, const Forward& f, unsigned char* lds, uint32_t lds0) {
+  typedef typename C4T<P>::T T;
+  typedef GemmShape<P, LAYER> S;
+  constexpr bool S3 = P == C4_S3, HEAD = LAYER == 3;
+  static_assert(S3 || P == C4_BF16, "tiers with few-frame tiles");
+  constexpr int CIN = S::CIN, COUT = S::COUT, HIN = S::HIN, HOUT = S::HOUT, PP = HOUT * HOUT;
+  constexpr int BM = 64, BN = 128, PT = PP / BM, CTL = COUT / BN;
+  constexpr int TERMS = S3 ? (X3 ? 2 : 3) : 1, ROWA = S3 ? 64 : 128, UA = ROWA / 16;
+  constexpr int CE = 16 / (int)sizeof(T), BKE = 128 / (int)sizeof(T), NKB = 9 * CIN / BKE;
+  constexpr int AUNITS = TERMS * BN * UA, UNITS = AUNITS + BM * 8, NI = UNITS / 512, NIA = AUNITS / 512;
+  constexpr int STAGE = UNITS * 16, NS = LDS_BYTES / STAGE < 5 ? LDS_BYTES / STAGE : 5;
+  static_assert(UNITS % 512 == 0 && AUNITS % 512 == 0 && NI - NIA == 1, "eight waves fill a stage");
+  static_assert(NS >= 3 && NKB >= NS && 2 * 4 * 16 * 64 * 4 <= LDS_BYTES, "ring");
+  __shared__ float pool_s[256], zw_s[4][kClasses];
+  __shared__ int last_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
+  const int pg = wave & 3, cg = wave >> 2;
+  int frames = 0;
+  for (int i = 0; i < a.n_preds; ++i) frames += a.c4[i] ? a.q.counts[a.pred[i]] : 0;
+  const T* act_in = reinterpret_cast<const T*>(LAYER == 2 ? a.c4_act2 : a.c4_act3);
+  for (int t = blockIdx.x; t < frames * PT * CTL; t += gridDim.x) {
+    const int fi = t / (PT * CTL), pt = t / CTL % PT, cb = t % CTL;
+    int slot = 0, off = fi, ebase = 0;
+    for (int i = 0; i < a.n_preds; ++i) {
+      const int c = a.c4[i] ? a.q.counts[a.pred[i]] : 0;
+      if (off < c) { slot = i; break; }
+      off -= c;
+      ebase += a.q.counts[a.pred[i]];
+    }
+    const int k = a.pred[slot];
+    const int64_t ent = (int64_t)ebase + off;
+    if (ent >= a.act_cap) continue;         // cannot happen (the front kernel reports it)
+    const unsigned long long t0 = wall_clock64();
+    const unsigned char* img = static_cast<const unsigned char*>(a.c4_img[slot][LAYER - 2][P]) + (size_t)cb * BN * ROWA;
+    // the position row and chunk this lane gathers
+    const int r = wave * 8 + (lane >> 3), p = pt * BM + r, oi = p / HOUT, oj = p % HOUT;
+    const int chunk = ((lane & 7) ^ c4_swz<8>(r)) * CE;
+    const T* bsrc = act_in + ent * (HIN * HIN * CIN);
+    auto issue = [&](int kb) {
+      const uint32_t base = lds0 + (kb % NS) * STAGE;
+#pragma unroll
+      for (int i = 0; i < NIA; ++i) {
+        const int U = (wave + 8 * i) * 64 + lane;
+        const unsigned char* src;
+        if constexpr (S3) {
+          const int term = U / (BN * 4), rr = U / 4 % BN;
+          src = img + (size_t)kb * 3 * COUT * 64 + ((size_t)term * COUT + rr) * 64 + (U % 4) * 16;
+        } else {
+          src = img + (size_t)kb * COUT * 128 + (size_t)U * 16;
+        }
+        lds_dma16(src, __builtin_amdgcn_readfirstlane(base + (wave + 8 * i) * 1024));
+      }
+      const int ke = kb * BKE + chunk, tap = ke / CIN, ch = ke % CIN;
+      const int y = 2 * oi + tap / 3 - 1, x = 2 * oj + tap % 3 - 1;
+      const bool ok = y >= 0 && x >= 0;
+      lds_dma16(ok ? static_cast<const void*>(bsrc + (y * HIN + x) * CIN + ch) : a.zero_page,
+                __builtin_amdgcn_readfirstlane(base + (wave + 8 * NIA) * 1024));
+    };
+    floatx4 acc[4];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) acc[nt] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s0 = 0; s0 < NS - 1; ++s0) issue(s0);
+#pragma unroll 1
+    for (int kb = 0; kb < NKB; ++kb) {
+      // this wave's copies of block kb have landed; those of later blocks may be in flight
+      const int ahead = min(NS - 2, NKB - 1 - kb);
+      if (NS >= 5 && ahead >= 3) wait_vmcnt<3 * NI>();
+      else if (NS >= 4 && ahead >= 2) wait_vmcnt<2 * NI>();
+      else if (ahead >= 1) wait_vmcnt<NI>();
+      else wait_vmcnt<0>();
+      __syncthreads();
+      if (kb + NS - 1 < NKB) issue(kb + NS - 1);
+      const unsigned char* A = lds + (kb % NS) * STAGE;
+      const unsigned char* Bm = A + AUNITS * 16;
+      const int rb = pg * 16 + l16;
+      if constexpr (S3) {
+        bf16x8 x[3];
+        split3(*reinterpret_cast<const float4*>(Bm + (rb * 8 + ((2 * g) ^ c4_swz<8>(rb))) * 16),
+               *reinterpret_cast<const float4*>(Bm + (rb * 8 + ((2 * g + 1) ^ c4_swz<8>(rb))) * 16), x);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+          const int ra = cg * 64 + nt * 16 + l16;
+          bf16x8 w[3];
+#pragma unroll
+          for (int u = 0; u < TERMS; ++u)
+            w[u] = *reinterpret_cast<const bf16x8*>(A + ((u * BN + ra) * 4 + (g ^ c4_swz<4>(ra))) * 16);
+          if constexpr (X3) {
+            floatx4 c = c4_mfma(w[0], x[1], acc[nt]);
+            c = c4_mfma(w[1], x[0], c);
+            acc[nt] = c4_mfma(w[0], x[0], c);
+          } else {
+            acc[nt] = mfma_s3(w, x, acc[nt]);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          const bf16x8 x = *reinterpret_cast<const bf16x8*>(Bm + (rb * 8 + ((4 * ks + g) ^ c4_swz<8>(rb))) * 16);
+#pragma unroll
+          for (int nt = 0; nt < 4; ++nt) {
+            const int ra = cg * 64 + nt * 16 + l16;
+            acc[nt] = c4_mfma(*reinterpret_cast<const bf16x8*>(A + (ra * 8 + ((4 * ks + g) ^ c4_swz<8>(ra))) * 16), x, acc[nt]);
+          }
+        }
+      }
+    }
+    const float* bias = a.bias[slot][LAYER];
+    if constexpr (!HEAD) {
+      T* o = reinterpret_cast<T*>(a.c4_act3) + ent * (PP * COUT) + (int64_t)(pt * BM + pg * 16 + l16) * COUT;
+      unsigned* amax = a.c4_act_max ? a.c4_act_max + k * 4 + 2 : nullptr;
+      float m = 0.f;
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        // (BF16: image rows in c4_l3_channel's order, four consecutive channels all the same)
+        const int row = cb * BN + cg * 64 + nt * 16 + 4 * g, ch = S3 ? row : c4_l3_channel(row);
+        const float4 bb = *reinterpret_cast<const float4*>(bias + ch);
+        const float v0 = fmaxf(acc[nt][0] + bb.x, 0.f), v1 = fmaxf(acc[nt][1] + bb.y, 0.f);
+        const float v2 = fmaxf(acc[nt][2] + bb.z, 0.f), v3 = fmaxf(acc[nt][3] + bb.w, 0.f);
+        m = fmaxf(m, fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)));
+        c4_store4<P>(o + ch, v0, v1, v2, v3);
+      }
+      if constexpr (S3) c4_track_max(amax, m);
+      __syncthreads();                 // the next item's first stages overwrite the ring
+    } else {
+      // bias + ReLU of every position, then per channel the sum over the frame's positions in
+      // the large tile's order: lane l16's four positions, then the sixteen lanes
+      __syncthreads();
+      float* hs = reinterpret_cast<float*>(lds);           // [cg][pg][nt][r][lane]
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        const float4 bb = *reinterpret_cast<const float4*>(bias + cb * BN + cg * 64 + nt * 16 + 4 * g);
+        const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) hs[((wave * 4 + nt) * 4 + q) * 64 + lane] = fmaxf(acc[nt][q] + bv[q], 0.f);
+      }
+      __syncthreads();
+      float mine = 0.f;                                    // wave (cg, pg): channel tile nt = pg
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float sum = 0.f;
+#pragma unroll
+        for (int m4 = 0; m4 < 4; ++m4) sum += hs[(((cg * 4 + m4) * 4 + pg) * 4 + q) * 64 + lane];
+        sum = row_sum16(sum) * (1.f / PP);
+        mine = l16 == q ? sum : mine;
+      }
+      float* pool = static_cast<float*>(a.c4_act2) + (int64_t)fi * COUT;
+      if (l16 < 4) {
+        const unsigned old = atomicExch(reinterpret_cast<unsigned*>(pool + cb * BN + cg * 64 + pg * 16 + 4 * g + l16),
+                                        __float_as_uint(mine));
+        asm volatile("" : : "v"(old));                     // wait for the exchange to be done
+      }
+      __syncthreads();
+      if (tid == 0) {
+        const int n = atomicAdd(&a.c4_few_cnt[fi], 1);
+        last_s = n == CTL - 1;
+        if (last_s) atomicExch(&a.c4_few_cnt[fi], 0);      // ready for the next launch
+      }
+      __syncthreads();
+      if (last_s) {
+        if (tid < COUT)
+          pool_s[tid] = __hip_atomic_load(pool + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (wave < 4) {                                    // channels 64 wave .. + 63, as one wave of the large tile
+          const int cls = l16 < kClasses ? l16 : 0;
+          float zc = 0.f;
+#pragma unroll
+          for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int ch = wave * 64 + nt * 16 + 4 * g + q;
+              zc += pool_s[ch] * a.fc_w[slot][ch * kClasses + cls];
+            }
+          if (l16 >= kClasses) zc = 0.f;
+          zc = (__shfl(zc, l16) + __shfl(zc, 16 + l16)) + (__shfl(zc, 32 + l16) + __shfl(zc, 48 + l16));
+          if (lane < kClasses) zw_s[wave][lane] = zc;
+        }
+        __syncthreads();
+        if (wave == 0) {
+          const uint32_t e = a.q.entries[(int64_t)k * a.q.cap + off];
+          bool pass = false, defer = false;
+          if (lane == 0) {
+            float z[kClasses];
+#pragma unroll
+            for (int c = 0; c < kClasses; ++c) {
+              float sum = 0.f;
+              for (int w2 = 0; w2 < 4; ++w2) sum += zw_s[w2][c];
+              z[c] = sum + a.fc_b[slot][c];
+            }
+            const uint32_t idx = entry_idx(e);
+            if (f.logits != nullptr)
+              for (int c = 0; c < kClasses; ++c) f.logits[(int64_t)idx * kClasses + c] = (double)z[c];
+            const float d = class_margin(z, a.class_mask[slot]);
+            const float th = theta_of(f, k, idx);
+            pass = d > th;
+            defer = f.defer.entries != nullptr && fabsf(d - th) < f.tau[k];
+          }
+          if (f.logits == nullptr) forward_decision(f, k, e, lane == 0, defer, pass);
+        }
+      }
+      __syncthreads();                 // the next item reuses LDS
+    }
+    if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
+  }
+}
+
 // X3 (with P = C4_S3 only): the three-product arithmetic of the C4_X3 tier
 template <int P, int LAYER, bool X3 = false>
 __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
@@ -727,6 +970,12 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
   const T* act_in = reinterpret_cast<const T*>(LAYER == 2 ? a.c4_act2 : a.c4_act3);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
+  if constexpr (S3) {
+    if (c4_is_few<P, LAYER>(a)) {
+      c4_few<P, LAYER, X3, NS * STAGE>(a, f, lds, lds0);
+      return;
+    }
+  }
   // tiles: per slot ceil(count * PP / BM) x COUT / BN
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i)
@@ -1056,6 +1305,10 @@ __global__ __launch_bounds__(512) void c4_gemm_bf16_kernel(GcnnArgs a, Forward f
   const T* act_in = reinterpret_cast<const T*>(LAYER == 2 ? a.c4_act2 : a.c4_act3);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
+  if (c4_is_few<P, LAYER>(a)) {
+    c4_few<P, LAYER, false, NS * STAGE>(a, f, lds, lds0);
+    return;
+  }
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i)
     if (a.c4[i]) total += (int)(((int64_t)a.q.counts[a.pred[i]] * PP + BM - 1) / BM) * (COUT / BN);

@@ -116,6 +116,7 @@ struct GcnnArgs {
   void* c4_act2;                               // layer-2 outputs [act_cap][32][32][64]
   void* c4_act3;                               // layer-3 outputs [act_cap][16][16][128]
   int64_t act_cap;                             // evaluations one launch may hold
+  int* c4_few_cnt;                             // [C4_FEW_FRAMES] zero between launches: workgroups of a frame done
   unsigned* c4_act_max;                        // calibration: [predicate][4] activation maxima (bits)
   const void* zero_page;                       // 128 zero bytes (padding taps of the GEMM gathers)
 };
@@ -177,6 +178,7 @@ void launch_crop_pass(const CropArgs& a, const Forward& f, int grid, hipStream_t
 // mid x hi; layer 1 the two leading weight terms): about 2^-16 relative, the re-score tier between
 // a BF16 first pass and the FP32 tier (policy rescore3).
 enum { C4_F32 = 0, C4_BF16 = 1, C4_FP8 = 2, C4_S3 = 3, C4_X3 = 4 };
+constexpr int C4_FEW_FRAMES = 4096;              // more than a launch with few-frame layer-4 tiles holds
 struct C4FrontPack {
   std::vector<float> w1b;             // layer 1 (bf16 fragment order)
   std::vector<float> w2b, w2f;        // layer 2 (bf16 / fp32 fragment order, fp32 values)

@@ -1227,6 +1227,9 @@ static int pack_models(hydro_session* s) {
       // the FP32 tier), and the activation maxima of calibration
       if ((rc = sess_alloc(s, &ga.c4_act2, (size_t)s->act_cap * 32 * 32 * 64 * sizeof(float)))) return rc;
       if ((rc = sess_alloc(s, &ga.c4_act3, (size_t)s->act_cap * 16 * 16 * 128 * sizeof(float)))) return rc;
+      if ((rc = sess_alloc(s, (void**)&ga.c4_few_cnt, C4_FEW_FRAMES * sizeof(int)))) return rc;
+      HIP_TRY(hipMemsetAsync(ga.c4_few_cnt, 0, C4_FEW_FRAMES * sizeof(int), s->stream));
+      HIP_TRY(hipStreamSynchronize(s->stream));
       ga.c4_act_max = nullptr;
     }
     ga.esc_half = mx;
