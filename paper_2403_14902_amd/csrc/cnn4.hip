@@ -89,52 +89,97 @@ constexpr int F_NB = 8;            // bands per frame (four layer-2 rows each)
 constexpr int F_RING = 9;          // layer-1 rows held: the band's eight and the one above
 constexpr int F_SLOTS = 65;        // layer-1 columns of a row: even 0..62, then odd -1..63
 constexpr int F_FROWS = 17;        // frame rows a band reads
-constexpr int F_FPITCH = 388;      // bf16 elements per staged frame row: [0] unused, [1..3] the left
-                                   // pad column, [4 + 3x + c] column x channel c
+constexpr int F_FX0 = 8;           // element of column 0 in a staged frame row (16-byte aligned); the
+                                   // left pad column is the three elements before it
+constexpr int F_FPITCH = F_FX0 + 128 * 3;
 // Layer 1's K slot (lane group g, element e of a 16x16x32 fragment) -> k = 9u + 3v + c: lane
 // groups 0..2 hold the first 8 of the 9 (pixel, channel) values of input row g, lane group 3 the
-// ninth of rows 0..2; slots 27.. (k >= 27) have zero weights.  Each lane then reads five aligned
+// ninth of rows 0..2 and then three slots whose activation is 1 and whose weights are the bias in three
+// bf16 terms (27..29: the fp32 bias exactly); 30: nothing.  Each lane then reads five aligned
 // dwords of one staged row (or the ninth element of each row) instead of eight 2-byte elements.
-__host__ __device__ inline int c4_l1_k(int g, int e) { return g < 3 ? 9 * g + e : e < 3 ? 9 * e + 8 : 27; }
+__host__ __device__ inline int c4_l1_k(int g, int e) { return g < 3 ? 9 * g + e : e < 3 ? 9 * e + 8 : e < 6 ? 24 + e : 30; }
 
-template <int P> struct FrontCfg;
-// bytes per layer-1 column slot (32 channels + padding: the slot pitch in 16-byte units is odd so
-// that eight consecutive slots fall on distinct bank groups)
-template <> struct FrontCfg<C4_F32> { static constexpr int PITCH = 144; };
-template <> struct FrontCfg<C4_BF16> { static constexpr int PITCH = 80; };
-template <> struct FrontCfg<C4_FP8> { static constexpr int PITCH = 48; };
+// Per tier: waves per workgroup, bytes per layer-1 column slot (32 channels, FP32 arithmetic in bf16
+// planes of 64 bytes, + padding: the slot pitch in 16-byte units is odd so that eight consecutive
+// slots fall on distinct bank groups), output channels per wave of layer 2
+template <int P, bool X3> struct FrontCfg;
+template <bool X3> struct FrontCfg<C4_F32, X3> { static constexpr int NW = 8, PLANES = X3 ? 2 : 3, PITCH = X3 ? 144 : 208, CW = 32; };
+template <> struct FrontCfg<C4_BF16, false> { static constexpr int NW = 4, PLANES = 1, PITCH = 80, CW = 64; };
+template <> struct FrontCfg<C4_FP8, false> { static constexpr int NW = 4, PLANES = 1, PITCH = 48, CW = 64; };
 
-// bytes per position row of the layer-2 output staging (64 channels + 16 bytes of padding)
-template <int P> constexpr int F_TPITCH = 64 * C4T<P>::ES + 16;
-// the frame band area, which also stages the layer-2 output (4 waves x 32 positions) after
-// layer 1 has read the band
-template <int P>
-constexpr int F_FRAME_B = ((F_FROWS * F_FPITCH * 2 > 4 * 32 * F_TPITCH<P> ? F_FROWS * F_FPITCH * 2 : 4 * 32 * F_TPITCH<P>) + 15) / 16 * 16;
-template <int P> constexpr int front_lds_bytes() { return F_FRAME_B<P> + F_RING * F_SLOTS * FrontCfg<P>::PITCH; }
+// bytes per position row of a wave's layer-2 output staging (its channels + 16 bytes of padding)
+template <int P> constexpr int F_TPITCH = FrontCfg<P, false>::CW * C4T<P>::ES + 16;
+// the frame band area, which also stages the layer-2 output (32 positions a wave) after layer 1 has
+// read the band
+constexpr int c4_max(int x, int y) { return x < y ? y : x; }
+template <int P> constexpr int front_waves() { typedef FrontCfg<P, false> C; return C::NW; }
+template <int P> constexpr int F_FRAME_B = c4_max(F_FROWS * F_FPITCH * 2, front_waves<P>() * 32 * F_TPITCH<P>);
+// A ring row: even columns j at j / 2 slots, odd ones (from -1) at ODD + (j + 1) / 2 slots.  The gap
+// before the odd ones makes sixteen consecutive columns, which one store writes, fall on distinct
+// 16-byte bank groups: with a slot of p (odd) groups, even column 2m starts at group p m, odd column 2m + 1
+// at p m + 8.
+template <int PITCH> struct RingRow {
+  static constexpr int GAP = ((8 - PITCH / 16) % 16 + 16) % 16 * 16;
+  static constexpr int ODD = 32 * PITCH + GAP, BYTES = F_SLOTS * PITCH + GAP;
+};
+template <int P, bool X3> constexpr int front_ring_bytes() { typedef FrontCfg<P, X3> C; return F_RING * RingRow<C::PITCH>::BYTES; }
+template <int P, bool X3> constexpr int front_lds_bytes() { return F_FRAME_B<P> + front_ring_bytes<P, X3>(); }
 
-// Layer-1 column j -> its slot in a ring row.
-__device__ inline int f_slot(int j) { return (j & 1) ? 32 + ((j + 1) >> 1) : (j >> 1); }
+// Four values (>= 0) as PLANES bf16 planes `pitch` bytes apart: v = sum of the planes, exactly with three
+// and to 2^-16 with two.
+template <int PLANES>
+__device__ inline void c4_store_planes(unsigned char* dst, int pitch, const float (&v)[4]) {
+  float r[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+  for (int t = 0; t < PLANES; ++t) {
+    alignas(8) __bf16 h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      h[i] = static_cast<__bf16>(r[i]);
+      r[i] -= static_cast<float>(h[i]);
+    }
+    *reinterpret_cast<uint2*>(dst + t * pitch) = *reinterpret_cast<const uint2*>(h);
+  }
+}
 
-// X3 (with P = C4_F32 only): the three-product arithmetic of the C4_X3 tier
+// Where channel ch (a multiple of 4) of a position stored as two planes starts: [32-channel group][hi, mid][32].
+__device__ inline unsigned char* c4_plane_ptr(void* pos, int ch) {
+  return static_cast<unsigned char*>(pos) + (ch >> 5) * 128 + (ch & 31) * 2;
+}
+
+// What bounds it: vector instructions and latency, not the matrix cores (25 % busy in BF16 before).
+// Hence the layer-1 gather as five loads at addresses fixed for the launch, two permutes and two
+// shifts, the biases inside the MFMAs (layer 1 in spare K slots, layer 2 as the accumulators' start),
+// and for the FP32 arithmetic the split of layer 1's outputs into bf16 terms once, where they are
+// written to the ring, with eight waves (four, splitting at every read: 113 us a frame in the
+// three-product tier, now 66).  8,192 uint8 frames in BF16: 603 -> 565 us; eight waves of half the channels
+// each took the same time there, what they gained in latency spent on twice the ring reads.
+// X3 (with P = C4_F32 only): the three-product arithmetic of the C4_X3 tier; its layer-2 outputs are
+// stored as two bf16 planes, [position][32-channel group][hi, mid][32], in the bytes of the fp32 values.
 template <int P, bool U8, bool X3 = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == C4_F32 ? 1 : 2)))
+__global__ __launch_bounds__((FrontCfg<P, X3>::NW * 64)) __attribute__((amdgpu_waves_per_eu(2)))
 void c4_front_kernel(GcnnArgs a) {
   typedef typename C4T<P>::T T;
+  typedef FrontCfg<P, X3> C;
   constexpr int ES = C4T<P>::ES;
-  constexpr int PITCH = FrontCfg<P>::PITCH;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[front_lds_bytes<P>()];
+  constexpr int PITCH = C::PITCH, PLANES = C::PLANES, NTHR = C::NW * 64;
+  constexpr bool F32 = P == C4_F32;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[front_lds_bytes<P, X3>()];
   __shared__ unsigned long long ticks_s[kMaxK];
-  // per-slot epilogue constants: layer-1 bias [32], layer-2 bias [64], FP8 layer-2 scales [64]
-  __shared__ __attribute__((aligned(16))) float consts_s[160];
-  __shared__ __attribute__((aligned(16))) bf16x8 w1_s[2][64];   // layer-1 fragments (bf16 tiers)
+  // per-slot epilogue constants: layer-2 bias [64], FP8 layer-2 scales [64]
+  __shared__ __attribute__((aligned(16))) float consts_s[128];
+  // layer-1 fragments: [channel tile]; X3: [term][channel tile] (three terms stay in registers, LDS is full)
+  constexpr int W1N = X3 ? 4 : F32 ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) bf16x8 w1_s[W1N][64];
   __bf16* fb = reinterpret_cast<__bf16*>(lds);          // staged frame band (raw values, bf16)
   unsigned char* ring = lds + F_FRAME_B<P>;                // layer-1 output rows
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, l16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (tid < kMaxK) ticks_s[tid] = 0;
-  // the left pad column (slot 32) of every ring row is a zero activation
-  for (int q = tid; q < F_RING * (PITCH / 4); q += 256)
-    reinterpret_cast<uint32_t*>(ring + (q / (PITCH / 4)) * F_SLOTS * PITCH + 32 * PITCH)[q % (PITCH / 4)] = 0u;
+  // the left pad column (the first odd one) of every ring row is a zero activation
+  typedef RingRow<PITCH> RR;
+  for (int q = tid; q < F_RING * (PITCH / 4); q += NTHR)
+    reinterpret_cast<uint32_t*>(ring + (q / (PITCH / 4)) * RR::BYTES + RR::ODD)[q % (PITCH / 4)] = 0u;
 
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i) total += a.c4[i] ? a.q.counts[a.pred[i]] : 0;
@@ -143,7 +188,7 @@ void c4_front_kernel(GcnnArgs a) {
   // next frame's first band during the last band), and converted into LDS after it.
   constexpr int CPR = U8 ? 24 : 48;
   constexpr int NCHUNK = F_FROWS * CPR;
-  constexpr int NPF = (NCHUNK + 255) / 256;
+  constexpr int NPF = (NCHUNK + NTHR - 1) / NTHR;
   constexpr int FROWB = 128 * 3 * (U8 ? 1 : 2);
   u32x4 pf[NPF];
   // the loads are unconditional (indices clamped; a clamped chunk is never committed), so that the
@@ -151,32 +196,35 @@ void c4_front_kernel(GcnnArgs a) {
 #define C4_FISSUE(frm_, band_)                                                                     \
   do {                                                                                             \
     _Pragma("unroll") for (int c = 0; c < NPF; ++c) {                                              \
-      const int q = min(tid + 256 * c, NCHUNK - 1);                                                \
+      const int q = min(tid + NTHR * c, NCHUNK - 1);                                               \
       const int y = max(16 * (band_) - 1 + q / CPR, 0);                                            \
       pf[c] = reinterpret_cast<const u32x4*>((frm_) + (int64_t)y * FROWB)[q % CPR];                \
     }                                                                                              \
   } while (0)
+  const uint32_t pad2 = __builtin_amdgcn_perm(__float_as_uint(a.pad_raw), __float_as_uint(a.pad_raw), 0x07060302u);
 #define C4_FCOMMIT(band_)                                                                          \
   do {                                                                                             \
-    /* the pad column (elements 1..3 of each row; the area also stages layer-2 output) */           \
-    if (tid < F_FROWS * 4) fb[(tid >> 2) * F_FPITCH + (tid & 3)] = static_cast<__bf16>(a.pad_raw); \
+    /* the pad column (the three elements before column 0; the area also stages layer-2 output) */ \
+    if (tid < F_FROWS * 2)                                                                         \
+      reinterpret_cast<uint32_t*>(fb + (tid >> 1) * F_FPITCH)[2 + (tid & 1)] = pad2;               \
     _Pragma("unroll") for (int c = 0; c < NPF; ++c) {                                              \
-      const int q = tid + 256 * c;                                                                 \
+      const int q = tid + NTHR * c;                                                                \
       if (q < NCHUNK) {                                                                            \
-        const int r = q / CPR, j = q % CPR, y = 16 * (band_) - 1 + r;                              \
-        __bf16* dst = fb + r * F_FPITCH + 4 + (U8 ? 16 : 8) * j;                                   \
-        if (y < 0) {                                                                               \
-          _Pragma("unroll") for (int e = 0; e < (U8 ? 16 : 8); ++e) dst[e] = static_cast<__bf16>(a.pad_raw); \
-        } else if (U8) {                                                                           \
-          _Pragma("unroll") for (int h = 0; h < 4; ++h) {                                          \
-            alignas(8) __bf16 e4[4];                                                               \
-            _Pragma("unroll") for (int e = 0; e < 4; ++e)                                          \
-              e4[e] = static_cast<__bf16>((float)((pf[c][h] >> (8 * e)) & 0xFFu));                 \
-            *reinterpret_cast<uint2*>(dst + 4 * h) = *reinterpret_cast<const uint2*>(e4);           \
+        const int r = q / CPR, j = q % CPR;                                                        \
+        u32x4* dst = reinterpret_cast<u32x4*>(fb + r * F_FPITCH + F_FX0 + (U8 ? 16 : 8) * j);      \
+        const bool above = (band_) == 0 && r == 0;     /* the row above the frame */               \
+        if (U8) {                                                                                  \
+          u32x4 h[2];                                                                              \
+          _Pragma("unroll") for (int w = 0; w < 8; ++w) {                                          \
+            /* bf16 of a byte: the upper half of its float (exact) */                              \
+            const uint32_t b = pf[c][w >> 1] >> (16 * (w & 1));                                    \
+            const uint32_t f0 = __float_as_uint((float)(b & 255u)), f1 = __float_as_uint((float)(b >> 8 & 255u)); \
+            h[w >> 2][w & 3] = above ? pad2 : __builtin_amdgcn_perm(f1, f0, 0x07060302u);          \
           }                                                                                        \
+          dst[0] = h[0];                                                                           \
+          dst[1] = h[1];                                                                           \
         } else {                                                                                   \
-          *reinterpret_cast<uint2*>(dst) = make_uint2(pf[c][0], pf[c][1]);                         \
-          *reinterpret_cast<uint2*>(dst + 4) = make_uint2(pf[c][2], pf[c][3]);                     \
+          dst[0] = above ? (u32x4){pad2, pad2, pad2, pad2} : pf[c];                                \
         }                                                                                          \
       }                                                                                            \
     }                                                                                              \
@@ -187,18 +235,34 @@ void c4_front_kernel(GcnnArgs a) {
   // Few frames (a re-score band, a small query): a frame's bands are shared among up to eight
   // workgroups, as many as leave every workgroup one item at most.  A segment that does not start at
   // band 0 first runs layer 1 alone of the band before it (its last row is the one above the
-  // segment).  One frame in FP32: 90 -> 22 us.
+  // segment).  Some 20 frames in FP32: 90 -> 22 us, 16 with the eight waves.
   int segs = 1;
   while (segs < F_NB && total * segs * 2 <= (int)gridDim.x) segs *= 2;
   const int seg_nb = F_NB / segs;
   total *= segs;
 
+  // Layer 1's gather.  The 9 values of input row u for output column j (pixels 2j-1 .. 2j+1) are
+  // elements 6j + 5 .. 6j + 13 of the staged row: dwords from element 6j + 4 hold them in pairs.
+  // Lane groups 0..2 read dwords 0..4 of row g, group 3 dword 4 of rows 0..2.
+  constexpr int RP = F_FPITCH / 2;            // dwords per staged row
+  constexpr int L1R = 8 / C::NW;              // layer-1 rows per wave
+  const uint32_t* gp[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i)
+    gp[i] = reinterpret_cast<const uint32_t*>(fb) + 2 * L1R * wave * RP + (g < 3 ? g * RP + i : min(i, 2) * RP + 4) + 3 * l16 + 2;
+  // group 3: word 0 = ninths of rows 0 and 1, word 1 = ninth of row 2 and 1.0, word 2 = 1.0, 1.0, word 3 = 0
+  const uint32_t sel0 = g < 3 ? 0x05040302u : 0x07060302u, sel1 = g < 3 ? 0x05040302u : 0x03020706u;
+  const uint32_t m1 = g < 3 ? ~0u : 0xFFFFu, c1 = g < 3 ? 0u : 0x3F800000u, m2 = g < 3 ? ~0u : 0u, c2 = g < 3 ? 0u : 0x3F803F80u;
+
   // per-slot state (reloaded when the slot changes)
   int cur = -1;
-  bf16x8 w1t[P == C4_F32 ? 3 : 1][2];   // layer-1 weights, FP32 arithmetic: [term][channel tile]
+  bf16x8 w1t[F32 && !X3 ? 3 : 1][2];                 // layer-1 weights, FP32 arithmetic: [term][channel tile]
   bf16x8 w2b[P == C4_BF16 ? 9 : 1][2][2];            // [tap][channel half of the tap][32-channel tile]
+  bf16x8 w2x[X3 ? 9 : 1][2][2];                      // three-product tier: [tap][term][the wave's channel tile]
   i32x8 w2q[P == C4_FP8 ? 3 : 1][P == C4_FP8 ? 4 : 1];
   float inv_s1 = 1.f, inv_s2 = 1.f;
+  // layer 2: this wave's output row of the band and first channel
+  const int lrow = wave & 3, lch = (wave >> 2) * C::CW;
 
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     int slot = 0, off = t / segs, ebase = 0;
@@ -219,18 +283,17 @@ void c4_front_kernel(GcnnArgs a) {
     if (slot != cur) {
       cur = slot;
       // (the previous frame's last barrier ordered every read of the previous slot's constants)
-      if (tid < 32) consts_s[tid] = a.bias[slot][0][tid];
-      else if (tid < 96) consts_s[tid] = a.bias[slot][1][tid - 32];
-      else if (tid < 160)
-        consts_s[tid] = P == C4_FP8 ? a.c4_wscale[slot][0][tid - 96] * a.c4_ascale[slot][0] : 1.f;
-      if constexpr (P == C4_F32) {
+      if (tid < 64) consts_s[tid] = a.bias[slot][1][tid];
+      else if (tid < 128)
+        consts_s[tid] = P == C4_FP8 ? a.c4_wscale[slot][0][tid - 64] * a.c4_ascale[slot][0] : 1.f;
+      if constexpr (F32 && !X3) {
         const bf16x8* w1 = static_cast<const bf16x8*>(a.c4_w1f[slot]);
 #pragma unroll
         for (int t = 0; t < 3; ++t)
 #pragma unroll
           for (int ct = 0; ct < 2; ++ct) w1t[t][ct] = w1[(t * 2 + ct) * 64 + lane];
       } else {
-        if (tid < 128) w1_s[tid >> 6][tid & 63] = static_cast<const bf16x8*>(a.c4_w1b[slot])[tid];
+        if (tid < W1N * 64) w1_s[tid >> 6][tid & 63] = static_cast<const bf16x8*>(X3 ? a.c4_w1f[slot] : a.c4_w1b[slot])[tid];
       }
       if constexpr (P == C4_BF16) {
         const bf16x8* w2 = static_cast<const bf16x8*>(a.c4_w2[slot][C4_BF16]);
@@ -240,6 +303,15 @@ void c4_front_kernel(GcnnArgs a) {
           for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2) w2b[tp][h][c2] = w2[((tp * 2 + h) * 2 + c2) * 64 + lane];
+      }
+      if constexpr (X3) {
+        const bf16x8* w2 = static_cast<const bf16x8*>(a.c4_w2[slot][C4_S3]);
+#pragma unroll
+        for (int tp = 0; tp < 9; ++tp)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) w2x[tp][u][c] = w2[((tp * 4 + lch / 16 + c) * 3 + u) * 64 + lane];
       }
       if constexpr (P == C4_FP8) {
         const i32x8* w2 = static_cast<const i32x8*>(a.c4_w2[slot][C4_FP8]);
@@ -277,7 +349,7 @@ void c4_front_kernel(GcnnArgs a) {
     if (!(pf_valid && pf_idx == idx && pf_band == bs)) C4_FISSUE(frame, bs);
     C4_FCOMMIT(bs);
     pf_valid = false;
-    T* out2 = reinterpret_cast<T*>(a.c4_act2) + ent * (32 * 32 * 64);
+    unsigned char* out2 = static_cast<unsigned char*>(a.c4_act2) + ent * (32 * 32 * 64 * ES);
     unsigned* amax1 = a.c4_act_max ? a.c4_act_max + k * 4 + 0 : nullptr;
     unsigned* amax2 = a.c4_act_max ? a.c4_act_max + k * 4 + 1 : nullptr;
 
@@ -297,81 +369,88 @@ void c4_front_kernel(GcnnArgs a) {
       // the ring slot of layer-1 row -1 is zero for the first band
       const int base_slot = (8 * b) % F_RING;   // ring index of layer-1 row 8b - 1
       if (b == 0)
-        for (int q = tid; q < F_SLOTS * PITCH / 4; q += 256) reinterpret_cast<uint32_t*>(ring)[q] = 0u;
+        for (int q = tid; q < RR::BYTES / 4; q += NTHR) reinterpret_cast<uint32_t*>(ring)[q] = 0u;
       __syncthreads();
 
-      // ---- layer 1: rows 8b + 2w, 8b + 2w + 1 (local i = 2w, 2w+1), 64 columns each
-#pragma unroll 1
-      for (int pt = 0; pt < 8; ++pt) {
-        const int il = 2 * wave + (pt >> 2), j = (pt & 3) * 16 + l16;
-        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        // the 9 values of input row u for output column j (pixels 2j-1 .. 2j+1) are elements
-        // 6j+1 .. 6j+9 of the staged row; dwords from element 6j hold them in pairs
-        const uint32_t* rw = reinterpret_cast<const uint32_t*>(fb + (2 * il) * F_FPITCH + 6 * j);
-        constexpr int RP = F_FPITCH / 2;      // dwords per staged row
-        uint32_t d[5];
+      // ---- layer 1: the wave's rows (local i = L1R w ..), four tiles of 16 columns each
 #pragma unroll
-        for (int i = 0; i < 5; ++i) d[i] = rw[g < 3 ? g * RP + i : (i < 3 ? i * RP + 4 : 4)];
-        uint32_t xw[4];
+      for (int ir = 0; ir < L1R; ++ir) {
+        const int ridx = (base_slot + 1 + L1R * wave + ir) % F_RING;
+        unsigned char* drow = ring + ridx * RR::BYTES + ((l16 & 1) ? RR::ODD + ((l16 + 1) >> 1) * PITCH : (l16 >> 1) * PITCH) +
+                              4 * g * (F32 ? 2 : ES);
+        bf16x8 wf[W1N];
+        if constexpr (!F32 || X3)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t row = __builtin_amdgcn_alignbit(d[i + 1], d[i], 16);   // elements 2i+1, 2i+2
-          const uint32_t ninth = i == 0 ? (d[0] >> 16) | (d[1] & 0xFFFF0000u) : i == 1 ? d[2] >> 16 : 0u;
-          xw[i] = g < 3 ? row : ninth;
-        }
-        bf16x8 xb;
-        __builtin_memcpy(&xb, xw, sizeof(xb));
-        if constexpr (P == C4_F32) {
-          // raw frame values are exact in bf16 and the weights are the sum of their three terms:
-          // every product exact, fp32 sums (smallest term first); X3 drops the lowest term
-#pragma unroll
-          for (int ct = 0; ct < 2; ++ct) {
-            if constexpr (!X3) acc[ct] = c4_mfma(w1t[2][ct], xb, acc[ct]);
-            acc[ct] = c4_mfma(w1t[1][ct], xb, acc[ct]);
-            acc[ct] = c4_mfma(w1t[0][ct], xb, acc[ct]);
-          }
-        } else {
-          acc[0] = c4_mfma(w1_s[0][lane], xb, acc[0]);
-          acc[1] = c4_mfma(w1_s[1][lane], xb, acc[1]);
-        }
-        const int ridx = (base_slot + 1 + il) % F_RING;
-        unsigned char* dst = ring + (ridx * F_SLOTS + f_slot(j)) * PITCH;
+          for (int i = 0; i < W1N; ++i) wf[i] = w1_s[i][lane];
         float m = 0.f;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          const float4 bb = *reinterpret_cast<const float4*>(consts_s + ct * 16 + 4 * g);
-          const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
-          float v[4];
+        for (int jt = 0; jt < 4; ++jt) {
+          uint32_t d[5];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            v[r] = fmaxf(acc[ct][r] + bv[r], 0.f);
-            m = fmaxf(m, v[r]);
-            v[r] *= inv_s1;
+          for (int i = 0; i < 5; ++i) d[i] = gp[i][2 * ir * RP + 48 * jt];
+          uint32_t xw[4];
+          xw[0] = __builtin_amdgcn_perm(d[1], d[0], sel0);
+          xw[1] = (__builtin_amdgcn_perm(d[2], d[1], sel1) & m1) | c1;
+          xw[2] = (__builtin_amdgcn_alignbit(d[3], d[2], 16) & m2) | c2;
+          xw[3] = __builtin_amdgcn_alignbit(d[4], d[3], 16) & m2;
+          bf16x8 xb;
+          __builtin_memcpy(&xb, xw, sizeof(xb));
+#pragma unroll
+          for (int ct = 0; ct < 2; ++ct) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            // FP32 arithmetic: raw frame values are exact in bf16 and the weights are the sum of their
+            // three terms: every product exact, fp32 sums (smallest term first); X3 drops the lowest
+            if constexpr (X3) {
+              acc = c4_mfma(wf[2 + ct], xb, acc);
+              acc = c4_mfma(wf[ct], xb, acc);
+            } else if constexpr (F32) {
+              acc = c4_mfma(w1t[2][ct], xb, acc);
+              acc = c4_mfma(w1t[1][ct], xb, acc);
+              acc = c4_mfma(w1t[0][ct], xb, acc);
+            } else {
+              acc = c4_mfma(wf[ct], xb, acc);
+            }
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[r], 0.f);
+            unsigned char* dst = drow + 8 * jt * PITCH + ct * 16 * (F32 ? 2 : ES);
+            if constexpr (F32) {
+              if (!X3 && amax1 != nullptr) m = fmaxf(m, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+              c4_store_planes<PLANES>(dst, 64, v);
+            } else {
+              if constexpr (P == C4_FP8)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] *= inv_s1;
+              c4_store4<P>(dst, v[0], v[1], v[2], v[3]);
+            }
           }
-          c4_store4<P>(dst + (ct * 16 + 4 * g) * ES, v[0], v[1], v[2], v[3]);
         }
-        if constexpr (P == C4_F32) c4_track_max(amax1, m);
+        if constexpr (F32 && !X3) c4_track_max(amax1, m);
       }
       __syncthreads();
       if (b >= b0) {             // (the band before a segment: layer 1 only)
-
-      // ---- layer 2: output row 4b + w, columns 0..31 (two position tiles).  The FP8 and FP32
-      // tiers split the k-steps over two accumulation chains (the BF16 tier has no registers
-      // left for a second chain: its layer-2 weights take 144)
-      floatx4 acc[P == C4_BF16 ? 1 : 2][4][2];
+      // ---- layer 2: output row 4b + lrow, columns 0..31 (two position tiles), channels lch ..; the sums
+      // start from the bias
+      floatx4 acc[F32 ? 2 : P == C4_FP8 ? 4 : 1][2];
       floatx16 acc32[P == C4_BF16 ? 2 : 1];
       if constexpr (P == C4_BF16) {
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) acc32[c2][e] = 0.f;
+          for (int vq = 0; vq < 4; ++vq) {
+            const float4 bb = *reinterpret_cast<const float4*>(consts_s + c2 * 32 + 8 * vq + 4 * (lane >> 5));
+            acc32[c2][4 * vq] = bb.x; acc32[c2][4 * vq + 1] = bb.y; acc32[c2][4 * vq + 2] = bb.z; acc32[c2][4 * vq + 3] = bb.w;
+          }
+      } else if constexpr (F32) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) acc[c][mt] = *reinterpret_cast<const floatx4*>(consts_s + lch + 16 * c + 4 * g);
       } else {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-          for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) acc[h][ct][mt] = (floatx4){0.f, 0.f, 0.f, 0.f};
+          for (int mt = 0; mt < 2; ++mt) acc[ct][mt] = (floatx4){0.f, 0.f, 0.f, 0.f};
       }
       // ring row of layer-1 row 8b + 2w + u - 1 is (base_slot + 2w + u) mod 9
       if constexpr (P == C4_FP8) {
@@ -380,20 +459,19 @@ void c4_front_kernel(GcnnArgs a) {
           int tp = 4 * s + g;
           tp = tp > 8 ? 8 : tp;       // taps 9..11: zero weights
           const int u = tp / 3, v = tp % 3;
-          const int rr = (base_slot + 2 * wave + u) % F_RING;
+          const int rr = (base_slot + 2 * lrow + u) % F_RING;
           i32x8 xb[2];
 #pragma unroll
           for (int mt = 0; mt < 2; ++mt) {
             const int j = mt * 16 + l16;
-            const int sl = v == 1 ? j : v == 0 ? 32 + j : 33 + j;
-            const uint4* src = reinterpret_cast<const uint4*>(ring + (rr * F_SLOTS + sl) * PITCH);
+            const uint4* src = reinterpret_cast<const uint4*>(ring + rr * RR::BYTES + j * PITCH + (v == 1 ? 0 : RR::ODD + (v >> 1) * PITCH));
             const uint4 lo = src[0], hi = src[1];
             xb[mt] = (i32x8){(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
           }
 #pragma unroll
           for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt) acc[s & 1][ct][mt] = c4_mfma(w2q[s][ct], xb[mt], acc[s & 1][ct][mt]);
+            for (int mt = 0; mt < 2; ++mt) acc[ct][mt] = c4_mfma(w2q[s][ct], xb[mt], acc[ct][mt]);
         }
       } else if constexpr (P == C4_BF16) {
         // the wave's 32 positions (lane % 32) x two 32-channel tiles; k-step (tap, h): channels
@@ -402,11 +480,11 @@ void c4_front_kernel(GcnnArgs a) {
 #pragma unroll
         for (int tp = 0; tp < 9; ++tp) {
           const int u = tp / 3, v = tp % 3;
-          const int rr = (base_slot + 2 * wave + u) % F_RING;
-          const int sl = v == 1 ? j : v == 0 ? 32 + j : 33 + j;
+          const int rr = (base_slot + 2 * lrow + u) % F_RING;
+          const unsigned char* src = ring + rr * RR::BYTES + j * PITCH + (v == 1 ? 0 : RR::ODD + (v >> 1) * PITCH) + 16 * hg;
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
-            const bf16x8 xb = *reinterpret_cast<const bf16x8*>(ring + (rr * F_SLOTS + sl) * PITCH + (16 * h + 8 * hg) * 2);
+            const bf16x8 xb = *reinterpret_cast<const bf16x8*>(src + 32 * h);
             acc32[0] = c4_mfma32(w2b[tp][h][0], xb, acc32[0]);
             acc32[1] = c4_mfma32(w2b[tp][h][1], xb, acc32[1]);
           }
@@ -415,105 +493,90 @@ void c4_front_kernel(GcnnArgs a) {
         }
       } else {
         // FP32 arithmetic from bf16 MFMAs: per tap, lane group g takes input channels 8g..8g+7
-        // (one 16x16x32 k-step); the fp32 layer-1 activations are split into three bf16 terms
-        // and multiplied with the three-term weights (L2-resident, [tap][ct][term][lane]); the
-        // six products down to 2^-24 relative are summed, smallest first
+        // (one 16x16x32 k-step) of the ring's planes, multiplied with the three-term weights
+        // ([tap][ct][term][lane]; X3 holds its two terms in registers, the three terms are read from
+        // L2); the six products down to 2^-24 relative (X3: the three leading ones) are summed,
+        // smallest first
         const bf16x8* w2 = static_cast<const bf16x8*>(a.c4_w2[slot][C4_S3]);
-#pragma unroll 1
+#pragma unroll
         for (int tp = 0; tp < 9; ++tp) {
           const int u = tp / 3, v = tp % 3;
-          const int rr = (base_slot + 2 * wave + u) % F_RING;
+          const int rr = (base_slot + 2 * lrow + u) % F_RING;
           bf16x8 xs[2][3];
 #pragma unroll
           for (int mt = 0; mt < 2; ++mt) {
             const int j = mt * 16 + l16;
-            const int sl = v == 1 ? j : v == 0 ? 32 + j : 33 + j;
-            const float4* src = reinterpret_cast<const float4*>(ring + (rr * F_SLOTS + sl) * PITCH + 32 * g);
-            const float4 p0 = src[0], p1 = src[1];
-            const float xv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+            const unsigned char* src = ring + rr * RR::BYTES + j * PITCH + (v == 1 ? 0 : RR::ODD + (v >> 1) * PITCH) + 16 * g;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const __bf16 h = static_cast<__bf16>(xv[e]);
-              const float r1 = xv[e] - static_cast<float>(h);
-              const __bf16 m = static_cast<__bf16>(r1);
-              xs[mt][0][e] = h;
-              xs[mt][1][e] = m;
-              xs[mt][2][e] = static_cast<__bf16>(r1 - static_cast<float>(m));
-            }
+            for (int pl = 0; pl < PLANES; ++pl) xs[mt][pl] = *reinterpret_cast<const bf16x8*>(src + 64 * pl);
           }
 #pragma unroll
-          for (int ct = 0; ct < 4; ++ct) {
-            const bf16x8 wh = w2[((tp * 4 + ct) * 3 + 0) * 64 + lane];
-            const bf16x8 wm = w2[((tp * 4 + ct) * 3 + 1) * 64 + lane];
-            const bf16x8 wl = w2[((tp * 4 + ct) * 3 + 2) * 64 + lane];
+          for (int c = 0; c < 2; ++c) {
+            if constexpr (X3) {
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-              floatx4 c = acc[0][ct][mt];
-              if constexpr (X3) {       // hi x hi + hi x mid + mid x hi (about 2^-16 relative)
-                c = c4_mfma(wh, xs[mt][1], c);
-                c = c4_mfma(wm, xs[mt][0], c);
-              } else {
-                c = c4_mfma(wh, xs[mt][2], c);
-                c = c4_mfma(wm, xs[mt][1], c);
-                c = c4_mfma(wh, xs[mt][1], c);
-                c = c4_mfma(wl, xs[mt][0], c);
-                c = c4_mfma(wm, xs[mt][0], c);
+              for (int mt = 0; mt < 2; ++mt) {
+                acc[c][mt] = c4_mfma(w2x[tp][0][c], xs[mt][1], acc[c][mt]);
+                acc[c][mt] = c4_mfma(w2x[tp][1][c], xs[mt][0], acc[c][mt]);
+                acc[c][mt] = c4_mfma(w2x[tp][0][c], xs[mt][0], acc[c][mt]);
               }
-              acc[0][ct][mt] = c4_mfma(wh, xs[mt][0], c);
+            } else {
+              const int ct = lch / 16 + c;
+              const bf16x8 w[3] = {w2[((tp * 4 + ct) * 3 + 0) * 64 + lane], w2[((tp * 4 + ct) * 3 + 1) * 64 + lane],
+                                   w2[((tp * 4 + ct) * 3 + 2) * 64 + lane]};
+#pragma unroll
+              for (int mt = 0; mt < 2; ++mt) acc[c][mt] = mfma_s3(w, xs[mt], acc[c][mt]);
             }
           }
+          if (X3 && (tp & 1)) __builtin_amdgcn_sched_barrier(0);   // (as above)
         }
       }
-      // bias + ReLU -> layer-2 activations of row 4b + w, staged through this wave's slice of the
+      // ReLU -> layer-2 activations of row 4b + lrow, staged through this wave's slice of the
       // (now free) frame band area so that the global stores are whole contiguous lines
       {
-        const int orow = 4 * b + wave;
-        unsigned char* tw = lds + wave * 32 * F_TPITCH<P>;
+        const int orow = 4 * b + lrow;
+        constexpr int TP = F_TPITCH<P>;
+        unsigned char* tw = lds + wave * 32 * TP;
         float m = 0.f;
-        // 8 quads of 4 consecutive channels per lane: (position j, first channel c0, values)
+        // quads of 4 consecutive channels per lane: (position j, first channel c0 of the wave's, values)
 #pragma unroll
-        for (int qd = 0; qd < 8; ++qd) {
+        for (int qd = 0; qd < (F32 ? 4 : 8); ++qd) {
           int j, c0;
-          float x[4];
+          float v[4];
           if constexpr (P == C4_BF16) {
             const int c2 = qd >> 2, vq = qd & 3;
             j = lane & 31;
             c0 = c2 * 32 + 8 * vq + 4 * (lane >> 5);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = acc32[c2][4 * vq + r];
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc32[c2][4 * vq + r], 0.f);
+          } else if constexpr (F32) {
+            const int mt = qd >> 1, c = qd & 1;
+            j = mt * 16 + l16;
+            c0 = c * 16 + 4 * g;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[c][mt][r], 0.f);
+            if (!X3 && amax2 != nullptr) m = fmaxf(m, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
           } else {
             const int mt = qd >> 2, ct = qd & 3;
             j = mt * 16 + l16;
             c0 = ct * 16 + 4 * g;
+            const float4 bb = *reinterpret_cast<const float4*>(consts_s + c0);
+            const float4 ss = *reinterpret_cast<const float4*>(consts_s + 64 + c0);
+            const float bv[4] = {bb.x, bb.y, bb.z, bb.w}, sv[4] = {ss.x, ss.y, ss.z, ss.w};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = acc[0][ct][mt][r] + acc[1][ct][mt][r];
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[ct][mt][r] * sv[r] + bv[r], 0.f) * inv_s2;
           }
-          const float4 bb = *reinterpret_cast<const float4*>(consts_s + 32 + c0);
-          const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
-          float sv[4] = {1.f, 1.f, 1.f, 1.f};
-          if constexpr (P == C4_FP8) {
-            const float4 ss = *reinterpret_cast<const float4*>(consts_s + 96 + c0);
-            sv[0] = ss.x; sv[1] = ss.y; sv[2] = ss.z; sv[3] = ss.w;
-          }
-          float v[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            float xr = x[r];
-            if constexpr (P == C4_FP8) xr *= sv[r];
-            v[r] = fmaxf(xr + bv[r], 0.f);
-            m = fmaxf(m, v[r]);
-            v[r] *= inv_s2;
-          }
-          c4_store4<P>(tw + j * F_TPITCH<P> + c0 * ES, v[0], v[1], v[2], v[3]);
+          if constexpr (X3) c4_store_planes<2>(tw + j * TP + c0 * 2, 64, v);
+          else c4_store4<P>(tw + j * TP + c0 * ES, v[0], v[1], v[2], v[3]);
         }
-        if constexpr (P == C4_F32) c4_track_max(amax2, m);
-        // the wave's 32 positions x 64 channels are contiguous in the output: 16 bytes a lane
-        constexpr int RB = 64 * ES;                      // bytes of one position
-        u32x4* dst = reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(out2) + (int64_t)orow * 32 * RB);
+        if constexpr (F32 && !X3) c4_track_max(amax2, m);
+        // the wave's 32 positions x its channels: whole runs of RB bytes, 16 bytes a lane
+        constexpr int RB = C::CW * ES;
+        unsigned char* dst = out2 + (int64_t)orow * 32 * (64 * ES) + lch * ES;
 #pragma unroll
         for (int i = 0; i < RB / 32; ++i) {
-          const int off = i * 1024 + lane * 16;
-          dst[off / 16] = *reinterpret_cast<const u32x4*>(tw + (off / RB) * F_TPITCH<P> + off % RB);
+          const int o = i * 1024 + lane * 16;
+          *reinterpret_cast<u32x4*>(dst + (o / RB) * (64 * ES) + o % RB) =
+              *reinterpret_cast<const u32x4*>(tw + (o / RB) * TP + o % RB);
         }
       }
       }
@@ -575,8 +638,8 @@ __host__ __device__ inline int c4_nkb(int prec, int layer) {
 // Epilogue of one GEMM tile (acc: the 64 x 64 block of wave (wm, wn) of the tile).  Layer 3: bias +
 // ReLU, stored as the next layer's activations.  Layer 4: bias + ReLU, mean over each frame's 64
 // positions, this wave's share of the FC, then the margin and decision (or the logits).
-// PERM: the tile's channels follow c4_l3_channel (BF16 third convolution).
-template <int P, int LAYER, bool PERM = false>
+// PERM: the tile's channels follow c4_l3_channel (BF16 third convolution).  X3: stored as two bf16 planes.
+template <int P, int LAYER, bool PERM = false, bool X3 = false>
 __device__ inline void c4_gemm_epilogue(const GcnnArgs& a, const Forward& f, const floatx4 (&acc)[4][4], int slot,
                                         int k, int cb, int ebase, int64_t row0, int64_t rows, const float* ep_bias,
                                         const float* ep_scale, const float* fcw_s, float (*zpart)[kClasses]) {
@@ -639,7 +702,10 @@ __device__ inline void c4_gemm_epilogue(const GcnnArgs& a, const Forward& f, con
           m = fmaxf(m, valid ? v[r] : 0.f);
           v[r] *= inv_out;
         }
-        if (valid) c4_store4<P>(o + ch, v[0], v[1], v[2], v[3]);
+        if (valid) {
+          if constexpr (X3) c4_store_planes<2>(c4_plane_ptr(o, ch), 64, v);
+          else c4_store4<P>(o + ch, v[0], v[1], v[2], v[3]);
+        }
       }
     }
     if constexpr (P == C4_F32 || P == C4_S3) c4_track_max(amax, m);
@@ -804,8 +870,13 @@ __device__ inline void c4_few(const GcnnArgs& a, const Forward& f, unsigned char
       const int rb = pg * 16 + l16;
       if constexpr (S3) {
         bf16x8 x[3];
-        split3(*reinterpret_cast<const float4*>(Bm + (rb * 8 + ((2 * g) ^ c4_swz<8>(rb))) * 16),
-               *reinterpret_cast<const float4*>(Bm + (rb * 8 + ((2 * g + 1) ^ c4_swz<8>(rb))) * 16), x);
+        if constexpr (X3) {
+          x[0] = *reinterpret_cast<const bf16x8*>(Bm + (rb * 8 + (g ^ c4_swz<8>(rb))) * 16);
+          x[1] = *reinterpret_cast<const bf16x8*>(Bm + (rb * 8 + ((4 + g) ^ c4_swz<8>(rb))) * 16);
+        } else {
+          split3(*reinterpret_cast<const float4*>(Bm + (rb * 8 + ((2 * g) ^ c4_swz<8>(rb))) * 16),
+                 *reinterpret_cast<const float4*>(Bm + (rb * 8 + ((2 * g + 1) ^ c4_swz<8>(rb))) * 16), x);
+        }
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
           const int ra = cg * 64 + nt * 16 + l16;
@@ -846,7 +917,9 @@ __device__ inline void c4_few(const GcnnArgs& a, const Forward& f, unsigned char
         const float v0 = fmaxf(acc[nt][0] + bb.x, 0.f), v1 = fmaxf(acc[nt][1] + bb.y, 0.f);
         const float v2 = fmaxf(acc[nt][2] + bb.z, 0.f), v3 = fmaxf(acc[nt][3] + bb.w, 0.f);
         m = fmaxf(m, fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)));
-        c4_store4<P>(o + ch, v0, v1, v2, v3);
+        const float v[4] = {v0, v1, v2, v3};
+        if constexpr (X3) c4_store_planes<2>(c4_plane_ptr(o, ch), 64, v);
+        else c4_store4<P>(o + ch, v0, v1, v2, v3);
       }
       if constexpr (S3) c4_track_max(amax, m);
       __syncthreads();                 // the next item's first stages overwrite the ring
@@ -1061,7 +1134,7 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
         // one 32-deep k-step: lane group g takes k = 8 g .. 8 g + 7 (A chunk g of each 64-byte
         // row, B chunks 2 g and 2 g + 1 of each 128-byte fp32 row); the fp32 activations are
         // split a = hi + mid + lo in bf16 and the six products down to 2^-24 relative are summed,
-        // smallest first
+        // smallest first (X3: the previous layer has stored hi and mid, three products)
         bf16x8 aw[3][NT];
 #pragma unroll
         for (int term = 0; term < ATERMS; ++term)
@@ -1073,33 +1146,28 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           const int r = wm * WM + mt * 16 + l16;
-          const floatx4 x0 = *reinterpret_cast<const floatx4*>(B + (r * UPR + ((2 * g) ^ c4_swz<UPR>(r))) * 16);
-          const floatx4 x1 = *reinterpret_cast<const floatx4*>(B + (r * UPR + ((2 * g + 1) ^ c4_swz<UPR>(r))) * 16);
-          bf16x8 xh, xm, xl;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float v = e < 4 ? x0[e] : x1[e - 4];
-            const __bf16 h = static_cast<__bf16>(v);
-            const float r1 = v - static_cast<float>(h);
-            const __bf16 m = static_cast<__bf16>(r1);
-            xh[e] = h;
-            xm[e] = m;
-            xl[e] = static_cast<__bf16>(r1 - static_cast<float>(m));
+          bf16x8 x[3];
+          if constexpr (X3) {       // stored as planes: chunks 0..3 of the row hi, 4..7 mid
+            x[0] = *reinterpret_cast<const bf16x8*>(B + (r * UPR + (g ^ c4_swz<UPR>(r))) * 16);
+            x[1] = *reinterpret_cast<const bf16x8*>(B + (r * UPR + ((4 + g) ^ c4_swz<UPR>(r))) * 16);
+          } else {
+            split3(*reinterpret_cast<const float4*>(B + (r * UPR + ((2 * g) ^ c4_swz<UPR>(r))) * 16),
+                   *reinterpret_cast<const float4*>(B + (r * UPR + ((2 * g + 1) ^ c4_swz<UPR>(r))) * 16), x);
           }
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt) {
             floatx4 c = acc[nt][mt];
             if constexpr (X3) {         // hi x hi + hi x mid + mid x hi (about 2^-16 relative)
-              c = c4_mfma(aw[0][nt], xm, c);
-              c = c4_mfma(aw[1][nt], xh, c);
+              c = c4_mfma(aw[0][nt], x[1], c);
+              c = c4_mfma(aw[1][nt], x[0], c);
             } else {
-              c = c4_mfma(aw[0][nt], xl, c);
-              c = c4_mfma(aw[1][nt], xm, c);
-              c = c4_mfma(aw[0][nt], xm, c);
-              c = c4_mfma(aw[2][nt], xh, c);
-              c = c4_mfma(aw[1][nt], xh, c);
+              c = c4_mfma(aw[0][nt], x[2], c);
+              c = c4_mfma(aw[1][nt], x[1], c);
+              c = c4_mfma(aw[0][nt], x[1], c);
+              c = c4_mfma(aw[2][nt], x[0], c);
+              c = c4_mfma(aw[1][nt], x[0], c);
             }
-            acc[nt][mt] = c4_mfma(aw[0][nt], xh, c);
+            acc[nt][mt] = c4_mfma(aw[0][nt], x[0], c);
           }
         }
       } else if constexpr (P == C4_FP8) {
@@ -1184,7 +1252,7 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
       compute(kb % NS);
     }
 
-    c4_gemm_epilogue<P, LAYER>(a, f, acc, slot, k, cb, ebase, row0, rows, ep_bias, ep_scale, fcw_s, zpart);
+    c4_gemm_epilogue<P, LAYER, false, X3>(a, f, acc, slot, k, cb, ebase, row0, rows, ep_bias, ep_scale, fcw_s, zpart);
     if (tid == 0) ticks_s[k] += wall_clock64() - t0;
     __syncthreads();   // the next tile's prologue rewrites LDS (stages, constants, zpart)
   }
@@ -1491,8 +1559,9 @@ __global__ __launch_bounds__(512) void c4_gemm_bf16_kernel(GcnnArgs a, Forward f
 // ---------------------------------------------------------------- launch
 template <int P, bool X3 = false>
 static void launch_front(const GcnnArgs& a, int grid, hipStream_t s) {
-  if (a.fr.dtype == HYDRO_DTYPE_U8) hipLaunchKernelGGL((c4_front_kernel<P, true, X3>), dim3(grid), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((c4_front_kernel<P, false, X3>), dim3(grid), dim3(256), 0, s, a);
+  constexpr int nthr = FrontCfg<P, X3>::NW * 64;
+  if (a.fr.dtype == HYDRO_DTYPE_U8) hipLaunchKernelGGL((c4_front_kernel<P, true, X3>), dim3(grid), dim3(nthr), 0, s, a);
+  else hipLaunchKernelGGL((c4_front_kernel<P, false, X3>), dim3(grid), dim3(nthr), 0, s, a);
 }
 
 void launch_c4_pass(const GcnnArgs& a, const Forward& f, int prec, int grid, hipStream_t s) {
@@ -1574,10 +1643,16 @@ static inline float c4_w(const float* w, int cin, int oc, int k) {
   return w[((size_t)(oc * cin + ch) * 3 + tap / 3) * 3 + tap % 3];
 }
 
-void c4_pack_front(const float* w1, float scale1, const float* w2, const float* s2, C4FrontPack* out) {
-  // layer 1: k = 9u + 3v + c (27 real), K slots per c4_l1_k
+void c4_pack_front(const float* w1, float scale1, const float* b1, const float* w2, const float* s2, C4FrontPack* out) {
+  // layer 1: k = 9u + 3v + c (27 real), then the bias (its activation is 1) in three bf16 terms that
+  // add up to it exactly; K slots per c4_l1_k
   auto w1k = [&](int oc, int kk) -> float {
-    if (kk >= 27) return 0.f;
+    if (kk >= 30) return 0.f;
+    if (kk >= 27) {
+      float v = b1[oc];
+      for (int t = 27; t < kk; ++t) v -= c4_bf16_value(c4_bf16_bits(v));
+      return c4_bf16_value(c4_bf16_bits(v));
+    }
     const int u = kk / 9, t = kk % 9, v = t / 3, c = t % 3;
     return scale1 * w1[((size_t)(oc * 3 + c) * 3 + u) * 3 + v];
   };

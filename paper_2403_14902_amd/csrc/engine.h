@@ -186,7 +186,7 @@ struct C4FrontPack {
   std::vector<uint8_t> w2q;           // layer 2 e4m3
 };
 bool c4_shape_ok(int in_hw, int n_layers, const int* widths);
-void c4_pack_front(const float* w1, float scale1, const float* w2, const float* s2, C4FrontPack* out);
+void c4_pack_front(const float* w1, float scale1, const float* b1, const float* w2, const float* s2, C4FrontPack* out);
 size_t c4_img_bytes(int prec, int layer);
 void c4_pack_img(int prec, int layer, const float* w, const float* scale, unsigned char* out);
 uint8_t c4_fp8_e4m3(float x);

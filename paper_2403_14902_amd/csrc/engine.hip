@@ -892,7 +892,13 @@ static int pack_c4(hydro_session* s, const HostModel& hm, float scale1, int i) {
     ga.c4_wscale[i][l - 1] = dp;
   }
   C4FrontPack fp;
-  c4_pack_front(hm.cw[0].data(), scale1, hm.cw[1].data(), sc[0].data(), &fp);
+  std::vector<float> b1(hm.m.widths[0]);       // layer 1's bias with the normalisation folded in
+  for (int o = 0; o < hm.m.widths[0]; ++o) {
+    double sum = 0;
+    for (int t = 0; t < 27; ++t) sum += hm.cw[0][(size_t)o * 27 + t];
+    b1[o] = (float)(hm.cb[0][o] - 2.0 * sum);
+  }
+  c4_pack_front(hm.cw[0].data(), scale1, b1.data(), hm.cw[1].data(), sc[0].data(), &fp);
   {
     std::vector<uint16_t> b(fp.w1b.size());
     for (size_t t = 0; t < b.size(); ++t) b[t] = f32_to_bf16_bits(fp.w1b[t]);
