@@ -58,15 +58,22 @@ constexpr int CB1 = 16;             // layer-1 channels per slab
 // Pixel strides (elements) of the layer-1 slab and the layer-2 output are padded so that the 16
 // lanes of an MFMA row group, which read 16 different pixels, spread over the LDS banks.
 template <typename T> struct Pad {
-  static constexpr int S1P = CB1 + (sizeof(T) == 4 ? 4 : 0);   // fp32: 16-byte aligned pixels
-  static constexpr int L2E = 16 / (int)sizeof(T);      // extra elements per layer-2 pixel
+  // bytes of activations per layer-1 slab pixel (fp32: three bf16 planes of 16 channels), and its pitch
+  static constexpr int S1D = CB1 * (sizeof(T) == 4 ? 6 : 2);
+  static constexpr int S1PB = S1D + (sizeof(T) == 4 ? 16 : 0);
+};
+// Layer-2 pixel of width class m: bf16, or for the FP32 tier three bf16 planes (the widest class: fp32,
+// its planes do not fit LDS), + 16 bytes
+template <typename T, int M> struct PadL2 {
+  static constexpr bool PLANES = sizeof(T) == 4 && M < 4;
+  static constexpr int D = 32 * M * (PLANES ? 6 : (int)sizeof(T)), PB = D + 16;
 };
 
 template <typename T, int MMAX = 4> struct CnnLds {
   static constexpr int FR_BYTES = (H0 + 1) * FRS * 2;
   static constexpr int S1_OFF = (FR_BYTES + 15) / 16 * 16;
-  static constexpr int S1_BYTES = S1_W * S1_W * Pad<T>::S1P * (int)sizeof(T);
-  static constexpr int L2_BYTES_MAX = L2_W * L2_W * (32 * MMAX + Pad<T>::L2E) * (int)sizeof(T);
+  static constexpr int S1_BYTES = S1_W * S1_W * Pad<T>::S1PB;
+  static constexpr int L2_BYTES_MAX = L2_W * L2_W * PadL2<T, MMAX>::PB;
   static constexpr int REGION = (S1_OFF + S1_BYTES) > L2_BYTES_MAX ? (S1_OFF + S1_BYTES) : L2_BYTES_MAX;
 };
 
@@ -75,7 +82,7 @@ constexpr int DBUF = 64;
 // width), two per CU, so one frame's barriers and per-frame work overlap another frame's MFMAs.
 
 // packed-layer geometry: [slab][kstep][ntile][64][KPL]
-// layer 1: K = 27 in (row u, column v, channel c) order, k = 9u + 3v + c, padded to KSTEP
+// layer 1: K = 27 and the bias in conv1_k's slots
 template <typename T>
 __host__ __device__ constexpr int cnn_ksteps(int layer, int m) {
   return layer == 0 ? (27 + Mf<T>::KSTEP - 1) / Mf<T>::KSTEP
@@ -85,9 +92,9 @@ __host__ __device__ constexpr int cnn_ksteps(int layer, int m) {
 __host__ __device__ constexpr int cnn_slabs(int layer, int m) { return layer == 2 ? 1 : m; }
 __host__ __device__ constexpr int cnn_ntiles(int layer, int m) { return layer == 0 ? 1 : layer == 1 ? 2 * m : 4 * m; }
 
-// Per-slot constants staged in LDS when a workgroup's slot changes: biases of the three layers
-// (offsets 0, 64, 192) and, in the bf16 kernels, the FC weights and bias.
-constexpr int CB_L2 = 64, CB_L3 = 192, CB_N = 448;
+// Per-slot constants staged in LDS when a workgroup's slot changes: biases of layers 2 and 3
+// (layer 1's is among its weights) and, in the bf16 kernels, the FC weights and bias.
+constexpr int CB_L2 = 0, CB_L3 = 128, CB_N = 384;
 constexpr int FCW_MAX = 256 * kClasses;
 
 struct CnnShared {
@@ -185,11 +192,11 @@ __device__ inline void frame_store(const CnnArgs& a, const FramePrefetch<NT>& pf
   const __bf16 padv = static_cast<__bf16>(a.pad_raw);
   for (int e = tid; e < FRS; e += NT) FR[e] = padv;                                // top border row
   for (int e = tid; e < H0 * 3; e += NT) FR[(e / 3 + 1) * FRS + FR_X0 - 3 + e % 3] = padv;  // left border
-  T* S1 = reinterpret_cast<T*>(region + CnnLds<T>::S1_OFF);
-  for (int p = tid; p < (2 * S1_W - 1) * CB1; p += NT) {
-    const int q = p / CB1, c = p % CB1;
+  constexpr int WP = Pad<T>::S1D / 4;             // words per pixel
+  for (int p = tid; p < (2 * S1_W - 1) * WP; p += NT) {
+    const int q = p / WP, c = p % WP;
     const int y = q < S1_W ? 0 : q - S1_W + 1, x = q < S1_W ? q : 0;
-    S1[(y * S1_W + x) * Pad<T>::S1P + c] = static_cast<T>(0.f);
+    reinterpret_cast<uint32_t*>(region + CnnLds<T>::S1_OFF + (y * S1_W + x) * Pad<T>::S1PB)[c] = 0u;
   }
 }
 
@@ -261,9 +268,13 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
                           bool next_valid, uint32_t next_idx, __bf16* feat_dst, float* z_out) {
   constexpr int NT = NWV * 64;                       // threads
   constexpr int C2 = 32 * M, C3 = 64 * M;
-  constexpr int S1P = Pad<T>::S1P, C2P = C2 + Pad<T>::L2E;
-  // FP32 tier (T = float): fp32 activations, bf16 MFMAs on three-term operands, in the bf16
-  // fragment layout (k-steps of 32, 8 per lane)
+  constexpr int S1PB = Pad<T>::S1PB, L2PB = PadL2<T, M>::PB;
+  // FP32 tier (T = float): bf16 MFMAs on three-term operands, in the bf16 fragment layout (k-steps
+  // of 32, 8 per lane); activations held in LDS as their three terms, or in fp32 and split at
+  // every read where the terms do not fit (layer 2 of the widest class).  A layer-1 output is read
+  // 2.25 times by each of one to four channel groups, a layer-2 output by all eight waves, so
+  // splitting where they are written saves most of the vector work: FP32 kernel 861 -> 680 us a
+  // launch on the 10,007-frame query, with layer 1's gather in five words instead of eight elements
   constexpr bool S3 = sizeof(T) == 4;
   typedef typename std::conditional<S3, __bf16, T>::type KT;
   constexpr int KSTEP = Mf<KT>::KSTEP, KPL = Mf<KT>::KPL;
@@ -276,11 +287,10 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
 
   const __bf16* FR = reinterpret_cast<const __bf16*>(region);
-  T* S1 = reinterpret_cast<T*>(region + CnnLds<T>::S1_OFF);
-  T* L2 = reinterpret_cast<T*>(region);
+  unsigned char* S1 = region + CnnLds<T>::S1_OFF;
+  unsigned char* L2 = region;
 
   const T* const* wpk = reinterpret_cast<const T* const*>(a.w_bf[slot]);   // (bf16 tier)
-  const float* b1 = sh.cb;
   const float* b2 = sh.cb + CB_L2;
   const float* b3 = sh.cb + CB_L3;
   // The narrow classes fetch the next frame now: their layer 3 is too short to cover the HBM
@@ -330,42 +340,25 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
   // ---- layer-1 im2col fragments of this wave's MPW m-tiles (cached when several slabs reuse them)
   constexpr int MPW = 64 / NWV;                      // layer-1 m-tiles per wave
   constexpr bool kCacheA1 = sizeof(T) == 2 && M > 1 && NWV == 8;
-  frag a1[kCacheA1 ? MPW : 1][KS1];
-  auto gather1b = [&](int mt) -> bf16x8 {
-    const int px = mt * 16 + l16, i = px >> 5, j = px & 31;
-    const __bf16* rowp = FR + 2 * i * FRS + 5 + 6 * j;
-    alignas(16) __bf16 t8[8];
+  bf16x8 a1[kCacheA1 ? MPW : 1];
+  static_assert(KS1 == 1 && MPW % 2 == 0, "layer 1: one k-step, whole rows of tiles");
+  // (position j of row i: values from element 5 + 6 j of FR rows 2 i .. 2 i + 2; the wave's tiles are at
+  // fixed distances from its first)
+  constexpr int RP = FRS / 2;
+  const uint32_t* gp[5];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = min(8 * g + e, 26);
-      t8[e] = rowp[(k / 9) * FRS + k % 9];
-    }
-    return *reinterpret_cast<const bf16x8*>(t8);
-  };
-  auto gather1 = [&](int mt, int ks) -> frag {
-    const int px = mt * 16 + l16, i = px >> 5, j = px & 31;
-    // im2col row of output (i, j): FR row 2i+u, elements 5 + 6j + (3v + c), k = 9u + 3v + c
-    const __bf16* rowp = FR + 2 * i * FRS + 5 + 6 * j;
-    // padded k (27..31, zero weights) reads element 26, a finite value: the reads need no
-    // per-lane predication, so the tiles' reads can be scheduled ahead of the MFMAs
-    if constexpr (sizeof(T) == 2) {
-      alignas(16) __bf16 t8[8];
+  for (int i = 0; i < 5; ++i)
+    gp[i] = reinterpret_cast<const uint32_t*>(FR) + wave * MPW * RP + (g < 3 ? g * RP + i : min(i, 2) * RP + 4) + 3 * l16 + 2;
+  const uint32_t sel0 = conv1_sel(g);
+  auto gather1 = [&](int q) -> bf16x8 {               // tile wave * MPW + q (MPW is even)
+    uint32_t d[5];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = min(ks * 32 + 8 * g + e, 26);
-        t8[e] = rowp[(k / 9) * FRS + k % 9];
-      }
-      return *reinterpret_cast<const bf16x8*>(t8);
-    } else {
-      const int k = min(ks * 4 + g, 26);
-      return (float)rowp[(k / 9) * FRS + k % 9];
-    }
+    for (int i = 0; i < 5; ++i) d[i] = gp[i][(q >> 1) * 2 * RP + (q & 1) * 48];
+    return conv1_frag(d, g == 3, sel0);
   };
   if constexpr (kCacheA1) {
 #pragma unroll
-    for (int q = 0; q < MPW; ++q)
-#pragma unroll
-      for (int ks = 0; ks < KS1; ++ks) a1[q][ks] = gather1(wave * MPW + q, ks);
+    for (int q = 0; q < MPW; ++q) a1[q] = gather1(q);
   }
 
   floatx4 acc2[MT2][NW2];
@@ -390,74 +383,57 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
       for (int ks = 0; ks < KS1; ++ks) w1f[ks] = w1p[ks * 64 + lane];
     }
     (void)w1t;
-    float bb1[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) bb1[r] = b1[slab * CB1 + 4 * g + r];
     if (!kEarlyFetch && slab == 0 && feat_dst != nullptr) {
       frame_features<NT>(FR, fscale, ff);
       frame_features_put<NT>(ff, sh.feat);
     }
-    auto l1_store = [&](int mt, const floatx4& acc) {
-      const int px = mt * 16 + l16, i = px >> 5, j = px & 31;
-      store4<T>(S1 + ((i + 1) * S1_W + (j + 1)) * S1P + 4 * g, fmaxf(acc[0] + bb1[0], 0.f),
-                fmaxf(acc[1] + bb1[1], 0.f), fmaxf(acc[2] + bb1[2], 0.f), fmaxf(acc[3] + bb1[3], 0.f));
+    auto l1_store = [&](int q, const floatx4& acc) {
+      const int px = (wave * MPW + q) * 16 + l16, i = px >> 5, j = px & 31;
+      unsigned char* dst = S1 + ((i + 1) * S1_W + (j + 1)) * S1PB + 8 * g;
+      const float v[4] = {fmaxf(acc[0], 0.f), fmaxf(acc[1], 0.f), fmaxf(acc[2], 0.f), fmaxf(acc[3], 0.f)};
+      if constexpr (S3) store_planes<3>(dst, 2 * CB1, v);
+      else store4<__bf16>(reinterpret_cast<__bf16*>(dst), v[0], v[1], v[2], v[3]);
     };
-    if constexpr (sizeof(T) == 2 && !kCacheA1 && KS1 == 1) {
-      // tiles in pairs: both gathers, both MFMAs, then both epilogues, so one tile's LDS and
-      // MFMA latencies overlap the other's
-      const floatx4 zero = (floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-      for (int q = 0; q < MPW; q += 2) {
-        const int mt = wave * MPW + q;
-        const frag av0 = gather1(mt, 0), av1 = gather1(mt + 1, 0);
-        const floatx4 acc0 = mfma(w1f[0], av0, zero), acc1 = mfma(w1f[0], av1, zero);
-        l1_store(mt, acc0);
-        l1_store(mt + 1, acc1);
+    const floatx4 zero = (floatx4){0.f, 0.f, 0.f, 0.f};
+    // tiles in pairs: both gathers, both MFMAs, then both epilogues, so one tile's LDS and MFMA
+    // latencies overlap the other's.  FP32 tier: the raw frame values are exact in bf16, so the
+    // three weight terms give every product exactly (smallest term first)
+#pragma unroll (S3 ? 2 : 4)
+    for (int q = 0; q < MPW; q += 2) {
+      bf16x8 av0, av1;
+      if constexpr (kCacheA1) {
+        av0 = a1[q];
+        av1 = a1[q + 1];
+      } else {
+        av0 = gather1(q);
+        av1 = gather1(q + 1);
       }
-    } else if constexpr (S3) {
-      // FP32 tier: the raw frame values are exact in bf16, so the three weight terms give every
-      // product exactly (smallest term first); tiles in pairs
-#pragma unroll 2
-      for (int q = 0; q < MPW; q += 2) {
-        const int mt = wave * MPW + q;
-        const bf16x8 av0 = gather1b(mt), av1 = gather1b(mt + 1);
-        floatx4 acc0 = (floatx4){0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+      floatx4 acc0 = zero, acc1 = zero;
+      if constexpr (S3) {
 #pragma unroll
         for (int t = 2; t >= 0; --t) {
           acc0 = mfma(w1t[t], av0, acc0);
           acc1 = mfma(w1t[t], av1, acc1);
         }
-        l1_store(mt, acc0);
-        l1_store(mt + 1, acc1);
+      } else {
+        acc0 = mfma(w1f[0], av0, zero);
+        acc1 = mfma(w1f[0], av1, zero);
       }
-    } else {
-#pragma unroll 8
-      for (int q = 0; q < MPW; ++q) {
-        const int mt = wave * MPW + q;
-        floatx4 acc = (floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) {
-          frag av;
-          if constexpr (kCacheA1) av = a1[q][ks];
-          else av = gather1(mt, ks);
-          acc = mfma(w1f[ks], av, acc);
-        }
-        l1_store(mt, acc);
-      }
+      l1_store(q, acc0);
+      l1_store(q + 1, acc1);
     }
     __syncthreads();
     if constexpr (S3) {
       // FP32 tier, layer 2 partial of this slab: K = 9 taps x 16 channels in k-steps of 32 (lane
-      // group g: tap (32 ks + 8 g) / 16, channels from 8 (g % 2)); a k-step's weights are
-      // requested before its activation reads and splits
+      // group g: tap (32 ks + 8 g) / 16, channels from 8 (g % 2)); the weights run a k-step ahead
       const bf16x8* w2t[3] = {s3w(1, 0), s3w(1, 1), s3w(1, 2)};
-#pragma unroll 1
-      for (int ks = 0; ks < KS2; ++ks) {
-        bf16x8 w[NW2][3];
+      auto l2w = [&](int ks, bf16x8 (&w)[NW2][3]) {
 #pragma unroll
         for (int n = 0; n < NW2; ++n)
 #pragma unroll
           for (int t = 0; t < 3; ++t) w[n][t] = w2t[t][((slab * KS2 + ks) * NT2 + ng2 * NW2 + n) * 64 + lane];
+      };
+      auto l2_step = [&](int ks, const bf16x8 (&w)[NW2][3]) {
         const int k0 = ks * 32 + 8 * g;
         const int tp = min(k0 / CB1, 8);        // padded k (zero weights) reads a valid tap
         const int c0 = k0 % CB1;
@@ -465,12 +441,31 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
 #pragma unroll
         for (int q = 0; q < MT2; ++q) {
           const int px = (mg2 * MT2 + q) * 16 + l16, i = px >> 4, j = px & 15;
-          const float4* src = reinterpret_cast<const float4*>(S1 + ((2 * i + u) * S1_W + 2 * j + v) * S1P + c0);
+          const unsigned char* src = S1 + ((2 * i + u) * S1_W + 2 * j + v) * S1PB + c0 * 2;
           bf16x8 x[3];
-          split3(src[0], src[1], x);
+#pragma unroll
+          for (int t = 0; t < 3; ++t) x[t] = *reinterpret_cast<const bf16x8*>(src + t * 2 * CB1);
 #pragma unroll
           for (int n = 0; n < NW2; ++n) acc2[q][n] = mfma_s3(w[n], x, acc2[q][n]);
-          __builtin_amdgcn_sched_barrier(0);    // one position tile's operands live at a time
+          if (M == 4) __builtin_amdgcn_sched_barrier(0);    // one position tile's operands live at a time
+        }
+      };
+      if constexpr (M == 4) {          // (no registers for two sets; a k-step's 96 MFMAs cover the latency)
+        bf16x8 w[NW2][3];
+#pragma unroll 1
+        for (int ks = 0; ks < KS2; ++ks) {
+          l2w(ks, w);
+          l2_step(ks, w);
+        }
+      } else {
+        bf16x8 wa[NW2][3], wb[NW2][3];
+        l2w(0, wa);
+#pragma unroll
+        for (int ks = 0; ks < KS2; ++ks) {
+          if (ks + 1 < KS2) l2w(ks + 1, ks & 1 ? wa : wb);
+          __builtin_amdgcn_sched_barrier(0);
+          l2_step(ks, ks & 1 ? wb : wa);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     } else {
@@ -508,7 +503,7 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
   #pragma unroll
             for (int q = 0; q < MT2; ++q) {
               const int px = (mg2 * MT2 + q) * 16 + l16, i = px >> 4, j = px & 15;
-              av[q] = ld_frag<T>(S1 + ((2 * i + u) * S1_W + 2 * j + v) * S1P + c0);
+              av[q] = ld_frag<T>(reinterpret_cast<const T*>(S1 + ((2 * i + u) * S1_W + 2 * j + v) * S1PB) + c0);
             }
   #pragma unroll
             for (int n = 0; n < NW2; ++n)
@@ -540,14 +535,18 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
 #pragma unroll
     for (int q = 0; q < MT2; ++q) {
       const int px = (mg2 * MT2 + q) * 16 + l16, i = px >> 4, j = px & 15;
-      store4<T>(L2 + ((i + 1) * L2_W + (j + 1)) * C2P + ch, fmaxf(acc2[q][n][0] + bb0, 0.f),
-                fmaxf(acc2[q][n][1] + bb1v, 0.f), fmaxf(acc2[q][n][2] + bb2, 0.f), fmaxf(acc2[q][n][3] + bb3, 0.f));
+      unsigned char* dst = L2 + ((i + 1) * L2_W + (j + 1)) * L2PB;
+      const float v[4] = {fmaxf(acc2[q][n][0] + bb0, 0.f), fmaxf(acc2[q][n][1] + bb1v, 0.f),
+                          fmaxf(acc2[q][n][2] + bb2, 0.f), fmaxf(acc2[q][n][3] + bb3, 0.f)};
+      if constexpr (PadL2<T, M>::PLANES) store_planes<3>(dst + 2 * ch, 2 * C2, v);
+      else store4<T>(reinterpret_cast<T*>(dst) + ch, v[0], v[1], v[2], v[3]);
     }
   }
-  for (int p = tid; p < (2 * L2_W - 1) * (C2 / 4); p += NT) {
-    const int qq = p / (C2 / 4), c = (p % (C2 / 4)) * 4;
+  constexpr int WP2 = PadL2<T, M>::D / 16;               // 16-byte chunks per pixel
+  for (int p = tid; p < (2 * L2_W - 1) * WP2; p += NT) {
+    const int qq = p / WP2, c = p % WP2;
     const int y = qq < L2_W ? 0 : qq - L2_W + 1, x = qq < L2_W ? qq : 0;
-    store4<T>(L2 + (y * L2_W + x) * C2P + c, 0.f, 0.f, 0.f, 0.f);
+    reinterpret_cast<uint4*>(L2 + (y * L2_W + x) * L2PB)[c] = make_uint4(0u, 0u, 0u, 0u);
   }
   __syncthreads();
 
@@ -580,7 +579,7 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
 #pragma unroll
     for (int q = 0; q < MT3; ++q) {
       const int px = (mh * MT3 + q) * 16 + l16, i = px >> 3, j = px & 7;
-      av[q] = ld_frag<T>(L2 + ((2 * i + u) * L2_W + 2 * j + v) * C2P + c0);
+      av[q] = ld_frag<T>(reinterpret_cast<const T*>(L2 + ((2 * i + u) * L2_W + 2 * j + v) * L2PB) + c0);
     }
 #pragma unroll
     for (int n = 0; n < NW3; ++n)
@@ -608,33 +607,51 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
     for (int d = 0; d < PD3; ++d) l3_step(KS3 - PD3 + d, bw3[d]);
   } else {
     // FP32 tier: the frame is requested before layer 3 (its wait falls on the first k-step only);
-    // per k-step the weight terms are requested before the activation reads and splits
+    // the weight terms run a k-step ahead
     if (!kEarlyFetch) frame_issue<NT>(a, next_idx, pf);
     if (!kEarlyFetch && feat_dst != nullptr && wave == 0 && lane < 24)
       reinterpret_cast<uint4*>(feat_dst)[lane] = reinterpret_cast<const uint4*>(sh.feat)[lane];
     (void)bw3;
     const bf16x8* w3t[3] = {s3w(2, 0), s3w(2, 1), s3w(2, 2)};
-#pragma unroll 1
-    for (int ks = 0; ks < KS3; ++ks) {
-      bf16x8 w[NW3][3];
+    auto l3w = [&](int ks, bf16x8 (&w)[NW3][3]) {
 #pragma unroll
       for (int n = 0; n < NW3; ++n)
 #pragma unroll
         for (int t = 0; t < 3; ++t) w[n][t] = w3t[t][(ks * NT3 + ng * NW3 + n) * 64 + lane];
+    };
+    auto l3_s3step = [&](int ks, const bf16x8 (&w)[NW3][3]) {
       const int k0 = ks * 32 + 8 * g;
       const int tp = k0 / C2, c0 = k0 % C2;
       const int u = tp / 3, v = tp % 3;
 #pragma unroll
       for (int q = 0; q < MT3; ++q) {
         const int px = (mh * MT3 + q) * 16 + l16, i = px >> 3, j = px & 7;
-        const float4* src = reinterpret_cast<const float4*>(L2 + ((2 * i + u) * L2_W + 2 * j + v) * C2P + c0);
+        const unsigned char* src = L2 + ((2 * i + u) * L2_W + 2 * j + v) * L2PB;
         bf16x8 x[3];
-        split3(src[0], src[1], x);
+        if constexpr (PadL2<T, M>::PLANES) {
+#pragma unroll
+          for (int t = 0; t < 3; ++t) x[t] = *reinterpret_cast<const bf16x8*>(src + 2 * c0 + t * 2 * C2);
+        } else {
+          const float4* p = reinterpret_cast<const float4*>(src + 4 * c0);
+          split3(p[0], p[1], x);
+        }
 #pragma unroll
         for (int n = 0; n < NW3; ++n) acc3[q][n] = mfma_s3(w[n], x, acc3[q][n]);
-        __builtin_amdgcn_sched_barrier(0);
+        if (!PadL2<T, M>::PLANES) __builtin_amdgcn_sched_barrier(0);   // one tile's operands live at a time
       }
+    };
+    bf16x8 wa[NW3][3], wb[NW3][3];
+    l3w(0, wa);
+#pragma unroll 1
+    for (int ks = 0; ks + 1 < KS3; ks += 2) {
+      l3w(ks + 1, wb);
+      __builtin_amdgcn_sched_barrier(0);
+      l3_s3step(ks, wa);
+      l3w(min(ks + 2, KS3 - 1), wa);
+      __builtin_amdgcn_sched_barrier(0);
+      l3_s3step(ks + 1, wb);
     }
+    if constexpr (KS3 % 2 == 1) l3_s3step(KS3 - 1, wa);
   }
   // ReLU + pooled partial sums over this wave's positions
 #pragma unroll
@@ -650,9 +667,6 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
       if (l16 == 0) sh.gpart[mh][ch0 + r] = s;
     }
   }
-  if (MG3 == 1) {
-    for (int c = tid; c < C3; c += NT) sh.gpart[1][c] = 0.f;
-  }
   __syncthreads();
   // wave 0: FC (lanes over channels) -> z; the other waves store the next frame meanwhile
   if (wave == 0) {
@@ -663,7 +677,9 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
 #pragma unroll
     for (int q = 0; q < M; ++q) {
       const int ch = lane + 64 * q;
-      const float gch = (sh.gpart[0][ch] + sh.gpart[1][ch]) * (1.0f / 64.0f);
+      float gs = sh.gpart[0][ch];
+      if constexpr (MG3 == 2) gs += sh.gpart[1][ch];
+      const float gch = gs * (1.0f / 64.0f);
 #pragma unroll
       for (int c = 0; c < kClasses; ++c) zp[c] += gch * fw[ch * kClasses + c];
     }
@@ -685,9 +701,10 @@ void cnn_fused_kernel(CnnArgs a, Forward f) {
   constexpr int MMAX = (VSET & 4) ? 4 : (VSET & 2) ? 2 : 1;   // widest class of the launch
   __shared__ __attribute__((aligned(16))) unsigned char region[CnnLds<T, MMAX>::REGION];
   __shared__ CnnShared sh;
-  // FC weights of the current slot (bf16 kernels; the FP32 kernel has no LDS left and reads them
+  // FC weights of the current slot (the FP32 kernel of the widest class has no LDS left and reads them
   // from global memory)
-  __shared__ float fcw_s[sizeof(T) == 2 ? 64 * MMAX * kClasses : 1];
+  constexpr bool FCL = sizeof(T) == 2 || MMAX < 4;
+  __shared__ float fcw_s[FCL ? 64 * MMAX * kClasses : 1];
   const int tid = threadIdx.x;
   if (tid == 0) sh.d_n = 0;
   if (tid < kMaxK) sh.ticks[tid] = 0;
@@ -745,17 +762,16 @@ void cnn_fused_kernel(CnnArgs a, Forward f) {
     const int v = a.variant[slot];
     if (slot != loaded) {
       const int m = v == CNN_W4 ? 4 : v == CNN_W2 ? 2 : 1;
-      for (int q = tid; q < 16 * m; q += NT) sh.cb[q] = a.bias[slot][0][q];
       for (int q = tid; q < 32 * m; q += NT) sh.cb[CB_L2 + q] = a.bias[slot][1][q];
       for (int q = tid; q < 64 * m; q += NT) sh.cb[CB_L3 + q] = a.bias[slot][2][q];
       if (tid < kClasses) sh.fcb[tid] = a.fc_b[slot][tid];
-      if constexpr (sizeof(T) == 2) {
+      if constexpr (FCL) {
         for (int q = tid; q < 64 * m * kClasses; q += NT) fcw_s[q] = a.fc_w[slot][q];
       }
       __syncthreads();
       loaded = slot;
     }
-    const float* fcw = sizeof(T) == 2 ? fcw_s : a.fc_w[slot];
+    const float* fcw = FCL ? fcw_s : a.fc_w[slot];
     const uint32_t e = ring_e[nf % (2 * ECH)];
     const uint32_t idx = entry_idx(e);
     const float th = ring_th[nf % (2 * ECH)];
@@ -813,13 +829,20 @@ static size_t packed_elems_t(int variant, int layer) {
   return (size_t)cnn_slabs(layer, m) * cnn_ksteps<T>(layer, m) * cnn_ntiles(layer, m) * 64 * Mf<T>::KPL;
 }
 
-size_t cnn_packed_elems(int variant, int layer, int prec) {
-  return prec == HYDRO_PREC_BF16 ? packed_elems_t<__bf16>(variant, layer) : packed_elems_t<float>(variant, layer);
+size_t cnn_packed_elems(int variant, int layer) { return packed_elems_t<__bf16>(variant, layer); }
+
+// Term t (0, 1, 2) of v as a sum of three bf16 values.
+static float bf16_term(float v, int t) {
+  for (;; --t) {
+    const float h = static_cast<float>(static_cast<__bf16>(v));
+    if (t == 0) return h;
+    v -= h;
+  }
 }
 
-// Pack one conv layer ([co][ci][3][3] fp32, scaled by `scale`) into fragment order.
+// Pack one conv layer ([co][ci][3][3] fp32, scaled by `scale`) into fragment order; bias: layer 1's.
 template <typename T>
-static void pack_t(int variant, int layer, const float* w, float scale, float* out) {
+static void pack_t(int variant, int layer, const float* w, float scale, const float* bias, float* out) {
   const int m = mult_of(variant);
   const int KSTEP = Mf<T>::KSTEP, KPL = Mf<T>::KPL;
   const int slabs = cnn_slabs(layer, m), ks_n = cnn_ksteps<T>(layer, m), nt_n = cnn_ntiles(layer, m);
@@ -836,11 +859,16 @@ static void pack_t(int variant, int layer, const float* w, float scale, float* o
             int oc, ic, tap;
             bool valid;
             if (layer == 0) {
-              // k = 9u + 3v + c
-              tap = (k / 9) * 3 + (k % 9) / 3;
-              ic = k % 3;
+              // k = 9u + 3v + c in conv1_k's slots, then the bias in three bf16 terms
+              const int kk = conv1_k(lane >> 4, e);
+              tap = (kk / 9) * 3 + (kk % 9) / 3;
+              ic = kk % 3;
               oc = sl * CB1 + n;
-              valid = k < 27;
+              valid = kk < 27;
+              if (kk >= 27) {
+                out[o++] = kk < 30 ? bf16_term(bias[oc], kk - 27) : 0.f;
+                continue;
+              }
             } else if (layer == 1) {
               tap = k / CB1;
               ic = sl * CB1 + k % CB1;
@@ -856,9 +884,8 @@ static void pack_t(int variant, int layer, const float* w, float scale, float* o
           }
 }
 
-void cnn_pack_layer(int variant, int layer, int prec, const float* w_canon, float scale, float* out) {
-  if (prec == HYDRO_PREC_BF16) pack_t<__bf16>(variant, layer, w_canon, scale, out);
-  else pack_t<float>(variant, layer, w_canon, scale, out);
+void cnn_pack_layer(int variant, int layer, const float* w_canon, float scale, const float* bias, float* out) {
+  pack_t<__bf16>(variant, layer, w_canon, scale, bias, out);
 }
 
 void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s) {
@@ -881,12 +908,16 @@ void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hip
     launch_f64_cnn(b, f, grid, s);
     return;
   }
-  // FP32: one persistent launch over every queue of the pass.  BF16: one launch per width class
-  // (a shared launch would give the narrow classes the widest one's register allocation and code
-  // footprint, measured slower): the widest class runs 8-wave workgroups, one per CU; the two
-  // narrower classes run 4-wave workgroups, two per CU, so one workgroup's LDS phases overlap the
-  // other's matrix phases.
-  if (!(a.prec == HYDRO_PREC_BF16 && tier == TIER_FIRST)) {
+  // The FP32 re-score tier: one persistent launch over every queue of the pass (its queues are a band
+  // of a few hundred frames; a launch per class has a tail per class).  A first pass, whose queues
+  // are long: one launch per width class (a shared launch would give the narrow classes the
+  // widest one's register allocation and code footprint).  BF16: the widest class
+  // runs 8-wave workgroups, one per CU; the two narrower classes 4-wave workgroups, two per CU, so
+  // one workgroup's LDS phases overlap the other's matrix phases.  FP32: the layer-1 slab leaves room
+  // for one workgroup per CU, of 8 waves (10,007 frames through the classes in turn: 440 / 550 / 1040 us;
+  // one launch for all: 490 / 575 / 1080; 16 waves for the narrower two: 465 / 550, with spills).
+  const bool bf = a.prec == HYDRO_PREC_BF16;
+  if (tier != TIER_FIRST) {
     hipLaunchKernelGGL((cnn_fused_kernel<float, 7>), dim3(grid), dim3(NTHR), 0, s, a, f);
     return;
   }
@@ -904,7 +935,11 @@ void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hip
       b.fc_w[j] = a.fc_w[i]; b.fc_b[j] = a.fc_b[i]; b.esc_act[j] = a.esc_act[i];
     }
     if (b.n_preds == 0) continue;
-    if (v == CNN_W4) hipLaunchKernelGGL((cnn_fused_kernel<__bf16, 4>), dim3(grid), dim3(NTHR), 0, s, b, f);
+    if (!bf) {
+      if (v == CNN_W4) hipLaunchKernelGGL((cnn_fused_kernel<float, 4>), dim3(grid), dim3(NTHR), 0, s, b, f);
+      else if (v == CNN_W2) hipLaunchKernelGGL((cnn_fused_kernel<float, 2, 8>), dim3(grid), dim3(512), 0, s, b, f);
+      else hipLaunchKernelGGL((cnn_fused_kernel<float, 1, 8>), dim3(grid), dim3(512), 0, s, b, f);
+    } else if (v == CNN_W4) hipLaunchKernelGGL((cnn_fused_kernel<__bf16, 4>), dim3(grid), dim3(NTHR), 0, s, b, f);
     else if (v == CNN_W2) hipLaunchKernelGGL((cnn_fused_kernel<__bf16, 2, 4>), dim3(grid * 2), dim3(256), 0, s, b, f);
     else hipLaunchKernelGGL((cnn_fused_kernel<__bf16, 1, 4>), dim3(grid * 2), dim3(256), 0, s, b, f);
   }

@@ -92,13 +92,6 @@ constexpr int F_FROWS = 17;        // frame rows a band reads
 constexpr int F_FX0 = 8;           // element of column 0 in a staged frame row (16-byte aligned); the
                                    // left pad column is the three elements before it
 constexpr int F_FPITCH = F_FX0 + 128 * 3;
-// Layer 1's K slot (lane group g, element e of a 16x16x32 fragment) -> k = 9u + 3v + c: lane
-// groups 0..2 hold the first 8 of the 9 (pixel, channel) values of input row g, lane group 3 the
-// ninth of rows 0..2 and then three slots whose activation is 1 and whose weights are the bias in three
-// bf16 terms (27..29: the fp32 bias exactly); 30: nothing.  Each lane then reads five aligned
-// dwords of one staged row (or the ninth element of each row) instead of eight 2-byte elements.
-__host__ __device__ inline int c4_l1_k(int g, int e) { return g < 3 ? 9 * g + e : e < 3 ? 9 * e + 8 : e < 6 ? 24 + e : 30; }
-
 // Per tier: waves per workgroup, bytes per layer-1 column slot (32 channels, FP32 arithmetic in bf16
 // planes of 64 bytes, + padding: the slot pitch in 16-byte units is odd so that eight consecutive
 // slots fall on distinct bank groups), output channels per wave of layer 2
@@ -124,23 +117,6 @@ template <int PITCH> struct RingRow {
 };
 template <int P, bool X3> constexpr int front_ring_bytes() { typedef FrontCfg<P, X3> C; return F_RING * RingRow<C::PITCH>::BYTES; }
 template <int P, bool X3> constexpr int front_lds_bytes() { return F_FRAME_B<P> + front_ring_bytes<P, X3>(); }
-
-// Four values (>= 0) as PLANES bf16 planes `pitch` bytes apart: v = sum of the planes, exactly with three
-// and to 2^-16 with two.
-template <int PLANES>
-__device__ inline void c4_store_planes(unsigned char* dst, int pitch, const float (&v)[4]) {
-  float r[4] = {v[0], v[1], v[2], v[3]};
-#pragma unroll
-  for (int t = 0; t < PLANES; ++t) {
-    alignas(8) __bf16 h[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      h[i] = static_cast<__bf16>(r[i]);
-      r[i] -= static_cast<float>(h[i]);
-    }
-    *reinterpret_cast<uint2*>(dst + t * pitch) = *reinterpret_cast<const uint2*>(h);
-  }
-}
 
 // Where channel ch (a multiple of 4) of a position stored as two planes starts: [32-channel group][hi, mid][32].
 __device__ inline unsigned char* c4_plane_ptr(void* pos, int ch) {
@@ -416,7 +392,7 @@ void c4_front_kernel(GcnnArgs a) {
             unsigned char* dst = drow + 8 * jt * PITCH + ct * 16 * (F32 ? 2 : ES);
             if constexpr (F32) {
               if (!X3 && amax1 != nullptr) m = fmaxf(m, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
-              c4_store_planes<PLANES>(dst, 64, v);
+              store_planes<PLANES>(dst, 64, v);
             } else {
               if constexpr (P == C4_FP8)
 #pragma unroll
@@ -565,7 +541,7 @@ void c4_front_kernel(GcnnArgs a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[ct][mt][r] * sv[r] + bv[r], 0.f) * inv_s2;
           }
-          if constexpr (X3) c4_store_planes<2>(tw + j * TP + c0 * 2, 64, v);
+          if constexpr (X3) store_planes<2>(tw + j * TP + c0 * 2, 64, v);
           else c4_store4<P>(tw + j * TP + c0 * ES, v[0], v[1], v[2], v[3]);
         }
         if constexpr (F32 && !X3) c4_track_max(amax2, m);
@@ -703,7 +679,7 @@ __device__ inline void c4_gemm_epilogue(const GcnnArgs& a, const Forward& f, con
           v[r] *= inv_out;
         }
         if (valid) {
-          if constexpr (X3) c4_store_planes<2>(c4_plane_ptr(o, ch), 64, v);
+          if constexpr (X3) store_planes<2>(c4_plane_ptr(o, ch), 64, v);
           else c4_store4<P>(o + ch, v[0], v[1], v[2], v[3]);
         }
       }
@@ -918,7 +894,7 @@ __device__ inline void c4_few(const GcnnArgs& a, const Forward& f, unsigned char
         const float v2 = fmaxf(acc[nt][2] + bb.z, 0.f), v3 = fmaxf(acc[nt][3] + bb.w, 0.f);
         m = fmaxf(m, fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)));
         const float v[4] = {v0, v1, v2, v3};
-        if constexpr (X3) c4_store_planes<2>(c4_plane_ptr(o, ch), 64, v);
+        if constexpr (X3) store_planes<2>(c4_plane_ptr(o, ch), 64, v);
         else c4_store4<P>(o + ch, v0, v1, v2, v3);
       }
       if constexpr (S3) c4_track_max(amax, m);
@@ -1645,7 +1621,7 @@ static inline float c4_w(const float* w, int cin, int oc, int k) {
 
 void c4_pack_front(const float* w1, float scale1, const float* b1, const float* w2, const float* s2, C4FrontPack* out) {
   // layer 1: k = 9u + 3v + c (27 real), then the bias (its activation is 1) in three bf16 terms that
-  // add up to it exactly; K slots per c4_l1_k
+  // add up to it exactly; K slots per conv1_k
   auto w1k = [&](int oc, int kk) -> float {
     if (kk >= 30) return 0.f;
     if (kk >= 27) {
@@ -1659,13 +1635,13 @@ void c4_pack_front(const float* w1, float scale1, const float* b1, const float* 
   out->w1b.assign(2 * 64 * 8, 0.f);
   for (int ct = 0; ct < 2; ++ct)
     for (int l = 0; l < 64; ++l)
-      for (int e = 0; e < 8; ++e) out->w1b[(ct * 64 + l) * 8 + e] = w1k(ct * 16 + (l & 15), c4_l1_k(l >> 4, e));
+      for (int e = 0; e < 8; ++e) out->w1b[(ct * 64 + l) * 8 + e] = w1k(ct * 16 + (l & 15), conv1_k(l >> 4, e));
   // FP32 arithmetic: the bf16 fragments' values split into three bf16 terms [term][ct][lane][8]
   out->w1s3.assign(3 * 2 * 64 * 8, 0);
   for (int ct = 0; ct < 2; ++ct)
     for (int l = 0; l < 64; ++l)
       for (int e = 0; e < 8; ++e) {
-        float v = w1k(ct * 16 + (l & 15), c4_l1_k(l >> 4, e));
+        float v = w1k(ct * 16 + (l & 15), conv1_k(l >> 4, e));
         for (int t = 0; t < 3; ++t) {
           const uint16_t h = c4_bf16_bits(v);
           out->w1s3[(((size_t)t * 2 + ct) * 64 + l) * 8 + e] = h;

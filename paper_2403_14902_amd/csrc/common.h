@@ -277,6 +277,45 @@ __device__ inline floatx4 mfma_s3(const bf16x8 (&w)[3], const bf16x8 (&x)[3], fl
   return mfma_bf16(w[0], x[0], c);
 }
 
+// Four values as PLANES bf16 planes `pitch` bytes apart: v = sum of the planes, exactly with three and to
+// 2^-16 with two.
+template <int PLANES>
+__device__ inline void store_planes(unsigned char* dst, int pitch, const float (&v)[4]) {
+  float r[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+  for (int t = 0; t < PLANES; ++t) {
+    alignas(8) __bf16 h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      h[i] = static_cast<__bf16>(r[i]);
+      r[i] -= static_cast<float>(h[i]);
+    }
+    *reinterpret_cast<uint2*>(dst + t * pitch) = *reinterpret_cast<const uint2*>(h);
+  }
+}
+
+// First convolution (3 channels, K = 27) on one 16x16x32 MFMA k-step.  K slot (lane group g, element e)
+// -> k = 9u + 3v + c: lane groups 0..2 hold the first 8 of the 9 (pixel, channel) values of input row
+// g, lane group 3 the ninth of rows 0..2 and then three slots whose activation is 1 and whose
+// weights are the bias in three bf16 terms (27..29: the fp32 bias exactly); 30: nothing.
+__host__ __device__ inline int conv1_k(int g, int e) { return g < 3 ? 9 * g + e : e < 3 ? 9 * e + 8 : e < 6 ? 24 + e : 30; }
+
+// Its activation fragment.  A position's nine values of one staged bf16 row start at an odd element; five
+// aligned words from the element before hold them, so that a lane of group g < 3 funnel-shifts its
+// row's eight values out of words d[0..4], and one of group 3 takes the upper halves (the ninth values) of
+// d[0..2], which it has read as word 4 of rows 0..2.  sel0: conv1_sel(g).
+__device__ inline uint32_t conv1_sel(int g) { return g < 3 ? 0x05040302u : 0x07060302u; }
+__device__ inline bf16x8 conv1_frag(const uint32_t (&d)[5], bool g3, uint32_t sel0) {
+  uint32_t x[4];
+  x[0] = __builtin_amdgcn_perm(d[1], d[0], sel0);
+  x[1] = g3 ? (d[2] >> 16) | 0x3F800000u : __builtin_amdgcn_alignbit(d[2], d[1], 16);
+  x[2] = g3 ? 0x3F803F80u : __builtin_amdgcn_alignbit(d[3], d[2], 16);
+  x[3] = g3 ? 0u : __builtin_amdgcn_alignbit(d[4], d[3], 16);
+  bf16x8 f;
+  __builtin_memcpy(&f, x, sizeof(f));
+  return f;
+}
+
 // Wave-aggregated append: every active lane with `want` set gets a unique slot in *counter.
 __device__ inline int wave_append(int* counter, bool want) {
   unsigned long long m = __ballot(want);

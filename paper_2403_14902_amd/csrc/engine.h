@@ -207,8 +207,8 @@ int mlp_tile_bn(int cfg);
 // Copy every per-predicate field of slot i of src into slot j of dst.
 void mlp_copy_slot(MlpArgs& dst, int j, const MlpArgs& src, int i);
 void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s);
-size_t cnn_packed_elems(int variant, int layer, int prec);
-void cnn_pack_layer(int variant, int layer, int prec, const float* w_canon, float scale, float* out);
+size_t cnn_packed_elems(int variant, int layer);
+void cnn_pack_layer(int variant, int layer, const float* w_canon, float scale, const float* bias, float* out);
 int cnn_variant_of(int in_hw, int n_layers, const int* widths);
 int cnn_grid_hint(int variant, int tier);
 

@@ -1161,9 +1161,9 @@ static int pack_models(hydro_session* s) {
         float* dp;
         uint16_t* bp;
         {
-          size_t n = cnn_packed_elems(hm.variant, l, HYDRO_PREC_BF16);
+          size_t n = cnn_packed_elems(hm.variant, l);
           std::vector<float> pf(n);
-          cnn_pack_layer(hm.variant, l, HYDRO_PREC_BF16, hm.cw[l].data(), (float)sc, pf.data());
+          cnn_pack_layer(hm.variant, l, hm.cw[l].data(), (float)sc, bias.data(), pf.data());
           std::vector<uint16_t> pb(n);
           for (size_t t = 0; t < n; ++t) pb[t] = f32_to_bf16_bits(pf[t]);
           if ((rc = upload(s, pb.data(), n, &bp))) return rc;
