@@ -611,6 +611,16 @@ __host__ __device__ inline int c4_nkb(int prec, int layer) {
 }
 
 
+// The k-block worked on as number i, of those that PER_TAP make up a tap.  The taps come by the parity
+// of the pixels they read - (0,0) (0,2) (2,0) (2,2), (0,1) (2,1), (1,0) (1,2), (1,1) - so that a pixel's
+// up to four reads follow each other and hit L2: in row order the 32 workgroups of an XCD come back to
+// it a whole frame each later (4 MB), and layer 4 read every activation twice from memory.
+template <int PER_TAP>
+__device__ inline int c4_kblock(int i) {
+  const int n = i / PER_TAP;
+  return (int)(0x453718620ull >> (4 * n) & 15) * PER_TAP + (i - n * PER_TAP);
+}
+
 // Epilogue of one GEMM tile (acc: the 64 x 64 block of wave (wm, wn) of the tile).  Layer 3: bias +
 // ReLU, stored as the next layer's activations.  Layer 4: bias + ReLU, mean over each frame's 64
 // positions, this wave's share of the FC, then the margin and decision (or the logits).
@@ -806,8 +816,9 @@ __device__ inline void c4_few(const GcnnArgs& a, const Forward& f, unsigned char
     const int r = wave * 8 + (lane >> 3), p = pt * BM + r, oi = p / HOUT, oj = p % HOUT;
     const int chunk = ((lane & 7) ^ c4_swz<8>(r)) * CE;
     const T* bsrc = act_in + ent * (HIN * HIN * CIN);
-    auto issue = [&](int kb) {
-      const uint32_t base = lds0 + (kb % NS) * STAGE;
+    auto issue = [&](int n) {
+      const uint32_t base = lds0 + (n % NS) * STAGE;
+      const int kb = c4_kblock<NKB / 9>(n);
 #pragma unroll
       for (int i = 0; i < NIA; ++i) {
         const int U = (wave + 8 * i) * 64 + lane;
@@ -1072,8 +1083,9 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
       bch[i - NIA] = (u_slot ^ c4_swz<UPR>(rb)) * CE;  // element offset of the chunk in the k-block
     }
     // stage kb of A (packed image, a straight copy) and B (im2col gathers) into LDS buffer buf
-    auto issue = [&](int kb, int buf) {
+    auto issue = [&](int n, int buf) {
       const uint32_t base = lds0 + buf * STAGE;
+      const int kb = NKB % 9 == 0 ? c4_kblock<NKB % 9 == 0 ? NKB / 9 : 1>(n) : n;   // (FP8 layer 3: blocks of two taps)
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         const int q = wave + 8 * i;
@@ -1238,11 +1250,20 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
 // BF16 layers 3 and 4 (the first pass): the implicit GEMM of c4_gemm_kernel with its pipeline
 // restructured so that the matrix cores are not left waiting on LDS or memory latency:
 //  - one stream of k-blocks over all of a workgroup's tiles: the first stages of the next tile are
-//    loaded during the current tile's last k-blocks and its epilogue;
+//    loaded during the current tile's last k-blocks and its epilogue, and nothing a tile does on its
+//    way waits for a load (queue offsets are kept in LDS, biases and FC weights are reloaded when the
+//    predicate changes; a wave's loads complete in issue order, so any such wait would drain the ring);
+//  - both operands come in by buffer loads to LDS: a lane's offset within a tile is the same for every
+//    tile and the tap is a scalar offset, so a load costs one or two vector instructions, and padding is
+//    an offset past the end, which reads zero;
 //  - each k-block's fragments are read into registers one MFMA step ahead (two register sets), and
-//    the barrier that publishes the next k-block and frees the oldest buffer sits between the two
-//    MFMA steps of a k-block, so that every wave arrives at it with MFMAs in its pipe and issues
-//    its next fragment reads before the MFMAs that follow.
+//    the barrier that publishes the next k-block and frees the oldest buffer sits between two
+//    MFMA steps; the reads of the next step and the loads are dealt out between the MFMAs, and a tile's
+//    stores are not waited for before two k-blocks of the next.
+// Layer 3 moves 196 KB per frame between memory and the CU and 442 KB from L2 into LDS, layer 4 65 and
+// 295 KB: 8,192 frames 450 -> 384 us (805 TFLOP/s) and 300 -> 284 us (1,088); with every activation in
+// L2 they take 312 and 263, with no loads at all 260 and 206 us: what is left is memory latency that
+// LDS has no room to cover.
 // The arithmetic (operands, products and the order in which they are added) is the generic
 // kernel's.
 // Epilogue of a four-frame layer-4 tile: wave (wm, wn) holds frames 2 wm and 2 wm + 1 of the tile
@@ -1312,220 +1333,243 @@ __device__ inline void c4_head4_epilogue(const GcnnArgs& a, const Forward& f, co
   }
 }
 
-struct C4Tile {
-  int slot, k, cb, ebase;
-  int64_t row0, rows;
-  bool valid;
-};
-
 template <int LAYER>
 __global__ __launch_bounds__(512) void c4_gemm_bf16_kernel(GcnnArgs a, Forward f) {
   constexpr int P = C4_BF16;
   typedef __bf16 T;
   typedef GemmCfg<P> G;
   typedef GemmShape<P, LAYER> S;
-  constexpr int UPR = G::UPR, CE = G::CE, BKE = G::ROWB / 2;
   constexpr int CIN = S::CIN, COUT = S::COUT, HIN = S::HIN, HOUT = S::HOUT, PP = HOUT * HOUT;
-  // layer 3: one frame per tile (a wave: 64 positions x 64 channels), three 48 KB stages; layer 4:
-  // four frames per tile (a wave: two frames x 64 channels), two 64 KB stages, so the weight image
-  // is read once per four frames
+  // layer 3: one frame per tile (a wave: 64 positions x 64 channels), three 48 KB stages of 64 k;
+  // layer 4: four frames per tile (a wave: two frames x 64 channels), so the weight image is read once
+  // per four frames, in four 32 KB stages of 32 k (two of 64 k left the loads one k-block to arrive)
   constexpr bool HEAD = LAYER == 3;
-  constexpr int BM = HEAD ? 4 * PP : S::BM, BN = S::BN, WM = HEAD ? 2 * PP : 64, WN = 64;
+  constexpr int BM = HEAD ? 4 * PP : S::BM, BN = S::BN, WM = HEAD ? 2 * PP : 64, WN = 64, FPT = BM / PP;
   constexpr int MT = WM / 16, NT = WN / 16, WGM = BM / WM;
-  constexpr int NKB = 9 * CIN / BKE;
+  constexpr int ROWB = HEAD ? 64 : 128, UPR = ROWB / 16, KS = ROWB / 64;   // MFMA steps per k-block
+  constexpr int NKB = 9 * CIN * 2 / ROWB;
   constexpr int AUNITS = BN * UPR, UNITS = AUNITS + BM * UPR, NI = UNITS / 512, NIA = AUNITS / 512, NB = NI - NIA;
-  constexpr int STAGE = UNITS * 16, NS = HEAD ? 2 : 3;
-  static_assert(9 * CIN % BKE == 0 && NKB >= NS, "whole k-blocks, at least one per stage");
-  static_assert(UNITS % 512 == 0 && AUNITS % 512 == 0 && WGM * (BN / WN) == 8, "tile layout");
-  static_assert(!HEAD || (BN == COUT && MT == 8 && NT == 4), "layer 4: whole frames, all channels");
+  constexpr int STAGE = UNITS * 16, NS = HEAD ? 4 : 3;
+  // layer 3: loads of a k-block issued in the following one's first step, stores of a tile's epilogue
+  constexpr int LH = NI / 2, ST = MT * NT * 4 * 2 / 16;
+  constexpr uint32_t SHIFT = (HIN + 1) * CIN * 2;        // bytes from a frame's position (-1, -1) to (0, 0)
+  constexpr uint32_t FRAME_B = HIN * HIN * CIN * 2, OOB = 0x80000000u;
+  static_assert(9 * CIN * 2 % ROWB == 0 && CIN * 2 % ROWB == 0 && NKB >= NS, "whole k-blocks of one tap each");
+  static_assert(UNITS % 512 == 0 && AUNITS % 512 == 0 && WGM * (BN / WN) == 8 && BN == COUT, "tile layout");
+  static_assert(!HEAD || (MT == 8 && NT == 4), "layer 4: whole frames");
+  static_assert(FPT * FRAME_B + SHIFT < OOB, "a masked offset is past the end");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * STAGE];
   __shared__ float zpart[8][2][kClasses];
   __shared__ __attribute__((aligned(16))) float ep_bias[BN];
   __shared__ float fcw_s[HEAD ? COUT * kClasses : 1];
   __shared__ unsigned long long ticks_s[kMaxK];
+  __shared__ int tile_s[kMaxK + 1], base_s[kMaxK], cnt_s[kMaxK];   // per slot: first tile, first act frame, frames
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
   const int wm = wave % WGM, wn = wave / WGM;
   if (tid < kMaxK) ticks_s[tid] = 0;
-  const T* act_in = reinterpret_cast<const T*>(LAYER == 2 ? a.c4_act2 : a.c4_act3);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
   if (c4_is_few<P, LAYER>(a)) {
     c4_few<P, LAYER, false, NS * STAGE>(a, f, lds, lds0);
     return;
   }
-  int total = 0;
-  for (int i = 0; i < a.n_preds; ++i)
-    if (a.c4[i]) total += (int)(((int64_t)a.q.counts[a.pred[i]] * PP + BM - 1) / BM) * (COUT / BN);
-  const int u_slot = lane % UPR;
-
-  // past the last tile: no rows (the B loads read the zero page) and the weight image of the
-  // launch's first 4-layer slot (a valid image whatever the other slots hold; nothing uses them)
-  int first_c4 = 0;
-  for (int i = a.n_preds - 1; i >= 0; --i)
-    if (a.c4[i]) first_c4 = i;
-  auto decode = [&](int t) {
-    C4Tile r{};
-    r.slot = first_c4;
-    r.valid = t < total;
-    if (!r.valid) return r;
-    r.slot = 0;
-    int off = t;
+  if (tid == 0) {
+    int tiles = 0, frames = 0;
     for (int i = 0; i < a.n_preds; ++i) {
-      const int c = a.c4[i] ? (int)(((int64_t)a.q.counts[a.pred[i]] * PP + BM - 1) / BM) * (COUT / BN) : 0;
-      if (off < c) { r.slot = i; break; }
-      off -= c;
-      r.ebase += a.q.counts[a.pred[i]];
+      const int c = a.q.counts[a.pred[i]];
+      tile_s[i] = tiles;
+      base_s[i] = frames;
+      cnt_s[i] = c;
+      if (a.c4[i]) tiles += (c + FPT - 1) / FPT;
+      frames += c;
     }
-    r.k = a.pred[r.slot];
-    r.cb = off % (COUT / BN);
-    r.row0 = (int64_t)(off / (COUT / BN)) * BM;
-    r.rows = (int64_t)a.q.counts[r.k] * PP;
-    return r;
+    tile_s[a.n_preds] = tiles;
+  }
+  __syncthreads();
+  const int n_slots = a.n_preds;
+  const int total = __builtin_amdgcn_readfirstlane(tile_s[n_slots]);
+  // slot of tile t, searched from an earlier tile's
+  auto slot_of = [&](int t, int slot) {
+    while (t >= tile_s[slot + 1]) ++slot;
+    return __builtin_amdgcn_readfirstlane(slot);
   };
-  // B rows this lane gathers for a tile, per load: the element offset of its chunk at tap (0, 0)
-  // (input position (2i - 1, 2j - 1) of output (i, j)) and 3 flag bits: output row 0 (tap row 0
-  // reads padding), output column 0 (tap column 0 reads padding), no row (past the queue).  A
-  // stride-2 3x3 convolution with HIN = 2 HOUT reads padding nowhere else.
-  struct Gather { int64_t off[NB]; uint32_t flags; };
-  auto gather = [&](const C4Tile& tl, Gather& q) {
-    q.flags = 0;
+
+  // ---- issue side
+  // weights: the packed image is the LDS image of rows of 128 bytes (chunk u of row r at slot
+  // u ^ (r % 8)); rows of 64 bytes take half a row, chunk j at slot j ^ (r / 2 % 4)
+  const int arow = tid / UPR, aslot = tid % UPR;
+  const uint32_t va = ROWB == 128 ? tid * 16
+                                  : arow * 128 + ((aslot ^ ((arow >> 1) & 3)) ^ (arow & 7)) * 16;
+  // activations: row (output position) rb of the tile, chunk of the slot, at tap (0, 0), from the
+  // tile's first position less SHIFT; flag bits per load: output row 0 (tap row 0 reads padding),
+  // output column 0 (tap column 0 does).  A stride-2 3x3 convolution with HIN = 2 HOUT reads padding
+  // nowhere else.
+  uint32_t vb0[NB], flags = 0;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int U = (wave + 8 * (NIA + i)) * 64 + lane - AUNITS;
-      const int rb = U / UPR;
-      const int64_t row = tl.row0 + rb;
-      const bool valid = tl.valid && row < tl.rows && tl.ebase + row / PP < a.act_cap;
-      const int64_t e = valid ? row / PP : 0;
-      const int p = valid ? (int)(row % PP) : 0;
-      const int oi = p / HOUT, oj = p % HOUT;
-      q.off[i] = ((int64_t)(valid ? tl.ebase : 0) + e) * (HIN * HIN * CIN) +
-                 ((int64_t)(2 * oi - 1) * HIN + (2 * oj - 1)) * CIN + (u_slot ^ c4_swz<UPR>(rb)) * CE;
-      q.flags |= ((oi == 0 ? 1u : 0u) | (oj == 0 ? 2u : 0u) | (valid ? 0u : 4u)) << (3 * i);
+  for (int i = 0; i < NB; ++i) {
+    const int rb = (tid + 512 * i) / UPR, p = rb % PP, oi = p / HOUT, oj = p % HOUT;
+    vb0[i] = (uint32_t)(((rb / PP) * HIN * HIN + 2 * oi * HIN + 2 * oj) * CIN * 2 + (tid % UPR ^ c4_swz<UPR>(rb)) * 16);
+    flags |= ((oi == 0 ? 1u : 0u) | (oj == 0 ? 2u : 0u)) << (2 * i);
+  }
+  const unsigned char* act_in = reinterpret_cast<const unsigned char*>(LAYER == 2 ? a.c4_act2 : a.c4_act3);
+  i32x4 ra, rb;
+  uint32_t vb[NB];
+  int it = blockIdx.x, islot = 0, ikb = 0;
+  // the issue side's tile: its image, its rows (past the last tile, or frames past the queue or the
+  // activation buffer: zeros)
+  auto set_tile = [&]() {
+    int valid = 0, frame0 = 0;
+    if (it < total) {
+      islot = slot_of(it, islot);
+      const int first = (it - tile_s[islot]) * FPT;
+      frame0 = __builtin_amdgcn_readfirstlane(base_s[islot] + first);
+      valid = __builtin_amdgcn_readfirstlane(min(cnt_s[islot] - first, (int)a.act_cap - frame0));
+    }
+    ra = buffer_rsrc(a.c4_img[islot][LAYER - 2][P], 9 * CIN * 2 * COUT);
+    rb = buffer_rsrc(act_in + (int64_t)frame0 * FRAME_B - SHIFT, FPT * FRAME_B + SHIFT);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) vb[i] = (tid + 512 * i) / UPR / PP < valid ? vb0[i] : OOB;
+  };
+  // load i of the issue side's k-block into buffer buf
+  auto issue = [&](int i, int buf) {
+    const uint32_t dst = lds0 + buf * STAGE + wave * 1024 + i * 8192;
+    const int kb = c4_kblock<NKB / 9>(ikb);
+    if (i < NIA) {
+      const uint32_t off = (ROWB == 128 ? kb : kb >> 1) * COUT * 128 + i * (512 / UPR) * 128;
+      buf_lds_dma16(ra, ROWB == 128 ? va : va ^ ((kb & 1) * 64), off, dst);
+    } else {
+      const int tap = kb * (ROWB / 2) / CIN, dy = tap / 3, dx = tap - 3 * dy;
+      const uint32_t bad = (dy == 0 ? 1u : 0u) | (dx == 0 ? 2u : 0u);
+      buf_lds_dma16(rb, (flags >> (2 * (i - NIA))) & bad ? OOB : vb[i - NIA],
+                    (uint32_t)((dy * HIN + dx) * CIN * 2 + kb * ROWB % (CIN * 2)), dst);
     }
   };
-  // source addresses of k-block kb of a tile: A (packed weight image, a straight copy), B (im2col:
-  // k-block kb is tap kb * BKE / CIN, channels from kb * BKE % CIN)
-  // (img: the tile's weight image, from tile_img)
-  auto tile_img = [&](const C4Tile& tl) {
-    return static_cast<const unsigned char*>(a.c4_img[tl.slot][LAYER - 2][P]) + (size_t)tl.cb * BN * G::ROWB;
-  };
-  auto addrs = [&](const unsigned char* img0, const Gather& q, int kb, const void* (&src)[NI]) {
-    const unsigned char* img = img0 + (size_t)kb * COUT * G::ROWB;
-    const int tap = kb * BKE / CIN, dy = tap / 3, dx = tap % 3;
-    const int64_t toff = (int64_t)(dy * HIN + dx) * CIN + kb * BKE % CIN;
-    const uint32_t bad = 4u | (dy == 0 ? 1u : 0u) | (dx == 0 ? 2u : 0u);
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      if (i < NIA) {
-        src[i] = img + (size_t)((wave + 8 * i) * 64 + lane) * 16;
-      } else {
-        const bool ok = ((q.flags >> (3 * (i - NIA))) & bad) == 0;
-        src[i] = ok ? static_cast<const void*>(act_in + q.off[i - NIA] + toff) : a.zero_page;
-      }
+  auto advance = [&]() {
+    if (++ikb == NKB) {
+      ikb = 0;
+      it += gridDim.x;
+      set_tile();
     }
   };
-  auto dma = [&](const void* const (&src)[NI], int buf) {
-    const uint32_t base = lds0 + buf * STAGE;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) lds_dma16(src[i], __builtin_amdgcn_readfirstlane(base + (wave + 8 * i) * 1024));
-  };
-  struct Frag { bf16x8 a[NT], b[MT]; };
-  // MFMA step ks (k = 32 ks .. 32 ks + 31 of the k-block) of buffer buf: lane group g reads chunk
-  // 4 ks + g of each row
-  auto frags = [&](int buf, int ks, Frag& F) {
-    const unsigned char* A = lds + buf * STAGE;
-    const unsigned char* B = A + AUNITS * 16;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int r = wn * WN + nt * 16 + l16;
-      F.a[nt] = *reinterpret_cast<const bf16x8*>(A + (r * UPR + ((4 * ks + g) ^ c4_swz<UPR>(r))) * 16);
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int r = wm * WM + mt * 16 + l16;
-      F.b[mt] = *reinterpret_cast<const bf16x8*>(B + (r * UPR + ((4 * ks + g) ^ c4_swz<UPR>(r))) * 16);
-    }
+
+  // ---- compute side
+  struct Frag { bf16x8 v[NT + MT]; };              // channel tiles, position tiles
+  // fragment i of MFMA step ks (k = 32 ks .. 32 ks + 31 of the k-block) of buffer buf: lane group g
+  // reads chunk 4 ks + g of each row
+  auto frag = [&](int buf, int ks, int i) {
+    const unsigned char* A = lds + buf * STAGE + l16 * ROWB + ((4 * ks + g) ^ c4_swz<UPR>(l16)) * 16;
+    return *reinterpret_cast<const bf16x8*>(i < NT ? A + (wn * WN + i * 16) * ROWB
+                                                   : A + AUNITS * 16 + (wm * WM + (i - NT) * 16) * ROWB);
   };
   floatx4 acc[NT][MT];
-  auto mma = [&](const Frag& F) {
+  // One step: the MFMAs of F, the reads of the next step's fragments and the loads [l0, l1) of the
+  // issue side's k-block, dealt out between them.  (Issued in front, they held every wave's MFMAs back
+  // until the memory pipeline had taken the loads of all eight: half of the step.)
+  auto step = [&](const Frag& F, Frag& N, int nbuf, int nks, int l0, int l1, int lbuf) {
+    constexpr int MM = NT * MT, R = NT + MT, LEFT = MM - R;
+    static_assert(LEFT > 0 && MM >= R, "a read behind each of the first MFMAs");
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int n = 0; n < MM; ++n) {
+      acc[n / MT][n % MT] = c4_mfma(F.v[n / MT], F.v[NT + n % MT], acc[n / MT][n % MT]);
+      if (n < R) N.v[n] = frag(nbuf, nks, n);
+      else
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = c4_mfma(F.a[nt], F.b[mt], acc[nt][mt]);
+        for (int l = l0; l < l1; ++l)
+          if (n - R == (l - l0) * LEFT / (l1 - l0)) issue(l, lbuf);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 
-  // The compute side walks this workgroup's tiles; the issue side walks the same stream of
-  // k-blocks NS k-blocks ahead (its tile changes once per tile, after a k-block's MFMAs).
   int t = blockIdx.x;
-  C4Tile cur = decode(t);
-  if (cur.valid) {
-    int it = t, ikb = 0;
-    C4Tile itl = cur;
-    Gather ig;
-    gather(itl, ig);
-    const unsigned char* iimg = tile_img(itl);
-    auto advance = [&]() {
-      if (++ikb == NKB) {
-        ikb = 0;
-        it += gridDim.x;
-        itl = decode(it);
-        gather(itl, ig);
-        iimg = tile_img(itl);
-      }
-    };
+  if (t < total) {
+    // past the last tile the weights of the last slot seen are loaded (nothing uses them)
+    islot = slot_of(t, 0);
+    set_tile();
     // prologue: the stream's first NS k-blocks
 #pragma unroll
     for (int s0 = 0; s0 < NS; ++s0) {
-      const void* src[NI];
-      addrs(iimg, ig, ikb, src);
-      dma(src, s0);
+#pragma unroll
+      for (int l = 0; l < NI; ++l) issue(l, s0);
       advance();
     }
     wait_vmcnt<(NS - 1) * NI>();
     __syncthreads();
-    Frag F0, F1;
-    frags(0, 0, F0);
-    int buf = 0;                      // buffer of the current k-block
+    Frag F[2];
+#pragma unroll
+    for (int i = 0; i < NT + MT; ++i) F[0].v[i] = frag(0, 0, i);
+    int buf = 0, slot = islot, loaded = -1;        // buffer of the current k-block
+    bool stored = false;                           // the previous tile's epilogue has stored its results
+    (void)stored;
+    unsigned long long t0 = wall_clock64();
     for (;;) {
-      const unsigned long long t0 = wall_clock64();
-      // epilogue constants of this tile (the previous tile's closing barrier ordered every read)
-      for (int i = tid; i < BN; i += 512) ep_bias[i] = a.bias[cur.slot][LAYER][cur.cb * BN + i];
-      if constexpr (HEAD)
-        for (int i = tid; i < COUT * kClasses; i += 512) fcw_s[i] = a.fc_w[cur.slot][i];
+      slot = slot_of(t, loaded < 0 ? 0 : slot);
+      const int k = a.pred[slot];
+      if (slot != loaded) {
+        // epilogue constants of this predicate (the previous tile's closing barrier ordered every read)
+        if (loaded >= 0) {
+          const unsigned long long now = wall_clock64();
+          if (tid == 0) ticks_s[a.pred[loaded]] += now - t0;
+          t0 = now;
+        }
+        for (int i = tid; i < BN; i += 512) ep_bias[i] = a.bias[slot][LAYER][i];
+        if constexpr (HEAD)
+          for (int i = tid; i < COUT * kClasses; i += 512) fcw_s[i] = a.fc_w[slot][i];
+        loaded = slot;
+      }
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = (floatx4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-      for (int kb = 0; kb < NKB; ++kb) {
-        // the next k-block of the issue stream goes into this buffer once every wave has read
-        // it; its addresses are formed while the MFMAs run (no branch in the loop body, so the
-        // compiler can interleave them)
-        const void* src[NI];
-        addrs(iimg, ig, ikb, src);
-        frags(buf, 1, F1);
-        mma(F0);
-        // publish k-block kb + 1 (issued NS - 1 k-blocks ago; the NS - 2 after it may stay in
-        // flight) and free this buffer
-        wait_vmcnt<(NS - 2) * NI>();
+      // the step in front of which the next k-block is published (it was issued NS - 1 k-blocks ago,
+      // the NS - 2 after it may stay in flight) and this one's buffer freed, whose fragments every wave
+      // has read; nl loads of a k-block start to fill it.  extra: stores issued after that k-block's
+      // loads, which a wait that let only loads through would wait for too.
+      auto turn = [&](const Frag& G0, Frag& G1, int nl, bool extra) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this step's fragments
+        if (extra) wait_vmcnt<(NS - 2) * NI + (HEAD ? 0 : ST)>();
+        else wait_vmcnt<(NS - 2) * NI>();
         __syncthreads();
-        dma(src, buf);
-        buf = buf + 1 == NS ? 0 : buf + 1;
-        frags(buf, 0, F0);            // the next k-block's first step (unused after the last)
-        mma(F1);
+        const int nbuf = buf + 1 == NS ? 0 : buf + 1;
+        step(G0, G1, nbuf, 0, 0, nl, buf);             // (reads unused after the last tile)
+        buf = nbuf;
+      };
+      if constexpr (KS == 1) {
+        static_assert(KS == 2 || NKB % 2 == 0, "two k-blocks per trip: the register sets alternate");
+#pragma unroll 1
+        for (int kb = 0; kb < NKB; kb += 2) {
+          turn(F[0], F[1], NI, false);
+          advance();
+          turn(F[1], F[0], NI, false);
+          advance();
+        }
+      } else {
+        // a k-block's loads are issued half in its turn and half in the next k-block's first step, but
+        // all before the epilogue's stores
+        step(F[0], F[1], buf, 1, 0, 0, 0);
+        turn(F[1], F[0], NI - LH, stored);
+#pragma unroll 1
+        for (int kb = 1; kb < NKB; ++kb) {
+          __builtin_amdgcn_s_waitcnt(0xC07F);
+          step(F[0], F[1], buf, 1, NI - LH, NI, buf == 0 ? NS - 1 : buf - 1);
+          advance();
+          turn(F[1], F[0], NI - LH, stored && kb == 1);
+        }
+#pragma unroll
+        for (int l = NI - LH; l < NI; ++l) issue(l, buf == 0 ? NS - 1 : buf - 1);
         advance();
+        stored = base_s[slot] + (t - tile_s[slot]) < a.act_cap;
       }
+      const int64_t row0 = (int64_t)(t - tile_s[slot]) * BM, rows = (int64_t)cnt_s[slot] * PP;
       if constexpr (HEAD)
-        c4_head4_epilogue(a, f, acc, cur.slot, cur.k, cur.row0, cur.rows, ep_bias, fcw_s, zpart);
+        c4_head4_epilogue(a, f, acc, slot, k, row0, rows, ep_bias, fcw_s, zpart);
       else
-        c4_gemm_epilogue<P, LAYER, true>(a, f, acc, cur.slot, cur.k, cur.cb, cur.ebase, cur.row0, cur.rows, ep_bias,
-                                         nullptr, fcw_s, zpart[0]);
-      if (tid == 0) ticks_s[cur.k] += wall_clock64() - t0;
+        c4_gemm_epilogue<P, LAYER, true>(a, f, acc, slot, k, 0, base_s[slot], row0, rows, ep_bias, nullptr, fcw_s,
+                                         zpart[0]);
       __syncthreads();                // epilogue constants and zpart are rewritten next
       t += gridDim.x;
-      cur = decode(t);
-      if (!cur.valid) break;
+      if (t >= total) break;
     }
+    if (tid == 0) ticks_s[a.pred[slot]] += wall_clock64() - t0;
     wait_vmcnt<0>();                  // the loads issued past the last tile
   }
   __syncthreads();

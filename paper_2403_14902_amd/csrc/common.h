@@ -242,6 +242,19 @@ __device__ inline void lds_dma16(const void* src, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds_off)
                : "memory", "m0");
 }
+// The same by a buffer load: lane's source is base + voff + soff; offsets at or past the resource's
+// size read zero.  voff is per lane, the rest uniform.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+__device__ inline i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t p = (uint64_t)(uintptr_t)base;
+  return (i32x4){(int)__builtin_amdgcn_readfirstlane((uint32_t)p),
+                 (int)__builtin_amdgcn_readfirstlane((uint32_t)(p >> 32) & 0xffffu), (int)bytes, 0x00027000};
+}
+__device__ inline void buf_lds_dma16(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               : : "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff)),
+                   "s"(__builtin_amdgcn_readfirstlane(lds_off)) : "memory", "m0");
+}
 // s_waitcnt vmcnt(N) (other counters not waited for)
 template <int N>
 __device__ inline void wait_vmcnt() {
