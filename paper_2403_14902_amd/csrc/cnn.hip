@@ -77,7 +77,6 @@ template <typename T, int MMAX = 4> struct CnnLds {
   static constexpr int REGION = (S1_OFF + S1_BYTES) > L2_BYTES_MAX ? (S1_OFF + S1_BYTES) : L2_BYTES_MAX;
 };
 
-constexpr int DBUF = 64;
 // First pass, the two narrower classes: workgroups of four waves (with the LDS of their own
 // width), two per CU, so one frame's barriers and per-frame work overlap another frame's MFMAs.
 
@@ -102,33 +101,10 @@ struct CnnShared {
   float fcb[kClasses];
   float gpart[2][256];
   float z[kClasses];
-  uint32_t d_e[DBUF];
-  uint8_t d_k[DBUF];
-  uint8_t d_f[DBUF];
-  int d_n;
+  DecisionBuf dec;
   unsigned long long ticks[kMaxK];
   __attribute__((aligned(16))) __bf16 feat[192];   // router features of the current frame
 };
-
-__device__ void flush_decisions(const Forward& f, CnnShared& sh, int n_slots, const int* pred) {
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    const int n = sh.d_n;
-    bool active = lane < n;
-    uint32_t e = active ? sh.d_e[lane] : 0u;
-    int k = active ? (int)sh.d_k[lane] : -1;
-    uint8_t fl = active ? sh.d_f[lane] : 0;
-    for (int i = 0; i < n_slots; ++i) {
-      int kk = pred[i];
-      if (__ballot(active && k == kk) == 0) continue;
-      forward_decision(f, kk, e, active && k == kk, (fl & 2) != 0, (fl & 1) != 0);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) sh.d_n = 0;
-  __syncthreads();
-}
 
 // Raw frame bytes held in registers between the issue of their loads and their LDS store
 // (the next frame is fetched while the current one is in layer 3).
@@ -706,7 +682,7 @@ void cnn_fused_kernel(CnnArgs a, Forward f) {
   constexpr bool FCL = sizeof(T) == 2 || MMAX < 4;
   __shared__ float fcw_s[FCL ? 64 * MMAX * kClasses : 1];
   const int tid = threadIdx.x;
-  if (tid == 0) sh.d_n = 0;
+  if (tid == 0) sh.dec.n = 0;
   if (tid < kMaxK) sh.ticks[tid] = 0;
   // queue prefix offsets, kept in LDS (read when entries are staged)
   __shared__ int cum_s[kMaxK + 1];
@@ -797,18 +773,14 @@ void cnn_fused_kernel(CnnArgs a, Forward f) {
       } else {
         float d = class_margin(z, a.class_mask[slot]);
         bool defer = f.defer.entries != nullptr && fabsf(d - th) < f.tau[k];
-        int n = sh.d_n;
-        sh.d_e[n] = e;
-        sh.d_k[n] = (uint8_t)k;
-        sh.d_f[n] = (uint8_t)((d > th ? 1 : 0) | (defer ? 2 : 0));
-        sh.d_n = n + 1;
+        decision_set(sh.dec, sh.dec.n++, k, e, defer, d > th);
       }
       sh.ticks[k] += wall_clock64() - t0;
     }
     __syncthreads();
-    if (sh.d_n == DBUF) flush_decisions(f, sh, a.n_preds, a.pred);
+    if (sh.dec.n == DBUF) decision_flush(f, sh.dec, a.n_preds, a.pred);
   }
-  if (f.logits == nullptr) flush_decisions(f, sh, a.n_preds, a.pred);
+  if (f.logits == nullptr) decision_flush(f, sh.dec, a.n_preds, a.pred);
   __syncthreads();
   if (tid < kMaxK && sh.ticks[tid] && a.count_ticks) atomicAdd(&a.st->r_ticks[tid], sh.ticks[tid]);
 }

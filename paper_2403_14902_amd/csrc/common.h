@@ -409,4 +409,38 @@ __device__ inline void forward_decision(const Forward& f, int k, uint32_t e, boo
   if (more) f.pend_out[slot] = make_entry(idx, mask);
 }
 
+// Decisions of one workgroup, forwarded together: each forwarding adds to counters that every workgroup
+// of the launch adds to, and the L2s of the XCDs pass those around at tens of nanoseconds an addition
+// (one by one, the decisions took most of the layer-wise CNNs' head).
+constexpr int DBUF = 64;
+struct DecisionBuf {
+  uint32_t e[DBUF];
+  uint8_t k[DBUF], f[DBUF];
+  int n;
+};
+__device__ inline void decision_set(DecisionBuf& b, int i, int k, uint32_t e, bool defer, bool pass) {
+  b.e[i] = e;
+  b.k[i] = (uint8_t)k;
+  b.f[i] = (uint8_t)((pass ? 1 : 0) | (defer ? 2 : 0));
+}
+// by the whole workgroup; pred: the launch's predicates.  b is empty and usable on return.
+__device__ inline void decision_flush(const Forward& f, DecisionBuf& b, int n_slots, const int* pred) {
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    const bool active = lane < b.n;
+    const uint32_t e = active ? b.e[lane] : 0u;
+    const int k = active ? (int)b.k[lane] : -1;
+    const uint8_t fl = active ? b.f[lane] : 0;
+    for (int i = 0; i < n_slots; ++i) {
+      const int kk = pred[i];
+      if (__ballot(active && k == kk) == 0) continue;
+      forward_decision(f, kk, e, active && k == kk, (fl & 2) != 0, (fl & 1) != 0);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) b.n = 0;
+  __syncthreads();
+}
+
 }  // namespace hydro
