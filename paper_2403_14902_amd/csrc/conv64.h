@@ -2,12 +2,15 @@
 // (f64.hip) and of the crop predicates (crop.hip).
 //
 // One MFMA tile is 16 output channels (A, weights) x 16 output positions (B, activations) and four
-// products deep.  Both operands are read straight from memory in the layout they already have:
-// a lane's four consecutive input channels of one tap are 16 bytes of fp32 weights ([co][tap][ci])
-// and 32 bytes of FP64 activations (NHWC), one element for each of four MFMAs (lane group g of 16
-// holds channels 4g..4g+3 of a 16-channel block, the same on both sides, so the order in which the
-// MFMAs take them does not matter).  An MFMA holds its SIMD for 64 cycles, four of them 256, so
-// the 48 bytes per lane that feed them come from L1 / L2 with nothing staged in LDS.
+// products deep.  A lane's four channels of a 16-channel block (lane group g of 16 holds channels
+// 4g..4g+3, the same on both sides, so the order in which the MFMAs take them does not matter) are one
+// element each for four MFMAs.  An MFMA holds its SIMD for 64 cycles, four of them 256, so the 48 bytes
+// per lane that feed them come from L1 / L2 with nothing staged in LDS - if neighbouring lanes read
+// neighbouring bytes: a wave's 16-byte load takes the CU's address unit 16 cycles then, and 64 with a
+// row per lane (weights [co][tap][ci] and activations NHWC kept it busy for three times the MFMAs'
+// time).  Weights are packed in the order the lanes take them (conv64_pack); activations between
+// layers are planes of two channels, a row's even columns before its odd ones, so that the positions of
+// a tile, which read every second column, read one run.
 //
 // The result's row of register r, lane group g is 4r + g (read back from a lane-layout probe);
 // the weight rows are permuted so that it holds channel 4g + r, and each lane stores four
@@ -19,6 +22,7 @@
 namespace hydro {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
+typedef double doublex2 __attribute__((ext_vector_type(2)));
 
 // The raw frame that layer 1 reads: pixel (y, x) of the image is pixel (y0 + y, x0 + x) of a frame
 // of row_px pixels per row.
@@ -34,23 +38,34 @@ __device__ inline Image64 image64(const FrameSrc& fr, uint32_t idx, int row_px, 
   return Image64{static_cast<const char*>(fr.base) + (size_t)idx * (size_t)fr.elems * item, fr.dtype, row_px, y0, x0};
 }
 
-// Normalised value of one element (the frame exactly as the definition has it, in FP64).
-__device__ inline double image64_at(const Image64& im, int y, int x, int c) {
-  const int o = ((im.y0 + y) * im.row_px + im.x0 + x) * 3 + c;
-  double v;
-  if (im.dtype == HYDRO_DTYPE_BF16) v = (double)(float)static_cast<const __bf16*>(im.base)[o];
-  else if (im.dtype == HYDRO_DTYPE_U8) v = (double)static_cast<const uint8_t*>(im.base)[o] / 255.0;
-  else v = (double)static_cast<const float*>(im.base)[o];
-  return (v - 0.5) * 4.0;
+// Normalised value of one element (the frame exactly as the definition has it, in FP64: 4 (v - 1/2) is
+// one rounding either way).
+__device__ inline double image64_norm(double v) { return fma(v, 4.0, -2.0); }
+__device__ inline double image64_value(float v) { return image64_norm((double)v); }
+__device__ inline double image64_value(__bf16 v) { return image64_norm((double)(float)v); }
+__device__ inline double image64_value(uint8_t b) {
+  // b / 255 correctly rounded: the product with 1 / 255, corrected once (equal for all 256 bytes)
+  constexpr double r = 1.0 / 255.0;
+  const double q = (double)b * r;
+  return image64_norm(fma(fma(-255.0, q, (double)b), r, q));
 }
 
-// One layer: weights [cout][9][cin] fp32 (cin = 3 for the first layer, else a multiple of 16; cout a
-// multiple of 16), bias [cout], input hin x win, output ho x wo = ceil(hin / 2) x ceil(win / 2).
+// One layer: weights fp32 as conv64_pack leaves them (cin = 3 for the first layer, else a multiple of 16;
+// cout a multiple of 16), bias [cout], input hin x win, output ho x wo = ceil(hin / 2) x ceil(win / 2).
+// last: the output is [position][cout], for the head.
 struct Conv64 {
   const float* w;
   const float* bias;
   int cin, cout, hin, win, ho, wo;
+  bool last;
 };
+
+// Index of channel ch at position (i, j) in a layer's output.
+__device__ inline int conv64_at(const Conv64& L, int i, int j, int ch) {
+  if (L.last) return (i * L.wo + j) * L.cout + ch;
+  const int wh = (L.wo + 1) >> 1;
+  return ((((ch >> 1) * L.ho + i) * 2 + (j & 1)) * wh + (j >> 1)) * 2 + (ch & 1);
+}
 
 // 16-channel blocks of the sum (all nine taps); the first layer's 27 products are one block.
 __device__ inline int conv64_blocks(const Conv64& L, bool first) { return first ? 1 : 9 * (L.cin >> 4); }
@@ -62,42 +77,53 @@ __device__ inline void conv64_acc(const Conv64& L, const Image64& im, const doub
                                   doublex4 (&acc)[CT]) {
   const int lane = lane_id(), g = lane >> 4, l16 = lane & 15;
   const int p = p0 + l16, i = p / L.wo, j = p - i * L.wo;
-  const bool pok = i < L.ho;
-  const int co = o0 + 4 * (l16 & 3) + (l16 >> 2);          // this lane's weight row (permuted, see above)
+  // taps inside the image, bit 3 u + v
+  const uint32_t cols = (j > 0 ? 1u : 0u) | 2u | (2 * j + 1 < L.win ? 4u : 0u);
+  const uint32_t inside = i < L.ho ? (i > 0 ? cols : 0u) | cols << 3 | (2 * i + 1 < L.hin ? cols << 6 : 0u) : 0u;
   if constexpr (FIRST) {
-    // k = 4q + g = tap * 3 + channel, 27 of 28 used
-    const float* w = L.w + (size_t)co * 27;
+    // k = 4q + g = tap * 3 + channel, 27 of 28 used (tap 9 is never inside)
+    const floatx4* w = reinterpret_cast<const floatx4*>(L.w) + ((size_t)(o0 >> 4) * 64 + lane) * 2;
+    const int at = i < L.ho ? ((im.y0 + 2 * i) * im.row_px + im.x0 + 2 * j) * 3 : 0;   // element of tap (1, 1)
     double xv[7];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      const int k = 4 * q + g, t = k / 3, c = k - 3 * t;
-      const int y = 2 * i + t / 3 - 1, x = 2 * j + t % 3 - 1;
-      xv[q] = pok && k < 27 && y >= 0 && x >= 0 && y < L.hin && x < L.win ? image64_at(im, y, x, c) : 0.0;
-    }
-#pragma unroll
-    for (int c = 0; c < CT; ++c)
+    auto gather = [&](auto* src) {
 #pragma unroll
       for (int q = 0; q < 7; ++q) {
-        const int k = 4 * q + g;
-        const double wv = k < 27 ? (double)w[c * 16 * 27 + k] : 0.0;
-        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv, xv[q], acc[c], 0, 0, 0);
+        const int k = 4 * q + g, t = k / 3, u = t / 3;
+        const int o = ((u - 1) * im.row_px + t - 3 * u - 1) * 3 + k - 3 * t;
+        const bool ok = (inside >> t) & 1u;
+        const double v = image64_value(src[ok ? at + o : 0]);
+        xv[q] = ok ? v : 0.0;
       }
+    };
+    if (im.dtype == HYDRO_DTYPE_BF16) gather(static_cast<const __bf16*>(im.base));
+    else if (im.dtype == HYDRO_DTYPE_U8) gather(static_cast<const uint8_t*>(im.base));
+    else gather(static_cast<const float*>(im.base));
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const floatx4 wl = w[c * 128], wh = w[c * 128 + 1];
+#pragma unroll
+      for (int q = 0; q < 7; ++q)
+        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(q < 4 ? wl[q & 3] : wh[q & 3]), xv[q], acc[c], 0, 0, 0);
+    }
   } else {
-    const int nc = L.cin >> 4;
-    const size_t row = (size_t)9 * L.cin;
-    const float* w = L.w + (size_t)co * row + 4 * g;
+    const int nc = L.cin >> 4, wh = (L.win + 1) >> 1, plane = L.hin * wh * 2;
+    const floatx4* w = reinterpret_cast<const floatx4*>(L.w) + (size_t)(o0 >> 4) * 9 * nc * 64 + lane;
+    // tap (1, 1), in the even columns; tap columns 0 and 2 are odd columns j - 1 and j
+    const doublex2* xg = reinterpret_cast<const doublex2*>(in) + 2 * g * plane + 4 * i * wh + j;
     int t = b0 / nc, c0 = b0 - t * nc;
     for (int b = b0; b < b1; ++t, c0 = 0) {
-      const int y = 2 * i + t / 3 - 1, x = 2 * j + t % 3 - 1;
-      const bool ok = pok && y >= 0 && x >= 0 && y < L.hin && x < L.win;
-      const double* xp = in + ((size_t)(ok ? y : 0) * L.win + (ok ? x : 0)) * L.cin + 4 * g;
+      const int u = t / 3, v = t - 3 * u;
+      const bool ok = (inside >> t) & 1u;
+      const doublex2* xp = ok ? xg + (u - 1) * 2 * wh + (v == 1 ? 0 : v == 0 ? wh - 1 : wh)
+                              : reinterpret_cast<const doublex2*>(in);
       const int be = min(b1, b + nc - c0);
 #pragma unroll 4
       for (int bb = b; bb < be; ++bb) {
-        doublex4 xv = *reinterpret_cast<const doublex4*>(xp + (size_t)(c0 + bb - b) * 16);
+        const doublex2 x01 = xp[(c0 + bb - b) * 8 * plane], x23 = xp[((c0 + bb - b) * 8 + 1) * plane];
+        const double xv[4] = {x01[0], x01[1], x23[0], x23[1]};
         floatx4 wv[CT];
 #pragma unroll
-        for (int c = 0; c < CT; ++c) wv[c] = *reinterpret_cast<const floatx4*>(w + c * 16 * row + (size_t)bb * 16);
+        for (int c = 0; c < CT; ++c) wv[c] = w[((size_t)c * 9 * nc + bb) * 64];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const double xq = ok ? xv[q] : 0.0;
@@ -110,11 +136,12 @@ __device__ inline void conv64_acc(const Conv64& L, const Image64& im, const doub
   }
 }
 
-// Bias, ReLU and store of one tile (out: [position][cout]).
+// Bias, ReLU and store of one tile.
 template <int CT>
 __device__ inline void conv64_store(const Conv64& L, const doublex4 (&acc)[CT], double* out, int p0, int o0) {
   const int lane = lane_id(), g = lane >> 4, l16 = lane & 15;
-  if (p0 + l16 >= L.ho * L.wo) return;
+  const int p = p0 + l16, i = p / L.wo, j = p - i * L.wo;
+  if (i >= L.ho) return;
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
     const int ch = o0 + 16 * c + 4 * g;
@@ -124,7 +151,8 @@ __device__ inline void conv64_store(const Conv64& L, const doublex4 (&acc)[CT], 
       const double s = acc[c][r] + (double)L.bias[ch + r];
       v[r] = s > 0.0 ? s : 0.0;
     }
-    *reinterpret_cast<doublex4*>(out + (size_t)(p0 + l16) * L.cout + ch) = v;
+    *reinterpret_cast<doublex2*>(out + conv64_at(L, i, j, ch)) = (doublex2){v[0], v[1]};
+    *reinterpret_cast<doublex2*>(out + conv64_at(L, i, j, ch + 2)) = (doublex2){v[2], v[3]};
   }
 }
 

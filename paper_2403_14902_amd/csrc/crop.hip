@@ -7,9 +7,11 @@
 // workgroup is left with a long tail of large crops.
 //
 // The convolutions run on FP64 matrix instructions (conv64.h).  65,536 crops of 64x64 frames, sides
-// log-uniform 2..64, 16-32-64 CNN, largest first: 2.64 ms of kernel time (36 GFLOP; about twice that
+// log-uniform 2..64, 16-32-64 CNN, largest first: 2.40 ms of kernel time (36 GFLOP; about twice that
 // with the last tile of each layer filled up, most crops being smaller than a tile in layers 2 and
-// 3), against 12.9 ms with one output per thread.  Query 13.85 -> 3.09 ms.
+// 3; matrix cores busy 41 % of it, the rest is the chain of short layers), against 12.9 ms with one
+// output per thread.  Query 13.85 -> 2.84 ms.  (Looking the next item up during the current one,
+// forwarding decisions in batches, or requesting blocks ahead of their MFMAs changed nothing.)
 #include "conv64.h"
 #include "engine.h"
 
@@ -79,6 +81,7 @@ __device__ inline const double* crop_layers(const CropArgs& a, int slot, const I
     L.cout = crop_pad(a.widths[slot][l]);
     L.ho = (L.hin + 1) / 2;
     L.wo = (L.win + 1) / 2;
+    L.last = l == nl - 1;
     double* out = buf + ((l & 1) ? off : 0);
     if (l == 0) conv64_wg<true>(L, im, nullptr, out, wave, kCropThreads / 64);
     else conv64_wg<false>(L, im, buf + ((l & 1) ? 0 : off), out, wave, kCropThreads / 64);
@@ -91,7 +94,7 @@ __device__ inline const double* crop_layers(const CropArgs& a, int slot, const I
 }
 
 // Four workgroups per CU: 122 VGPRs; left to itself the compiler takes 132, which lets in three
-// (query 3.47 against 3.09 ms).
+// (query 3.47 against 3.09 ms, before weights and activations were laid out for coalesced loads).
 __global__ __launch_bounds__(kCropThreads, 4) void k_crop_cnn(CropArgs a, Forward f) {
   __shared__ __attribute__((aligned(32))) double act_s[kCropLds];
   __shared__ double part[kCropThreads], g_s[256], z_s[kClasses];
@@ -126,7 +129,7 @@ __global__ __launch_bounds__(kCropThreads, 4) void k_crop_cnn(CropArgs a, Forwar
     for (int l = 0; l < a.n_layers[slot]; ++l) {
       hl = (hl + 1) / 2;
       wl = (wl + 1) / 2;
-      const int n = hl * wl * crop_pad(a.widths[slot][l]);
+      const int n = (int)conv64_doubles(hl, wl, crop_pad(a.widths[slot][l]), l == a.n_layers[slot] - 1);
       if (l & 1) need1 = max(need1, n);
       else need0 = max(need0, n);
     }

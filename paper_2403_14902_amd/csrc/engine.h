@@ -58,7 +58,7 @@ struct CnnArgs {
   const float* fc_b[kMaxK];
   const float* b_canon[kMaxK][3];
   float pad_raw;                    // raw frame value that normalises to 0
-  const float* wt_canon[kMaxK][3];  // FP64 tier: canonical weights as [co][3][3][ci]
+  const float* wt_canon[kMaxK][3];  // FP64 tier: canonical weights as conv64_pack leaves them
   double* esc_act[kMaxK];           // FP64 tier: per-entry activations (esc_cap entries per slot)
   int64_t esc_stride;               // doubles per entry: outputs of layers 1 and 3, then layer 2's
   int64_t esc_off;                  // ... which starts here
@@ -89,7 +89,7 @@ struct GcnnArgs {
   const float* bias[kMaxK][HYDRO_MAX_LAYERS];
   const float* fc_w[kMaxK];
   const float* fc_b[kMaxK];
-  const float* wt_canon[kMaxK][HYDRO_MAX_LAYERS]; // FP64 tier: [co][3][3][ci]
+  const float* wt_canon[kMaxK][HYDRO_MAX_LAYERS]; // FP64 tier: conv64_pack
   const float* b_canon[kMaxK][HYDRO_MAX_LAYERS];
   float pad_raw;
   void* act[2];                     // activations of every queued frame (all slots, in order)
@@ -153,7 +153,7 @@ struct F64Args {
   int n_layers[kMaxK];
   int in_hw[kMaxK];
   int widths[kMaxK][HYDRO_MAX_LAYERS];            // multiples of 16
-  const float* wt[kMaxK][HYDRO_MAX_LAYERS];       // [co][3][3][ci]
+  const float* wt[kMaxK][HYDRO_MAX_LAYERS];       // conv64_pack
   const float* bias[kMaxK][HYDRO_MAX_LAYERS];
   const float* fc_w[kMaxK];
   const float* fc_b[kMaxK];
@@ -168,6 +168,13 @@ struct F64Args {
 };
 void launch_f64_cnn(const F64Args& a, const Forward& f, int grid, hipStream_t s);
 
+// Weights [cout][cin][9] in the order of the FP64 MFMAs' operands (conv64.h), channels padded to
+// whole tiles.
+std::vector<float> conv64_pack(const float* w, int cin, int cout, bool first);
+// Doubles that a layer's h x w output takes there (the planes hold whole pairs of columns).
+__host__ __device__ inline int64_t conv64_doubles(int h, int w, int channels, bool last) {
+  return (int64_t)h * (last ? w : (w + 1) & ~1) * channels;
+}
 __host__ __device__ inline int crop_pad(int c) { return (c + 15) & ~15; }   // channels of an MFMA tile
 void launch_crop_pass(const CropArgs& a, const Forward& f, int grid, hipStream_t s);
 

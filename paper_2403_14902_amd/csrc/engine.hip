@@ -1010,14 +1010,9 @@ static int pack_models(hydro_session* s) {
       for (int l = 0; l < m.n_layers; ++l) {
         const int co = m.widths[l];
         cr.widths[i][l] = co;
-        // [co][tap][ci], channel counts padded to whole MFMA tiles
-        const int cop = crop_pad(co), cip = l == 0 ? 3 : crop_pad(cin);
-        std::vector<float> wt((size_t)cop * 9 * cip, 0.f), bias(cop, 0.f);
-        for (int o = 0; o < co; ++o) {
-          bias[o] = hm.cb[l][o];
-          for (int c = 0; c < cin; ++c)
-            for (int t = 0; t < 9; ++t) wt[((size_t)o * 9 + t) * cip + c] = hm.cw[l][((size_t)o * cin + c) * 9 + t];
-        }
+        const std::vector<float> wt = conv64_pack(hm.cw[l].data(), cin, co, l == 0);
+        std::vector<float> bias(crop_pad(co), 0.f);
+        std::copy(hm.cb[l].begin(), hm.cb[l].end(), bias.begin());
         float* dp;
         if ((rc = upload(s, wt.data(), wt.size(), &dp))) return rc;
         cr.wt[i][l] = dp;
@@ -1155,10 +1150,7 @@ static int pack_models(hydro_session* s) {
         if ((rc = upload(s, bias.data(), bias.size(), &dp))) return rc;
         ga.bias[i][l] = dp;
         {
-          std::vector<float> wt(hm.cw[l].size());
-          for (int o = 0; o < co; ++o)
-            for (int c = 0; c < cin; ++c)
-              for (int t = 0; t < 9; ++t) wt[((size_t)o * 9 + t) * cin + c] = hm.cw[l][((size_t)o * cin + c) * 9 + t];
+          const std::vector<float> wt = conv64_pack(hm.cw[l].data(), cin, co, l == 0);
           if ((rc = upload(s, wt.data(), wt.size(), &dp))) return rc;
           ga.wt_canon[i][l] = dp;
         }
@@ -1221,11 +1213,7 @@ static int pack_models(hydro_session* s) {
         if ((rc = upload(s, bias.data(), bias.size(), &dp))) return rc;
         ca.bias[i][l] = dp;
         {
-          // [co][3][3][ci]: the FP64 tier's lanes read consecutive input channels of one tap
-          std::vector<float> wt(hm.cw[l].size());
-          for (int o = 0; o < co; ++o)
-            for (int c = 0; c < cin; ++c)
-              for (int t = 0; t < 9; ++t) wt[((size_t)o * 9 + t) * cin + c] = hm.cw[l][((size_t)o * cin + c) * 9 + t];
+          const std::vector<float> wt = conv64_pack(hm.cw[l].data(), cin, co, l == 0);
           if ((rc = upload(s, wt.data(), wt.size(), &dp))) return rc;
           ca.wt_canon[i][l] = dp;
         }
@@ -1556,9 +1544,9 @@ static int session_create(const hydro_model* models, int32_t k, const hydro_poli
         h = (h + 1) / 2;
         w = (w + 1) / 2;
         const int co = m.widths[l], cip = l == 0 ? 3 : crop_pad(cin);
-        act = std::max<int64_t>(act, (int64_t)h * w * crop_pad(co));
+        act = std::max<int64_t>(act, conv64_doubles(h, w, crop_pad(co), l == m.n_layers - 1));
         act_raw = std::max<int64_t>(act_raw, (int64_t)h * w * co);
-        w_pad += (int64_t)crop_pad(co) * (9 * cip + 1) - (int64_t)co * (9 * cin + 1);
+        w_pad += (int64_t)crop_pad(co) * ((l == 0 ? 32 : 9 * cip) + 1) - (int64_t)co * (9 * cin + 1);
         cin = co;
       }
     }

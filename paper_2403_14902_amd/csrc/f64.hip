@@ -9,10 +9,12 @@
 // that (band calibration runs every sample frame here) take one 16-wave workgroup each, all
 // layers in one launch.
 //
-// Bound by the FP64 matrix rate (76 TFLOP/s measured with registers alone): 1,024 frames through the
-// 16m-32m-64m CNNs of m = 1, 2, 4 (108 GFLOP) take 1.9 + 0.2 ms, 50 TFLOP/s; with one scalar
-// product chain per thread (and a chain of global loads in each) they took 90 + 5 ms, which was 95 %
-// of a one-shot query of 2,048 frames (139 -> 9.7 ms).
+// Bound by the FP64 matrix rate (76 TFLOP/s measured with registers alone) and by the waits between the
+// layers of a frame: 1,024 frames through the 64-128-256 CNN (81 GFLOP) take 1.69 + 0.17 ms (entries
+// beyond esc_cap, layers of the others), 44 TFLOP/s; 1.99 + 0.22 ms with weights [co][tap][ci] and NHWC
+// activations, whose loads took the address units longer than the MFMAs.  Calibrating three CNNs this
+// way is 3.0 ms of a one-shot query of 2,048 frames; with one scalar product chain per thread it was
+// 118 of 139 ms.
 #include "conv64.h"
 #include "engine.h"
 
@@ -29,6 +31,7 @@ __device__ inline Conv64 f64_layer(const F64Args& a, int slot, int l) {
   L.cout = a.widths[slot][l];
   L.hin = L.win = a.in_hw[slot] >> l;
   L.ho = L.wo = L.hin >> 1;
+  L.last = l == a.n_layers[slot] - 1;
   return L;
 }
 
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(F64_LAYER_THREADS) void f64_layer_kernel(F64Args a,
     const int ch = o0 + 4 * (lane >> 4) + wave, p = p0 + (lane & 15);
     const double s = ((red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane])) +
                      (double)L.bias[ch];
-    if (p < L.ho * L.wo) out[(int64_t)p * L.cout + ch] = s > 0.0 ? s : 0.0;
+    if (p < L.ho * L.wo) out[conv64_at(L, p / L.wo, p % L.wo, ch)] = s > 0.0 ? s : 0.0;
     __syncthreads();           // red is rewritten by the next unit
   }
 }
@@ -131,6 +134,28 @@ __global__ __launch_bounds__(F64_WG_THREADS) void f64_entry_kernel(F64Args a, Fo
     }
     __syncthreads();           // z and the scratch are reused by the next entry
   }
+}
+
+// Per 16 output channels, 16-channel block of the sum (tap outermost) and lane (g, l16): channels
+// 4g..4g+3 of weight row 4 (l16 % 4) + l16 / 4.  First layer, per 16 output channels and lane: products
+// 4q + g of the 27 (tap, channel), q = 0..7.
+std::vector<float> conv64_pack(const float* w, int cin, int cout, bool first) {
+  const int cip = first ? cin : crop_pad(cin), ct = crop_pad(cout) / 16;
+  const int nc = cip / 16, nb = first ? 1 : 9 * nc, per = first ? 8 : 4;
+  std::vector<float> out((size_t)ct * nb * 64 * per, 0.f);
+  float* d = out.data();
+  for (int c = 0; c < ct; ++c)
+    for (int b = 0; b < nb; ++b)
+      for (int lane = 0; lane < 64; ++lane, d += per) {
+        const int g = lane >> 4, l16 = lane & 15, o = c * 16 + 4 * (l16 & 3) + (l16 >> 2);
+        if (o >= cout) continue;
+        for (int q = 0; q < per; ++q) {
+          const int k = 4 * q + g;                                 // first layer
+          const int t = first ? k / 3 : b / nc, ch = first ? k % 3 : b % nc * 16 + 4 * g + q;
+          if (t < 9 && ch < cin) d[q] = w[((size_t)o * cin + ch) * 9 + t];
+        }
+      }
+  return out;
 }
 
 void launch_f64_cnn(const F64Args& a, const Forward& f, int grid, hipStream_t s) {
