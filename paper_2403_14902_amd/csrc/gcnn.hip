@@ -27,6 +27,14 @@ __host__ __device__ inline bool g_first_k(int k, int* u, int* r) {
 }
 
 // Four channels of one position: bias, ReLU, store.
+// Output channel of row r of a layer's channel tile ct.  Of two tiles, lane group g of 16 holds rows
+// 4g .. 4g + 3 each: channels 8g .. 8g + 7 of the pair's 32, so that a lane stores 16 bytes of bf16, not
+// 8 a tile (a store takes the address unit a cycle per 64 bytes that it touches).
+__host__ __device__ inline int g_channel(int cout, int ct, int r) {
+  return cout % 32 == 0 ? (ct >> 1) * 32 + 8 * (r >> 2) + 4 * (ct & 1) + (r & 3) : ct * 16 + r;
+}
+
+// Bias, ReLU and store of channels ch .. ch + 3 (o and b: theirs) ...
 template <typename T>
 __device__ inline void store_relu4(T* o, floatx4 v, float4 b) {
   const float v0 = fmaxf(v[0] + b.x, 0.f), v1 = fmaxf(v[1] + b.y, 0.f);
@@ -36,6 +44,20 @@ __device__ inline void store_relu4(T* o, floatx4 v, float4 b) {
     *reinterpret_cast<uint2*>(o) = *reinterpret_cast<const uint2*>(h);
   } else {
     *reinterpret_cast<float4*>(o) = make_float4(v0, v1, v2, v3);
+  }
+}
+// ... or ch .. ch + 7, from the two tiles of a pair.
+template <typename T>
+__device__ inline void store_relu8(T* o, floatx4 v, floatx4 w, const float* b) {
+  const float4 b0 = *reinterpret_cast<const float4*>(b), b1 = *reinterpret_cast<const float4*>(b + 4);
+  if constexpr (sizeof(T) == 2) {
+    alignas(16) __bf16 h[8];
+    store_relu4(h, v, b0);
+    store_relu4(h + 4, w, b1);
+    *reinterpret_cast<uint4*>(o) = *reinterpret_cast<const uint4*>(h);
+  } else {
+    store_relu4(o, v, b0);
+    store_relu4(o + 4, w, b1);
   }
 }
 
@@ -118,7 +140,7 @@ __global__ __launch_bounds__(256) void gconv_first_any_kernel(GcnnArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (j >= ncw) continue;
-        const int ch = ct * GT_N + j * 16 + 4 * g;
+        const int ch = g_channel(cout, ct * 4 + j, 4 * g);
 #pragma unroll
         for (int r = 0; r < 4; ++r) out[ch + r] = static_cast<T>(fmaxf(acc[j][r] + bias[ch + r], 0.f));
       }
@@ -135,7 +157,8 @@ __global__ __launch_bounds__(256) void gconv_first_any_kernel(GcnnArgs a) {
 // workgroups per CU (one waits while the other multiplies); each wave holds 64 positions.
 // fp32 arithmetic: the weights as three bf16 terms, the activations split on the fly (split3).
 // Bound by the copies: at 64 bf16 channels a block brings 40 KB for 2.1 MFLOP.  16-32-64 and 32-64-128
-// CNNs on 8,192 128x128 frames (12,288 evaluations): layers 2 and 3 take 1.7 ms in bf16; register-staged
+// CNNs on 8,192 128x128 frames (12,288 evaluations): layers 2 and 3 take 1.5 ms in bf16 (8-byte
+// stores: 1.7); register-staged
 // 128-position tiles, and one wave per 16 positions where Cin is 16, took 3.6.  The FP32 band of the
 // same query: 0.53 ms, on fp32 MFMAs 1.0.
 template <typename T, int BN> struct GD {
@@ -282,8 +305,10 @@ __global__ __launch_bounds__(256, 2) void gconv_dma_kernel(GcnnArgs a, int layer
         }
       }
     }
-    // bias + ReLU; lane holds channels 4g..4g+3 of tile c for position 16q + l16 of its wave
-    const int ch0 = cb * BN + wc * G::CT * 16 + 4 * g;
+    // bias + ReLU; lane holds channels g_channel(4g .. 4g + 3) of tile c for position 16q + l16 of its wave
+    // (BN 16: channels that do not come in pairs of tiles)
+    constexpr int PER = BN > 16 ? 8 : 4;
+    const int ch0 = cb * BN + wc * G::CT * 16 + PER * g;
     const float* bias = a.bias[slot][layer] + ch0;
     T* out = static_cast<T*>(a.act[layer & 1]);
 #pragma unroll
@@ -291,8 +316,13 @@ __global__ __launch_bounds__(256, 2) void gconv_dma_kernel(GcnnArgs a, int layer
       const int r = r0 + wp * 64 + q * 16 + l16, e = e0 + r / P, p = r % P;
       if (e >= cnt) continue;
       T* o = out + ((int64_t)ebase + e) * a.act_stride + (int64_t)p * cout + ch0;
+      if constexpr (BN > 16) {
+        static_assert(G::CT % 2 == 0, "pairs of tiles");
 #pragma unroll
-      for (int c = 0; c < G::CT; ++c) store_relu4(o + c * 16, acc[c][q], *reinterpret_cast<const float4*>(bias + c * 16));
+        for (int c = 0; c < G::CT; c += 2) store_relu8(o + c * 16, acc[c][q], acc[c + 1][q], bias + c * 16);
+      } else {
+        store_relu4(o, acc[0][q], *reinterpret_cast<const float4*>(bias));
+      }
     }
     __syncthreads();   // the next tile's first block overwrites buffer 0
   }
@@ -304,8 +334,10 @@ __global__ __launch_bounds__(256, 2) void gconv_dma_kernel(GcnnArgs a, int layer
 // GF_X0 with the border pixel before it, rows above the frame holding the pad value.  A position's nine
 // values of one row start at an odd element: five aligned words hold them, and a lane's eight K
 // slots (g_first_k) are four funnel shifts of one row's words.  HBM-bound: 12,288 evaluations of
-// 128x128 uint8 frames into 16 or 32 channels read and write 2.7 GB in 0.87 ms (one load and one fp32
-// LDS word per value, eight LDS reads per fragment: 3.26 ms).
+// 128x128 uint8 frames into 16 or 32 channels read and write 2.7 GB in 0.64 ms: the rows of the next tile
+// are requested while this one is computed, weights and biases stay in LDS (both loaded where they were
+// used, and 8-byte stores: 0.87 ms; one load and one fp32 LDS word per value, eight LDS reads per
+// fragment: 3.26 ms).
 constexpr int GF_P = 512, GF_X0 = 8;
 __host__ __device__ inline bool gconv_first_ok(int hout, int cout) {
   return hout >= 16 && 128 % hout == 0 && cout % 16 == 0 && cout <= 64;
@@ -322,77 +354,126 @@ __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
   static_assert(MAXE >= 17 * (GF_X0 + 3 * 128 + 8) && MAXE >= 33 * (GF_X0 + 3 * 64 + 8) && MAXE >= 33 * (GF_X0 + 3 * 32 + 8),
                 "staged rows");
   __shared__ __attribute__((aligned(16))) uint16_t xin[MAXE];
+  constexpr int TERMS = sizeof(T) == 4 ? 3 : 1;
+  __shared__ __attribute__((aligned(16))) __bf16 w_s[TERMS * 4 * 512];   // the predicate's weights [term][tile]
+  __shared__ __attribute__((aligned(16))) float bias_s[64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
   const uint16_t pad = a.fr.dtype == HYDRO_DTYPE_BF16 ? 0x3F00 : 0x42FF;     // 0.5, 127.5 in bf16
+  const bool u8 = a.fr.dtype != HYDRO_DTYPE_BF16;
   int total = 0;
   for (int i = 0; i < a.n_preds; ++i) {
     const int hout = a.in_hw[i] >> 1;
     total += a.q.counts[a.pred[i]] * (hout / gf_rows(hout));
   }
-  for (int t = blockIdx.x; t < total; t += gridDim.x) {
-    int slot = 0, off = t, ebase = 0;
+  struct Tile { int slot, e, ebase, oi0, lg; };        // lg: log2 of the frame side (a power of two)
+  auto decode = [&](int t) {
+    Tile r{};
+    int off = t;
     for (int i = 0; i < a.n_preds; ++i) {
-      const int hout = a.in_hw[i] >> 1;
-      const int c = a.q.counts[a.pred[i]] * (hout / gf_rows(hout));
-      if (off < c) { slot = i; break; }
+      const int hout = a.in_hw[i] >> 1, n = a.q.counts[a.pred[i]];
+      const int c = n * (hout / gf_rows(hout));
+      if (off < c) { r.slot = i; break; }
       off -= c;
-      ebase += a.q.counts[a.pred[i]];
+      r.ebase += n;
     }
-    const int hin = a.in_hw[slot], hout = hin >> 1, ro = gf_rows(hout), RS = gf_stride(hin);
-    const int cout = a.widths[slot][0], nct = cout / 16;
-    const int tpf = hout / ro, e = off / tpf, oi0 = (off % tpf) * ro;
-    const uint32_t idx = entry_idx(a.q.entries[(int64_t)a.pred[slot] * a.q.cap + e]);
-    // staged row r is input row y = 2 oi0 - 1 + r (y < 0 only for r = 0 of the first tile)
-    const int rows_in = 2 * ro + 1;
-    const bool u8 = a.fr.dtype != HYDRO_DTYPE_BF16;
-    const int cpr = u8 ? hin * 3 / 16 : hin * 3 / 8;         // 16-byte chunks per row
+    const int hout = a.in_hw[r.slot] >> 1, ro = gf_rows(hout), tpf = hout / ro;
+    r.e = off / tpf;
+    r.oi0 = (off - r.e * tpf) * ro;
+    r.lg = 31 - __builtin_clz(a.in_hw[r.slot]);
+    return r;
+  };
+  auto entry = [&](const Tile& r) { return a.q.entries[(int64_t)a.pred[r.slot] * a.q.cap + r.e]; };
+  // Staged row r of a tile is input row y = 2 oi0 - 1 + r (y < 0 only for r = 0 of a frame's first tile), as
+  // 16-byte chunks: at most 864 of bf16 values, 432 of bytes.  A tile's chunks are requested while the
+  // previous tile is computed, its queue entry a tile earlier.
+  u32x4 v[4];
+  auto request = [&](const Tile& r, uint32_t e) {
+    const int hin = 1 << r.lg, lc = u8 ? r.lg - 4 : r.lg - 3, cpr = 3 << lc;
+    const int n = (2 * gf_rows(hin >> 1) + 1) * cpr, first = r.oi0 == 0 ? cpr : 0;
     const unsigned char* src = static_cast<const unsigned char*>(a.fr.base) +
-                               ((int64_t)idx * a.fr.elems + (int64_t)(2 * oi0 - 1) * hin * 3) * (u8 ? 1 : 2);
-    for (int q = tid; q < rows_in * cpr; q += 256) {
-      const int r = q / cpr, c = q - r * cpr;
-      const bool in = 2 * oi0 - 1 + r >= 0;
-      uint16_t* dst = xin + r * RS + GF_X0 + c * (u8 ? 16 : 8);
-      const uint32_t padw = pad | (uint32_t)pad << 16;
-      u32x4 v = (u32x4){padw, padw, padw, padw};
-      if (u8) {
-        u32x4 lo = v, hi = v;
-        if (in) {
-          const u32x4 b = *reinterpret_cast<const u32x4_any*>(src + (int64_t)q * 16);
+                               ((int64_t)entry_idx(e) * a.fr.elems + (int64_t)(2 * r.oi0 - 1) * hin * 3) * (u8 ? 1 : 2);
 #pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            // bf16 of a byte: the upper half of its float
-            const uint32_t f0 = __float_as_uint((float)(b[w] & 255u)), f1 = __float_as_uint((float)(b[w] >> 8 & 255u));
-            const uint32_t f2 = __float_as_uint((float)(b[w] >> 16 & 255u)), f3 = __float_as_uint((float)(b[w] >> 24));
-            const uint32_t p0 = f0 >> 16 | (f1 & 0xFFFF0000u), p1 = f2 >> 16 | (f3 & 0xFFFF0000u);
-            if (w < 2) { lo[2 * w] = p0; lo[2 * w + 1] = p1; }
-            else { hi[2 * w - 4] = p0; hi[2 * w - 3] = p1; }
-          }
+    for (int i = 0; i < 4; ++i) {
+      if (i >= 2 && u8) break;
+      const int q = min(max(tid + 256 * i, first), n - 1);      // (chunks of no use are read again)
+      v[i] = *reinterpret_cast<const u32x4_any*>(src + (int64_t)q * 16);
+    }
+  };
+  auto stage = [&](const Tile& r) {
+    const int hin = 1 << r.lg, lc = u8 ? r.lg - 4 : r.lg - 3, cpr = 3 << lc, RS = gf_stride(hin);
+    const int rows = 2 * gf_rows(hin >> 1) + 1;
+    const uint32_t padw = pad | (uint32_t)pad << 16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = tid + 256 * i, y = (q >> lc) / 3, c = q - y * cpr;
+      if ((i >= 2 && u8) || q >= rows * cpr) break;
+      const bool in = y > 0 || r.oi0 > 0;
+      if (u8) {
+        u32x4 lo, hi;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          // bf16 of a byte: the upper half of its float
+          const uint32_t b = v[i][w];
+          const uint32_t f0 = __float_as_uint((float)(b & 255u)), f1 = __float_as_uint((float)(b >> 8 & 255u));
+          const uint32_t f2 = __float_as_uint((float)(b >> 16 & 255u)), f3 = __float_as_uint((float)(b >> 24));
+          const uint32_t p0 = in ? f0 >> 16 | (f1 & 0xFFFF0000u) : padw, p1 = in ? f2 >> 16 | (f3 & 0xFFFF0000u) : padw;
+          if (w < 2) { lo[2 * w] = p0; lo[2 * w + 1] = p1; }
+          else { hi[2 * w - 4] = p0; hi[2 * w - 3] = p1; }
         }
-        reinterpret_cast<u32x4*>(dst)[0] = lo;
-        reinterpret_cast<u32x4*>(dst)[1] = hi;
+        u32x4* dst = reinterpret_cast<u32x4*>(xin + y * RS + GF_X0 + c * 16);
+        dst[0] = lo;
+        dst[1] = hi;
       } else {
-        if (in) v = *reinterpret_cast<const u32x4_any*>(src + (int64_t)q * 16);
-        *reinterpret_cast<u32x4*>(dst) = v;
+        u32x4 x = v[i];
+        if (!in) x = (u32x4){padw, padw, padw, padw};
+        *reinterpret_cast<u32x4*>(xin + y * RS + GF_X0 + c * 8) = x;
       }
     }
-    for (int r = tid; r < rows_in; r += 256)
+    if (tid < rows)
 #pragma unroll
-      for (int c = 1; c <= 3; ++c) xin[r * RS + GF_X0 - c] = pad;
+      for (int c = 1; c <= 3; ++c) xin[tid * RS + GF_X0 - c] = pad;
+  };
+  int t = blockIdx.x, loaded = -1;
+  if (t >= total) return;
+  const int last = total - 1;
+  Tile cur = decode(t), nx = decode(min(t + (int)gridDim.x, last));
+  request(cur, entry(cur));
+  uint32_t e_nx = entry(nx);
+  for (; t < total; t += gridDim.x) {
+    const int slot = cur.slot, cout = a.widths[slot][0], nct = cout / 16;
+    if (slot != loaded) {
+      for (int q = tid; q < TERMS * nct * 64; q += 256) {
+        const int term = q / (nct * 64), o = q - term * nct * 64;
+        const __bf16* src = term == 0 ? a.w_bf[slot][0] : a.w_ml[slot][0] + (int64_t)(term - 1) * nct * 512;
+        reinterpret_cast<u32x4*>(w_s)[term * 256 + o] = reinterpret_cast<const u32x4*>(src)[o];
+      }
+      if (tid < cout) bias_s[tid] = a.bias[slot][0][tid];
+      loaded = slot;
+    }
+    stage(cur);
     __syncthreads();
-    const float* bias = a.bias[slot][0];
-    T* o0 = reinterpret_cast<T*>(a.act[0]) + ((int64_t)ebase + e) * a.act_stride + (int64_t)oi0 * hout * cout;
-    const int np = ro * hout;                       // a multiple of 64
+    const Tile at = cur;
+    if (t + (int)gridDim.x < total) {
+      cur = nx;
+      request(cur, e_nx);
+      nx = decode(min(t + 2 * (int)gridDim.x, last));
+      e_nx = entry(nx);
+    }
+    const int hout = 1 << (at.lg - 1), RS = gf_stride(2 << (at.lg - 1));
+    T* o0 = reinterpret_cast<T*>(a.act[0]) + ((int64_t)at.ebase + at.e) * a.act_stride + (int64_t)at.oi0 * hout * cout;
+    const int np = gf_rows(hout) * hout;            // a multiple of 64
+    auto tile_mfma = [&](int c, bf16x8 x) {
+      const bf16x8* w = reinterpret_cast<const bf16x8*>(w_s) + c * 64 + lane;
+      floatx4 acc = (floatx4){0.f, 0.f, 0.f, 0.f};
+      if constexpr (TERMS == 3) acc = mfma_bf16(w[256], x, mfma_bf16(w[512], x, acc));
+      return mfma_bf16(w[0], x, acc);
+    };
     for (int pt = wave * 32; pt < np; pt += 128) {
-      floatx4 acc[4][2];
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[c][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
       const uint16_t* base[2];                      // element before the position's first value
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const int pl = pt + q * 16 + l16;
-        base[q] = xin + 2 * (pl / hout) * RS + GF_X0 - 4 + 6 * (pl % hout);
+        base[q] = xin + 2 * (pl >> (at.lg - 1)) * RS + GF_X0 - 4 + 6 * (pl & (hout - 1));
       }
       bf16x8 xf[2];
 #pragma unroll
@@ -407,14 +488,36 @@ __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
         if (g == 3) f = (u32x4){(d[0] >> 16) | (d[1] & 0xFFFF0000u), d[2] >> 16, 0u, 0u};
         xf[q] = *reinterpret_cast<const bf16x8*>(&f);
       }
+      T* o = o0 + (int64_t)(pt + l16) * cout;
+      if (cout % 32 == 0) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (c >= nct) continue;
+        for (int c = 0; c < 4; c += 2) {
+          if (c >= nct) break;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          acc[c][q] = first_mfma<T>(a, slot, c, lane, xf[q], acc[c][q]);
-          const int ch = c * 16 + 4 * g;
-          store_relu4(o0 + (int64_t)(pt + q * 16 + l16) * cout + ch, acc[c][q], *reinterpret_cast<const float4*>(bias + ch));
+          for (int q = 0; q < 2; ++q)
+            store_relu8(o + q * 16 * cout + c * 16 + 8 * g, tile_mfma(c, xf[q]), tile_mfma(c + 1, xf[q]),
+                        bias_s + c * 16 + 8 * g);
+        }
+      } else {
+        // an odd number of tiles: the lane groups of the two position tiles trade places, so that each lane
+        // holds eight channels of one position
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          if (c >= nct) break;
+          const float4 b = *reinterpret_cast<const float4*>(bias_s + c * 16 + 4 * g);
+          if constexpr (sizeof(T) == 2) {
+            alignas(8) T h[2][4];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) store_relu4(h[q], tile_mfma(c, xf[q]), b);
+            const uint2 v0 = *reinterpret_cast<const uint2*>(h[0]), v1 = *reinterpret_cast<const uint2*>(h[1]);
+            const auto lo = __builtin_amdgcn_permlane16_swap(v0.x, v1.x, false, false);
+            const auto hi = __builtin_amdgcn_permlane16_swap(v0.y, v1.y, false, false);
+            *reinterpret_cast<uint4*>(o + (g & 1) * 16 * cout + c * 16 + (g >> 1) * 8) =
+                make_uint4(lo[0], hi[0], lo[1], hi[1]);
+          } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) store_relu4(o + q * 16 * cout + c * 16 + 4 * g, tile_mfma(c, xf[q]), b);
+          }
         }
       }
     }
@@ -535,7 +638,7 @@ void gcnn_pack_layer(int layer, int cin, int cout, const float* w, float scale, 
       for (int lane = 0; lane < 64; ++lane)
         for (int e = 0; e < 8; ++e) {
           const int k = ks * 32 + 8 * (lane >> 4) + e;
-          const int oc = ct * 16 + (lane & 15);
+          const int oc = g_channel(cout, ct, lane & 15);
           int tap = k / cin, ic = k % cin;
           bool used = tap < 9;
           if (layer == 0) {
@@ -620,9 +723,9 @@ void launch_gcnn_layerwise(const GcnnArgs& a, const Forward& f, int tier, int gr
     if (l == 0) {
       bool first_ok = true;
       for (int i = 0; i < a.n_preds; ++i) first_ok = first_ok && gconv_first_ok(a.in_hw[i] >> 1, a.widths[i][0]);
-      if (first_ok) {
-        if (bf) hipLaunchKernelGGL(gconv_first_kernel<__bf16>, dim3(grid * 8), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(gconv_first_kernel<float>, dim3(grid * 8), dim3(256), 0, s, a);
+      if (first_ok) {                  // (as many workgroups as the registers let in: their tiles are a stream)
+        if (bf) hipLaunchKernelGGL(gconv_first_kernel<__bf16>, dim3(grid * 5), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(gconv_first_kernel<float>, dim3(grid * 4), dim3(256), 0, s, a);
       } else {
         if (bf) hipLaunchKernelGGL(gconv_first_any_kernel<__bf16>, dim3(grid * 4), dim3(256), 0, s, a);
         else hipLaunchKernelGGL(gconv_first_any_kernel<float>, dim3(grid * 4), dim3(256), 0, s, a);
