@@ -304,6 +304,11 @@ constexpr int kRouteThreads = 256, kRouteItems = 8, kRouteChunk = kRouteThreads 
 // each chunk's reservation round trip exposed (2 per CU: 17 % slower at 2^22-tuple waves), and
 // halving the chunk (4 entries per thread, 8 workgroups per CU) nearly doubled the time.
 constexpr int kRouteBlocksPerCu = 4;
+// Short rounds are cut into chunks of fewer entries per thread, 64 to 127 chunks, because a thread takes its
+// entries' look-ups one after the other: rounds of about 8,192 tuples 14 -> 8 us, with learned keys 22 -> 11,
+// with the result cache 42 -> 12 (more chunks than that add to the queues' counters one after the other, at
+// tens of nanoseconds each).
+constexpr int kRouteSpread = 64;
 
 __global__ __launch_bounds__(kRouteThreads) void k_route(RouteArgs a) {
   __shared__ int order[kMaxK];
@@ -326,7 +331,11 @@ __global__ __launch_bounds__(kRouteThreads) void k_route(RouteArgs a) {
   const int wv = threadIdx.x / kWave, lane = lane_id();
   const unsigned long long below = (1ull << lane) - 1ull;
   uint32_t n_learned = 0, n_stats = 0, n_stale = 0;
-  for (int64_t base = (int64_t)blockIdx.x * kRouteChunk; base < total; base += (int64_t)gridDim.x * kRouteChunk) {
+  // entries per thread: fewer than kRouteItems where the tuples then still make no more than
+  // kRouteSpread chunks (a thread takes its entries' lookups one after the other)
+  const int items = (int)min((int64_t)kRouteItems, max((int64_t)1, total / (kRouteSpread * kRouteThreads)));
+  const int chunk = items * kRouteThreads;
+  for (int64_t base = (int64_t)blockIdx.x * chunk; base < total; base += (int64_t)gridDim.x * chunk) {
     uint32_t e[kRouteItems];
     int kk[kRouteItems], off[kRouteItems];
 #pragma unroll
@@ -334,6 +343,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_route(RouteArgs a) {
       const int64_t i = base + r * kRouteThreads + threadIdx.x;
       e[r] = 0u;
       kk[r] = -1;
+      if (r >= items) continue;
       if (reuse) {
         if (i < total) e[r] = i < n_in ? a.pend_in[i] : make_entry(a.adm_lo + (uint32_t)(i - n_in), 0u);
         uint32_t cached;
@@ -474,6 +484,39 @@ __global__ __launch_bounds__(256) void k_res_write(const uint32_t* bits, int64_t
     int bit = __ffs(b) - 1;
     out[pos++] = id_base + w * 32 + bit;
     b &= b - 1;
+  }
+}
+
+// The three passes in one launch, a bitmap word per thread: 5 us, the three launches 13 and the gaps
+// between them (most pushes are this small; longer bitmaps need more than a workgroup's stores).
+constexpr int kResSmall = 1024;
+__global__ __launch_bounds__(kResSmall) void k_res_small(const uint32_t* bits, int nwords, DevState* st, int* base_out,
+                                                         int64_t id_base, int64_t* out) {
+  __shared__ int wsum[kResSmall / kWave];
+  const int w = (int)threadIdx.x, lane = lane_id();
+  uint32_t b = w < nwords ? bits[w] : 0u;
+  const int base = st->n_result, n = __popc(b);
+  int inc = n;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int up = __shfl_up(inc, o);
+    if (lane >= o) inc += up;
+  }
+  if (lane == kWave - 1) wsum[w / kWave] = inc;
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int v = 0; v < kResSmall / kWave; ++v) {
+    before += v < w / kWave ? wsum[v] : 0;
+    all += wsum[v];
+  }
+  int pos = base + before + inc - n;
+  while (b) {
+    const int bit = __ffs(b) - 1;
+    out[pos++] = id_base + (int64_t)w * 32 + bit;
+    b &= b - 1;
+  }
+  if (w == 0) {
+    *base_out = base;
+    st->n_result = base + all;         // (every thread has read it: the barrier above)
   }
 }
 
@@ -2263,10 +2306,13 @@ int hydro_session_push(hydro_session* s, const hydro_frames* frames, const float
           router_nn_keys(s->rnn, s->st, s->pend[in_slot], in_slot, ra.adm_lo, ra.adm_hi, s->n_cu, st);
         }
       }
-      // enough workgroups for the round's live tuples (at most act_cap), up to kRouteBlocksPerCu per CU
+      // enough workgroups for the chunks of the round's live tuples (at most act_cap; short rounds make
+      // shorter chunks, less than 2 kRouteSpread of them), up to kRouteBlocksPerCu per CU
       const int64_t live_bound = std::min<int64_t>(s->act_cap, n);
-      const int route_grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)s->n_cu * kRouteBlocksPerCu,
-                                                                          (live_bound + kRouteChunk - 1) / kRouteChunk));
+      const int64_t route_chunks =
+          std::max<int64_t>((live_bound + kRouteChunk - 1) / kRouteChunk,
+                            std::min<int64_t>(2 * kRouteSpread, (live_bound + kRouteThreads - 1) / kRouteThreads));
+      const int route_grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)s->n_cu * kRouteBlocksPerCu, route_chunks));
       hipLaunchKernelGGL(k_route, dim3(route_grid), dim3(kRouteThreads), 0, st, ra);
       if (host_mode && !host_rc) host_rc = host_round_copy(s, st);
       if (timed && ev[1]) hipEventRecord(ev[1], st);
@@ -2306,10 +2352,15 @@ int hydro_session_push(hydro_session* s, const hydro_frames* frames, const float
     // ordered result materialisation for this push
     if (nwords > 0) {
       const int nb = (int)((nwords + 255) / 256);
-      hipLaunchKernelGGL(k_res_count, dim3(nb), dim3(256), 0, st, s->result_bits, nwords, s->res_blocks);
-      hipLaunchKernelGGL(k_res_scan, dim3(1), dim3(1024), 0, st, s->res_blocks, nb, s->st, s->res_base);
-      hipLaunchKernelGGL(k_res_write, dim3(nb), dim3(256), 0, st, s->result_bits, nwords, s->res_blocks, fr.id_base,
-                         s->out_ids);
+      if (nwords <= kResSmall) {
+        hipLaunchKernelGGL(k_res_small, dim3(1), dim3(kResSmall), 0, st, s->result_bits, (int)nwords, s->st, s->res_base,
+                           fr.id_base, s->out_ids);
+      } else {
+        hipLaunchKernelGGL(k_res_count, dim3(nb), dim3(256), 0, st, s->result_bits, nwords, s->res_blocks);
+        hipLaunchKernelGGL(k_res_scan, dim3(1), dim3(1024), 0, st, s->res_blocks, nb, s->st, s->res_base);
+        hipLaunchKernelGGL(k_res_write, dim3(nb), dim3(256), 0, st, s->result_bits, nwords, s->res_blocks, fr.id_base,
+                           s->out_ids);
+      }
     }
   };
 
