@@ -248,20 +248,22 @@ __global__ __launch_bounds__(256) void rnn_keys_kernel(KeyArgs a) {
   }
 }
 
-// Online training, one workgroup of four waves: TSTEPS Adam steps per round on successive windows
+// Online training, one workgroup of eight waves: TSTEPS Adam steps per round on successive windows
 // of TB logged outcomes (newest first), masked binary cross-entropy on the evaluated predicate.
-// Both contractions run on fp32 MFMA (16x16x4): the forward pass H = F W1 (64 x 192 x 64; wave w
-// owns samples 16w..16w+15) and the W1 gradient F^T dH (192 x 64 x 64; wave w owns feature rows
-// 48w..48w+47).  Every global read the launch needs (parameters, Adam moments, the windows'
+// Both contractions run on fp32 MFMA (16x16x4): the forward pass H = F W1 (64 x 192 x 64; wave w of
+// each half of the hidden units owns samples 16w..16w+15) and the W1 gradient F^T dH (192 x 64 x 64; it
+// owns feature rows 48w..48w+47).  Two waves per SIMD, because one wave's LDS and MFMA latencies and
+// Adam's square roots and divisions follow each other (four waves: 48 us a round, eight: 37).  Every global read the launch needs (parameters, Adam moments, the windows'
 // features, the judge's counters) is issued up front; parameters live in LDS across the steps and
 // each thread keeps the Adam moments of the parameters it updates in registers, writing
 // everything back once at the end.
 constexpr int FSB = RF + 2;  // LDS row stride (bf16) of the sample features
 constexpr int HS = RH + 4;   // LDS row stride of H and dH
 constexpr int NREST = RH + RH * RK + RK;   // b1, W2, b2
-constexpr int REST_PER = (NREST + 255) / 256;
+constexpr int TT = 512;          // threads of the training workgroup
+constexpr int REST_PER = (NREST + TT - 1) / TT;
 
-__global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint32_t* __restrict__ ring,
+__global__ __launch_bounds__(TT) void rnn_train_kernel(DevState* st, const uint32_t* __restrict__ ring,
                                                         const __bf16* __restrict__ feats, float* __restrict__ params,
                                                         float* __restrict__ am, float* __restrict__ av,
                                                         __bf16* __restrict__ w1_frag, float lr) {
@@ -271,10 +273,12 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
   __shared__ float dHs[TB * HS];   // dL/dh, [b][j]
   __shared__ float rest[NREST];    // b1 | W2 | b2
   __shared__ float part[4 * NREST];  // per-wave partial gradients of b1 | W2 | b2
+  __shared__ float pos[2][TB];     // partial logits of the two halves of the hidden units
   __shared__ float dO[TB], yv[TSTEPS * TB];
   __shared__ int kk[TSTEPS * TB];
   __shared__ int s_go;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, l16 = lane & 15;
+  // wave w of half hf: samples 16 w .. + 15 (forward), inputs 48 w .. + 47 (W1), hidden units 32 hf .. + 31
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6 & 3, hf = tid >> 8, g = lane >> 4, l16 = lane & 15;
   const unsigned long long head = st->ring_head;
   const int steps0 = st->train_steps;
   if (!st->learned_active || (long long)head < (long long)TB) return;  // uniform across the workgroup
@@ -283,28 +287,28 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
   // ---- all global reads up front
   {
     const float4* p4 = reinterpret_cast<const float4*>(params);
-    float4 wv[RF * RH / 4 / 256];
+    float4 wv[RF * RH / 4 / TT];
 #pragma unroll
-    for (int r = 0; r < RF * RH / 4 / 256; ++r) wv[r] = p4[tid + 256 * r];
+    for (int r = 0; r < RF * RH / 4 / TT; ++r) wv[r] = p4[tid + TT * r];
 #pragma unroll
-    for (int r = 0; r < RF * RH / 4 / 256; ++r) reinterpret_cast<float4*>(W1s)[tid + 256 * r] = wv[r];
+    for (int r = 0; r < RF * RH / 4 / TT; ++r) reinterpret_cast<float4*>(W1s)[tid + TT * r] = wv[r];
   }
-  for (int q = tid; q < NREST; q += 256) rest[q] = params[RF * RH + q];
-  float m1[3][4][4], v1[3][4][4];
+  for (int q = tid; q < NREST; q += TT) rest[q] = params[RF * RH + q];
+  float m1[3][2][4], v1[3][2][4];
 #pragma unroll
   for (int mt = 0; mt < 3; ++mt)
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int q = (48 * w + 16 * mt + 4 * g + r) * RH + 16 * nt + l16;
+        const int q = (48 * w + 16 * mt + 4 * g + r) * RH + 32 * hf + 16 * nt + l16;
         m1[mt][nt][r] = am[q];
         v1[mt][nt][r] = av[q];
       }
   float mr[REST_PER], vr[REST_PER];
 #pragma unroll
   for (int c = 0; c < REST_PER; ++c) {
-    const int q = tid + 256 * c;
+    const int q = tid + TT * c;
     mr[c] = q < NREST ? am[RF * RH + q] : 0.f;
     vr[c] = q < NREST ? av[RF * RH + q] : 0.f;
   }
@@ -317,11 +321,11 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
   }
   {
     constexpr int CH = TSTEPS * TB * (RF / 8);    // 16-byte chunks of features
-    uint4 fv[(CH + 255) / 256];
-    int dsto[(CH + 255) / 256];
+    uint4 fv[(CH + TT - 1) / TT];
+    int dsto[(CH + TT - 1) / TT];
 #pragma unroll
-    for (int r = 0; r < (CH + 255) / 256; ++r) {
-      const int q = tid + 256 * r;
+    for (int r = 0; r < (CH + TT - 1) / TT; ++r) {
+      const int q = tid + TT * r;
       dsto[r] = -1;
       if (q < CH) {
         const int sb = q / (RF / 8), f8 = q % (RF / 8), back = sb / TB, b = sb % TB;
@@ -333,7 +337,7 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
       }
     }
 #pragma unroll
-    for (int r = 0; r < (CH + 255) / 256; ++r)
+    for (int r = 0; r < (CH + TT - 1) / TT; ++r)
       if (dsto[r] >= 0) {
         // FSB is even, so each chunk lands 4-byte aligned
         uint32_t* d = reinterpret_cast<uint32_t*>(&Fb[dsto[r]]);
@@ -360,24 +364,24 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
     const float* W2s = rest + RH;
     const float* b2s = rest + RH + RH * RK;
 
-    // forward on MFMA: lane holds h[s = 16w + 4g + r][j = 16nt + l16]
-    floatx4 acc[4];
+    // forward on MFMA: lane holds h[s = 16w + 4g + r][j = 32hf + 16nt + l16]
+    floatx4 acc[2];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    for (int nt = 0; nt < 2; ++nt) acc[nt] = (floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
     for (int ks = 0; ks < RF / 4; ++ks) {
       const float a_ = (float)F[(16 * w + l16) * FSB + 4 * ks + g];
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_, W1s[(4 * ks + g) * RH + 16 * nt + l16], acc[nt], 0, 0, 0);
+      for (int nt = 0; nt < 2; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a_, W1s[(4 * ks + g) * RH + 32 * hf + 16 * nt + l16], acc[nt], 0, 0, 0);
     }
     float po[4] = {0.f, 0.f, 0.f, 0.f};
     int ksl[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) ksl[r] = kk[back * TB + 16 * w + 4 * g + r];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const int j = 16 * nt + l16;
+    for (int nt = 0; nt < 2; ++nt) {
+      const int j = 32 * hf + 16 * nt + l16;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         acc[nt][r] += b1s[j];
@@ -386,22 +390,24 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
         po[r] += h * W2s[j * RK + ksl[r]];
       }
     }
-    // logit of the evaluated slot: reduce over the 16 lanes of the group
+    // logit of the evaluated slot: reduce over the 16 lanes of the group, then over the halves
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       po[r] = row_sum16(po[r]);
+      if (l16 == 0) pos[hf][16 * w + 4 * g + r] = po[r];
     }
+    __syncthreads();
     float d[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int sidx = 16 * w + 4 * g + r;
-      const float o = po[r] + b2s[ksl[r]];
+      const float o = pos[0][sidx] + pos[1][sidx] + b2s[ksl[r]];
       d[r] = (1.0f / (1.0f + __expf(-o)) - yv[back * TB + sidx]) * (1.0f / TB);
-      if (l16 == 0) dO[sidx] = d[r];
+      if (hf == 0 && l16 == 0) dO[sidx] = d[r];
     }
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const int j = 16 * nt + l16;
+    for (int nt = 0; nt < 2; ++nt) {
+      const int j = 32 * hf + 16 * nt + l16;
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         dHs[(16 * w + 4 * g + r) * HS + j] = acc[nt][r] > 0.f ? d[r] * W2s[j * RK + ksl[r]] : 0.f;
@@ -410,29 +416,29 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
 
     const int t_adam = steps + 1;
     const float c1 = 1.f / (1.f - powf(0.9f, (float)t_adam)), c2 = 1.f / (1.f - powf(0.999f, (float)t_adam));
-    // W1 gradient on MFMA: lane holds g[i = 48w + 16mt + 4g + r][j = 16nt + l16]
-    floatx4 gacc[3][4];
+    // W1 gradient on MFMA: lane holds g[i = 48w + 16mt + 4g + r][j = 32hf + 16nt + l16]
+    floatx4 gacc[3][2];
 #pragma unroll
     for (int mt = 0; mt < 3; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) gacc[mt][nt] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      for (int nt = 0; nt < 2; ++nt) gacc[mt][nt] = (floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll 2
     for (int ks = 0; ks < TB / 4; ++ks) {
       const int b = 4 * ks + g;
-      float a3[3], b4[4];
+      float a3[3], b2[2];
 #pragma unroll
       for (int mt = 0; mt < 3; ++mt) a3[mt] = (float)F[b * FSB + 48 * w + 16 * mt + l16];
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) b4[nt] = dHs[b * HS + 16 * nt + l16];
+      for (int nt = 0; nt < 2; ++nt) b2[nt] = dHs[b * HS + 32 * hf + 16 * nt + l16];
 #pragma unroll
       for (int mt = 0; mt < 3; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-          gacc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a3[mt], b4[nt], gacc[mt][nt], 0, 0, 0);
+        for (int nt = 0; nt < 2; ++nt)
+          gacc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a3[mt], b2[nt], gacc[mt][nt], 0, 0, 0);
     }
-    // b1, W2, b2 gradients: wave w sums its own 16 samples (lane j = hidden unit) into part[w],
-    // the owners add the four partials below
-    {
+    // b1, W2, b2 gradients: the first half's wave w sums its own 16 samples (lane j = hidden unit) into
+    // part[w], the owners add the four partials below
+    if (hf == 0) {
       float gb1 = 0.f, gb2 = 0.f, gw2[RK];
 #pragma unroll
       for (int kc = 0; kc < RK; ++kc) gw2[kc] = 0.f;
@@ -457,10 +463,10 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
 #pragma unroll
     for (int mt = 0; mt < 3; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
+      for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int q = (48 * w + 16 * mt + 4 * g + r) * RH + 16 * nt + l16;
+          const int q = (48 * w + 16 * mt + 4 * g + r) * RH + 32 * hf + 16 * nt + l16;
           const float gq = gacc[mt][nt][r];
           const float m = 0.9f * m1[mt][nt][r] + 0.1f * gq;
           const float v = 0.999f * v1[mt][nt][r] + 0.001f * gq * gq;
@@ -471,7 +477,7 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
     __syncthreads();  // partials complete
 #pragma unroll
     for (int c = 0; c < REST_PER; ++c) {
-      const int q = tid + 256 * c;
+      const int q = tid + TT * c;
       if (q < NREST) {
         const float gq = part[q] + part[NREST + q] + part[2 * NREST + q] + part[3 * NREST + q];
         const float m = 0.9f * mr[c] + 0.1f * gq;
@@ -498,10 +504,10 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
 #pragma unroll
   for (int mt = 0; mt < 3; ++mt)
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = 48 * w + 16 * mt + 4 * g + r, j = 16 * nt + l16, q = i * RH + j;
+        const int i = 48 * w + 16 * mt + 4 * g + r, j = 32 * hf + 16 * nt + l16, q = i * RH + j;
         const float np = W1s[q];
         am[q] = m1[mt][nt][r];
         av[q] = v1[mt][nt][r];
@@ -512,7 +518,7 @@ __global__ __launch_bounds__(256) void rnn_train_kernel(DevState* st, const uint
       }
 #pragma unroll
   for (int c = 0; c < REST_PER; ++c) {
-    const int q = tid + 256 * c;
+    const int q = tid + TT * c;
     if (q < NREST) {
       am[RF * RH + q] = mr[c];
       av[RF * RH + q] = vr[c];
@@ -632,7 +638,7 @@ void router_nn_keys(RouterNN* r, DevState* st, const uint32_t* pend_in, int in_s
 }
 
 void router_nn_learn(RouterNN* r, DevState* st, hipStream_t s) {
-  hipLaunchKernelGGL(rnn_train_kernel, dim3(1), dim3(256), 0, s, st, r->ring, r->feats, r->params, r->adam_m,
+  hipLaunchKernelGGL(rnn_train_kernel, dim3(1), dim3(TT), 0, s, st, r->ring, r->feats, r->params, r->adam_m,
                      r->adam_v, r->w1_frag, 3e-3f);
 }
 
@@ -691,7 +697,7 @@ extern "C" int hydro_router_train_debug(int32_t k, const uint16_t* feats, const 
          hipMemcpy(m, adam_m, NPARAM * sizeof(float), hipMemcpyHostToDevice) == hipSuccess &&
          hipMemcpy(v, adam_v, NPARAM * sizeof(float), hipMemcpyHostToDevice) == hipSuccess;
     if (ok) {
-      hipLaunchKernelGGL(rnn_train_kernel, dim3(1), dim3(256), 0, nullptr, st, ring, f, p, m, v, frag, lr);
+      hipLaunchKernelGGL(rnn_train_kernel, dim3(1), dim3(TT), 0, nullptr, st, ring, f, p, m, v, frag, lr);
       ok = hipDeviceSynchronize() == hipSuccess &&
            hipMemcpy(params, p, NPARAM * sizeof(float), hipMemcpyDeviceToHost) == hipSuccess &&
            hipMemcpy(adam_m, m, NPARAM * sizeof(float), hipMemcpyDeviceToHost) == hipSuccess &&
