@@ -55,25 +55,39 @@ constexpr int S1_W = H1 + 1;        // layer-1 slab row stride in pixels (top/le
 constexpr int L2_W = H2 + 1;
 constexpr int CB1 = 16;             // layer-1 channels per slab
 
-// Pixel strides (elements) of the layer-1 slab and the layer-2 output are padded so that the 16
-// lanes of an MFMA row group, which read 16 different pixels, spread over the LDS banks.
+// A 16-byte LDS read of a wave takes lanes 0 .. 7 and 16 .. 23 together (8 .. 15 and 24 .. 31, and so on):
+// eight pixels two columns apart, two neighbouring 16-byte units of each, which must be sixteen
+// different units of LDS's 256 bytes.  So a row holds its even columns before its odd ones, and a pixel
+// pitch is twice an odd number of units; the odd columns start a unit later, so that the 8-byte stores
+// of consecutive columns differ too.  (With columns in order at padded pitches every read took two passes.
+// Cycles lost to bank conflicts, share of a CU's: bf16 width 128 0.305 -> 0.15, width 64 0.287 -> 0.19; 16,384 frames:
+// 1494 -> 1450, 541 -> 510 and, width 32, 256 -> 246 us; FP32, three terms: 0.126 -> 0.117, width 32 808 -> 755 us.)
 template <typename T> struct Pad {
-  // bytes of activations per layer-1 slab pixel (fp32: three bf16 planes of 16 channels), and its pitch
-  static constexpr int S1D = CB1 * (sizeof(T) == 4 ? 6 : 2);
-  static constexpr int S1PB = S1D + (sizeof(T) == 4 ? 16 : 0);
+  // bytes of a layer-1 slab pixel (fp32: three bf16 planes of 16 channels), and of a row
+  static constexpr int S1PB = CB1 * (sizeof(T) == 4 ? 6 : 2), S1RB = S1_W * S1PB + 16;
+  static_assert(S1PB / 16 % 4 == 2, "pitch");
+  // byte b of pixel (y, x), borders included
+  __host__ __device__ static constexpr int at(int y, int x, int b) {
+    return y * S1RB + (x & 1) * ((S1_W + 1) / 2 * S1PB + 16) + (x >> 1) * S1PB + b;
+  }
 };
-// Layer-2 pixel of width class m: bf16, or for the FP32 tier three bf16 planes (the widest class: fp32,
-// its planes do not fit LDS), + 16 bytes
+// Layer-2 pixel of width class m: bf16, or for the FP32 tier three bf16 planes (the widest class: fp32, its
+// planes do not fit LDS, nor does a pitch that suits its 32-byte reads)
 template <typename T, int M> struct PadL2 {
   static constexpr bool PLANES = sizeof(T) == 4 && M < 4;
-  static constexpr int D = 32 * M * (PLANES ? 6 : (int)sizeof(T)), PB = D + 16;
+  static constexpr int D = 32 * M * (PLANES ? 6 : (int)sizeof(T));
+  static constexpr int PB = D + (sizeof(T) == 4 && !PLANES ? 16 : 32), RB = L2_W * PB + 16;
+  static_assert((sizeof(T) == 4 && !PLANES) || PB / 16 % 4 == 2, "pitch");
+  __host__ __device__ static constexpr int at(int y, int x, int b) {
+    return y * RB + (x & 1) * ((L2_W + 1) / 2 * PB + 16) + (x >> 1) * PB + b;
+  }
 };
 
 template <typename T, int MMAX = 4> struct CnnLds {
   static constexpr int FR_BYTES = (H0 + 1) * FRS * 2;
   static constexpr int S1_OFF = (FR_BYTES + 15) / 16 * 16;
-  static constexpr int S1_BYTES = S1_W * S1_W * Pad<T>::S1PB;
-  static constexpr int L2_BYTES_MAX = L2_W * L2_W * PadL2<T, MMAX>::PB;
+  static constexpr int S1_BYTES = S1_W * Pad<T>::S1RB;
+  static constexpr int L2_BYTES_MAX = L2_W * PadL2<T, MMAX>::RB;
   static constexpr int REGION = (S1_OFF + S1_BYTES) > L2_BYTES_MAX ? (S1_OFF + S1_BYTES) : L2_BYTES_MAX;
 };
 
@@ -168,11 +182,11 @@ __device__ inline void frame_store(const CnnArgs& a, const FramePrefetch<NT>& pf
   const __bf16 padv = static_cast<__bf16>(a.pad_raw);
   for (int e = tid; e < FRS; e += NT) FR[e] = padv;                                // top border row
   for (int e = tid; e < H0 * 3; e += NT) FR[(e / 3 + 1) * FRS + FR_X0 - 3 + e % 3] = padv;  // left border
-  constexpr int WP = Pad<T>::S1D / 4;             // words per pixel
+  constexpr int WP = Pad<T>::S1PB / 4;            // words per pixel
   for (int p = tid; p < (2 * S1_W - 1) * WP; p += NT) {
     const int q = p / WP, c = p % WP;
     const int y = q < S1_W ? 0 : q - S1_W + 1, x = q < S1_W ? q : 0;
-    reinterpret_cast<uint32_t*>(region + CnnLds<T>::S1_OFF + (y * S1_W + x) * Pad<T>::S1PB)[c] = 0u;
+    *reinterpret_cast<uint32_t*>(region + CnnLds<T>::S1_OFF + Pad<T>::at(y, x, 4 * c)) = 0u;
   }
 }
 
@@ -244,7 +258,8 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
                           bool next_valid, uint32_t next_idx, __bf16* feat_dst, float* z_out) {
   constexpr int NT = NWV * 64;                       // threads
   constexpr int C2 = 32 * M, C3 = 64 * M;
-  constexpr int S1PB = Pad<T>::S1PB, L2PB = PadL2<T, M>::PB;
+  typedef Pad<T> P1;
+  typedef PadL2<T, M> P2;
   // FP32 tier (T = float): bf16 MFMAs on three-term operands, in the bf16 fragment layout (k-steps
   // of 32, 8 per lane); activations held in LDS as their three terms, or in fp32 and split at
   // every read where the terms do not fit (layer 2 of the widest class).  A layer-1 output is read
@@ -382,8 +397,7 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
       frame_features_put<NT>(ff, sh.feat);
     }
     auto l1_store = [&](int q, const floatx4& acc) {
-      const int px = (wave * MPW + q) * 16 + l16, i = px >> 5, j = px & 31;
-      unsigned char* dst = S1 + ((i + 1) * S1_W + (j + 1)) * S1PB + 8 * g;
+      unsigned char* dst = S1 + P1::at(wave * MPW / 2 + 1, l16 + 1, 8 * g) + (q >> 1) * P1::S1RB + (q & 1) * 8 * P1::S1PB;
       const float v[4] = {fmaxf(acc[0], 0.f), fmaxf(acc[1], 0.f), fmaxf(acc[2], 0.f), fmaxf(acc[3], 0.f)};
       if constexpr (S3) store_planes<3>(dst, 2 * CB1, v);
       else store4<__bf16>(reinterpret_cast<__bf16*>(dst), v[0], v[1], v[2], v[3]);
@@ -432,10 +446,10 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
         const int tp = min(k0 / CB1, 8);        // padded k (zero weights) reads a valid tap
         const int c0 = k0 % CB1;
         const int u = tp / 3, v = tp % 3;
+        const unsigned char* src0 = S1 + P1::at(2 * mg2 * MT2 + u, 2 * l16 + v, c0 * 2);
 #pragma unroll
         for (int q = 0; q < MT2; ++q) {
-          const int px = (mg2 * MT2 + q) * 16 + l16, i = px >> 4, j = px & 15;
-          const unsigned char* src = S1 + ((2 * i + u) * S1_W + 2 * j + v) * S1PB + c0 * 2;
+          const unsigned char* src = src0 + q * 2 * P1::S1RB;
           bf16x8 x[3];
 #pragma unroll
           for (int t = 0; t < 3; ++t) x[t] = *reinterpret_cast<const bf16x8*>(src + t * 2 * CB1);
@@ -469,11 +483,9 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
         const int k0 = ks * KSTEP + KPL * g, t = min(k0 / CB1, 8), c0 = k0 % CB1;   // (padded k: a valid tap, zero weights)
         const int u = t / 3, v = t - 3 * u;
         frag av[MT2];
+        const unsigned char* src = S1 + P1::at(2 * mg2 * MT2 + u, 2 * l16 + v, c0 * (int)sizeof(T));
 #pragma unroll
-        for (int q = 0; q < MT2; ++q) {
-          const int px = (mg2 * MT2 + q) * 16 + l16, i = px >> 4, j = px & 15;
-          av[q] = ld_frag<T>(reinterpret_cast<const T*>(S1 + ((2 * i + u) * S1_W + 2 * j + v) * S1PB) + c0);
-        }
+        for (int q = 0; q < MT2; ++q) av[q] = ld_frag<T>(reinterpret_cast<const T*>(src + q * 2 * P1::S1RB));
 #pragma unroll
         for (int n = 0; n < NW2; ++n)
 #pragma unroll
@@ -528,11 +540,9 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
             if (t > 8) t = 8;                       // padded k (zero weights) reads a valid tap
             const int u = t / 3, v = t % 3;
             frag av[MT2];
+            const unsigned char* src = S1 + P1::at(2 * mg2 * MT2 + u, 2 * l16 + v, c0 * (int)sizeof(T));
   #pragma unroll
-            for (int q = 0; q < MT2; ++q) {
-              const int px = (mg2 * MT2 + q) * 16 + l16, i = px >> 4, j = px & 15;
-              av[q] = ld_frag<T>(reinterpret_cast<const T*>(S1 + ((2 * i + u) * S1_W + 2 * j + v) * S1PB) + c0);
-            }
+            for (int q = 0; q < MT2; ++q) av[q] = ld_frag<T>(reinterpret_cast<const T*>(src + q * 2 * P1::S1RB));
   #pragma unroll
             for (int n = 0; n < NW2; ++n)
   #pragma unroll
@@ -564,8 +574,7 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
     const float bb0 = b2[ch], bb1v = b2[ch + 1], bb2 = b2[ch + 2], bb3 = b2[ch + 3];
 #pragma unroll
     for (int q = 0; q < MT2; ++q) {
-      const int px = (mg2 * MT2 + q) * 16 + l16, i = px >> 4, j = px & 15;
-      unsigned char* dst = L2 + ((i + 1) * L2_W + (j + 1)) * L2PB;
+      unsigned char* dst = L2 + P2::at(mg2 * MT2 + q + 1, l16 + 1, 0);
       const float v[4] = {fmaxf(acc2[q][n][0] + bb0, 0.f), fmaxf(acc2[q][n][1] + bb1v, 0.f),
                           fmaxf(acc2[q][n][2] + bb2, 0.f), fmaxf(acc2[q][n][3] + bb3, 0.f)};
       if constexpr (PadL2<T, M>::PLANES) store_planes<3>(dst + 2 * ch, 2 * C2, v);
@@ -576,7 +585,7 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
   for (int p = tid; p < (2 * L2_W - 1) * WP2; p += NT) {
     const int qq = p / WP2, c = p % WP2;
     const int y = qq < L2_W ? 0 : qq - L2_W + 1, x = qq < L2_W ? qq : 0;
-    reinterpret_cast<uint4*>(L2 + (y * L2_W + x) * L2PB)[c] = make_uint4(0u, 0u, 0u, 0u);
+    reinterpret_cast<uint4*>(L2 + P2::at(y, x, 0))[c] = make_uint4(0u, 0u, 0u, 0u);
   }
   __syncthreads();
 
@@ -606,11 +615,9 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
     const int t = k0 / C2, c0 = k0 % C2;
     const int u = t / 3, v = t % 3;
     frag av[MT3];
+    const unsigned char* src = L2 + P2::at(4 * mh * MT3 + 2 * (l16 >> 3) + u, 2 * (l16 & 7) + v, c0 * (int)sizeof(T));
 #pragma unroll
-    for (int q = 0; q < MT3; ++q) {
-      const int px = (mh * MT3 + q) * 16 + l16, i = px >> 3, j = px & 7;
-      av[q] = ld_frag<T>(reinterpret_cast<const T*>(L2 + ((2 * i + u) * L2_W + 2 * j + v) * L2PB) + c0);
-    }
+    for (int q = 0; q < MT3; ++q) av[q] = ld_frag<T>(reinterpret_cast<const T*>(src + q * 4 * P2::RB));
 #pragma unroll
     for (int n = 0; n < NW3; ++n)
 #pragma unroll
@@ -653,10 +660,10 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
       const int k0 = ks * 32 + 8 * g;
       const int tp = k0 / C2, c0 = k0 % C2;
       const int u = tp / 3, v = tp % 3;
+      const unsigned char* src0 = L2 + P2::at(4 * mh * MT3 + 2 * (l16 >> 3) + u, 2 * (l16 & 7) + v, 0);
 #pragma unroll
       for (int q = 0; q < MT3; ++q) {
-        const int px = (mh * MT3 + q) * 16 + l16, i = px >> 3, j = px & 7;
-        const unsigned char* src = L2 + ((2 * i + u) * L2_W + 2 * j + v) * L2PB;
+        const unsigned char* src = src0 + q * 4 * P2::RB;
         bf16x8 x[3];
         if constexpr (PadL2<T, M>::PLANES) {
 #pragma unroll
