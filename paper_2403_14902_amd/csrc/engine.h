@@ -29,7 +29,7 @@ struct MlpArgs {
   int part_w[kMaxK];                // hidden units per partial-logit part (half the tile width)
   int tile_cfg[kMaxK];              // GEMM tile configuration (see mlp_tile_bn)
   int64_t part_cap;
-  double* esc_h[kMaxK];             // FP64 tier: partial hidden sums [chunk][esc_cap][hidden]
+  double* esc_h[kMaxK];             // FP64 tier: partial hidden sums [chunk][entry][hidden], 256-long chunks of esc_cap entries
   int esc_cap;
   float* splitk_ws;                 // raw sums of split tiles' parts: split_slots tiles of 128 x 128
   int split_slots;

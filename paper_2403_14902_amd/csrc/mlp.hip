@@ -396,14 +396,29 @@ __global__ __launch_bounds__(256) void mlp_head_kernel(MlpArgs a, Forward f) {
 }
 
 // FP64 tier: frames normalised in fp64 exactly as defined; canonical fp32 weights widened to
-// fp64.  The first esc_cap escalated entries of each predicate are evaluated across many
-// workgroups: work item = (predicate, group of 8 entries, 256 hidden units, 256-long chunk of
-// the input) -> partial hidden sums; a second launch adds the chunks (one workgroup per entry:
-// with one wave, H / 64 x D / 256 dependent loads took up to 0.3 ms of a round), applies ReLU, GEMM2,
-// the margin and the decision.  Entries beyond esc_cap run there, one group per block.
+// fp64.  Escalated entries of each predicate are evaluated across many workgroups: work item =
+// (predicate, group of 8 entries, 256 hidden units, chunk of the input) -> partial hidden sums; a
+// second launch adds the chunks (one workgroup per entry: with one wave, H / 64 x D / 256 dependent
+// loads took up to 0.3 ms of a round), applies ReLU, GEMM2, the margin and the decision.  The partial
+// sums have room for esc_cap entries of 256-long chunks: more entries get longer chunks, down to one
+// chunk an entry; what is still beyond runs in the second launch, one group per block.  1,024 entries
+// of 12,288 inputs and 2,048 hidden units: 50 ms with all but 128 of them in the second launch, 4.4 ms
+// so (11.6 TFLOP/s, LDS reads of the inputs).  Tiles of 16 entries on FP64 matrix instructions take
+// 3.4 ms there but 52 us instead of 35 in a query's rounds of a few entries.
 constexpr int F64_B = 8;
 constexpr int F64_DCH = 256;
 int mlp_f64_chunks(int d_in) { return (d_in + F64_DCH - 1) / F64_DCH; }
+
+// A predicate's share of the layer-parallel part: entries, 256-long units of input a chunk, chunks
+struct F64Split { int ne, len, nch; };
+__device__ inline F64Split mlp_f64_split(int count, int cap, int D) {
+  const int units = (D + F64_DCH - 1) / F64_DCH;
+  if (count <= cap) return {count, 1, units};
+  const int all = cap * units, ne = min(count, all);      // (far below 2^31: 8 H `all` bytes are allocated)
+  const int room = min(all / ne, units);
+  const int len = (units + room - 1) / room;
+  return {ne, len, (units + len - 1) / len};
+}
 
 __device__ inline double frame_norm64_flat(const FrameSrc& fr, uint32_t idx, int64_t d) {
   const int64_t o = (int64_t)idx * fr.elems + d;
@@ -415,33 +430,29 @@ __device__ inline double frame_norm64_flat(const FrameSrc& fr, uint32_t idx, int
 }
 
 __global__ __launch_bounds__(256) void mlp_f64_hidden_kernel(MlpArgs a) {
-  __shared__ double xs[F64_B][256];
+  __shared__ double xs[F64_B][F64_DCH];
   __shared__ uint32_t ents[F64_B];
   const int tid = threadIdx.x;
+  auto items = [&](int i, const F64Split& sp) { return (sp.ne + F64_B - 1) / F64_B * ((a.hidden[i] + 255) / 256) * sp.nch; };
   int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) {
-    const int ne = min(a.q.counts[a.pred[i]], a.esc_cap);
-    total += (ne + F64_B - 1) / F64_B * (a.hidden[i] / 256 + (a.hidden[i] % 256 ? 1 : 0)) *
-             ((a.d_in[i] + F64_DCH - 1) / F64_DCH);
-  }
+  for (int i = 0; i < a.n_preds; ++i) total += items(i, mlp_f64_split(a.q.counts[a.pred[i]], a.esc_cap, a.d_in[i]));
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     int slot = 0, off = t;
+    F64Split sp = {0, 1, 1};
     for (int i = 0; i < a.n_preds; ++i) {
-      const int ne = min(a.q.counts[a.pred[i]], a.esc_cap);
-      const int c = (ne + F64_B - 1) / F64_B * (a.hidden[i] / 256 + (a.hidden[i] % 256 ? 1 : 0)) *
-                    ((a.d_in[i] + F64_DCH - 1) / F64_DCH);
-      if (off < c) { slot = i; break; }
+      sp = mlp_f64_split(a.q.counts[a.pred[i]], a.esc_cap, a.d_in[i]);
+      const int c = items(i, sp);
+      slot = i;
+      if (off < c) break;
       off -= c;
     }
     const int k = a.pred[slot];
     const int D = a.d_in[slot], H = a.hidden[slot];
-    const int ne = min(a.q.counts[k], a.esc_cap);
-    const int nch = (D + F64_DCH - 1) / F64_DCH;
-    const int nhb = H / 256 + (H % 256 ? 1 : 0);
-    const int ch = off % nch;
-    const int hb = (off / nch) % nhb;
-    const int grp = off / (nch * nhb);
-    const int nb = min(F64_B, ne - grp * F64_B);
+    const int nhb = (H + 255) / 256;
+    const int ch = off % sp.nch;
+    const int hb = (off / sp.nch) % nhb;
+    const int grp = off / (sp.nch * nhb);
+    const int nb = min(F64_B, sp.ne - grp * F64_B);
     if (tid < F64_B) ents[tid] = tid < nb ? a.q.entries[(int64_t)k * a.q.cap + grp * F64_B + tid] : 0u;
     __syncthreads();
     const int j = hb * 256 + tid;
@@ -449,11 +460,11 @@ __global__ __launch_bounds__(256) void mlp_f64_hidden_kernel(MlpArgs a) {
 #pragma unroll
     for (int b = 0; b < F64_B; ++b) s[b] = 0.0;
     const float* W1 = a.w1_canon[slot];
-    const int d_lo = ch * F64_DCH, d_hi = min(D, d_lo + F64_DCH);
-    for (int d0 = d_lo; d0 < d_hi; d0 += 256) {
-      const int dl = min(256, d_hi - d0);
-      for (int q = tid; q < F64_B * 256; q += 256) {
-        const int b = q >> 8, dd = q & 255;
+    const int d_lo = ch * sp.len * F64_DCH, d_hi = min(D, d_lo + sp.len * F64_DCH);
+    for (int d0 = d_lo; d0 < d_hi; d0 += F64_DCH) {
+      const int dl = min(F64_DCH, d_hi - d0);
+      for (int q = tid; q < F64_B * F64_DCH; q += 256) {
+        const int b = q / F64_DCH, dd = q % F64_DCH;
         xs[b][dd] = (b < nb && dd < dl) ? frame_norm64_flat(a.fr, entry_idx(ents[b]), d0 + dd) : 0.0;
       }
       __syncthreads();
@@ -468,15 +479,16 @@ __global__ __launch_bounds__(256) void mlp_f64_hidden_kernel(MlpArgs a) {
       __syncthreads();
     }
     if (j < H) {
-      double* hp = a.esc_h[slot] + ((int64_t)ch * a.esc_cap) * H;
+      double* hp = a.esc_h[slot] + (int64_t)ch * sp.ne * H;
       for (int b = 0; b < nb; ++b) hp[(int64_t)(grp * F64_B + b) * H + j] = s[b];
     }
     __syncthreads();
   }
 }
 
-// Decisions of the layer-parallel entries; entries beyond esc_cap: groups of 4 per block, the whole
-// input and hidden width in one block.
+// Decisions of the layer-parallel entries; the entries beyond them: groups of 4 per block, the whole
+// input and hidden width in one block, 256 hidden units at a time (all of them at once, a thread's
+// eight units behind eight branches, waited for every weight by itself).
 constexpr int R64_B = 4;
 constexpr int R64_DCH = 256;
 
@@ -487,16 +499,17 @@ __global__ __launch_bounds__(256) void mlp_f64_entry_kernel(MlpArgs a, Forward f
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // the layer-parallel entries: their hidden units' chunk sums added, ReLU, GEMM2, decision
   int heads = 0;
-  for (int i = 0; i < a.n_preds; ++i) heads += min(a.q.counts[a.pred[i]], a.esc_cap);
+  for (int i = 0; i < a.n_preds; ++i) heads += mlp_f64_split(a.q.counts[a.pred[i]], a.esc_cap, a.d_in[i]).ne;
   for (int t = blockIdx.x; t < heads; t += gridDim.x) {
     int slot = 0, off = t;
+    F64Split sp = {0, 1, 1};
     for (int i = 0; i < a.n_preds; ++i) {
-      const int c = min(a.q.counts[a.pred[i]], a.esc_cap);
-      if (off < c) { slot = i; break; }
-      off -= c;
+      sp = mlp_f64_split(a.q.counts[a.pred[i]], a.esc_cap, a.d_in[i]);
+      slot = i;
+      if (off < sp.ne) break;
+      off -= sp.ne;
     }
-    const int k = a.pred[slot], D = a.d_in[slot], H = a.hidden[slot];
-    const int nch = (D + F64_DCH - 1) / F64_DCH;
+    const int k = a.pred[slot], H = a.hidden[slot];
     double zp[kClasses];
 #pragma unroll
     for (int c = 0; c < kClasses; ++c) zp[c] = 0.0;
@@ -504,7 +517,7 @@ __global__ __launch_bounds__(256) void mlp_f64_entry_kernel(MlpArgs a, Forward f
       double h = (double)a.b1_canon[slot][j];
       const double* hp = a.esc_h[slot] + (int64_t)off * H + j;
 #pragma unroll 16
-      for (int c = 0; c < nch; ++c) h += hp[(int64_t)c * a.esc_cap * H];
+      for (int c = 0; c < sp.nch; ++c) h += hp[(int64_t)c * sp.ne * H];
       h = h > 0.0 ? h : 0.0;
 #pragma unroll
       for (int c = 0; c < kClasses; ++c) zp[c] = fma(h, (double)a.w2[slot][j * kClasses + c], zp[c]);
@@ -531,64 +544,60 @@ __global__ __launch_bounds__(256) void mlp_f64_entry_kernel(MlpArgs a, Forward f
     }
     __syncthreads();
   }
+  auto rest_of = [&](int i) {
+    const int n = a.q.counts[a.pred[i]];
+    return n - mlp_f64_split(n, a.esc_cap, a.d_in[i]).ne;
+  };
   int total = 0;
-  for (int i = 0; i < a.n_preds; ++i) total += (max(0, a.q.counts[a.pred[i]] - a.esc_cap) + R64_B - 1) / R64_B;
+  for (int i = 0; i < a.n_preds; ++i) total += (rest_of(i) + R64_B - 1) / R64_B;
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     int slot = 0, off = t;
     for (int i = 0; i < a.n_preds; ++i) {
-      const int c = (max(0, a.q.counts[a.pred[i]] - a.esc_cap) + R64_B - 1) / R64_B;
+      const int c = (rest_of(i) + R64_B - 1) / R64_B;
       if (off < c) { slot = i; break; }
       off -= c;
     }
     const int k = a.pred[slot];
-    const int rest = a.q.counts[k] - a.esc_cap;
+    const int rest = rest_of(slot);
     const int D = a.d_in[slot], H = a.hidden[slot];
     const int nb = min(R64_B, rest - off * R64_B);
-    if (tid < R64_B) ents[tid] = tid < nb ? a.q.entries[(int64_t)k * a.q.cap + a.esc_cap + off * R64_B + tid] : 0u;
+    if (tid < R64_B)
+      ents[tid] = tid < nb ? a.q.entries[(int64_t)k * a.q.cap + a.q.counts[k] - rest + off * R64_B + tid] : 0u;
     __syncthreads();
-    constexpr int JMAX = 8;            // hidden units per thread (H <= 2048)
-    double s[JMAX][R64_B];
-#pragma unroll
-    for (int j = 0; j < JMAX; ++j)
-#pragma unroll
-      for (int b = 0; b < R64_B; ++b) s[j][b] = 0.0;
-    const float* W1 = a.w1_canon[slot];
-    for (int d0 = 0; d0 < D; d0 += R64_DCH) {
-      for (int q = tid; q < R64_B * R64_DCH; q += blockDim.x) {
-        const int b = q / R64_DCH, dd = q % R64_DCH;
-        xs[b][dd] = (b < nb && d0 + dd < D) ? frame_norm64_flat(a.fr, entry_idx(ents[b]), d0 + dd) : 0.0;
-      }
-      __syncthreads();
-      const int dlim = min(R64_DCH, D - d0);
-      for (int dd = 0; dd < dlim; ++dd) {
-        const float* wr = W1 + (int64_t)(d0 + dd) * H;
-#pragma unroll
-        for (int j = 0; j < JMAX; ++j) {
-          const int col = tid + j * 256;
-          if (col < H) {
-            const double w = (double)wr[col];
-#pragma unroll
-            for (int b = 0; b < R64_B; ++b) s[j][b] = fma(w, xs[b][dd], s[j][b]);
-          }
-        }
-      }
-      __syncthreads();
-    }
     double zp[R64_B][kClasses];
 #pragma unroll
     for (int b = 0; b < R64_B; ++b)
 #pragma unroll
       for (int c = 0; c < kClasses; ++c) zp[b][c] = 0.0;
-    const float* b1 = a.b1_canon[slot];
     const float* w2 = a.w2[slot];
+    for (int j0 = 0; j0 < H; j0 += 256) {
+      const int col = j0 + tid;
+      double s[R64_B];
 #pragma unroll
-    for (int j = 0; j < JMAX; ++j) {
-      const int col = tid + j * 256;
+      for (int b = 0; b < R64_B; ++b) s[b] = 0.0;
+      for (int d0 = 0; d0 < D; d0 += R64_DCH) {
+        for (int q = tid; q < R64_B * R64_DCH; q += blockDim.x) {
+          const int b = q / R64_DCH, dd = q % R64_DCH;
+          xs[b][dd] = (b < nb && d0 + dd < D) ? frame_norm64_flat(a.fr, entry_idx(ents[b]), d0 + dd) : 0.0;
+        }
+        __syncthreads();
+        if (col < H) {
+          const int dlim = min(R64_DCH, D - d0);
+          const float* wr = a.w1_canon[slot] + (int64_t)d0 * H + col;
+#pragma unroll 16
+          for (int dd = 0; dd < dlim; ++dd) {
+            const double w = (double)wr[(int64_t)dd * H];
+#pragma unroll
+            for (int b = 0; b < R64_B; ++b) s[b] = fma(w, xs[b][dd], s[b]);
+          }
+        }
+        __syncthreads();
+      }
       if (col < H) {
-        const double bb = (double)b1[col];
+        const double bb = (double)a.b1_canon[slot][col];
 #pragma unroll
         for (int b = 0; b < R64_B; ++b) {
-          double h = s[j][b] + bb;
+          double h = s[b] + bb;
           h = h > 0.0 ? h : 0.0;
 #pragma unroll
           for (int c = 0; c < kClasses; ++c) zp[b][c] = fma(h, (double)w2[col * kClasses + c], zp[b][c]);

@@ -104,3 +104,24 @@ def test_mlp_whole_and_split_tiles(n, tier):
     err = np.abs(z - z64).max(axis=0)
     log(f"[gpu] mlp {n} rows tier {tier}: max |z - z64| {err.max():.3e}, bound {bound.min():.3e}")
     assert np.all(err <= bound)
+
+
+# both sides sum at most 4,800 and 384 products in FP64, a few 1e-16 relative each (the same tolerance as the
+# other FP64 tier tests)
+@pytest.mark.parametrize("cap", ["2", "128"])
+@pytest.mark.parametrize("hw,n", [(8, 1), (16, 5), (24, 7), (16, 17), (40, 23), (16, 130), (8, 260)])
+def test_f64_tier_splits(monkeypatch, cap, hw, n):
+    """FP64 tier: groups of 8 entries that are not full, whole and cut 256-long parts of the input, two
+    blocks of hidden units with the second half full, and more entries than esc_cap (longer chunks)
+    and than its room (one group per block)."""
+    monkeypatch.setenv("HYDRO_ESC_CAP", cap)
+    d_in, hidden = hw * hw * 3, 384
+    frames = hs.f64_to_bf16_bits(np.random.default_rng(n).random((n, hw, hw, 3)))
+    w = hs.make_model(hs.ModelDesc(arch="mlp", seed=911, d_in=d_in, hidden=hidden))
+    s = hydro.Session([hydro.ModelSpec.from_weights(w, 0b0000011111)], hydro.make_policy("score", precision="bf16"), hw, n)
+    z = s.logits(0, 2, torch.from_numpy(frames).cuda(), "bf16")
+    s.close()
+    z64 = ho.model_logits(w, frames, "bf16")
+    err = np.abs(z - z64).max()
+    log(f"[gpu] FP64 mlp {hw}x{hw}, {n} entries, cap {cap}: max |z - z64| = {err:.3e}")
+    assert err <= 1e-12
