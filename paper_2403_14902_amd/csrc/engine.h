@@ -209,6 +209,8 @@ void gcnn_pack_layer(int layer, int cin, int cout, const float* w, float scale, 
 constexpr int MLP_TILE_CONFIGS = 4;
 int mlp_f64_chunks(int d_in);    // input chunks of the FP64 MLP hidden pass
 void launch_mlp_pass(const MlpArgs& a, const Forward& f, int tier, int grid, hipStream_t s);
+// Slot i's folded weights and biases from its canonical ones.
+void launch_mlp_pack(const MlpArgs& a, int i, double scale, hipStream_t s);
 void launch_mlp_gemm(MlpArgs& b, int cfg, bool bf, hipStream_t s);
 int mlp_tile_bn(int cfg);
 // Copy every per-predicate field of slot i of src into slot j of dst.

@@ -1072,19 +1072,6 @@ static int pack_models(hydro_session* s) {
     }
     if (m.arch == HYDRO_ARCH_MLP) {
       const int D = m.in_h * m.in_w * 3, H = m.hidden;
-      std::vector<float> wt((size_t)H * D), b1f(H);
-      std::vector<uint16_t> wb((size_t)H * D);
-      for (int j = 0; j < H; ++j) {
-        double colsum = 0;
-        for (int d = 0; d < D; ++d) {
-          double w = hm.w1[(size_t)d * H + j];
-          colsum += w;
-          float v = (float)(w * scale);
-          wt[(size_t)j * D + d] = v;
-          wb[(size_t)j * D + d] = f32_to_bf16_bits(v);
-        }
-        b1f[j] = (float)((double)hm.b1[j] - 2.0 * colsum);
-      }
       int i = ma.n_preds++;
       ma.pred[i] = k;
       ma.d_in[i] = D;
@@ -1093,30 +1080,17 @@ static int pack_models(hydro_session* s) {
       int rc;
       float* dp;
       uint16_t* bp;
-      if ((rc = upload(s, wt.data(), wt.size(), &dp))) return rc;
+      // the folded forms are made on the device, from w1_canon (pack_mlp)
+      if ((rc = sess_alloc(s, (void**)&dp, ((size_t)H * D + H) * sizeof(float)))) return rc;
       ma.w1_f32[i] = dp;
-      if ((rc = upload(s, wb.data(), wb.size(), &bp))) return rc;
+      ma.b1_fold[i] = dp + (size_t)H * D;
+      if ((rc = sess_alloc(s, (void**)&bp, (size_t)H * D * sizeof(uint16_t)))) return rc;
       ma.w1_bf[i] = reinterpret_cast<const __bf16*>(bp);
       ma.w1_s3[i] = nullptr;
       if (s->fdtype == HYDRO_DTYPE_BF16 && D % 64 == 0 && H % 128 == 0 && !s->arena) {
-        // FP32 arithmetic on bf16 frames from three bf16 weight terms (see mlp_gemm_s3_kernel):
-        // hi = bf16(w), mid = bf16(w - hi), lo = bf16(w - hi - mid), each difference exact in fp32
-        std::vector<uint16_t> w3((size_t)3 * H * D);
-        for (size_t q = 0; q < (size_t)H * D; ++q) {
-          const float v = wt[q];
-          const uint16_t hi = f32_to_bf16_bits(v);
-          const float r1 = v - bf16_bits_to_f32(hi);
-          const uint16_t mid = f32_to_bf16_bits(r1);
-          const float r2 = r1 - bf16_bits_to_f32(mid);
-          w3[q] = hi;
-          w3[(size_t)H * D + q] = mid;
-          w3[(size_t)2 * H * D + q] = f32_to_bf16_bits(r2);
-        }
-        if ((rc = upload(s, w3.data(), w3.size(), &bp))) return rc;
+        if ((rc = sess_alloc(s, (void**)&bp, (size_t)3 * H * D * sizeof(uint16_t)))) return rc;
         ma.w1_s3[i] = reinterpret_cast<const __bf16*>(bp);
       }
-      if ((rc = upload(s, b1f.data(), b1f.size(), &dp))) return rc;
-      ma.b1_fold[i] = dp;
       if ((rc = upload(s, hm.w2.data(), hm.w2.size(), &dp))) return rc;
       ma.w2[i] = dp;
       if ((rc = upload(s, hm.b2.data(), hm.b2.size(), &dp))) return rc;
@@ -1954,6 +1928,15 @@ static int autotune_mlp(hydro_session* s) {
   return HYDRO_OK;
 }
 
+// The MLP predicates' folded weights, once their uploads are on the device.
+static int pack_mlp(hydro_session* s) {
+  if (s->mlp.n_preds == 0) return HYDRO_OK;
+  for (int i = 0; i < s->mlp.n_preds; ++i) launch_mlp_pack(s->mlp, i, s->fdtype == HYDRO_DTYPE_U8 ? 4.0 / 255.0 : 4.0, s->stream);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  return HYDRO_OK;
+}
+
 static int ensure_dtype(hydro_session* s, int dtype) {
   if (s->fdtype == dtype) return HYDRO_OK;
   if (s->fdtype != -1) return fail(HYDRO_EINVAL, "frame dtype differs from the session's first push");
@@ -1966,6 +1949,7 @@ static int ensure_dtype(hydro_session* s, int dtype) {
   HIP_TRY(hipStreamSynchronize(s->stream));
   int rc = pack_models(s);
   if (!rc) rc = flush_uploads(s);
+  if (!rc) rc = pack_mlp(s);
   s->up_host.clear();
   s->up_dev = nullptr;
   if (!rc && s->pol.autotune) rc = autotune_mlp(s);

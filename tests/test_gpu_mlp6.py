@@ -125,3 +125,22 @@ def test_f64_tier_splits(monkeypatch, cap, hw, n):
     err = np.abs(z - z64).max()
     log(f"[gpu] FP64 mlp {hw}x{hw}, {n} entries, cap {cap}: max |z - z64| = {err:.3e}")
     assert err <= 1e-12
+
+
+# fp32 sums of 192 or 768 products: the tolerance of the other fp32 MLP tests, 3e-5
+@pytest.mark.parametrize("dtype", ["u8", "bf16", "f32"])
+@pytest.mark.parametrize("hw,hidden", [(8, 128), (8, 384), (16, 256)])
+def test_folded_weights(dtype, hw, hidden):
+    """The folded weights and biases that a session makes on the device, in the forms of the tiers and of
+    each frame type's scale."""
+    n = 70
+    cfg = hs.WorkloadConfig(name="t", index=0, n=n, hw=hw, dtype=dtype, data_seed=5, models=[], targets=[(0.5,)])
+    frames = hs.make_frames(cfg, 0, n)
+    w = hs.make_model(hs.ModelDesc(arch="mlp", seed=912, d_in=hw * hw * 3, hidden=hidden))
+    z64 = ho.model_logits(w, frames, dtype)
+    s = hydro.Session([hydro.ModelSpec.from_weights(w, 0b0000011111)], hydro.make_policy("score", precision="bf16"), hw, n)
+    dev = torch.from_numpy(frames).cuda()
+    err = [np.abs(s.logits(0, t, dev, dtype) - z64).max() for t in (0, 1)]
+    s.close()
+    log(f"[gpu] folded weights {hw}x{hw} {dtype} {hidden}: max |z - z64| {err[0]:.3e}, {err[1]:.3e}")
+    assert err[0] <= 0.08 and err[1] <= 3e-5
