@@ -353,7 +353,8 @@ int hydro_session_round_log(const hydro_session* s, int32_t first, int32_t n, hy
  * (0 = the first-pass precision of the session, 1 = FP32, 2 = FP64, 3 = the BF16 re-score tier of
  * an FP8 session or the three-product tier of a rescore3 session; other sessions map 3 to their
  * first pass) and return its logits as
- * fp64 [n][10] in host memory.  Used for logit-error reports and kernel parity tests.  Runs between
+ * fp64 [n][10] in host memory.  Used for logit-error reports and kernel parity tests.  Waits for work
+ * on the default stream, which may be writing the frames (so do the calibration calls).  Runs between
  * queries only: ESTATE while a query is open (a push since the last reset or finish); it leaves
  * the session reset. */
 int hydro_session_logits(hydro_session* s, int32_t pred, int32_t tier, const hydro_frames* frames,

@@ -2521,6 +2521,8 @@ int hydro_session_logits(hydro_session* s, int32_t pred, int32_t tier, const hyd
   int rc = ensure_dtype(s, fr.dtype);
   if (rc) return rc;
   hipStream_t st = s->stream;
+  // work on the default stream may still be writing the frames, and the session's stream does not wait for it
+  HIP_TRY(hipStreamSynchronize(nullptr));
   HIP_TRY(hipStreamSynchronize(st));
   const int t = tier == 0 ? TIER_FIRST : tier == 1 ? TIER_F32 : tier == 2 ? TIER_F64 : TIER_MID;
   // queue of every tuple for this predicate at the chosen tier
