@@ -86,6 +86,8 @@ struct GcnnArgs {
   const __bf16* w_bf[kMaxK][HYDRO_MAX_LAYERS];    // packed fragments, layer 1 folded
   const __bf16* w_ml[kMaxK][HYDRO_MAX_LAYERS];    // fp32 arithmetic: what w_bf leaves of each fp32 weight, as two
                                                   // more bf16 terms (w = w_bf + mid + lo exactly), mid then lo
+  uint32_t wide_w[kMaxK];                         // bit l: layer l has weights that are multiplied in fp32 (gcnn.hip)
+  uint32_t* act_wide;                             // [act_cap] frames whose activations are: byte l for layer l's output
   const float* bias[kMaxK][HYDRO_MAX_LAYERS];
   const float* fc_w[kMaxK];
   const float* fc_b[kMaxK];

@@ -892,6 +892,17 @@ static float bf16_bits_to_f32(uint16_t b) {
   return f;
 }
 
+// v as three bf16 terms, `stride` apart, that add up to it exactly; a value that bf16 would round to
+// infinity starts with the largest finite one, and what is not finite stands in the first term alone.
+static void bf16_terms(float v, uint16_t* t, size_t stride) {
+  for (int i = 0; i < 3; ++i) {
+    uint16_t h = std::isnan(v) ? 0x7FC0 : f32_to_bf16_bits(v);
+    if (std::isfinite(v) && (h & 0x7FFF) == 0x7F80) --h;
+    t[i * stride] = h;
+    v = std::isfinite(v) ? v - bf16_bits_to_f32(h) : 0.f;
+  }
+}
+
 static double model_flops(const hydro_model& m) {
   if (m.arch == HYDRO_ARCH_HOST) {                               // six comparisons per sampled pixel
     const int st = m.color_stride > 1 ? m.color_stride : 1;
@@ -1152,12 +1163,8 @@ static int pack_models(hydro_session* s) {
           gcnn_pack_layer(l, cin, co, hm.cw[l].data(), (float)sc, pf.data());
           std::vector<uint16_t> pb(3 * n);
           for (size_t t = 0; t < n; ++t) {
-            float v = pf[t];
-            for (int term = 0; term < 3; ++term) {
-              const uint16_t h = f32_to_bf16_bits(v);
-              pb[term * n + t] = h;
-              v -= bf16_bits_to_f32(h);
-            }
+            bf16_terms(pf[t], &pb[t], n);
+            if (!(std::fabs(pf[t]) < 1073741824.f)) ga.wide_w[i] |= 1u << l;     // 2^30, or not finite
           }
           if ((rc = upload(s, pb.data(), n, &bp))) return rc;
           ga.w_bf[i][l] = reinterpret_cast<const __bf16*>(bp);
@@ -1266,9 +1273,13 @@ static int pack_models(hydro_session* s) {
       any_c4 = any_c4 || ga.c4[i];
     }
     ga.act_cap = s->act_cap;
-    if (generic)
+    if (generic) {
       for (int b = 0; b < 2; ++b)
         if ((rc = sess_alloc(s, &ga.act[b], (size_t)s->act_cap * mx * sizeof(float)))) return rc;
+      if ((rc = sess_alloc(s, (void**)&ga.act_wide, (size_t)s->act_cap * sizeof(uint32_t)))) return rc;
+      HIP_TRY(hipMemsetAsync(ga.act_wide, 0, (size_t)s->act_cap * sizeof(uint32_t), s->stream));
+      HIP_TRY(hipStreamSynchronize(s->stream));
+    }
     if (any_c4) {
       // dedicated kernels: layer-2 and layer-3 outputs of every evaluation of a launch (sized for
       // the FP32 tier), and the activation maxima of calibration

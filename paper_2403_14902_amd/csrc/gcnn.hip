@@ -9,6 +9,8 @@
 // exact in bf16) with the normalisation folded into its weights and border taps set to the raw
 // value that normalises to zero.  A head launch pools, applies FC and decides.  The FP64 tier
 // is in f64.hip.
+#include <type_traits>
+
 #include "engine.h"
 
 namespace hydro {
@@ -34,9 +36,9 @@ __host__ __device__ inline int g_channel(int cout, int ct, int r) {
   return cout % 32 == 0 ? (ct >> 1) * 32 + 8 * (r >> 2) + 4 * (ct & 1) + (r & 3) : ct * 16 + r;
 }
 
-// Bias, ReLU and store of channels ch .. ch + 3 (o and b: theirs) ...
+// Bias, ReLU and store of channels ch .. ch + 3 (o and b: theirs); returns the largest ...
 template <typename T>
-__device__ inline void store_relu4(T* o, floatx4 v, float4 b) {
+__device__ inline float store_relu4(T* o, floatx4 v, float4 b) {
   const float v0 = fmaxf(v[0] + b.x, 0.f), v1 = fmaxf(v[1] + b.y, 0.f);
   const float v2 = fmaxf(v[2] + b.z, 0.f), v3 = fmaxf(v[3] + b.w, 0.f);
   if constexpr (sizeof(T) == 2) {
@@ -45,40 +47,80 @@ __device__ inline void store_relu4(T* o, floatx4 v, float4 b) {
   } else {
     *reinterpret_cast<float4*>(o) = make_float4(v0, v1, v2, v3);
   }
+  return fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
 }
 // ... or ch .. ch + 7, from the two tiles of a pair.
 template <typename T>
-__device__ inline void store_relu8(T* o, floatx4 v, floatx4 w, const float* b) {
+__device__ inline float store_relu8(T* o, floatx4 v, floatx4 w, const float* b) {
   const float4 b0 = *reinterpret_cast<const float4*>(b), b1 = *reinterpret_cast<const float4*>(b + 4);
   if constexpr (sizeof(T) == 2) {
     alignas(16) __bf16 h[8];
-    store_relu4(h, v, b0);
-    store_relu4(h + 4, w, b1);
+    const float m0 = store_relu4(h, v, b0), m1 = store_relu4(h + 4, w, b1);
     *reinterpret_cast<uint4*>(o) = *reinterpret_cast<const uint4*>(h);
+    return fmaxf(m0, m1);
   } else {
-    store_relu4(o, v, b0);
-    store_relu4(o + 4, w, b1);
+    const float m0 = store_relu4(o, v, b0), m1 = store_relu4(o + 4, w, b1);
+    return fmaxf(m0, m1);
   }
+}
+
+// FP32 arithmetic from bf16 terms holds for finite values: of an infinity the split leaves inf - inf, and
+// products of its terms have either sign.  Values from 2^96 on (raw ones of a frame; an activation leaves a
+// mark with its frame, byte l of act_wide for layer l's output, which the head clears) and layers
+// with a weight from 2^30 on (wide_w) are multiplied in fp32 instead, on the same operands: the weight is the
+// sum of its terms, and fp32 step j takes value j of every lane.
+constexpr float G_WIDE = 7.9228162514264338e28f;      // 2^96
+constexpr uint32_t G_WIDE_BF = 0x6F80;                // its bf16 bits
+__device__ inline bool wide_bf16(bf16x8 x) {
+  u32x4 u;
+  __builtin_memcpy(&u, &x, sizeof(u));
+  uint32_t m = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) m = max(m, max(u[w] >> 16 & 0x7FFFu, u[w] & 0x7FFFu));
+  return m >= G_WIDE_BF;
+}
+__device__ inline float wide_weight(const __bf16* hi, const __bf16* mid, const __bf16* lo) {
+  return ((float)*hi + (float)*mid) + (float)*lo;
+}
+// One channel tile of the first layer in FP32, from the lane's fragments of the weights' terms: every product
+// of a frame value and a term is exact.
+__device__ inline floatx4 mfma_first(const __bf16* hi, const __bf16* mid, const __bf16* lo, bf16x8 x, bool wide) {
+  floatx4 c = (floatx4){0.f, 0.f, 0.f, 0.f};
+  if (wide) {
+    u32x4 u;
+    __builtin_memcpy(&u, &x, sizeof(u));
+#pragma unroll 1
+    for (int j = 0; j < 8; ++j) {       // (rolled: a rare path, which is to cost the others no registers)
+      const uint32_t d = j < 4 ? j < 2 ? u[0] : u[1] : j < 6 ? u[2] : u[3];
+      const float xv = __uint_as_float(j & 1 ? d & 0xFFFF0000u : d << 16);
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(wide_weight(hi + j, mid + j, lo + j), xv, c, 0, 0, 0);
+    }
+    return c;
+  }
+  auto frag = [](const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); };
+  return mfma_bf16(frag(hi), x, mfma_bf16(frag(mid), x, mfma_bf16(frag(lo), x, c)));
+}
+__device__ inline void mark_wide(const GcnnArgs& a, int64_t frame, int layer) {
+  reinterpret_cast<uint8_t*>(a.act_wide)[frame * 4 + layer] = 1;
 }
 
 constexpr int GT_M = 64;     // positions per tile
 constexpr int GT_N = 64;     // channels per tile
 
-// First layer of shapes that gconv_first_kernel does not take, one wave per 16 positions, its gather
-// straight from the frame (any in_hw, any Cout).
-// One channel tile of the first layer: the bf16 weights, or their three terms (every product with a
-// frame value exact), smallest first.
+// One channel tile of the first layer, weights from memory.
 template <typename T>
-__device__ inline floatx4 first_mfma(const GcnnArgs& a, int slot, int tile, int lane, bf16x8 x, floatx4 c) {
+__device__ inline floatx4 first_mfma(const GcnnArgs& a, int slot, int tile, int lane, bf16x8 x, bool wide) {
+  const __bf16* hi = a.w_bf[slot][0] + tile * 512 + lane * 8;
   if constexpr (sizeof(T) == 4) {
     const int64_t n = (int64_t)(a.widths[slot][0] / 16) * 512;       // elements of a term's image
-    const __bf16* lo = a.w_ml[slot][0] + tile * 512 + lane * 8;
-    c = mfma_bf16(*reinterpret_cast<const bf16x8*>(lo + n), x, c);
-    c = mfma_bf16(*reinterpret_cast<const bf16x8*>(lo), x, c);
+    const __bf16* mid = a.w_ml[slot][0] + tile * 512 + lane * 8;
+    return mfma_first(hi, mid, mid + n, x, wide);
   }
-  return mfma_bf16(*reinterpret_cast<const bf16x8*>(a.w_bf[slot][0] + tile * 512 + lane * 8), x, c);
+  return mfma_bf16(*reinterpret_cast<const bf16x8*>(hi), x, (floatx4){0.f, 0.f, 0.f, 0.f});
 }
 
+// First layer of shapes that gconv_first_kernel does not take, one wave per 16 positions, its gather
+// straight from the frame (any in_hw, any Cout).
 template <typename T>
 __global__ __launch_bounds__(256) void gconv_first_any_kernel(GcnnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
@@ -113,8 +155,6 @@ __global__ __launch_bounds__(256) void gconv_first_any_kernel(GcnnArgs a) {
     const int oi = p / hout, oj = p % hout;
     const uint32_t idx = entry_idx(a.q.entries[(int64_t)k * a.q.cap + e]);
     floatx4 acc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = (floatx4){0.f, 0.f, 0.f, 0.f};
     auto raw_at = [&](int u, int v, int c) {
       const int y = 2 * oi + u - 1, x = 2 * oj + v - 1;
       if (y < 0 || x < 0 || y >= hin || x >= hin) return a.pad_raw;
@@ -130,20 +170,27 @@ __global__ __launch_bounds__(256) void gconv_first_any_kernel(GcnnArgs a) {
       t8[q] = static_cast<__bf16>(used && rvalid ? raw_at(u, r / 3, r % 3) : 0.f);
     }
     const bf16x8 av = *reinterpret_cast<const bf16x8*>(t8);
+    const bool wide = sizeof(T) == 4 && ((a.wide_w[slot] & 1u) || __any(wide_bf16(av)));
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (j < ncw) acc[j] = first_mfma<T>(a, slot, ct * 4 + j, lane, av, acc[j]);
+      if (j < ncw) acc[j] = first_mfma<T>(a, slot, ct * 4 + j, lane, av, wide);
     // bias + ReLU -> activations (rows = channels 4g.., column = this lane's position)
     if (rvalid) {
       const float* bias = a.bias[slot][0];
       T* out = reinterpret_cast<T*>(a.act[0]) + ((int64_t)ebase + e) * a.act_stride + (int64_t)p * cout;
+      float top = 0.f;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (j >= ncw) continue;
         const int ch = g_channel(cout, ct * 4 + j, 4 * g);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[ch + r] = static_cast<T>(fmaxf(acc[j][r] + bias[ch + r], 0.f));
+        for (int r = 0; r < 4; ++r) {
+          const float v = fmaxf(acc[j][r] + bias[ch + r], 0.f);
+          out[ch + r] = static_cast<T>(v);
+          top = fmaxf(top, v);
+        }
       }
+      if (sizeof(T) == 4 && top >= G_WIDE) mark_wide(a, (int64_t)ebase + e, 0);
     }
   }
 }
@@ -262,49 +309,82 @@ __global__ __launch_bounds__(256, 2) void gconv_dma_kernel(GcnnArgs a, int layer
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[c][q] = (floatx4){0.f, 0.f, 0.f, 0.f};
     issue(0, 0);
+    // fp32: whether the tile's frames or the layer hold values beyond the split (the same for every wave; read
+    // behind the first block's copies, which are waited for next anyway)
+    bool wide = false;
+    if constexpr (G::F32) {
+#pragma unroll
+      for (int i = 0; i < G::BM / 64; ++i) {
+        const int e = min(e0 + (r0 + i * 64 + lane) / P, cnt - 1);
+        wide = wide || reinterpret_cast<const uint8_t*>(a.act_wide)[((int64_t)ebase + e) * 4 + layer - 1] != 0;
+      }
+      wide = __any(wide) || ((a.wide_w[slot] >> layer) & 1u);
+    }
+    auto k_loop = [&](auto wide_tag) {
+      constexpr bool WIDE = decltype(wide_tag)::value;
 #pragma unroll 1
-    for (int kb = 0; kb < nkb; ++kb) {
-      wait_vmcnt<0>();
-      __syncthreads();                 // block kb has landed; every wave is done with the other buffer
-      if (kb + 1 < nkb) issue(kb + 1, (kb + 1) & 1);
-      const unsigned char* X = lds + (kb & 1) * G::STAGE;
-      const unsigned char* W = X + G::BM * 128;
-      if constexpr (G::F32) {
-        bf16x8 wf[G::CT][3];
+      for (int kb = 0; kb < nkb; ++kb) {
+        wait_vmcnt<0>();
+        __syncthreads();                 // block kb has landed; every wave is done with the other buffer
+        if (kb + 1 < nkb) issue(kb + 1, (kb + 1) & 1);
+        const unsigned char* X = lds + (kb & 1) * G::STAGE;
+        const unsigned char* W = X + G::BM * 128;
+        if constexpr (WIDE) {
+#pragma unroll 1
+          for (int j = 0; j < 8; ++j) {
+            float xv[4];
 #pragma unroll
-        for (int c = 0; c < G::CT; ++c)
+            for (int q = 0; q < 4; ++q) {
+              const int r = wp * 64 + q * 16 + l16;
+              xv[q] = *reinterpret_cast<const float*>(X + r * 128 + ((2 * g + (j >> 2)) ^ (r & 7)) * 16 + (j & 3) * 4);
+            }
 #pragma unroll
-          for (int u = 0; u < 3; ++u)
-            wf[c][u] = *reinterpret_cast<const bf16x8*>(W + (u * G::NCT + wc * G::CT + c) * 1024 + lane * 16);
+            for (int c = 0; c < G::CT; ++c) {
+              const __bf16* w = reinterpret_cast<const __bf16*>(W + (wc * G::CT + c) * 1024 + lane * 16) + j;
+              const float wv = wide_weight(w, w + G::NCT * 512, w + 2 * G::NCT * 512);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = wp * 64 + q * 16 + l16;
-          bf16x8 x[3];
-          split3(*reinterpret_cast<const float4*>(X + r * 128 + ((2 * g) ^ (r & 7)) * 16),
-                 *reinterpret_cast<const float4*>(X + r * 128 + ((2 * g + 1) ^ (r & 7)) * 16), x);
+              for (int q = 0; q < 4; ++q) acc[c][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv, xv[q], acc[c][q], 0, 0, 0);
+            }
+          }
+        } else if constexpr (G::F32) {
+          bf16x8 wf[G::CT][3];
 #pragma unroll
-          for (int c = 0; c < G::CT; ++c) acc[c][q] = mfma_s3(wf[c], x, acc[c][q]);
-        }
-      } else {
+          for (int c = 0; c < G::CT; ++c)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          if (2 * kb + s >= KS) break;   // an odd number of k-steps: the last block holds one
-          bf16x8 xf[4], wf[G::CT];
+            for (int u = 0; u < 3; ++u)
+              wf[c][u] = *reinterpret_cast<const bf16x8*>(W + (u * G::NCT + wc * G::CT + c) * 1024 + lane * 16);
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int r = wp * 64 + q * 16 + l16;
-            xf[q] = *reinterpret_cast<const bf16x8*>(X + r * 128 + ((4 * s + g) ^ (r & 7)) * 16);
+            bf16x8 x[3];
+            split3(*reinterpret_cast<const float4*>(X + r * 128 + ((2 * g) ^ (r & 7)) * 16),
+                   *reinterpret_cast<const float4*>(X + r * 128 + ((2 * g + 1) ^ (r & 7)) * 16), x);
+#pragma unroll
+            for (int c = 0; c < G::CT; ++c) acc[c][q] = mfma_s3(wf[c], x, acc[c][q]);
           }
+        } else {
 #pragma unroll
-          for (int c = 0; c < G::CT; ++c)
-            wf[c] = *reinterpret_cast<const bf16x8*>(W + (s * G::NCT + wc * G::CT + c) * 1024 + lane * 16);
+          for (int s = 0; s < 2; ++s) {
+            if (2 * kb + s >= KS) break;   // an odd number of k-steps: the last block holds one
+            bf16x8 xf[4], wf[G::CT];
 #pragma unroll
-          for (int c = 0; c < G::CT; ++c)
+            for (int q = 0; q < 4; ++q) {
+              const int r = wp * 64 + q * 16 + l16;
+              xf[q] = *reinterpret_cast<const bf16x8*>(X + r * 128 + ((4 * s + g) ^ (r & 7)) * 16);
+            }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[c][q] = mfma_bf16(wf[c], xf[q], acc[c][q]);
+            for (int c = 0; c < G::CT; ++c)
+              wf[c] = *reinterpret_cast<const bf16x8*>(W + (s * G::NCT + wc * G::CT + c) * 1024 + lane * 16);
+#pragma unroll
+            for (int c = 0; c < G::CT; ++c)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) acc[c][q] = mfma_bf16(wf[c], xf[q], acc[c][q]);
+          }
         }
       }
-    }
+    };
+    if (G::F32 && wide) k_loop(std::true_type{});
+    else k_loop(std::false_type{});
     // bias + ReLU; lane holds channels g_channel(4g .. 4g + 3) of tile c for position 16q + l16 of its wave
     // (BN 16: channels that do not come in pairs of tiles)
     constexpr int PER = BN > 16 ? 8 : 4;
@@ -316,13 +396,16 @@ __global__ __launch_bounds__(256, 2) void gconv_dma_kernel(GcnnArgs a, int layer
       const int r = r0 + wp * 64 + q * 16 + l16, e = e0 + r / P, p = r % P;
       if (e >= cnt) continue;
       T* o = out + ((int64_t)ebase + e) * a.act_stride + (int64_t)p * cout + ch0;
+      float top = 0.f;
       if constexpr (BN > 16) {
         static_assert(G::CT % 2 == 0, "pairs of tiles");
 #pragma unroll
-        for (int c = 0; c < G::CT; c += 2) store_relu8(o + c * 16, acc[c][q], acc[c + 1][q], bias + c * 16);
+        for (int c = 0; c < G::CT; c += 2)
+          top = fmaxf(top, store_relu8(o + c * 16, acc[c][q], acc[c + 1][q], bias + c * 16));
       } else {
-        store_relu4(o, acc[0][q], *reinterpret_cast<const float4*>(bias));
+        top = store_relu4(o, acc[0][q], *reinterpret_cast<const float4*>(bias));
       }
+      if (G::F32 && top >= G_WIDE) mark_wide(a, (int64_t)ebase + e, layer);
     }
     __syncthreads();   // the next tile's first block overwrites buffer 0
   }
@@ -462,12 +545,13 @@ __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
     const int hout = 1 << (at.lg - 1), RS = gf_stride(2 << (at.lg - 1));
     T* o0 = reinterpret_cast<T*>(a.act[0]) + ((int64_t)at.ebase + at.e) * a.act_stride + (int64_t)at.oi0 * hout * cout;
     const int np = gf_rows(hout) * hout;            // a multiple of 64
+    bool wide = false;
     auto tile_mfma = [&](int c, bf16x8 x) {
-      const bf16x8* w = reinterpret_cast<const bf16x8*>(w_s) + c * 64 + lane;
-      floatx4 acc = (floatx4){0.f, 0.f, 0.f, 0.f};
-      if constexpr (TERMS == 3) acc = mfma_bf16(w[256], x, mfma_bf16(w[512], x, acc));
-      return mfma_bf16(w[0], x, acc);
+      const __bf16* w = w_s + (c * 64 + lane) * 8;
+      if constexpr (TERMS == 3) return mfma_first(w, w + 2048, w + 4096, x, wide);
+      return mfma_bf16(*reinterpret_cast<const bf16x8*>(w), x, (floatx4){0.f, 0.f, 0.f, 0.f});
     };
+    float top = 0.f;
     for (int pt = wave * 32; pt < np; pt += 128) {
       const uint16_t* base[2];                      // element before the position's first value
 #pragma unroll
@@ -488,6 +572,7 @@ __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
         if (g == 3) f = (u32x4){(d[0] >> 16) | (d[1] & 0xFFFF0000u), d[2] >> 16, 0u, 0u};
         xf[q] = *reinterpret_cast<const bf16x8*>(&f);
       }
+      if constexpr (TERMS == 3) wide = (a.wide_w[slot] & 1u) || (!u8 && __any(wide_bf16(xf[0]) || wide_bf16(xf[1])));
       T* o = o0 + (int64_t)(pt + l16) * cout;
       if (cout % 32 == 0) {
 #pragma unroll
@@ -495,8 +580,8 @@ __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
           if (c >= nct) break;
 #pragma unroll
           for (int q = 0; q < 2; ++q)
-            store_relu8(o + q * 16 * cout + c * 16 + 8 * g, tile_mfma(c, xf[q]), tile_mfma(c + 1, xf[q]),
-                        bias_s + c * 16 + 8 * g);
+            top = fmaxf(top, store_relu8(o + q * 16 * cout + c * 16 + 8 * g, tile_mfma(c, xf[q]), tile_mfma(c + 1, xf[q]),
+                                         bias_s + c * 16 + 8 * g));
         }
       } else {
         // an odd number of tiles: the lane groups of the two position tiles trade places, so that each lane
@@ -516,11 +601,13 @@ __global__ __launch_bounds__(256) void gconv_first_kernel(GcnnArgs a) {
                 make_uint4(lo[0], hi[0], lo[1], hi[1]);
           } else {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) store_relu4(o + q * 16 * cout + c * 16 + 4 * g, tile_mfma(c, xf[q]), b);
+            for (int q = 0; q < 2; ++q)
+              top = fmaxf(top, store_relu4(o + q * 16 * cout + c * 16 + 4 * g, tile_mfma(c, xf[q]), b));
           }
         }
       }
     }
+    if (TERMS == 3 && top >= G_WIDE) mark_wide(a, (int64_t)at.ebase + at.e, 0);
     __syncthreads();   // the next tile restages xin
   }
 }
@@ -555,10 +642,10 @@ __global__ __launch_bounds__(256) void gcnn_head_kernel(GcnnArgs a, Forward f) {
       float zp[kClasses];
 #pragma unroll
       for (int c = 0; c < kClasses; ++c) zp[c] = 0.f;
+      int64_t act_frame = off;
       if (active) {
-        int ebase = 0;
-        for (int i = 0; i < slot; ++i) ebase += a.q.counts[a.pred[i]];
-        const T* act = reinterpret_cast<const T*>(a.act[(L - 1) & 1]) + ((int64_t)ebase + off) * a.act_stride;
+        for (int i = 0; i < slot; ++i) act_frame += a.q.counts[a.pred[i]];
+        const T* act = reinterpret_cast<const T*>(a.act[(L - 1) & 1]) + act_frame * a.act_stride;
         const float* fw = a.fc_w[slot];
         constexpr int VE = 16 / (int)sizeof(T);      // channels per 16-byte load
         const int vpp = cl / VE;                     // loads per position
@@ -616,7 +703,10 @@ __global__ __launch_bounds__(256) void gcnn_head_kernel(GcnnArgs a, Forward f) {
         pass = d > th;
         defer = f.defer.entries != nullptr && fabsf(d - th) < f.tau[k];
       }
-      if (active && lane == 0) decision_set(dec, it * 4 + wave, k, e, defer, pass);
+      if (active && lane == 0) {
+        decision_set(dec, it * 4 + wave, k, e, defer, pass);
+        if (sizeof(T) == 4) a.act_wide[act_frame] = 0u;         // for the next launch
+      }
     }
     if (f.logits == nullptr) {
       if (threadIdx.x == 0) dec.n = min(4 * fpw, total - base);
@@ -656,7 +746,7 @@ void gcnn_copy_slot(GcnnArgs& dst, int j, const GcnnArgs& src, int i) {
   dst.pred[j] = src.pred[i]; dst.n_layers[j] = src.n_layers[i]; dst.in_hw[j] = src.in_hw[i];
   dst.class_mask[j] = src.class_mask[i]; dst.fc_w[j] = src.fc_w[i]; dst.fc_b[j] = src.fc_b[i];
   dst.esc_act[j] = src.esc_act[i]; dst.c4[j] = src.c4[i];
-  dst.c4_w1b[j] = src.c4_w1b[i]; dst.c4_w1f[j] = src.c4_w1f[i];
+  dst.c4_w1b[j] = src.c4_w1b[i]; dst.c4_w1f[j] = src.c4_w1f[i]; dst.wide_w[j] = src.wide_w[i];
   for (int l = 0; l < HYDRO_MAX_LAYERS; ++l) {
     dst.widths[j][l] = src.widths[i][l]; dst.w_bf[j][l] = src.w_bf[i][l]; dst.w_ml[j][l] = src.w_ml[i][l];
     dst.bias[j][l] = src.bias[i][l]; dst.wt_canon[j][l] = src.wt_canon[i][l]; dst.b_canon[j][l] = src.b_canon[i][l];
