@@ -1,0 +1,57 @@
+"""Rounding errors of the FP32 tiers against FP64, over long sums: no larger than those of fp32 arithmetic that
+rounds its sum after every four products, as an fp32 MFMA does (emulated on the CPU)."""
+import numpy as np
+import pytest
+
+import hydro_synth as hs
+from oracle import hydro_oracle as ho
+from tests.gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_2403_14902_amd import hydro  # noqa: E402
+
+MASK = 0b0000011111
+
+
+def _sum4(x, w, start=0):
+    """x @ w, the sum rounded to fp32 after every four products (each product and the four's sum exact)."""
+    acc = np.zeros((x.shape[0], w.shape[1]), dtype=np.float32)
+    x, w = x.astype(np.float64), w.astype(np.float64)
+    for k in range(start, x.shape[1], 4):
+        acc = (acc + x[:, k:k + 4] @ w[k:k + 4]).astype(np.float32)
+    return acc
+
+
+def _columns(x):
+    """[n][h][w][c] padded with zeros -> [n * h/2 * w/2][9 c] of a 3x3 stride-2 convolution, (tap, channel)."""
+    n, h, w, c = x.shape
+    p = np.zeros((n, h + 1, w + 1, c), dtype=x.dtype)
+    p[:, 1:, 1:] = x
+    cols = [p[:, u:u + h - 1:2, v:v + w - 1:2] for u in range(3) for v in range(3)]
+    return np.concatenate([q[:, :h // 2, :w // 2] for q in cols], axis=3).reshape(-1, 9 * c)
+
+
+def _cnn_fp32(weights, frames, dtype):
+    x = ((ho.frames_to_f64(frames, dtype) - 0.5) * 4.0).astype(np.float32)
+    for w, b in weights.tensors["convs"]:
+        n, h = x.shape[0], x.shape[1]
+        wk = np.transpose(w, (2, 3, 1, 0)).reshape(-1, w.shape[0])
+        x = np.maximum(_sum4(_columns(x), wk) + b, np.float32(0)).reshape(n, h // 2, h // 2, -1)
+    return x.astype(np.float64).mean(axis=(1, 2)) @ weights.tensors["Wfc"].astype(np.float64) + weights.tensors["bfc"]
+
+
+@pytest.mark.parametrize("hw,widths", [(16, (1024, 1024)), (16, (256, 512)), (16, (128, 128, 128, 128)), (4, (1024, 16))])
+def test_layerwise_fp32_error(hw, widths):
+    n = 32
+    cfg = hs.WorkloadConfig(name="t", index=0, n=n, hw=hw, dtype="bf16", data_seed=43, models=[], targets=[(0.5,)])
+    frames = hs.make_frames(cfg, 0, n)
+    w = hs.make_model(hs.ModelDesc(arch="cnn", seed=7, in_hw=hw, widths=widths))
+    s = hydro.Session([hydro.ModelSpec.from_weights(w, MASK)], hydro.make_policy("score"), hw, n)
+    z = s.logits(0, 1, torch.from_numpy(frames).cuda(), "bf16")
+    s.close()
+    z64 = ho.model_logits(w, frames, "bf16")
+    got, bound = (np.sqrt(((v - z64) ** 2).mean()) for v in (z, _cnn_fp32(w, frames, "bf16")))
+    log(f"[gpu] layer-wise {hw} {widths}: FP32 rms error {got:.3e}, fp32 sums of four products {bound:.3e}")
+    assert got <= bound
