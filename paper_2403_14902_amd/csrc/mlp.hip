@@ -138,6 +138,7 @@ __device__ inline void mlp_finish(const MlpArgs& a, const MlpUnit& m, floatx4 (&
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) zv[i][r] = 0.f;
+#pragma unroll 1
   for (int c = 0; c < kClasses; ++c) {
     float w2v[NT];
 #pragma unroll
@@ -164,9 +165,11 @@ __device__ inline void mlp_finish(const MlpArgs& a, const MlpUnit& m, floatx4 (&
 }
 
 // Tile shapes (rows of queued tuples x hidden units) an autotuner may pick per predicate.
-// Every launch covers the predicates of one tile shape.
+// Every launch covers the predicates of one tile shape.  The bound on the registers keeps two 128x128
+// workgroups on a CU (left alone, the compiler takes 258 with uint8 frames, which lets in one: 6,000 rows
+// of 12,288 inputs x 2,048 units 1,310 us, so 880), three 128x64 and five 64x64 ones.
 template <typename T, typename In, int BM, int BN>
-__global__ __launch_bounds__(256) void mlp_gemm_kernel(MlpArgs a) {
+__global__ __launch_bounds__(256, BM * BN == 16384 ? 2 : BM * BN == 8192 ? 3 : 5) void mlp_gemm_kernel(MlpArgs a) {
   constexpr int BK = MlpTile<T>::BK, LD = MlpTile<T>::LD;
   // every thread loads one run of each k-tile: 256 / BM threads per gathered frame row (PA
   // elements each) and 256 / BN per weight row (PB elements each)
