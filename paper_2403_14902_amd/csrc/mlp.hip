@@ -240,18 +240,30 @@ __global__ __launch_bounds__(256, BM * BN == 16384 ? 2 : BM * BN == 8192 ? 3 : 5
           for (int j = 0; j < FN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
       } else {
+        // a k-tile's products are summed by themselves and then added, so that the running sum is rounded once a
+        // k-tile (5,000 rows of 3,072 fp32 inputs in four parts: rms error 1.6e-6 with one sum, 0.5e-6 so; in seven
+        // parts 1.2e-6)
+        float af[FM][BK / 4];
 #pragma unroll
-        for (int ks = 0; ks < BK / 4; ++ks) {
-          float af[FM], bfr[FN];
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-          for (int i = 0; i < FM; ++i) af[i] = As[buf][(wm * WM + i * 16 + (lane & 15)) * LD + ks * 4 + (lane >> 4)];
+          for (int ks = 0; ks < BK / 4; ++ks)
+            af[i][ks] = As[buf][(wm * WM + i * 16 + (lane & 15)) * LD + ks * 4 + (lane >> 4)];
 #pragma unroll
-          for (int j = 0; j < FN; ++j) bfr[j] = Bs[buf][(wn * WN + j * 16 + (lane & 15)) * LD + ks * 4 + (lane >> 4)];
+        for (int j = 0; j < FN; ++j) {
+          float bfr[BK / 4];
 #pragma unroll
-          for (int i = 0; i < FM; ++i)
+          for (int ks = 0; ks < BK / 4; ++ks)
+            bfr[ks] = Bs[buf][(wn * WN + j * 16 + (lane & 15)) * LD + ks * 4 + (lane >> 4)];
+          floatx4 t[FM];
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], bfr[j], acc[i][j], 0, 0, 0);
+          for (int i = 0; i < FM; ++i) t[i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < BK / 4; ++ks)
+#pragma unroll
+            for (int i = 0; i < FM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i][ks], bfr[ks], t[i], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < FM; ++i) acc[i][j] += t[i];
         }
       }
     };
@@ -814,9 +826,13 @@ __global__ __launch_bounds__(512) void mlp_gemm_dma_kernel(MlpArgs a) {
 // terms carry all 24 bits of the fp32 significand), so x * w = x * hi + x * mid + x * lo with
 // every product exact (a bf16 x bf16 product fits fp32) and fp32 accumulation: the fp32 GEMM's
 // result up to summation order, from three bf16 MFMAs instead of eight fp32 ones (16x16x32 bf16
-// against 16x16x4 fp32).  128 x 128 tiles, four waves of 64 x 64, k-blocks of 64 elements (the
+// against 16x16x4 fp32).  The hi products are summed apart from the others,
+// which are 2^-8 of them and less, and in runs of M3_RUN k-blocks: few roundings fall on the whole sum, and
+// the error does not hang on how many parts a tile is split in (2,048 rows of 12,288 inputs x 512 units:
+// rms 1.7e-6 with one running sum in four parts, 0.33e-6 so; 0.55e-6 with runs of all three terms).
+// 128 x 128 tiles, four waves of 64 x 64, k-blocks of 64 elements (the
 // frame rows, then the hi, mid and lo weight rows) in a two-stage direct-to-LDS ring.
-constexpr int M3_BM = 128, M3_BN = 128, M3_NS = 2;
+constexpr int M3_BM = 128, M3_BN = 128, M3_NS = 2, M3_RUN = 4;
 __global__ __launch_bounds__(256) void mlp_gemm_s3_kernel(MlpArgs a) {
   constexpr int UPR = 8, ROWB = 128, BKE = 64;
   constexpr int UNITS = (M3_BM + 3 * M3_BN) * UPR;
@@ -863,11 +879,12 @@ __global__ __launch_bounds__(256) void mlp_gemm_s3_kernel(MlpArgs a) {
         lds_dma16(src[i] + (int64_t)kb * BKE, __builtin_amdgcn_readfirstlane(base + (wave + 4 * i) * 1024));
     };
 
-    floatx4 acc[MT][NT];
+    // sum: of the hi products of the runs so far; acc: of the current run's; low: of all mid and lo products
+    floatx4 acc[MT][NT], sum[MT][NT], low[MT][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int j = 0; j < NT; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < NT; ++j) sum[i][j] = low[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
     auto compute = [&](int buf) {
       const unsigned char* F = lds + buf * STAGE;
 #pragma unroll
@@ -891,8 +908,10 @@ __global__ __launch_bounds__(256) void mlp_gemm_s3_kernel(MlpArgs a) {
 #pragma unroll
           for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < NT; ++j) {
+              floatx4& c = term == 0 ? acc[i][j] : low[i][j];
+              c = mfma_bf16(af[i], bfr[j], c);
+            }
         }
       }
     };
@@ -903,14 +922,31 @@ __global__ __launch_bounds__(256) void mlp_gemm_s3_kernel(MlpArgs a) {
     // iteration also retires every wave's reads of the buffer the next copy overwrites
     if (nkb > 0) issue(kt0, 0);
 #pragma unroll 1
-    for (int kb = 0; kb < nkb; ++kb) {
-      wait_vmcnt<0>();
-      __syncthreads();
-      if (kb + 1 < nkb) issue(kt0 + kb + 1, (kb + 1) & 1);
-      compute(kb & 1);
+    for (int k0 = 0; k0 < nkb; k0 += M3_RUN) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < M3_RUN; ++u) {
+        const int kb = k0 + u;
+        if (u > 0 && kb >= nkb) break;
+        wait_vmcnt<0>();
+        __syncthreads();
+        if (kb + 1 < nkb) issue(kt0 + kb + 1, (kb + 1) & 1);
+        compute(kb & 1);
+      }
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) sum[i][j] += acc[i][j];
     }
 
-    mlp_finish<M3_BM, M3_BN, MT, NT>(a, m, acc, wm * WM, wn * WN);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) sum[i][j] += low[i][j];
+    mlp_finish<M3_BM, M3_BN, MT, NT>(a, m, sum, wm * WM, wn * WN);
     __syncthreads();
     if (tid == 0 && a.count_ticks) atomicAdd(&a.st->r_ticks[k], (unsigned long long)(wall_clock64() - t0));
   }

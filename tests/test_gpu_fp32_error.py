@@ -1,5 +1,6 @@
 """Rounding errors of the FP32 tiers against FP64, over long sums: no larger than those of fp32 arithmetic that
-rounds its sum after every four products, as an fp32 MFMA does (emulated on the CPU)."""
+rounds its sum after every four products, as an fp32 MFMA does, or after each of three products of bf16 terms
+(emulated on the CPU), in a given number of parts."""
 import numpy as np
 import pytest
 
@@ -54,4 +55,54 @@ def test_layerwise_fp32_error(hw, widths):
     z64 = ho.model_logits(w, frames, "bf16")
     got, bound = (np.sqrt(((v - z64) ** 2).mean()) for v in (z, _cnn_fp32(w, frames, "bf16")))
     log(f"[gpu] layer-wise {hw} {widths}: FP32 rms error {got:.3e}, fp32 sums of four products {bound:.3e}")
+    assert got <= bound
+
+
+def _bf16(x):
+    u = x.astype(np.float32).view(np.uint32)
+    return ((u + 0x7FFF + ((u >> 16) & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
+
+
+def _sum_terms(x, w):
+    """x @ w from three bf16 terms of w, the sum rounded to fp32 after 32 products of each, smallest first."""
+    hi = _bf16(w)
+    mid = _bf16(w - hi)
+    terms = [t.astype(np.float64) for t in ((w - hi) - mid, mid, hi)]
+    acc = np.zeros((x.shape[0], w.shape[1]), dtype=np.float32)
+    x = x.astype(np.float64)
+    for k in range(0, x.shape[1], 32):
+        for t in terms:
+            acc = (acc + x[:, k:k + 32] @ t[k:k + 32]).astype(np.float32)
+    return acc
+
+
+@pytest.mark.parametrize("hw,hidden,dtype,n,parts,block", [
+    (64, 512, "bf16", 2048, 8, 64),        # three bf16 terms
+    (64, 2048, "bf16", 600, 7, 64),
+    (32, 256, "bf16", 5000, 7, 64),
+    (32, 256, "f32", 5000, 7, 16),         # fp32 MFMAs
+    (64, 2048, "u8", 600, 7, 16),
+])
+def test_mlp_fp32_error(hw, hidden, dtype, n, parts, block):
+    rows, d_in = 64, hw * hw * 3
+    cfg = hs.WorkloadConfig(name="t", index=0, n=n, hw=hw, dtype=dtype, data_seed=44, models=[], targets=[(0.5,)])
+    some = hs.make_frames(cfg, 0, rows)
+    w = hs.make_model(hs.ModelDesc(arch="mlp", seed=5, d_in=d_in, hidden=hidden))
+    frames = torch.from_numpy(some).cuda().repeat(-(-n // rows), 1, 1, 1)[:n].contiguous()
+    s = hydro.Session([hydro.ModelSpec.from_weights(w, MASK)], hydro.make_policy("score"), hw, n)
+    z = s.logits(0, 1, frames, dtype)[:rows]
+    s.close()
+    z64 = ho.model_logits(w, some, dtype)
+    # the folded form: raw values times s W1, the normalisation in the bias
+    scale = 4.0 / 255.0 if dtype == "u8" else 4.0
+    t = {k: v.astype(np.float64) for k, v in w.tensors.items()}
+    wf = (t["W1"] * scale).astype(np.float32)
+    raw = (ho.frames_to_f64(some, dtype) * (255.0 if dtype == "u8" else 1.0)).reshape(rows, -1)
+    cuts = [d_in // block * p // parts * block for p in range(parts + 1)]
+    pre = np.zeros((rows, hidden), dtype=np.float32)
+    for lo, hi in zip(cuts, cuts[1:]):
+        pre += (_sum_terms if block == 64 else _sum4)(raw[:, lo:hi], wf[lo:hi])
+    h = np.maximum(pre + (t["b1"] - 2.0 * t["W1"].sum(axis=0)).astype(np.float32), np.float32(0))
+    got, bound = (np.sqrt(((v - z64) ** 2).mean()) for v in (z, h.astype(np.float64) @ t["W2"] + t["b2"]))
+    log(f"[gpu] MLP {d_in}-{hidden} {dtype}, {n} rows: FP32 rms error {got:.3e}, fp32 sums in {parts} parts {bound:.3e}")
     assert got <= bound
