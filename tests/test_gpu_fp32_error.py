@@ -106,3 +106,29 @@ def test_mlp_fp32_error(hw, hidden, dtype, n, parts, block):
     got, bound = (np.sqrt(((v - z64) ** 2).mean()) for v in (z, h.astype(np.float64) @ t["W2"] + t["b2"]))
     log(f"[gpu] MLP {d_in}-{hidden} {dtype}, {n} rows: FP32 rms error {got:.3e}, fp32 sums in {parts} parts {bound:.3e}")
     assert got <= bound
+
+
+# rms errors over these frames with the taps of layers 3 and 4 in row order and every product added to the running
+# sum, measured: the limits for any other order
+ROW_ORDER_RMS = {"u8": (1.3801e-7, 1.3577e-7, 1.0567e-7, 1.7617e-7),
+                 "bf16": (1.3124e-7, 1.1968e-7, 1.0091e-7, 1.5069e-7)}
+
+
+@pytest.mark.parametrize("dtype", ["u8", "bf16"])
+@pytest.mark.parametrize("model", range(4))
+def test_cnn4_fp32_error(model, dtype):
+    n = 512
+    cfg = hs.workload(5)
+    frames = hs.make_frames(cfg, 0, n)
+    if dtype == "bf16":
+        frames = hs.f64_to_bf16_bits(frames.astype(np.float64) / 255.0)
+    dev = torch.from_numpy(frames.view(np.int16) if dtype == "bf16" else frames).cuda()
+    s = hydro.Session([hydro.ModelSpec.from_weights(hs.make_model(cfg.models[model]), MASK)], hydro.make_policy("score"),
+                      128, n)
+    z64 = s.logits(0, 2, dev, dtype)
+    for part in (n, 100):                   # large tiles, few-frame tiles
+        e = np.sqrt(((s.logits(0, 1, dev[:part], dtype) - z64[:part]) ** 2).mean())
+        log(f"[gpu] 4-layer CNN {model} {dtype}, {part} frames: FP32 rms error {e:.4e}")
+        if part == n:
+            assert e <= ROW_ORDER_RMS[dtype][model]
+    s.close()
