@@ -948,9 +948,14 @@ void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hip
   // runs 8-wave workgroups, one per CU; the two narrower classes 4-wave workgroups, two per CU, so
   // one workgroup's LDS phases overlap the other's matrix phases.  FP32: the layer-1 slab leaves room
   // for one workgroup per CU, of 8 waves (10,007 frames through the classes in turn: 440 / 550 / 1040 us;
-  // one launch for all: 490 / 575 / 1080; 16 waves for the narrower two: 465 / 550, with spills).
+  // one launch for all: 490 / 575 / 1080; 16 waves for the narrower two: 465 / 550, with spills).  Up to 16
+  // frames a workgroup the classes' tails outweigh that, since a shared launch runs them beside each other
+  // (queries over three classes, FP32, shared against per class: 200 frames 305 / 376 us, 1,024 391 / 460,
+  // 4,096 721 / 773 or 747 / 745 in written order, 8,192 1,146 / 1,195 or 1,297 / 1,276).
   const bool bf = a.prec == HYDRO_PREC_BF16;
-  if (tier != TIER_FIRST) {
+  bool mixed = false;
+  for (int i = 1; i < a.n_preds; ++i) mixed = mixed || a.variant[i] != a.variant[0];
+  if (tier != TIER_FIRST || (!bf && mixed && a.most <= (int64_t)16 * grid)) {
     hipLaunchKernelGGL((cnn_fused_kernel<float, 7>), dim3(grid), dim3(NTHR), 0, s, a, f);
     return;
   }

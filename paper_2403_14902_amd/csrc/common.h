@@ -110,6 +110,7 @@ struct FrameSrc {
   int dtype;            // hydro_dtype
   int hw;               // frame side
   int64_t elems;        // elements per frame (hw*hw*3)
+  int64_t n;            // frames
 };
 
 // Device result cache (section 4.3, "Reuse-aware Routing": results of earlier queries reused

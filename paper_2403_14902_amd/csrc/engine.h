@@ -63,6 +63,7 @@ struct CnnArgs {
   int64_t esc_stride;               // doubles per entry: outputs of layers 1 and 3, then layer 2's
   int64_t esc_off;                  // ... which starts here
   int esc_cap;                      // entries handled layer-parallel; the rest run one per block
+  int64_t most;                     // evaluations that a launch may hold
   double* scratch64;                // FP64 tier fallback: per-block activation scratch
   int64_t scratch64_per_block;      // doubles
   int rest_grid;                    // blocks of the FP64 fallback launch (one scratch slot each)

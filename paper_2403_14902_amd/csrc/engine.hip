@@ -1780,6 +1780,7 @@ static void enqueue_tier(hydro_session* s, int tier, const FrameSrc& fr, const F
     a.st = s->st;
     a.count_ticks = 1;
     a.prec = s->pol.precision;
+    a.most = std::min<int64_t>(s->act_cap, fr.n);
     a.feats = tier == TIER_FIRST && s->fused_feats ? router_nn_feats_ptr(s->rnn) : nullptr;
     if (s->pol.grouped || a.n_preds == 1) {
       launch_cnn_pass(a, f, tier, s->n_cu, st);
@@ -1896,7 +1897,7 @@ static int autotune_mlp(hydro_session* s) {
       b.n_preds = 1;
       mlp_copy_slot(b, 0, ma, i);
       b.q = Queues{s->q1, s->st->qcount, s->cap};
-      b.fr = FrameSrc{frames, s->fdtype, s->fh, (int64_t)D};
+      b.fr = FrameSrc{frames, s->fdtype, s->fh, (int64_t)D, Q};
       b.st = s->st;
       b.part_cap = s->cap;
       b.count_ticks = 0;
@@ -2172,6 +2173,7 @@ int hydro_session_push(hydro_session* s, const hydro_frames* frames, const float
   src.dtype = fr.dtype;
   src.hw = fr.h;
   src.elems = (int64_t)fr.h * fr.w * 3;
+  src.n = n;
   if (fr.where == HYDRO_MEM_DEVICE) {
     src.base = fr.data;
   } else {
@@ -2549,7 +2551,7 @@ int hydro_session_logits(hydro_session* s, int32_t pred, int32_t tier, const hyd
   } else {
     HIP_TRY(hipMalloc(&dlog, fr.n * kClasses * sizeof(double)));
   }
-  FrameSrc src{fr.data, fr.dtype, fr.h, (int64_t)fr.h * fr.w * 3};
+  FrameSrc src{fr.data, fr.dtype, fr.h, (int64_t)fr.h * fr.w * 3, fr.n};
   Forward f = make_forward(s, t, 0, src, 1, 1, 0);
   f.logits = dlog;
   f.cache = ResultCache{};
