@@ -13,7 +13,6 @@
 // output per thread.  Query 13.85 -> 2.84 ms.  (Looking the next item up during the current one,
 // forwarding decisions in batches, or requesting blocks ahead of their MFMAs changed nothing.)
 #include "conv64.h"
-#include "engine.h"
 
 namespace hydro {
 
@@ -78,17 +77,21 @@ __device__ inline const double* crop_layers(const CropArgs& a, int slot, const I
   for (int l = 0; l < nl; ++l) {
     L.w = a.wt[slot][l];
     L.bias = a.bias[slot][l];
-    L.cout = crop_pad(a.widths[slot][l]);
+    const int width = a.widths[slot][l];
+    L.cout = crop_pad(width);
+    L.cstore = crop_store(width);
     L.ho = (L.hin + 1) / 2;
     L.wo = (L.win + 1) / 2;
     L.last = l == nl - 1;
     double* out = buf + ((l & 1) ? off : 0);
-    if (l == 0) conv64_wg<true>(L, im, nullptr, out, wave, kCropThreads / 64);
-    else conv64_wg<false>(L, im, buf + ((l & 1) ? 0 : off), out, wave, kCropThreads / 64);
+    const double* in = buf + ((l & 1) ? 0 : off);
+    if (l == 0) conv64_wg<CONV64_FIRST>(L, im, nullptr, out, wave, kCropThreads / 64);
+    else if (L.cin < 16) conv64_wg<CONV64_NARROW>(L, im, in, out, wave, kCropThreads / 64);
+    else conv64_wg<CONV64_WIDE>(L, im, in, out, wave, kCropThreads / 64);
     __syncthreads();
     L.hin = L.ho;
     L.win = L.wo;
-    L.cin = L.cout;
+    L.cin = width < 16 ? width : L.cout;
   }
   return buf + (((nl - 1) & 1) ? off : 0);
 }
@@ -129,17 +132,17 @@ __global__ __launch_bounds__(kCropThreads, 4) void k_crop_cnn(CropArgs a, Forwar
     for (int l = 0; l < a.n_layers[slot]; ++l) {
       hl = (hl + 1) / 2;
       wl = (wl + 1) / 2;
-      const int n = (int)conv64_doubles(hl, wl, crop_pad(a.widths[slot][l]), l == a.n_layers[slot] - 1);
+      const int n = (int)conv64_doubles(hl, wl, crop_store(a.widths[slot][l]), l == a.n_layers[slot] - 1);
       if (l & 1) need1 = max(need1, n);
       else need0 = max(need0, n);
     }
     const int C = a.widths[slot][a.n_layers[slot] - 1];
     if (need0 + need1 <= kCropLds) {
       const double* act = crop_layers(a, slot, im, box.z, box.w, act_s, need0, wave);
-      head64_wg<kCropThreads>(act, hl * wl, C, crop_pad(C), a.fc_w[slot], a.fc_b[slot], part, g_s, z_s);
+      head64_wg<kCropThreads>(act, hl * wl, C, crop_store(C), a.fc_w[slot], a.fc_b[slot], part, g_s, z_s);
     } else {
       const double* act = crop_layers(a, slot, im, box.z, box.w, buf, a.act_doubles, wave);
-      head64_wg<kCropThreads>(act, hl * wl, C, crop_pad(C), a.fc_w[slot], a.fc_b[slot], part, g_s, z_s);
+      head64_wg<kCropThreads>(act, hl * wl, C, crop_store(C), a.fc_w[slot], a.fc_b[slot], part, g_s, z_s);
     }
     if (tid < kWave) {
       const double d = class_margin(z_s, a.class_mask[slot]);

@@ -131,8 +131,8 @@ struct CropArgs {
   uint32_t class_mask[kMaxK];
   int n_layers[kMaxK];
   int widths[kMaxK][HYDRO_MAX_LAYERS];
-  // fp32 weights [co][3][3][ci] and biases, channel counts padded (crop_pad) with zeros: a padded
-  // channel's activation is zero and its weights are, so the sums are the layer's own
+  // fp32 weights as conv64_pack leaves them, biases padded (crop_pad) with zeros: a padded channel's
+  // activation is zero and its weights are, so the sums are the layer's own
   const float* wt[kMaxK][HYDRO_MAX_LAYERS];
   const float* bias[kMaxK][HYDRO_MAX_LAYERS];
   const float* fc_w[kMaxK];                    // [c_last][10]
@@ -178,7 +178,12 @@ std::vector<float> conv64_pack(const float* w, int cin, int cout, bool first);
 __host__ __device__ inline int64_t conv64_doubles(int h, int w, int channels, bool last) {
   return (int64_t)h * (last ? w : (w + 1) & ~1) * channels;
 }
+// MFMA steps of a layer whose (tap, channel) products are packed one after the other, four at a time (the
+// first layer: 7 of 8)
+__host__ __device__ inline int conv64_narrow_steps(int cin) { return (9 * cin + 15) / 16 * 4; }
 __host__ __device__ inline int crop_pad(int c) { return (c + 15) & ~15; }   // channels of an MFMA tile
+// Channels that are stored of c: whole pairs, from 16 on whole tiles, as the next layer reads them.
+__host__ __device__ inline int crop_store(int c) { return c < 16 ? (c + 1) & ~1 : crop_pad(c); }
 void launch_crop_pass(const CropArgs& a, const Forward& f, int grid, hipStream_t s);
 
 // Arithmetic tiers of the dedicated 4-layer CNN kernels.

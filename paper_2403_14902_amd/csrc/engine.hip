@@ -1571,21 +1571,22 @@ static int session_create(const hydro_model* models, int32_t k, const hydro_poli
       for (int l = 0; l < m.n_layers; ++l) {
         h = (h + 1) / 2;
         w = (w + 1) / 2;
-        const int co = m.widths[l], cip = l == 0 ? 3 : crop_pad(cin);
-        act = std::max<int64_t>(act, conv64_doubles(h, w, crop_pad(co), l == m.n_layers - 1));
+        const int co = m.widths[l];
+        act = std::max<int64_t>(act, conv64_doubles(h, w, crop_store(co), l == m.n_layers - 1));
         act_raw = std::max<int64_t>(act_raw, (int64_t)h * w * co);
-        w_pad += (int64_t)crop_pad(co) * ((l == 0 ? 32 : 9 * cip) + 1) - (int64_t)co * (9 * cin + 1);
+        w_pad += (int64_t)crop_pad(co) * ((cin < 16 ? 4 * conv64_narrow_steps(cin) : 9 * crop_pad(cin)) + 1) -
+                 (int64_t)co * (9 * cin + 1);
         cin = co;
       }
     }
-    // four workgroups per CU, as many as the LDS of k_crop_cnn lets in
+    // four workgroups per CU, as many as the LDS of k_crop_cnn lets in; fewer where the padding of channels
+    // would take more memory than the unpadded activations: of the allocation-free array any, of the GPU's
+    // more than 1 GiB (a session of 17 channels on large frames is not to be refused for 15 more)
     s->crop_grid = s->n_cu * 4;
     const int64_t act_pad = (act + 31) / 32 * 32;
-    if (s->arena) {
-      // padded channels take no more of the array than the unpadded ones would: fewer workgroups
-      const int64_t budget = (int64_t)s->n_cu * 4 * 2 * ((act_raw + 31) / 32 * 32) * 8 - w_pad * 4 - 8192;
-      s->crop_grid = (int)std::max<int64_t>(1, std::min<int64_t>(s->crop_grid, budget / (2 * act_pad * 8)));
-    }
+    int64_t room = (int64_t)s->n_cu * 4 * 2 * ((act_raw + 31) / 32 * 32) * 8;
+    room = s->arena ? room - w_pad * 4 - 8192 : std::max<int64_t>(room, (int64_t)1 << 30);
+    s->crop_grid = (int)std::max<int64_t>(1, std::min<int64_t>(s->crop_grid, room / (2 * act_pad * 8)));
     CropArgs& ca = s->crop;
     ca.act_doubles = act_pad;
     ca.fh = frame_h;

@@ -16,7 +16,6 @@
 // way is 3.0 ms of a one-shot query of 2,048 frames; with one scalar product chain per thread it was
 // 118 of 139 ms.
 #include "conv64.h"
-#include "engine.h"
 
 namespace hydro {
 
@@ -28,7 +27,7 @@ __device__ inline Conv64 f64_layer(const F64Args& a, int slot, int l) {
   L.w = a.wt[slot][l];
   L.bias = a.bias[slot][l];
   L.cin = l == 0 ? 3 : a.widths[slot][l - 1];
-  L.cout = a.widths[slot][l];
+  L.cout = L.cstore = a.widths[slot][l];
   L.hin = L.win = a.in_hw[slot] >> l;
   L.ho = L.wo = L.hin >> 1;
   L.last = l == a.n_layers[slot] - 1;
@@ -69,13 +68,13 @@ __global__ __launch_bounds__(F64_LAYER_THREADS) void f64_layer_kernel(F64Args a,
     if (layer == 0) {
       const uint32_t idx = entry_idx(a.q.entries[(int64_t)a.pred[slot] * a.q.cap + e]);
       const int p0 = (pu * 4 + wave) * 16;
-      conv64_acc<true, 1>(L, image64(a.fr, idx, L.win, 0, 0), nullptr, p0, o0, 0, 1, acc);
+      conv64_acc<CONV64_FIRST, 1>(L, image64(a.fr, idx, L.win, 0, 0), nullptr, p0, o0, 0, 1, acc);
       conv64_store<1>(L, acc, out, p0, o0);
       continue;
     }
     const double* in = act + ((layer & 1) ? 0 : a.esc_off);
-    const int nb = conv64_blocks(L, false), p0 = pu * 16;
-    conv64_acc<false, 1>(L, Image64{}, in, p0, o0, nb * wave / 4, nb * (wave + 1) / 4, acc);
+    const int nb = conv64_blocks(L, CONV64_WIDE), p0 = pu * 16;
+    conv64_acc<CONV64_WIDE, 1>(L, Image64{}, in, p0, o0, nb * wave / 4, nb * (wave + 1) / 4, acc);
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[0][r];
     __syncthreads();
@@ -114,8 +113,8 @@ __global__ __launch_bounds__(F64_WG_THREADS) void f64_entry_kernel(F64Args a, Fo
         const Conv64 L = f64_layer(a, slot, l);
         double* out = buf + ((l & 1) ? a.scratch_off : 0);
         const double* in = buf + ((l & 1) ? 0 : a.scratch_off);
-        if (l == 0) conv64_wg<true>(L, image64(a.fr, idx, L.win, 0, 0), nullptr, out, wave, F64_WG_THREADS / 64);
-        else conv64_wg<false>(L, Image64{}, in, out, wave, F64_WG_THREADS / 64);
+        if (l == 0) conv64_wg<CONV64_FIRST>(L, image64(a.fr, idx, L.win, 0, 0), nullptr, out, wave, F64_WG_THREADS / 64);
+        else conv64_wg<CONV64_WIDE>(L, Image64{}, in, out, wave, F64_WG_THREADS / 64);
         __syncthreads();
       }
       act = buf + (((nl - 1) & 1) ? a.scratch_off : 0);
@@ -137,11 +136,12 @@ __global__ __launch_bounds__(F64_WG_THREADS) void f64_entry_kernel(F64Args a, Fo
 }
 
 // Per 16 output channels, 16-channel block of the sum (tap outermost) and lane (g, l16): channels
-// 4g..4g+3 of weight row 4 (l16 % 4) + l16 / 4.  First layer, per 16 output channels and lane: products
-// 4q + g of the 27 (tap, channel), q = 0..7.
+// 4g..4g+3 of weight row 4 (l16 % 4) + l16 / 4.  First layer, and layers of fewer than 16 input channels, per 16
+// output channels and lane: products 4q + g of the (tap, channel)s, q = 0, 1, ....
 std::vector<float> conv64_pack(const float* w, int cin, int cout, bool first) {
-  const int cip = first ? cin : crop_pad(cin), ct = crop_pad(cout) / 16;
-  const int nc = cip / 16, nb = first ? 1 : 9 * nc, per = first ? 8 : 4;
+  const bool dense = first || cin < 16;
+  const int ct = crop_pad(cout) / 16, nc = crop_pad(cin) / 16;
+  const int nb = dense ? 1 : 9 * nc, per = dense ? conv64_narrow_steps(cin) : 4;
   std::vector<float> out((size_t)ct * nb * 64 * per, 0.f);
   float* d = out.data();
   for (int c = 0; c < ct; ++c)
@@ -150,8 +150,8 @@ std::vector<float> conv64_pack(const float* w, int cin, int cout, bool first) {
         const int g = lane >> 4, l16 = lane & 15, o = c * 16 + 4 * (l16 & 3) + (l16 >> 2);
         if (o >= cout) continue;
         for (int q = 0; q < per; ++q) {
-          const int k = 4 * q + g;                                 // first layer
-          const int t = first ? k / 3 : b / nc, ch = first ? k % 3 : b % nc * 16 + 4 * g + q;
+          const int k = 4 * q + g;                                 // dense
+          const int t = dense ? k / cin : b / nc, ch = dense ? k % cin : b % nc * 16 + 4 * g + q;
           if (t < 9 && ch < cin) d[q] = w[((size_t)o * cin + ch) * 9 + t];
         }
       }
