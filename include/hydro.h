@@ -293,7 +293,7 @@ int hydro_query(const hydro_frames* frames, const hydro_model* models, int32_t k
  * any device allocation.  Every device buffer of the query (packed weights, queues, live lists,
  * statistics, result bitmap and ids, FP64-tier activations, learned-router state) is carved from
  * one library-owned device array of HYDRO_NOALLOC_BYTES bytes, one per GPU, held until the
- * process ends.  No stream, event or graph is created.  Differences from hydro_query:
+ * process ends (with 8 MiB behind it for what layer-wise CNNs pad).  No stream, event or graph is created.  Differences from hydro_query:
  *   - frames must be in device memory (EUNSUPPORTED otherwise);
  *   - policy.use_graph, policy.autotune and policy.time_kernels must be 0 (EUNSUPPORTED);
  *   - the work runs on policy.stream, or on the null stream when that is NULL;

@@ -76,9 +76,11 @@ static hipError_t dev_alloc(void** p, size_t bytes) {
 // until the process ends.  In host code `scratch` is only a stand-in for the symbol: its device
 // address (per device) comes from hipGetSymbolAddress and is the only form passed to kernels and
 // copies.
-// (2 MiB beyond the stated size: the layer-wise CNNs' weight images, padded to whole MFMA steps, take
-// up to 64 KB a layer more than unpadded ones, and must not take it from a query's buffers.)
-constexpr size_t kArenaBytes = HYDRO_NOALLOC_BYTES + ((size_t)2 << 20);
+// A query's limit is the stated size.  Layer-wise CNNs may take kArenaPad more, what padding their first
+// layer to whole MFMA steps and a mark per frame take (pack_models adds it up), so that this takes
+// nothing from a query's buffers.
+constexpr size_t kArenaPad = (size_t)8 << 20;
+constexpr size_t kArenaBytes = HYDRO_NOALLOC_BYTES + kArenaPad;
 static __device__ __align__(256) unsigned char scratch[kArenaBytes];
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -831,7 +833,7 @@ static int sess_alloc(hydro_session* s, void** p, size_t bytes) {
     if (bytes == 0) bytes = 16;
     if (off > s->arena_cap || bytes > s->arena_cap - off) {
       *p = nullptr;
-      return fail(HYDRO_ECAPACITY, "the query needs more than the " + std::to_string(s->arena_cap) +
+      return fail(HYDRO_ECAPACITY, "the query needs more than the " + std::to_string(HYDRO_NOALLOC_BYTES) +
                                        " bytes of the allocation-free device arena");
     }
     *p = s->arena + off;
@@ -1024,6 +1026,11 @@ static int pack_c4(hydro_session* s, const HostModel& hm, float scale1, int i) {
   return HYDRO_OK;
 }
 
+// Bytes of an allocation-free session that do not count towards its limit (of kArenaPad in all).
+static void arena_pad(hydro_session* s, size_t bytes) {
+  if (s->arena) s->arena_cap = std::min(s->arena_cap + bytes, kArenaBytes);
+}
+
 static int pack_models(hydro_session* s) {
   const double scale = s->fdtype == HYDRO_DTYPE_U8 ? 4.0 / 255.0 : 4.0;
   const float pad_raw = s->fdtype == HYDRO_DTYPE_U8 ? 127.5f : 0.5f;
@@ -1159,6 +1166,7 @@ static int pack_models(hydro_session* s) {
         uint16_t* bp;
         {
           const size_t n = gcnn_packed_elems(l, cin, co);
+          arena_pad(s, (n - (size_t)(l == 0 ? 28 : 9 * cin) * co) * 4 + (l == 0 ? (size_t)co * 5 * 4 : 0));
           std::vector<float> pf(n);
           gcnn_pack_layer(l, cin, co, hm.cw[l].data(), (float)sc, pf.data());
           std::vector<uint16_t> pb(3 * n);
@@ -1276,6 +1284,7 @@ static int pack_models(hydro_session* s) {
     if (generic) {
       for (int b = 0; b < 2; ++b)
         if ((rc = sess_alloc(s, &ga.act[b], (size_t)s->act_cap * mx * sizeof(float)))) return rc;
+      arena_pad(s, (size_t)s->act_cap * sizeof(uint32_t) + 256);
       if ((rc = sess_alloc(s, (void**)&ga.act_wide, (size_t)s->act_cap * sizeof(uint32_t)))) return rc;
       HIP_TRY(hipMemsetAsync(ga.act_wide, 0, (size_t)s->act_cap * sizeof(uint32_t), s->stream));
       HIP_TRY(hipStreamSynchronize(s->stream));
@@ -2815,7 +2824,7 @@ int hydro_query_noalloc(const hydro_frames* frames, const hydro_model* models, i
   if (rc) return rc;
   hydro_session* s = nullptr;
   rc = session_create(models, k, policy, frames->h, frames->w, std::max<int64_t>(1, frames->n), arena,
-                      kArenaBytes, &s);
+                      HYDRO_NOALLOC_BYTES, &s);
   if (rc) return rc;
   rc = hydro_session_push(s, frames, thresholds, n_seg, seg_len);
   if (!rc) rc = finish_query(s, nullptr, out_ids, out_cap, out_n, out_stats);
