@@ -896,13 +896,19 @@ static float bf16_bits_to_f32(uint16_t b) {
 
 // v as three bf16 terms, `stride` apart, that add up to it exactly; a value that bf16 would round to
 // infinity starts with the largest finite one, and what is not finite stands in the first term alone.
-static void bf16_terms(float v, uint16_t* t, size_t stride) {
-  for (int i = 0; i < 3; ++i) {
-    uint16_t h = std::isnan(v) ? 0x7FC0 : f32_to_bf16_bits(v);
-    if (std::isfinite(v) && (h & 0x7FFF) == 0x7F80) --h;
-    t[i * stride] = h;
-    v = std::isfinite(v) ? v - bf16_bits_to_f32(h) : 0.f;
+static inline void bf16_terms(float v, uint16_t* t, size_t stride) {
+  uint32_t u;
+  memcpy(&u, &v, 4);
+  if ((u & 0x7FFFFFFFu) >= 0x7F7F8000u) {
+    const bool finite = (u & 0x7F800000u) != 0x7F800000u;
+    t[0] = finite ? (uint16_t)((u >> 31) << 15 | 0x7F7F) : std::isnan(v) ? 0x7FC0 : (uint16_t)(u >> 16);
+    v = finite ? v - bf16_bits_to_f32(t[0]) : 0.f;
+  } else {
+    t[0] = f32_to_bf16_bits(v);
+    v -= bf16_bits_to_f32(t[0]);
   }
+  t[stride] = f32_to_bf16_bits(v);
+  t[2 * stride] = f32_to_bf16_bits(v - bf16_bits_to_f32(t[stride]));
 }
 
 static double model_flops(const hydro_model& m) {
@@ -1170,10 +1176,12 @@ static int pack_models(hydro_session* s) {
           std::vector<float> pf(n);
           gcnn_pack_layer(l, cin, co, hm.cw[l].data(), (float)sc, pf.data());
           std::vector<uint16_t> pb(3 * n);
+          float top = 0.f;                       // (a NaN stays out of the comparison: its sum is one in any arithmetic)
           for (size_t t = 0; t < n; ++t) {
             bf16_terms(pf[t], &pb[t], n);
-            if (!(std::fabs(pf[t]) < 1073741824.f)) ga.wide_w[i] |= 1u << l;     // 2^30, or not finite
+            top = std::max(top, std::fabs(pf[t]));
           }
+          if (top >= 1073741824.f) ga.wide_w[i] |= 1u << l;     // 2^30
           if ((rc = upload(s, pb.data(), n, &bp))) return rc;
           ga.w_bf[i][l] = reinterpret_cast<const __bf16*>(bp);
           if ((rc = upload(s, pb.data() + n, 2 * n, &bp))) return rc;

@@ -15,6 +15,8 @@
 // activations, whose loads took the address units longer than the MFMAs.  Calibrating three CNNs this
 // way is 3.0 ms of a one-shot query of 2,048 frames; with one scalar product chain per thread it was
 // 118 of 139 ms.
+#include <algorithm>
+
 #include "conv64.h"
 
 namespace hydro {
@@ -143,18 +145,34 @@ std::vector<float> conv64_pack(const float* w, int cin, int cout, bool first) {
   const int ct = crop_pad(cout) / 16, nc = crop_pad(cin) / 16;
   const int nb = dense ? 1 : 9 * nc, per = dense ? conv64_narrow_steps(cin) : 4;
   std::vector<float> out((size_t)ct * nb * 64 * per, 0.f);
-  float* d = out.data();
-  for (int c = 0; c < ct; ++c)
-    for (int b = 0; b < nb; ++b)
-      for (int lane = 0; lane < 64; ++lane, d += per) {
-        const int g = lane >> 4, l16 = lane & 15, o = c * 16 + 4 * (l16 & 3) + (l16 >> 2);
-        if (o >= cout) continue;
-        for (int q = 0; q < per; ++q) {
-          const int k = 4 * q + g;                                 // dense
-          const int t = dense ? k / cin : b / nc, ch = dense ? k % cin : b % nc * 16 + 4 * g + q;
-          if (t < 9 && ch < cin) d[q] = w[((size_t)o * cin + ch) * 9 + t];
+  // weight row of lane l16 in channel tile c: [channel][tap] (nullptr: a padded one)
+  auto row = [&](int c, int l16) {
+    const int o = c * 16 + 4 * (l16 & 3) + (l16 >> 2);
+    return o < cout ? w + (size_t)o * cin * 9 : nullptr;
+  };
+  for (int c = 0; c < ct; ++c) {
+    float* d = out.data() + (size_t)c * nb * 64 * per;
+    if (dense) {
+      for (int l16 = 0; l16 < 16; ++l16)
+        if (const float* r = row(c, l16))
+          for (int t = 0, k = 0; t < 9; ++t)
+            for (int ch = 0; ch < cin; ++ch, ++k) d[((k & 3) * 16 + l16) * per + (k >> 2)] = r[ch * 9 + t];
+      continue;
+    }
+    const float* rows[16];
+    for (int l16 = 0; l16 < 16; ++l16) rows[l16] = row(c, l16);
+    for (int t = 0; t < 9; ++t)
+      for (int c0 = 0; c0 < cin; c0 += 4) {
+        float* e = d + ((size_t)(t * nc + (c0 >> 4)) * 64 + (c0 >> 2 & 3) * 16) * 4;
+        if (c0 + 4 <= cin && rows[15] != nullptr) {          // (the rows of a tile that is not full end with the last)
+          for (int l16 = 0; l16 < 16; ++l16, e += 4)
+            for (int q = 0; q < 4; ++q) e[q] = rows[l16][(c0 + q) * 9 + t];
+          continue;
         }
+        for (int l16 = 0; l16 < 16; ++l16, e += 4)
+          for (int q = 0; rows[l16] != nullptr && q < std::min(4, cin - c0); ++q) e[q] = rows[l16][(c0 + q) * 9 + t];
       }
+  }
   return out;
 }
 

@@ -9,6 +9,7 @@
 // exact in bf16) with the normalisation folded into its weights and border taps set to the raw
 // value that normalises to zero.  A head launch pools, applies FC and decides.  The FP64 tier
 // is in f64.hip.
+#include <algorithm>
 #include <type_traits>
 
 #include "engine.h"
@@ -723,25 +724,31 @@ void launch_gcnn_layerwise(const GcnnArgs& a, const Forward& f, int tier, int gr
 // ---------------------------------------------------------------- host side
 size_t gcnn_packed_elems(int layer, int cin, int cout) { return (size_t)g_ksteps(layer, cin) * (cout / 16) * 512; }
 
-// [kstep][channel tile of 16][64 lanes][8]; lane l: output channel tile*16 + l%16, k = 32 kstep + 8 (l/16) + e.
+// [kstep][channel tile of 16][64 lanes][8]; lane l: row l % 16 of the tile (g_channel), k = 32 kstep + 8 (l/16) + e.
+// Weights are read eight channels of a tap at a time, 16 rows beside each other (element by element, with the
+// indices divided out of each place, a 1,024-channel layer took twice as long).
 void gcnn_pack_layer(int layer, int cin, int cout, const float* w, float scale, float* out) {
-  size_t o = 0;
-  for (int ks = 0; ks < g_ksteps(layer, cin); ++ks)
-    for (int ct = 0; ct < cout / 16; ++ct)
-      for (int lane = 0; lane < 64; ++lane)
-        for (int e = 0; e < 8; ++e) {
-          const int k = ks * 32 + 8 * (lane >> 4) + e;
-          const int oc = g_channel(cout, ct, lane & 15);
-          int tap = k / cin, ic = k % cin;
-          bool used = tap < 9;
-          if (layer == 0) {
-            int u, r;
-            used = g_first_k(k, &u, &r);
-            tap = u * 3 + r / 3;
-            ic = r % 3;
-          }
-          out[o++] = used ? scale * w[((size_t)(oc * cin + ic) * 3 + tap / 3) * 3 + tap % 3] : 0.f;
-        }
+  std::fill(out, out + gcnn_packed_elems(layer, cin, cout), 0.f);
+  const int nct = cout / 16;
+  for (int ct = 0; ct < nct; ++ct) {
+    const float* rows[16];                                     // [ic][tap]
+    for (int r = 0; r < 16; ++r) rows[r] = w + (size_t)g_channel(cout, ct, r) * cin * 9;
+    float* dst = out + (size_t)ct * 512;
+    if (layer == 0) {
+      for (int k = 0; k < 32; ++k) {
+        int u, v;
+        if (!g_first_k(k, &u, &v)) continue;
+        for (int r = 0; r < 16; ++r) dst[((k >> 3) * 16 + r) * 8 + (k & 7)] = scale * rows[r][v % 3 * 9 + u * 3 + v / 3];
+      }
+      continue;
+    }
+    for (int tap = 0, k = 0; tap < 9; ++tap)
+      for (int ic = 0; ic < cin; ic += 8, k += 8) {
+        float* d = dst + (size_t)(k >> 5) * nct * 512 + (k >> 3 & 3) * 128;
+        for (int r = 0; r < 16; ++r, d += 8)
+          for (int e = 0; e < 8; ++e) d[e] = scale * rows[r][(ic + e) * 9 + tap];
+      }
+  }
 }
 
 // Slot i of src becomes slot j of dst.
