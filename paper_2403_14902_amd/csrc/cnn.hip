@@ -25,26 +25,8 @@
 
 namespace hydro {
 
-template <typename T> struct Mf;
-template <> struct Mf<__bf16> {
-  static constexpr int KSTEP = 32, KPL = 8;
-  typedef bf16x8 frag;
-};
-template <> struct Mf<float> {
-  static constexpr int KSTEP = 4, KPL = 1;
-  typedef float frag;
-};
-
-__device__ inline floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) { return mfma_bf16(a, b, c); }
-__device__ inline floatx4 mfma(float a, float b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-template <typename T>
-__device__ inline typename Mf<T>::frag ld_frag(const T* p) {
-  if constexpr (sizeof(T) == 2) return *reinterpret_cast<const bf16x8*>(p);
-  else return *p;
-}
+// k-steps of the 16x16x32 MFMA (the FP32 tier's too: bf16 terms), operands per lane
+constexpr int KSTEP = 32, KPL = 8;
 
 // geometry
 constexpr int H0 = 64, H1 = 32, H2 = 16, H3 = 8;
@@ -96,11 +78,8 @@ template <typename T, int MMAX = 4> struct CnnLds {
 
 // packed-layer geometry: [slab][kstep][ntile][64][KPL]
 // layer 1: K = 27 and the bias in conv1_k's slots
-template <typename T>
 __host__ __device__ constexpr int cnn_ksteps(int layer, int m) {
-  return layer == 0 ? (27 + Mf<T>::KSTEP - 1) / Mf<T>::KSTEP
-       : layer == 1 ? (9 * CB1 + Mf<T>::KSTEP - 1) / Mf<T>::KSTEP
-                    : 9 * 32 * m / Mf<T>::KSTEP;
+  return layer == 0 ? 1 : layer == 1 ? (9 * CB1 + KSTEP - 1) / KSTEP : 9 * 32 * m / KSTEP;
 }
 __host__ __device__ constexpr int cnn_slabs(int layer, int m) { return layer == 2 ? 1 : m; }
 __host__ __device__ constexpr int cnn_ntiles(int layer, int m) { return layer == 0 ? 1 : layer == 1 ? 2 * m : 4 * m; }
@@ -267,12 +246,10 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
   // splitting where they are written saves most of the vector work: FP32 kernel 861 -> 680 us a
   // launch on the 10,007-frame query, with layer 1's gather in five words instead of eight elements
   constexpr bool S3 = sizeof(T) == 4;
-  typedef typename std::conditional<S3, __bf16, T>::type KT;
-  constexpr int KSTEP = Mf<KT>::KSTEP, KPL = Mf<KT>::KPL;
-  typedef typename Mf<T>::frag frag;
+  typedef bf16x8 frag;
   // term t of the FP32 tier's packed layer l: fragments [slab][k-step][n-tile][lane]
   auto s3w = [&](int l, int t) {
-    const size_t per_term = (size_t)cnn_slabs(l, M) * cnn_ksteps<__bf16>(l, M) * cnn_ntiles(l, M) * 64;
+    const size_t per_term = (size_t)cnn_slabs(l, M) * cnn_ksteps(l, M) * cnn_ntiles(l, M) * 64;
     return reinterpret_cast<const bf16x8*>(a.w_s3[slot][l]) + t * per_term;
   };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, l16 = lane & 15;
@@ -281,13 +258,13 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
   unsigned char* S1 = region + CnnLds<T>::S1_OFF;
   unsigned char* L2 = region;
 
-  const T* const* wpk = reinterpret_cast<const T* const*>(a.w_bf[slot]);   // (bf16 tier)
+  const __bf16* const* wpk = a.w_bf[slot];   // (bf16 tier)
   const float* b2 = sh.cb + CB_L2;
   const float* b3 = sh.cb + CB_L3;
   // The narrow classes fetch the next frame now: their layer 3 is too short to cover the HBM
   // latency before the frame is stored (not the four-wave m = 2 form: no registers to spare).
   constexpr bool kEarlyFetch = M == 1 || (M == 2 && NWV == 8);
-  constexpr int KS1 = cnn_ksteps<KT>(0, M), KS2 = cnn_ksteps<KT>(1, M);
+  constexpr int KS1 = cnn_ksteps(0, M), KS2 = cnn_ksteps(1, M);
   constexpr int NT2 = 2 * M;
   // layer-2 wave tile: MT2 position tiles x NW2 channel tiles (the waves cover 16 x NT2)
   constexpr int MT2 = (M == 1 && NWV == 8) ? 2 : (M == 4 && sizeof(T) == 2) ? 8 : 4, NW2 = NT2 * (16 / MT2) / NWV;
@@ -420,12 +397,12 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
       if constexpr (S3) {
 #pragma unroll
         for (int t = 2; t >= 0; --t) {
-          acc0 = mfma(w1t[t], av0, acc0);
-          acc1 = mfma(w1t[t], av1, acc1);
+          acc0 = mfma_bf16(w1t[t], av0, acc0);
+          acc1 = mfma_bf16(w1t[t], av1, acc1);
         }
       } else {
-        acc0 = mfma(w1f[0], av0, zero);
-        acc1 = mfma(w1f[0], av1, zero);
+        acc0 = mfma_bf16(w1f[0], av0, zero);
+        acc1 = mfma_bf16(w1f[0], av1, zero);
       }
       l1_store(q, acc0);
       l1_store(q + 1, acc1);
@@ -485,11 +462,11 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
         frag av[MT2];
         const unsigned char* src = S1 + P1::at(2 * mg2 * MT2 + u, 2 * l16 + v, c0 * (int)sizeof(T));
 #pragma unroll
-        for (int q = 0; q < MT2; ++q) av[q] = ld_frag<T>(reinterpret_cast<const T*>(src + q * 2 * P1::S1RB));
+        for (int q = 0; q < MT2; ++q) av[q] = *reinterpret_cast<const frag*>(src + q * 2 * P1::S1RB);
 #pragma unroll
         for (int n = 0; n < NW2; ++n)
 #pragma unroll
-          for (int q = 0; q < MT2; ++q) acc2[q][n] = mfma(w[n], av[q], acc2[q][n]);
+          for (int q = 0; q < MT2; ++q) acc2[q][n] = mfma_bf16(w[n], av[q], acc2[q][n]);
         // (behind the last k-step the last fragment again, for nobody; the barrier keeps the loads here)
 #pragma unroll
         for (int n = 0; n < NW2; ++n) w[n] = w2s[(min(slab * KS2 + ks + 2, M * KS2 - 1) * NT2 + n) * 64];
@@ -542,11 +519,11 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
             frag av[MT2];
             const unsigned char* src = S1 + P1::at(2 * mg2 * MT2 + u, 2 * l16 + v, c0 * (int)sizeof(T));
   #pragma unroll
-            for (int q = 0; q < MT2; ++q) av[q] = ld_frag<T>(reinterpret_cast<const T*>(src + q * 2 * P1::S1RB));
+            for (int q = 0; q < MT2; ++q) av[q] = *reinterpret_cast<const frag*>(src + q * 2 * P1::S1RB);
   #pragma unroll
             for (int n = 0; n < NW2; ++n)
   #pragma unroll
-              for (int q = 0; q < MT2; ++q) acc2[q][n] = mfma(bw2[d][n], av[q], acc2[q][n]);
+              for (int q = 0; q < MT2; ++q) acc2[q][n] = mfma_bf16(bw2[d][n], av[q], acc2[q][n]);
             if constexpr (KS2 % PD2 == 0) {
               // unconditional refill; the last PD2 k-steps re-read the last fragment (unused).  The
               // scheduling barrier keeps the loads here: sunk to the end of the iteration (to
@@ -590,7 +567,7 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
   __syncthreads();
 
   // ---- layer 3: 4 position tiles (64 positions) x 4M channel tiles; wave tile MT3 x NW3
-  constexpr int KS3 = cnn_ksteps<KT>(2, M), NT3 = 4 * M;
+  constexpr int KS3 = cnn_ksteps(2, M), NT3 = 4 * M;
   constexpr int MT3 = (M == 1 && NWV == 8) ? 2 : 4, NW3 = NT3 * (4 / MT3) / NWV;
   constexpr int MG3 = 4 / MT3;                         // position groups (1 or 2)
   constexpr int PD3 = S3 ? 1 : ((M == 2 && NWV == 4) ? 2 : 3);
@@ -617,11 +594,11 @@ __device__ void cnn_frame(const CnnArgs& a, int slot, unsigned char* region, Cnn
     frag av[MT3];
     const unsigned char* src = L2 + P2::at(4 * mh * MT3 + 2 * (l16 >> 3) + u, 2 * (l16 & 7) + v, c0 * (int)sizeof(T));
 #pragma unroll
-    for (int q = 0; q < MT3; ++q) av[q] = ld_frag<T>(reinterpret_cast<const T*>(src + q * 4 * P2::RB));
+    for (int q = 0; q < MT3; ++q) av[q] = *reinterpret_cast<const frag*>(src + q * 4 * P2::RB);
 #pragma unroll
     for (int n = 0; n < NW3; ++n)
 #pragma unroll
-      for (int q = 0; q < MT3; ++q) acc3[q][n] = mfma(b[n], av[q], acc3[q][n]);
+      for (int q = 0; q < MT3; ++q) acc3[q][n] = mfma_bf16(b[n], av[q], acc3[q][n]);
   };
   if constexpr (sizeof(T) == 2) {
     // every k-step but the last PD3 refills its buffer PD3 k-steps ahead
@@ -856,13 +833,10 @@ int cnn_variant_of(int in_hw, int n_layers, const int* widths) {
 
 static int mult_of(int variant) { return variant == CNN_W1 ? 1 : variant == CNN_W2 ? 2 : 4; }
 
-template <typename T>
-static size_t packed_elems_t(int variant, int layer) {
+size_t cnn_packed_elems(int variant, int layer) {
   const int m = mult_of(variant);
-  return (size_t)cnn_slabs(layer, m) * cnn_ksteps<T>(layer, m) * cnn_ntiles(layer, m) * 64 * Mf<T>::KPL;
+  return (size_t)cnn_slabs(layer, m) * cnn_ksteps(layer, m) * cnn_ntiles(layer, m) * 64 * KPL;
 }
-
-size_t cnn_packed_elems(int variant, int layer) { return packed_elems_t<__bf16>(variant, layer); }
 
 // Term t (0, 1, 2) of v as a sum of three bf16 values.
 static float bf16_term(float v, int t) {
@@ -874,11 +848,9 @@ static float bf16_term(float v, int t) {
 }
 
 // Pack one conv layer ([co][ci][3][3] fp32, scaled by `scale`) into fragment order; bias: layer 1's.
-template <typename T>
-static void pack_t(int variant, int layer, const float* w, float scale, const float* bias, float* out) {
+void cnn_pack_layer(int variant, int layer, const float* w, float scale, const float* bias, float* out) {
   const int m = mult_of(variant);
-  const int KSTEP = Mf<T>::KSTEP, KPL = Mf<T>::KPL;
-  const int slabs = cnn_slabs(layer, m), ks_n = cnn_ksteps<T>(layer, m), nt_n = cnn_ntiles(layer, m);
+  const int slabs = cnn_slabs(layer, m), ks_n = cnn_ksteps(layer, m), nt_n = cnn_ntiles(layer, m);
   const int C2 = 32 * m;
   const int cin = layer == 0 ? 3 : layer == 1 ? 16 * m : C2;
   size_t o = 0;
@@ -915,10 +887,6 @@ static void pack_t(int variant, int layer, const float* w, float scale, const fl
             }
             out[o++] = valid ? scale * w[((size_t)(oc * cin + ic) * 3 + tap / 3) * 3 + tap % 3] : 0.f;
           }
-}
-
-void cnn_pack_layer(int variant, int layer, const float* w_canon, float scale, const float* bias, float* out) {
-  pack_t<__bf16>(variant, layer, w_canon, scale, bias, out);
 }
 
 void launch_cnn_pass(const CnnArgs& a, const Forward& f, int tier, int grid, hipStream_t s) {

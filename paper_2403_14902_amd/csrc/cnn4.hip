@@ -40,7 +40,6 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 __device__ inline floatx4 c4_mfma(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-__device__ inline floatx4 c4_mfma(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 // BF16 contractions use the 32x32x16 MFMA, which keeps the matrix pipe busy with few independent
 // accumulators.  Lane l supplies A[l % 32][8 (l / 32) + e] and B[8 (l / 32) + e][l % 32]; output
 // element (i, j) sits in lane j + 32 ((i / 4) % 2), value (i % 4) + 4 (i / 8).
@@ -568,15 +567,11 @@ void c4_front_kernel(GcnnArgs a) {
 }
 
 // ---------------------------------------------------------------- layers 3 and 4: implicit GEMM
+// ROWB: bytes of one LDS tile row per k-block; UPR: 16-byte units per row; CE: elements per unit
 template <int P> struct GemmCfg;
-// ROWB: bytes of one LDS tile row per k-block; UPR: 16-byte units per row; CE: elements per unit;
-// KSUB: MFMA k-steps per k-block
-// (128-byte rows: 2 bf16 / 8 fp32 / 1 fp8 MFMA k-steps per k-block and barrier)
-template <> struct GemmCfg<C4_F32> { static constexpr int ROWB = 128, UPR = 8, CE = 4, KSUB = 8; };
-template <> struct GemmCfg<C4_BF16> { static constexpr int ROWB = 128, UPR = 8, CE = 8, KSUB = 2; };
-template <> struct GemmCfg<C4_FP8> { static constexpr int ROWB = 128, UPR = 8, CE = 16, KSUB = 1; };
+template <> struct GemmCfg<C4_FP8> { static constexpr int ROWB = 128, UPR = 8, CE = 16; };
 // S3: B rows (fp32 activations) as FP32; A rows are three 64-byte bf16 rows (hi, mid, lo)
-template <> struct GemmCfg<C4_S3> { static constexpr int ROWB = 128, UPR = 8, CE = 4, KSUB = 1; };
+template <> struct GemmCfg<C4_S3> { static constexpr int ROWB = 128, UPR = 8, CE = 4; };
 
 // chunk swizzle of tile row r: rows of 4 units xor (r/2) mod 4, rows of 8 units xor r mod 8
 template <int UPR>
@@ -606,7 +601,7 @@ __host__ __device__ inline int c4_l3_channel(int row) {
 
 __host__ __device__ inline int c4_nkb(int prec, int layer) {
   const int cin = layer == 2 ? 64 : 128;
-  const int bke = prec == C4_FP8 ? 128 : prec == C4_BF16 ? 64 : 32;   // FP32 and S3: 32
+  const int bke = prec == C4_FP8 ? 128 : prec == C4_BF16 ? 64 : 32;   // S3: 32
   return (9 * cin + bke - 1) / bke;
 }
 
@@ -1156,7 +1151,8 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
             }
           }
         }
-      } else if constexpr (P == C4_FP8) {
+      } else {
+        static_assert(P == C4_FP8, "BF16 has a kernel of its own");
         i32x8 af[NT], bfr[MT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -1176,48 +1172,6 @@ __global__ __launch_bounds__(512) void c4_gemm_kernel(GcnnArgs a, Forward f) {
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = c4_mfma(af[nt], bfr[mt], acc[nt][mt]);
-      } else if constexpr (P == C4_BF16) {
-        // k-step ks reads chunk 4 ks + g of each row
-#pragma unroll
-        for (int ks = 0; ks < G::KSUB; ++ks) {
-          bf16x8 af[NT], bfr[MT];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const int r = wn * WN + nt * 16 + l16;
-            af[nt] = *reinterpret_cast<const bf16x8*>(A + (r * UPR + ((4 * ks + g) ^ c4_swz<UPR>(r))) * 16);
-          }
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            const int r = wm * WM + mt * 16 + l16;
-            bfr[mt] = *reinterpret_cast<const bf16x8*>(B + (r * UPR + ((4 * ks + g) ^ c4_swz<UPR>(r))) * 16);
-          }
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = c4_mfma(af[nt], bfr[mt], acc[nt][mt]);
-        }
-      } else {
-        // lane group g reads chunks 2g and 2g + 1 (8 values); k-step j uses value j
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          floatx4 af[NT], bfr[MT];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const int r = wn * WN + nt * 16 + l16;
-            af[nt] = *reinterpret_cast<const floatx4*>(A + (r * UPR + ((2 * g + h) ^ c4_swz<UPR>(r))) * 16);
-          }
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            const int r = wm * WM + mt * 16 + l16;
-            bfr[mt] = *reinterpret_cast<const floatx4*>(B + (r * UPR + ((2 * g + h) ^ c4_swz<UPR>(r))) * 16);
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-              for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = c4_mfma(af[nt][j], bfr[mt][j], acc[nt][mt]);
-        }
       }
     };
 
@@ -1700,13 +1654,6 @@ void c4_pack_front(const float* w1, float scale1, const float* b1, const float* 
           for (int e = 0; e < 8; ++e)
             out->w2b[(((tp * 2 + h) * 2 + c2) * 64 + l) * 8 + e] =
                 c4_w(w2, 32, c2 * 32 + (l & 31), tp * 32 + 16 * h + 8 * (l >> 5) + e);
-  // fp32 [tap][ct][lane][8]: output channel 16 ct + lane % 16, input channels 8 (lane / 16) + e
-  out->w2f.assign(9 * 4 * 64 * 8, 0.f);
-  for (int tp = 0; tp < 9; ++tp)
-    for (int ct = 0; ct < 4; ++ct)
-      for (int l = 0; l < 64; ++l)
-        for (int e = 0; e < 8; ++e)
-          out->w2f[((tp * 4 + ct) * 64 + l) * 8 + e] = c4_w(w2, 32, ct * 16 + (l & 15), tp * 32 + 8 * (l >> 4) + e);
   // FP32 arithmetic from bf16 terms, [tap][ct][term][lane][8]: the fp32 fragment's eight values
   // (output channel 16 ct + lane % 16, input channels 8 (lane / 16) + e) split hi, mid, lo
   out->w2s3.assign(9 * 4 * 3 * 64 * 8, 0);
@@ -1762,7 +1709,7 @@ void c4_pack_img(int prec, int layer, const float* w, const float* scale, unsign
         }
     return;
   }
-  const int es = prec == C4_FP8 ? 1 : prec == C4_BF16 ? 2 : 4;
+  const int es = prec == C4_FP8 ? 1 : 2;
   const int rowb = 128, upr = rowb / 16, ce = 16 / es, bke = rowb / es;
   const int nkb = c4_nkb(prec, layer);
   for (int kb = 0; kb < nkb; ++kb)
@@ -1777,14 +1724,9 @@ void c4_pack_img(int prec, int layer, const float* w, const float* scale, unsign
           const float v = kk < 9 * cin ? c4_w(w, cin, oc, kk) : 0.f;
           if (prec == C4_FP8) {
             dst[e] = c4_fp8_e4m3(v / scale[oc]);
-          } else if (prec == C4_BF16) {
-            uint32_t u;
-            memcpy(&u, &v, 4);
-            u += 0x7FFFu + ((u >> 16) & 1u);
-            const uint16_t h = (uint16_t)(u >> 16);
-            memcpy(dst + 2 * e, &h, 2);
           } else {
-            memcpy(dst + 4 * e, &v, 4);
+            const uint16_t h = c4_bf16_bits(v);
+            memcpy(dst + 2 * e, &h, 2);
           }
         }
       }

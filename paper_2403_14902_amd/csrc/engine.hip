@@ -1003,7 +1003,6 @@ static int pack_c4(hydro_session* s, const HostModel& hm, float scale1, int i) {
     uint16_t* bp;
     if ((rc = upload(s, b.data(), b.size(), &bp))) return rc;
     ga.c4_w1b[i] = bp;
-    float* dp;
     uint16_t* tp;
     if ((rc = upload(s, fp.w1s3.data(), fp.w1s3.size(), &tp))) return rc;
     ga.c4_w1f[i] = tp;
@@ -1011,8 +1010,6 @@ static int pack_c4(hydro_session* s, const HostModel& hm, float scale1, int i) {
     for (size_t t = 0; t < b2.size(); ++t) b2[t] = f32_to_bf16_bits(fp.w2b[t]);
     if ((rc = upload(s, b2.data(), b2.size(), &bp))) return rc;
     ga.c4_w2[i][C4_BF16] = bp;
-    if ((rc = upload(s, fp.w2f.data(), fp.w2f.size(), &dp))) return rc;
-    ga.c4_w2[i][C4_F32] = dp;
     uint8_t* qp;
     if ((rc = upload(s, fp.w2q.data(), fp.w2q.size(), &qp))) return rc;
     ga.c4_w2[i][C4_FP8] = qp;
@@ -1021,7 +1018,7 @@ static int pack_c4(hydro_session* s, const HostModel& hm, float scale1, int i) {
     ga.c4_w2[i][C4_S3] = sp;
   }
   for (int l = 2; l < 4; ++l)
-    for (int p = 0; p < 4; ++p) {
+    for (int p : {C4_BF16, C4_FP8, C4_S3}) {
       std::vector<unsigned char> img(c4_img_bytes(p, l));
       c4_pack_img(p, l, hm.cw[l].data(), sc[l - 1].data(), img.data());
       unsigned char* dp;
@@ -1152,6 +1149,7 @@ static int pack_models(hydro_session* s) {
       ga.n_layers[i] = m.n_layers;
       ga.in_hw[i] = m.in_h;
       ga.class_mask[i] = m.class_mask;
+      ga.c4[i] = c4_shape_ok(m.in_h, m.n_layers, m.widths) ? 1 : 0;
       int cin = 3;
       for (int l = 0; l < m.n_layers; ++l) {
         const int co = m.widths[l];
@@ -1170,7 +1168,7 @@ static int pack_models(hydro_session* s) {
         int rc;
         float* dp;
         uint16_t* bp;
-        {
+        if (!ga.c4[i]) {                         // (the dedicated kernels have images of their own)
           const size_t n = gcnn_packed_elems(l, cin, co);
           arena_pad(s, (n - (size_t)(l == 0 ? 28 : 9 * cin) * co) * 4 + (l == 0 ? (size_t)co * 5 * 4 : 0));
           std::vector<float> pf(n);
@@ -1204,7 +1202,6 @@ static int pack_models(hydro_session* s) {
       ga.fc_w[i] = dp;
       if ((rc = upload(s, hm.fcb.data(), hm.fcb.size(), &dp))) return rc;
       ga.fc_b[i] = dp;
-      ga.c4[i] = c4_shape_ok(m.in_h, m.n_layers, m.widths) ? 1 : 0;
       if (ga.c4[i] && (rc = pack_c4(s, hm, (float)scale, i))) return rc;
     } else {
       int i = ca.n_preds++;
