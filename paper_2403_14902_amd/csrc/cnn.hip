@@ -5,7 +5,8 @@
 // FC 10, m in {1, 2, 4}; every conv has stride 2, zero padding 1 (in normalised space), ReLU.
 //
 // Per frame, one workgroup (8 wave64s for the widest class; 4 for the two narrower ones in the
-// bf16 first pass, two workgroups per CU):
+// bf16 first pass, two workgroups per CU with the LDS of their own width, so that one frame's barriers
+// and per-frame work overlap another frame's MFMAs):
 //   FR   the raw frame in LDS as bf16 (exact for bf16 and uint8 inputs): rows of 64 pixels x 3
 //        channels (row stride 200 elements), with a one-pixel top/left border holding the raw
 //        value that normalises to zero.
@@ -72,9 +73,6 @@ template <typename T, int MMAX = 4> struct CnnLds {
   static constexpr int L2_BYTES_MAX = L2_W * PadL2<T, MMAX>::RB;
   static constexpr int REGION = (S1_OFF + S1_BYTES) > L2_BYTES_MAX ? (S1_OFF + S1_BYTES) : L2_BYTES_MAX;
 };
-
-// First pass, the two narrower classes: workgroups of four waves (with the LDS of their own
-// width), two per CU, so one frame's barriers and per-frame work overlap another frame's MFMAs.
 
 // packed-layer geometry: [slab][kstep][ntile][64][KPL]
 // layer 1: K = 27 and the bias in conv1_k's slots

@@ -11,15 +11,17 @@
 //   gemm4   layer 4 the same way (K = 1152, 256 channels), with the epilogue pooling each
 //           frame's 64 positions, applying FC, the class-subset margin and the decision.
 //
-// Arithmetic tiers (template P): FP32 (fp32 MFMA 16x16x4), BF16 (bf16 MFMA 16x16x32) and FP8
-// (OCP e4m3 operands on the scaled 16x16x128 MFMA with unit block scales; per-output-channel
-// weight scales and per-layer activation scales applied in fp32 in the epilogues).  Layer 1 runs
-// bf16 in the BF16 and FP8 tiers: raw uint8 / bf16 frame values are exact in bf16, and the
-// normalisation is folded into its weights.  Accumulation is fp32 throughout.
+// Arithmetic tiers (template P): FP32 and the three-product tier (bf16 MFMAs on operands split into
+// bf16 terms; layer 1 and 2's activations as planes of terms in LDS, layers 3 and 4's split where they are
+// read, or stored as two planes), BF16 (16x16x32 and 32x32x16 MFMAs) and FP8 (OCP e4m3 operands on
+// the scaled 16x16x128 MFMA with unit block scales; per-output-channel weight scales and per-layer
+// activation scales applied in fp32 in the epilogues).  Layer 1 runs bf16 in the BF16 and FP8 tiers:
+// raw uint8 / bf16 frame values are exact in bf16, and the normalisation is folded into its weights.
+// Accumulation is fp32 throughout.
 //
-// The GEMM tiles stage A (weights, pre-packed per k-block in the LDS image order) and B (the
-// im2col rows of the activations, gathered per 16-byte chunk) in a double-buffered LDS ring from
-// register stages.  LDS rows are XOR-swizzled by 16-byte chunk so that the sixteen rows an MFMA
+// The GEMM tiles copy A (weights, pre-packed per k-block in the LDS image order) and B (the im2col rows
+// of the activations, gathered per 16-byte chunk) straight from global memory into a ring of two to
+// five LDS stages.  LDS rows are XOR-swizzled by 16-byte chunk so that the sixteen rows an MFMA
 // fragment reads fall on distinct banks.
 #include <cmath>
 #include <cstring>

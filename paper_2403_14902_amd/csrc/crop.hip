@@ -19,7 +19,7 @@ namespace hydro {
 constexpr int kCropThreads = 256;
 constexpr int kOrderThreads = 1024;
 constexpr int kCropBuckets = 256;
-// Activations of a crop that fit this many doubles (both ping-pong buffers: crops up to about 26 x 26
+// Activations of a crop that fit this many doubles (both ping-pong buffers: square crops up to 24 x 24
 // with the 16-32-64 widths, four in five of a log-uniform side distribution) stay in LDS; 32 KB
 // each leaves room for four workgroups per CU.
 constexpr int kCropLds = 4096;

@@ -333,8 +333,8 @@ __global__ __launch_bounds__(kRouteThreads) void k_route(RouteArgs a) {
   const int wv = threadIdx.x / kWave, lane = lane_id();
   const unsigned long long below = (1ull << lane) - 1ull;
   uint32_t n_learned = 0, n_stats = 0, n_stale = 0;
-  // entries per thread: fewer than kRouteItems where the tuples then still make no more than
-  // kRouteSpread chunks (a thread takes its entries' lookups one after the other)
+  // entries per thread: fewer than kRouteItems where those would make fewer than kRouteSpread chunks (a thread
+  // takes its entries' lookups one after the other); less than two kRouteSpread then
   const int items = (int)min((int64_t)kRouteItems, max((int64_t)1, total / (kRouteSpread * kRouteThreads)));
   const int chunk = items * kRouteThreads;
   for (int64_t base = (int64_t)blockIdx.x * chunk; base < total; base += (int64_t)gridDim.x * chunk) {

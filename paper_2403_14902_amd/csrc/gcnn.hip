@@ -3,8 +3,7 @@
 // fused per-frame kernel (e.g. 128x128 frames with 4 layers).
 //
 // Each layer is one implicit-GEMM launch over every queued frame of the tier: rows = output
-// positions of all frames (a 64-row tile may span frames, so each weight fragment serves
-// 64 positions), columns = output channels, K = (tap, input channel).  Activations live in a
+// positions of all frames (a tile of 128 or 256 rows may span frames), columns = output channels, K = (tap, input channel).  Activations live in a
 // per-tier scratch (bf16 or fp32, NHWC per frame).  Layer 1 reads the raw frame (bf16 or uint8,
 // exact in bf16) with the normalisation folded into its weights and border taps set to the raw
 // value that normalises to zero.  A head launch pools, applies FC and decides.  The FP64 tier
@@ -29,7 +28,6 @@ __host__ __device__ inline bool g_first_k(int k, int* u, int* r) {
   return k < 27;
 }
 
-// Four channels of one position: bias, ReLU, store.
 // Output channel of row r of a layer's channel tile ct.  Of two tiles, lane group g of 16 holds rows
 // 4g .. 4g + 3 each: channels 8g .. 8g + 7 of the pair's 32, so that a lane stores 16 bytes of bf16, not
 // 8 a tile (a store takes the address unit a cycle per 64 bytes that it touches).
