@@ -207,9 +207,9 @@ __global__ __launch_bounds__(256) void gconv_first_any_kernel(GcnnArgs a) {
 // roundings, 1.9e-7; FP32 logits of 600 128x128 frames 511 -> 527 us).
 // Bound by the copies: at 64 bf16 channels a block brings 40 KB for 2.1 MFLOP.  16-32-64 and 32-64-128
 // CNNs on 8,192 128x128 frames (12,288 evaluations): layers 2 and 3 take 1.5 ms in bf16 (8-byte
-// stores: 1.7); register-staged
-// 128-position tiles, and one wave per 16 positions where Cin is 16, took 3.6.  The FP32 band of the
-// same query: 0.53 ms, on fp32 MFMAs 1.0.
+// stores: 1.7); register-staged 128-position tiles, and one wave per 16 positions where Cin is 16, took
+// 3.6.  The FP32 band of the same query: 0.66 ms (0.63 with six roundings a k-step; on fp32 MFMAs nearly
+// twice that).
 template <typename T, int BN> struct GD {
   static constexpr bool F32 = sizeof(T) == 4;
   static constexpr int KB = 128 / (int)sizeof(T), CE = 16 / (int)sizeof(T);   // values per block, per chunk
